@@ -106,7 +106,7 @@ constexpr int kSplitMinTiles = 16; // shorter private units are packed four to a
 struct WgDesc {      // one 256-thread workgroup: a shared tile list, then one private list per wavefront
     int32_t coop_ofs, n_coop;   // tiles every wavefront of the group sees (staged once through LDS)
     int32_t grp_base;           // row group that the shared list's ranges are relative to
-    int32_t row_tiles;          // bits 0-7: 16-row tiles per wavefront (1 or 2; the f32 kernel also takes 4);
+    int32_t row_tiles;          // bits 0-7: 16-row tiles per wavefront (1 or 2);
                                 // bits 8-31: full shared tiles
     WaveItem w[4];
     int32_t n_full[4];          // full tiles at the head of each wavefront's own list
@@ -179,6 +179,12 @@ hipError_t launch_read_rows(const Shape& s, const void* pool, const int32_t* src
 hipError_t launch_attention_partial(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand,
                                     PartialBuf part, const void* cand_k, const void* cand_v, const uint8_t* mask,
                                     void* out, ClassStreams& cs, hipStream_t st);
+hipError_t launch_attention_bf16(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand,
+                                 PartialBuf part, const void* cand_k, const void* cand_v, const uint8_t* mask,
+                                 void* out, ClassStreams& cs, hipStream_t st);
+hipError_t launch_attention_f32(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand,
+                                PartialBuf part, const void* cand_k, const void* cand_v, const uint8_t* mask, void* out,
+                                hipStream_t st);
 hipError_t launch_prefill_bf16(const Shape& s, const void* pool, const void* q, const PrefillWg* wgs,
                                const int32_t* tables, int n_wg, void* out, hipStream_t st);
 // workgroups [wg_first, wg_first + n_wg) of the plan: matrix units (row_tiles byte = kMatrixUnitRows)

@@ -1,5 +1,4 @@
-// Row writes, copy-on-write block copies, row read-back, the fp32 attention
-// kernel and the merge kernel (gfx950).
+// Row writes, copy-on-write block copies, row read-back and the merge kernel (gfx950).
 #include <hip/hip_runtime.h>
 
 #include "apar_internal.hpp"
@@ -15,12 +14,6 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
     if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40);  // quiet NaN
     u += 0x7fffu + ((u >> 16) & 1u);
     return (uint16_t)(u >> 16);
-}
-
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
 }
 
 // ---------------------------------------------------------------------------
@@ -216,106 +209,6 @@ __global__ __launch_bounds__(256) void copy_blocks(char* __restrict__ pool, cons
 }
 
 // ---------------------------------------------------------------------------
-// fp32 attention: one wavefront per query row, plain vector arithmetic, row-major
-// tiles.  Used by fp32 pools, where results must hold to 1e-5 and the matrix
-// cores' bf16 inputs would not.  Follows the same plan as the bf16 kernel: row c
-// of wavefront k of a workgroup walks the group's shared tiles and wavefront k's
-// own tiles and takes those whose row-group range contains its own.
-// grid = (plan workgroups, kv heads, 4 wavefronts x 4 row tiles x 16 rows); block = 64 lanes over the head dim.
-// ---------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(64) void attention_f32(const char* __restrict__ pool, const float* __restrict__ q,
-                                                    PlanDev plan, int n_cand, int n_q, int n_kv, int group,
-                                                    float scale_log2e, int64_t tile_bytes, PartialBuf part,
-                                                    const float* __restrict__ cand_k,
-                                                    const float* __restrict__ cand_v,
-                                                    const uint8_t* __restrict__ cand_mask,
-                                                    float* __restrict__ out) {
-    constexpr int E = D / 64;
-    const int lane = threadIdx.x;
-    const int kvh = blockIdx.y;
-    // row c of row tile nt of wavefront `wave`: tile nt holds row groups nt * cap .. of the wavefront
-    const int wave = blockIdx.z >> 6, nt = (blockIdx.z >> 4) & 3, c = blockIdx.z & 15;
-    const WgDesc* wg = plan.wgs + blockIdx.x;
-    if (nt >= (wg->row_tiles & 255)) return;
-    const WaveItem wi = wg->w[wave];
-    const int rps = plan.rows_per_slice, n_sl = plan.n_slices, rpt = plan.rows_per_thread;
-    const int cap = 16 / rps, jc = c / rps, within = c - jc * rps;
-    const int j = nt * cap + jc;
-    const int grp = wi.grp_lo + j;
-    const int rank = grp / n_sl, rr = (grp - rank * n_sl) * rps + within;
-    if (jc >= cap || j >= wi.n_grp || rr >= rpt) return;
-    const int listed = plan.dfs_threads ? plan.dfs_threads[rank] : rank;
-    const int cc = rr / group, hq = kvh * group + (rr - cc * group);
-    const int64_t qrow = ((int64_t)listed * n_cand + cc) * n_q + hq;
-    float qv[E], acc[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) qv[e] = q[qrow * D + lane + 64 * e], acc[e] = 0.0f;
-    float m = -INFINITY, l = 0.0f;
-    // a split group's four wavefront items hold the same rows and a quarter of the tiles each
-    const bool split = (wi.flags & kWaveSplit) != 0;
-    if (split && wave != 0) return;
-    const int n_lists = split ? 5 : 2;
-    for (int list = 0; list < n_lists; ++list) {
-        const WaveItem& src = wg->w[list < 2 ? wave : list - 1];
-        const TileRef* tiles = plan.tiles + (list == 0 ? wg->coop_ofs : src.tile_ofs);
-        const int n_tiles = list == 0 ? wg->n_coop : src.n_tiles;
-        const int my_j = list == 0 ? j + (wi.grp_lo - wg->grp_base) : j;
-        for (int t = 0; t < n_tiles; ++t) {
-            const int meta = tiles[t].meta;
-            const int lo = meta & 1023, hi = (meta >> 10) & 1023;
-            if (my_j < lo || my_j >= hi) continue;
-            // a causal tile (bit 30) shows its first row group `first` slots (bits 25-29), every further one one more
-            int valid = (meta >> 20) & 31;
-            if (meta >> 30) valid = min(valid, ((meta >> 25) & 31) + (my_j - lo));
-            const float* tile = reinterpret_cast<const float*>(pool + ((int64_t)tiles[t].blk * n_kv + kvh) * tile_bytes);
-            for (int tok = 0; tok < valid; ++tok) {
-                float dot = 0.0f;
-#pragma unroll
-                for (int e = 0; e < E; ++e) dot += qv[e] * tile[tok * D + lane + 64 * e];
-                const float sc = wave_sum(dot) * scale_log2e;
-                const float m_new = fmaxf(m, sc);
-                const float alpha = exp2f(m - m_new), pr = exp2f(sc - m_new);
-                l = l * alpha + pr;
-#pragma unroll
-                for (int e = 0; e < E; ++e) acc[e] = acc[e] * alpha + pr * tile[16 * D + tok * D + lane + 64 * e];
-                m = m_new;
-            }
-        }
-    }
-    if (wi.flags & kWaveDirect) {
-        if (cand_mask != nullptr) {  // multi-candidate call: the candidates this row may see
-            const uint32_t bits = cand_mask[(int64_t)listed * n_cand + cc];
-            for (int cp = 0; cp < n_cand; ++cp) {
-                if (!((bits >> cp) & 1u)) continue;
-                const int64_t base = (((int64_t)listed * n_cand + cp) * n_kv + kvh) * D;
-                float dot = 0.0f;
-#pragma unroll
-                for (int e = 0; e < E; ++e) dot += qv[e] * cand_k[base + lane + 64 * e];
-                const float sc = wave_sum(dot) * scale_log2e;
-                const float m_new = fmaxf(m, sc);
-                const float alpha = exp2f(m - m_new), pr = exp2f(sc - m_new);
-                l = l * alpha + pr;
-#pragma unroll
-                for (int e = 0; e < E; ++e) acc[e] = acc[e] * alpha + pr * cand_v[base + lane + 64 * e];
-                m = m_new;
-            }
-        }
-        const float inv = 1.0f / l;
-#pragma unroll
-        for (int e = 0; e < E; ++e) out[qrow * D + lane + 64 * e] = acc[e] * inv;
-        return;
-    }
-    const int64_t slot = ((int64_t)(wi.part_base + rank - wi.grp_lo / n_sl) * n_cand + cc) * n_q + hq;
-#pragma unroll
-    for (int e = 0; e < E; ++e) part.o[slot * D + lane + 64 * e] = acc[e];
-    if (lane == 0) {
-        part.ml[slot * 2] = m;
-        part.ml[slot * 2 + 1] = l;
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Merge: sixteen lanes per (listed thread, candidate, q head).  Folds the partial
 // results on the thread's root path (log-sum-exp in base 2), adds the candidate
 // keys the mask lets this candidate see, normalises and writes the output row.
@@ -435,10 +328,6 @@ __global__ __launch_bounds__(256) void merge_rows(PlanDev plan, PartialBuf part,
 
 }  // namespace
 
-hipError_t launch_attention_bf16(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand,
-                                 PartialBuf part, const void* cand_k, const void* cand_v, const uint8_t* mask,
-                                 void* out, ClassStreams& cs, hipStream_t st);
-
 // ---------------------------------------------------------------------------
 // Fixed workspace of apar_decode_attention_fixed: the plan tables and the partial results of one call live
 // in this array instead of in memory the library allocates.  Every GPU the library runs on holds its own
@@ -548,16 +437,7 @@ hipError_t launch_attention_partial(const Shape& s, const void* pool, const void
     if (plan.n_wg <= 0) return hipSuccess;
     if (s.dtype == APAR_BF16)
         return launch_attention_bf16(s, pool, q, plan, n_cand, part, cand_k, cand_v, mask, out, cs, st);
-    dim3 grid(plan.n_wg, s.n_kv, 256);
-    if (s.d == 64)
-        hipLaunchKernelGGL(attention_f32<64>, grid, dim3(64), 0, st, (const char*)pool, (const float*)q, plan, n_cand,
-                           s.n_q, s.n_kv, s.group, s.scale_log2e, s.tile_bytes, part, (const float*)cand_k,
-                           (const float*)cand_v, mask, (float*)out);
-    else
-        hipLaunchKernelGGL(attention_f32<128>, grid, dim3(64), 0, st, (const char*)pool, (const float*)q, plan, n_cand,
-                           s.n_q, s.n_kv, s.group, s.scale_log2e, s.tile_bytes, part, (const float*)cand_k,
-                           (const float*)cand_v, mask, (float*)out);
-    return hipGetLastError();
+    return launch_attention_f32(s, pool, q, plan, n_cand, part, cand_k, cand_v, mask, out, st);
 }
 
 hipError_t launch_merge(const Shape& s, const PlanDev& plan, PartialBuf part, const void* q, const void* cand_k,
