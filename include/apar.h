@@ -217,7 +217,9 @@ APAR_API int apar_decode_attention_spec(apar_pool* pool, const void* q_dev, cons
  * library allocates, every kernel runs on `hip_stream` itself, and the call creates no stream or
  * event and is never profiled.  It calls no hipMalloc, hipFree, hipHostMalloc or any other
  * allocating routine (what it needs besides - the workspace's address on the pool's device, a
- * pinned staging buffer of APAR_FIXED_PLAN_BYTES and one event - apar_pool_create obtained).
+ * pinned staging buffer of APAR_FIXED_PLAN_BYTES and one event - apar_pool_create obtained).  A unit that
+ * is cut into several workgroups leaves its rows' states in the workspace too; where the tables of that do not
+ * fit any more the units stay whole (same result to rounding).
  * Limits: the staged plan (128 bytes per workgroup, 8 per block read, 8 per listed thread and 4
  * per partial result to merge) must fit APAR_FIXED_PLAN_BYTES, and the partial results
  * ((head_dim + 2) floats per (partial row, q head); none when every sharing subtree fits one work
@@ -455,6 +457,9 @@ APAR_API int apar_plan_record_version(void);
  *   APAR_PLAN_DFS_THREADS rank -> index into the listed threads;
  *   APAR_PLAN_PATH_OFS    [n+1] offsets into PATH_IDS by listed index;  APAR_PLAN_PATH_IDS  the
  *                         partial-result rows merged for each listed thread (none: written directly);
+ *                         (The tables describe units.  A launch may cut a unit that is more than a compute unit's share
+ *                         of the call into several workgroups that fold their rows' states among themselves; neither
+ *                         the tables nor apar_plan_info count those.)
  *   APAR_PLAN_GEOMETRY    rows per thread, rows per slice, slices;
  *   APAR_PLAN_CHANGED_WORKGROUP_WORDS, APAR_PLAN_CHANGED_TILE_WORDS  if the last call carried its plan over
  *                         (apar_set_plan_reuse): which ints of the two tables it changed - the ints it rewrites

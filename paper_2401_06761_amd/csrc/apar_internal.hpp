@@ -113,6 +113,20 @@ struct WgDesc {      // one 256-thread workgroup: a shared tile list, then one p
 };
 static_assert(sizeof(WgDesc) == 128, "WgDesc is read with aligned scalar loads");
 
+// One workgroup (per kv head) of a launch some of whose units are cut into slices (attn_split.hpp).
+struct SplitBlock {
+    int32_t wg;               // the unit: index of its workgroup descriptor
+    int32_t slice;            // slice | slices of the unit << 16
+    int32_t state;            // where the unit's row states start, in 16-row tiles per kv head ...
+    int32_t cut;              // ... and the unit's number among those that are cut
+};
+struct SplitPlan {
+    const SplitBlock* blocks; // in launch order; null: no unit is cut and workgroups are units
+    int32_t n_blocks_class[3];
+    float* state;             // per cut unit: [kv head][slice][wavefront][row tile] states
+    int32_t* arrived;         // per cut unit: [kv head][wavefront], zero between launches
+};
+
 struct PlanDev {              // device pointers of one staged plan
     const WgDesc* wgs;
     const TileRef* tiles;
@@ -123,6 +137,7 @@ struct PlanDev {              // device pointers of one staged plan
     int32_t n_wg_class[3];       // matrix units, workgroups with 2 and with 1 row tiles per wavefront, stored in that order
     int32_t n_threads;
     int32_t rows_per_thread, rows_per_slice, n_slices;
+    SplitPlan split;
 };
 
 struct PrefillWg {            // one workgroup of the bf16 prefill kernel: consecutive query tokens of one thread
@@ -161,8 +176,13 @@ struct ClassStreams {
                           // no stream or event is ever created (for the entry point that must not allocate)
 };
 
+// Room for the row states of a launch some of whose units are cut into slices (attn_split.hpp), and the most such
+// units x kv heads.
+constexpr size_t kSplitStateBytes = (size_t)32 << 20;
+constexpr int kSplitMaxCut = 1024;
+
 // Where `device`'s copy of the library's static workspace (APAR_FIXED_PLAN_BYTES of plan tables followed by
-// APAR_FIXED_PARTIAL_BYTES of partial results) lives.  `device` must be the current device.  The address is
+// APAR_FIXED_PARTIAL_BYTES of partial results and kSplitStateBytes of row states) lives.  `device` must be the current device.  The address is
 // asked for once per device and kept.
 hipError_t fixed_workspace_of_device(int device, char** out);
 

@@ -124,6 +124,13 @@ struct apar_pool {
     hipEvent_t fixed_up = nullptr;
     bool fixed_pending = false;
 
+    // row states of launches whose units are cut into slices; obtained at pool creation
+    char* split_dev = nullptr;
+    size_t split_bytes = 0;
+    std::vector<SplitBlock> split_blocks;  // of the plan as it was built
+    int32_t n_split_class[3] = {0, 0, 0};
+    size_t n_split_cut = 0;
+
     bool profiling = false;
     std::vector<EventPair> decode_events, append_events;
     std::vector<hipEvent_t> spare_events;
@@ -303,6 +310,61 @@ bool same_params(const PlanParams& a, const PlanParams& b) {
            a.matrix_min_blocks == b.matrix_min_blocks;
 }
 
+// Which units of a decode plan are cut into slices (attn_split.hpp), and the launch's workgroups in order.  A unit's cost
+// is the tiles a wavefront of it walks.  With T = total cost / shares, but at least kSplitMinTiles, units of more than T
+// tiles become slices of about T; where no unit does, `out` stays empty and the launch has one workgroup per unit.
+// Measured (us per call, uncut / 256 / 512 / 1024 shares; trees of two fork levels, 32 q heads):
+//   bf16, 32 kv heads:  1 request 36 / 24 / 24 / 24,  4: 88 / 44 / 44 / 47,  16: 182 / 170 / 162 / 162,  32: 251 / 252 / 266 / 258
+//   bf16, 8 kv heads:   1 request 41 / 22 / 22 / 22,  4: 98 / 67 / 70 / 70,  16: 136 / 96 / 97 / 96
+//   one thread family of 32 k tokens, 8 kv heads: 106 / 58 / 59 / 63;  five candidates, 16 requests: 189 / 189 / 221 / 222
+//   fp32, 12 requests, 8 kv heads: 356 / 165 / 137 / 139 (its wavefronts are busy with products, not waiting)
+// Slices of 4, 2 and 1 tiles instead of kSplitMinTiles: 25, 32 and 32 against 22 us for one request with 8 kv heads.
+// Slices are worth their states and their fold only where they shorten the longest walk by more than kSplitMinGain
+// tiles (26 requests, 8 kv heads, units of 19 to 27 tiles: 46 us uncut, 49 us with every unit cut in two).  Their room is an
+// eighth of the pool, at most kSplitStateBytes.
+constexpr int kSplitShares = 256, kSplitSharesF32 = 512;
+constexpr int kSplitMinTiles = 6, kSplitMinGain = 16;
+void cut_into_slices(const PlanHost& ph, const Shape& s, size_t state_bytes, std::vector<SplitBlock>& out, int32_t (&n_class)[3],
+                     size_t& n_cut) {
+    out.clear();
+    n_class[0] = n_class[1] = n_class[2] = 0;
+    n_cut = 0;
+    auto cost = [](const WgDesc& wg) {
+        return wg.n_coop + std::max(std::max(wg.w[0].n_tiles, wg.w[1].n_tiles), std::max(wg.w[2].n_tiles, wg.w[3].n_tiles));
+    };
+    const size_t first = (size_t)ph.n_wg_class[0];
+    int64_t total = 0;
+    int longest = 0;
+    for (size_t k = first; k < ph.wgs.size(); ++k) {
+        const int c = cost(ph.wgs[k]);
+        total += c;
+        longest = std::max(longest, c);
+    }
+    const int64_t shares = s.dtype == APAR_F32 ? kSplitSharesF32 : kSplitShares;
+    int64_t tiles = std::max<int64_t>(kSplitMinTiles, (total * s.n_kv + shares - 1) / shares);
+    const int64_t tile_bytes = (int64_t)(s.d / 4 + 2) * 64 * sizeof(float);
+    for (; longest > tiles + kSplitMinGain; tiles += (tiles + 3) / 4) {
+        out.clear();
+        n_class[0] = (int32_t)first;
+        n_class[1] = n_class[2] = 0;
+        n_cut = 0;
+        int64_t state = 0;
+        for (size_t k = 0; k < ph.wgs.size(); ++k) {
+            const WgDesc& wg = ph.wgs[k];
+            const int n = k < first ? 1 : (int)std::min<int64_t>(64, (cost(wg) + tiles - 1) / tiles);
+            for (int j = 0; j < n; ++j) out.push_back(SplitBlock{(int32_t)k, j | n << 16, (int32_t)state, (int32_t)n_cut});
+            if (k >= first) n_class[(wg.row_tiles & 255) == 2 ? 1 : 2] += n;
+            if (n > 1) {
+                state += (int64_t)n * ((wg.w[0].flags & kWaveSplit) ? 1 : 4) * (wg.row_tiles & 255);
+                n_cut += 1;
+            }
+        }
+        if (state * s.n_kv * tile_bytes <= (int64_t)state_bytes && (int64_t)n_cut * s.n_kv <= kSplitMaxCut) return;
+    }
+    out.clear();
+    n_cut = 0;
+}
+
 // fixed: the plan and the partial results go to the device's static workspace, nothing is allocated, no
 // stream or event is created and profiling is off for the call.
 int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* cand_v, const uint8_t* mask,
@@ -388,24 +450,31 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     DeviceGuard guard(p->device);
     hipStream_t st = (hipStream_t)stream;
 
-    // stage the five tables in one copy
-    size_t ofs[6];
+    if (!carried) cut_into_slices(ph, p->shape, p->split_bytes, p->split_blocks, p->n_split_class, p->n_split_cut);  // (a carried plan keeps its cut)
+    // stage the tables in one copy
+    size_t ofs[7];
     ofs[0] = 0;
     ofs[1] = align_up(ofs[0] + ph.wgs.size() * sizeof(WgDesc), 256);
     ofs[2] = align_up(ofs[1] + ph.tiles.size() * sizeof(TileRef), 256);
     ofs[3] = align_up(ofs[2] + ph.dfs_threads.size() * 4, 256);
     ofs[4] = align_up(ofs[3] + ph.path_ofs.size() * 4, 256);
     ofs[5] = align_up(ofs[4] + ph.path_ids.size() * 4, 256);
+    ofs[6] = align_up(ofs[5] + p->split_blocks.size() * sizeof(SplitBlock), 256);
+    // (the counters of slices that have arrived are staged too, as zeros)
+    const size_t counter_bytes = p->n_split_cut * p->shape.n_kv * 4 * sizeof(int32_t);
+    const size_t staged = align_up(ofs[6] + counter_bytes, 256);
+    bool cut = !p->split_blocks.empty();
     const size_t slots = (size_t)ph.n_partial_rows * n_cand * p->shape.n_q;
     StageSlot* s = nullptr;
     char *host = nullptr, *dev = nullptr;
+    size_t fixed_bytes = 0;
     PartialBuf part = p->part;
     if (p->resident_behind) p->resident = nullptr;
     p->resident_behind = false;
     // a carried-over plan whose tables are still on the device from the previous call: only the words that
     // changed are sent, and written in place once the previous call's kernels are through
     // (small tables are staged whole instead: one copy, against a copy and a launch)
-    const bool in_place = carried && !fixed && p->resident && p->resident_bytes == ofs[5] && ofs[5] >= kCopyStreamMinBytes;
+    const bool in_place = carried && !fixed && p->resident && p->resident_bytes == staged && staged >= kCopyStreamMinBytes;
     if (!in_place) p->resident = nullptr;
     if (in_place) {
         p->resident_behind = true;
@@ -442,8 +511,10 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
         dev = p->fixed_dev;
         part.o = (float*)(p->fixed_dev + kFixedPlanBytes);
         part.ml = part.o + cap_slots * p->shape.d;
+        cut = cut && staged <= kFixedPlanBytes;
+        fixed_bytes = cut ? staged : ofs[5];
     } else {
-        if ((rc = acquire_stage(p, ofs[5], &s)) != APAR_OK) return rc;
+        if ((rc = acquire_stage(p, staged, &s)) != APAR_OK) return rc;
         host = s->host;
         dev = s->dev;
     }
@@ -453,6 +524,10 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
         memcpy(host + ofs[2], ph.dfs_threads.data(), ph.dfs_threads.size() * 4);
         memcpy(host + ofs[3], ph.path_ofs.data(), ph.path_ofs.size() * 4);
         if (!ph.path_ids.empty()) memcpy(host + ofs[4], ph.path_ids.data(), ph.path_ids.size() * 4);
+        if (cut) {
+            memcpy(host + ofs[5], p->split_blocks.data(), p->split_blocks.size() * sizeof(SplitBlock));
+            memset(host + ofs[6], 0, counter_bytes);
+        }
     }
 
     // partial-result buffer
@@ -472,13 +547,13 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     if (in_place) {
         // (already there)
     } else if (fixed) {
-        HIP_TRY(hipMemcpyAsync(dev, host, ofs[5], hipMemcpyHostToDevice, st));
+        HIP_TRY(hipMemcpyAsync(dev, host, fixed_bytes, hipMemcpyHostToDevice, st));
         HIP_TRY(hipEventRecord(p->fixed_up, st));
         p->fixed_pending = true;
-    } else if ((rc = upload(p, s, ofs[5], st)) != APAR_OK) {
+    } else if ((rc = upload(p, s, staged, st)) != APAR_OK) {
         return rc;
     }
-    PlanDev pd;
+    PlanDev pd{};
     pd.wgs = (const WgDesc*)(dev + ofs[0]);
     pd.tiles = (const TileRef*)(dev + ofs[1]);
     pd.dfs_threads = (const int32_t*)(dev + ofs[2]);
@@ -491,6 +566,12 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     pd.rows_per_thread = p->plan_geom[0];
     pd.rows_per_slice = p->plan_geom[1];
     pd.n_slices = p->plan_geom[2];
+    if (cut) {
+        pd.split.blocks = (const SplitBlock*)(dev + ofs[5]);
+        for (int k = 0; k < 3; ++k) pd.split.n_blocks_class[k] = p->n_split_class[k];
+        pd.split.arrived = (int32_t*)(dev + ofs[6]);
+        pd.split.state = (float*)(fixed ? p->fixed_dev + kFixedPlanBytes + kFixedPartBytes : p->split_dev);
+    }
 
     EventPair ev;
     const bool profiling = p->profiling && !fixed;
@@ -516,7 +597,7 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
         HIP_TRY(hipEventRecord(s->ev, st));
         s->pending = true;
         p->resident = s;
-        p->resident_bytes = ofs[5];
+        p->resident_bytes = staged;
     }
     p->last_plan = info;
     if (profiling)
@@ -747,7 +828,11 @@ int apar_pool_create(const apar_pool_config* cfg, void* kv_dev, size_t kv_bytes,
             rc = APAR_ERR_HIP;
         if (rc == APAR_OK && !hip_ok(hipEventCreateWithFlags(&p->fixed_up, hipEventDisableTiming), "hipEventCreate"))
             rc = APAR_ERR_HIP;
+        p->split_bytes = std::min(kSplitStateBytes, std::max((size_t)1 << 20, (size_t)(block * cfg->num_blocks) / 8));
+        if (rc == APAR_OK && !hip_ok(hipMalloc((void**)&p->split_dev, p->split_bytes), "hipMalloc(split)")) rc = APAR_ERR_HIP;
         if (rc != APAR_OK) {
+            if (p->split_dev) (void)hipFree(p->split_dev);
+            if (p->fixed_up) (void)hipEventDestroy(p->fixed_up);
             if (p->fixed_host) (void)hipHostFree(p->fixed_host);
             delete p;
             return rc;
@@ -789,6 +874,7 @@ int apar_pool_destroy(apar_pool* p) {
     if (p->copy_stream) (void)hipStreamDestroy(p->copy_stream);
     if (p->fixed_host) (void)hipHostFree(p->fixed_host);
     if (p->fixed_up) (void)hipEventDestroy(p->fixed_up);
+    if (p->split_dev) (void)hipFree(p->split_dev);
     if (p->part.o) (void)hipFree(p->part.o);
     if (p->part.ml) (void)hipFree(p->part.ml);
     auto drop = [](hipEvent_t e) {

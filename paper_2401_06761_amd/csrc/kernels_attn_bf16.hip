@@ -54,6 +54,7 @@
 #include <type_traits>
 
 #include "apar_internal.hpp"
+#include "attn_split.hpp"
 
 namespace apar {
 
@@ -214,7 +215,8 @@ constexpr int kOpenScratch = 16 * kOpenRowStride;   // one wavefront's row-major
 
 // NT = 16-row tiles per wavefront (1 or 2 are instantiated): a workgroup carries up to 64 * NT query rows.
 // F8: full blocks hold fp8 codes and two scales (APAR_BF16_FP8KV pools).
-template <int NT, bool F8>
+// SPLIT: several workgroups per unit, each with a slice of its tile lists (attn_split.hpp).
+template <int NT, bool F8, bool SPLIT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3 : 2))) void attention_bf16(const char* __restrict__ pool, const uint16_t* __restrict__ q,
                                                       PlanDev plan, int wg_first, int n_cand, int n_q, int n_kv,
                                                       int group, float scale_log2e, PartialBuf part,
@@ -231,10 +233,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int g4 = lane >> 4, c = lane & 15;
     const int kvh = blockIdx.x % n_kv;
-    const WgDesc* wg = plan.wgs + wg_first + blockIdx.x / n_kv;
-    const WaveItem wi = wg->w[wave];
-    const int n_coop = wg->n_coop;
-    const TileRef* coop = plan.tiles + wg->coop_ofs;
+    Slice slice;
+    if constexpr (SPLIT) {
+        slice = slice_of_block(plan.split, wg_first, n_kv);
+    } else {
+        slice.wg = wg_first + blockIdx.x / n_kv;
+    }
+    const WgDesc* wg = plan.wgs + slice.wg;
+    WaveItem wi = wg->w[wave];
+    int n_coop = wg->n_coop, coop_ofs = wg->coop_ofs, coop_full = wg->row_tiles >> 8;
+    int own_full = min(wg->n_full[wave], wi.n_tiles);
+    if constexpr (SPLIT) {
+        cut_list(slice, coop_ofs, n_coop, coop_full);
+        cut_list(slice, wi.tile_ofs, wi.n_tiles, own_full);
+    }
+    const TileRef* coop = plan.tiles + coop_ofs;
     const TileRef* mine = plan.tiles + wi.tile_ofs;
     const char* head_base = pool + (int64_t)kvh * kTileBytes;
     const int64_t block_stride = (int64_t)n_kv * kTileBytes;
@@ -311,7 +324,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3
     // issued); the open tiles after them go through a general loop.
     if (n_coop > 0) {
         const int shift = wi.grp_lo - wg->grp_base;  // shared ranges are relative to the group's base
-        const int n_coop_full = wg->row_tiles >> 8;
+        const int n_coop_full = coop_full;
         u32x4 rk[4], rv[4];
         // Shared tiles are fetched with plain loads, private ones (below) with non-temporal loads: a shared
         // tile may be read again by another workgroup (the units below an inlined segment all read it; so do
@@ -604,7 +617,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3
         }
     };
     char* scratch = lds + wave * kOpenScratch;
-    const int n_full = min(wg->n_full[wave], wi.n_tiles);
+    const int n_full = own_full;
     int t = 0;
     int meta = 16 << 20;
     if (F8 && n_full > 2) {
@@ -794,7 +807,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3
         __builtin_amdgcn_wave_barrier();
     }
 
-    if ((wi.flags & kWaveDirect) && cand_mask != nullptr) {
+    if ((wi.flags & kWaveDirect) && cand_mask != nullptr && (!SPLIT || slice.s == 0)) {
         // Multi-candidate call: each thread's candidates are one more tile of at most 8 token rows
         // (row-major, a row every n_kv * 128 elements), visible to a row only where its mask bit is set.
         const int rank_lo = wi.grp_lo / n_sl, rank_hi = (wi.grp_lo + wi.n_grp - 1) / n_sl;
@@ -833,6 +846,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3
             }
         }
     }
+
+    if constexpr (SPLIT)
+        if (!fold_slices<NT, 8>(plan.split, slice, n_kv, kvh, wave, (wi.flags & kWaveSplit) ? 1 : 4, lane, st)) return;
 
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -880,15 +896,16 @@ hipError_t launch_attention_bf16(const Shape& s, const void* pool, const void* q
     // the last one present runs on the caller's stream and the other beside it on a side stream that waits
     // for the caller's stream first and that the caller's stream then waits for.
     int first[3], last = -1, n_present = 0;
+    const bool split = plan.split.blocks != nullptr;
+    const int32_t* n_class = split ? plan.split.n_blocks_class : plan.n_wg_class;  // (matrix units are never cut)
     for (int cls = 0, f = 0; cls < 3; ++cls) {
         first[cls] = f;
-        f += plan.n_wg_class[cls];
-        if (cls > 0 && plan.n_wg_class[cls] > 0) last = cls, ++n_present;
-        if ((int64_t)plan.n_wg_class[cls] * s.n_kv > 0x7fffffff) return hipErrorInvalidValue;
+        f += n_class[cls];
+        if (cls > 0 && n_class[cls] > 0) last = cls, ++n_present;
+        if ((int64_t)n_class[cls] * s.n_kv > 0x7fffffff) return hipErrorInvalidValue;
     }
     hipError_t e;
-    if (plan.n_wg_class[0] > 0 &&
-        (e = launch_attention_units_bf16(s, pool, q, plan, first[0], plan.n_wg_class[0], n_cand, part, st)) != hipSuccess)
+    if (n_class[0] > 0 && (e = launch_attention_units_bf16(s, pool, q, plan, first[0], n_class[0], n_cand, part, st)) != hipSuccess)
         return e;
     if (last < 0) return hipSuccess;
     const bool side_by_side = n_present > 1 && !cs.serial;
@@ -905,7 +922,7 @@ hipError_t launch_attention_bf16(const Shape& s, const void* pool, const void* q
     int side = 0;
     bool used[2] = {false, false};
     for (int cls = 1; cls < 3; ++cls) {
-        const int count = plan.n_wg_class[cls];
+        const int count = n_class[cls];
         if (count == 0) continue;
         hipStream_t on = st;
         if (cls != last && side_by_side) {
@@ -913,16 +930,24 @@ hipError_t launch_attention_bf16(const Shape& s, const void* pool, const void* q
             if ((e = hipStreamWaitEvent(on, cs.fork, 0)) != hipSuccess) return e;
         }
         const unsigned n_wg = (unsigned)count * (unsigned)s.n_kv;
-#define APAR_LAUNCH(NTV, F8V)                                                                                           \
-    hipLaunchKernelGGL((attention_bf16<NTV, F8V>), dim3(n_wg), dim3(256), 0, on, (const char*)pool, (const uint16_t*)q, \
+#define APAR_LAUNCH(NTV, F8V, SPLITV)                                                                                   \
+    hipLaunchKernelGGL((attention_bf16<NTV, F8V, SPLITV>), dim3(n_wg), dim3(256), 0, on, (const char*)pool, (const uint16_t*)q, \
                        plan, first[cls], n_cand, s.n_q, s.n_kv, s.group, s.scale_log2e, part,                           \
                        (const uint16_t*)cand_k, (const uint16_t*)cand_v, mask, (uint16_t*)out)
         if (s.fp8_sealed) {
-            if (cls == 1) APAR_LAUNCH(2, true);
-            else APAR_LAUNCH(1, true);
+            if (split) {
+                if (cls == 1) APAR_LAUNCH(2, true, true);
+                else APAR_LAUNCH(1, true, true);
+            } else {
+                if (cls == 1) APAR_LAUNCH(2, true, false);
+                else APAR_LAUNCH(1, true, false);
+            }
+        } else if (split) {
+            if (cls == 1) APAR_LAUNCH(2, false, true);
+            else APAR_LAUNCH(1, false, true);
         } else {
-            if (cls == 1) APAR_LAUNCH(2, false);
-            else APAR_LAUNCH(1, false);
+            if (cls == 1) APAR_LAUNCH(2, false, false);
+            else APAR_LAUNCH(1, false, false);
         }
 #undef APAR_LAUNCH
         if ((e = hipGetLastError()) != hipSuccess) return e;

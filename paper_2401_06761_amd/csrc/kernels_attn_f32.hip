@@ -22,6 +22,7 @@
 // Measured against one wavefront per query row in plain vector arithmetic, every row reading its blocks for
 // itself: twelve depth-2 trees (32 / 8 heads, d = 128, 0.28 GB read) 704 -> 355 us; one request of three
 // threads (2 heads, d = 64) 56 -> 16 us for the call; error against 64 bits 5.2e-7 -> 4.5e-7 and 2.2e-7 -> 1.9e-7.
+// With its heaviest units cut into slices (attn_split.hpp) the first of these takes 137 us, error 3.1e-7.
 //
 // A row that does not see a block meets it with probability 0, and 0 times an infinity or a NaN is a NaN.  Blocks of
 // other threads must not do that to a row: a wavefront whose results are not all finite takes its rows again, one by
@@ -29,6 +30,7 @@
 #include <hip/hip_runtime.h>
 
 #include "apar_internal.hpp"
+#include "attn_split.hpp"
 
 namespace apar {
 
@@ -98,8 +100,8 @@ __device__ __forceinline__ void accumulate(const f32x4 (&v)[4][D / 64], Row<D>& 
             st.o[jj] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[i][jj / 4][jj % 4], p[i], st.o[jj], 0, 0, 0);
 }
 
-// NT = 16-row tiles per wavefront.
-template <int D, int NT>
+// NT = 16-row tiles per wavefront; SPLIT: several workgroups per unit, each with a slice of its lists (attn_split.hpp).
+template <int D, int NT, bool SPLIT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attention_f32(
     const char* __restrict__ pool, const float* __restrict__ q, PlanDev plan, int wg_first, int n_cand, int n_q, int n_kv,
     int group, float scale_log2e, PartialBuf part, const float* __restrict__ cand_k, const float* __restrict__ cand_v,
@@ -112,9 +114,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int g4 = lane >> 4, c = lane & 15;
     const int kvh = blockIdx.x % n_kv;
-    const WgDesc* wg = plan.wgs + wg_first + blockIdx.x / n_kv;
-    const WaveItem wi = wg->w[wave];
-    if (wi.n_grp == 0) return;  // (a split unit's wavefronts all have rows; nobody waits for this one)
+    Slice slice;
+    if constexpr (SPLIT) {
+        slice = slice_of_block(plan.split, wg_first, n_kv);
+    } else {
+        slice.wg = wg_first + blockIdx.x / n_kv;
+    }
+    const WgDesc* wg = plan.wgs + slice.wg;
+    WaveItem wi = wg->w[wave];
+    if (wi.n_grp == 0) return;  // (a wave-split unit's wavefronts all have rows; nobody waits for this one)
+    int coop_ofs = wg->coop_ofs, n_coop = wg->n_coop, n_full = 0;
+    if constexpr (SPLIT) {
+        cut_list(slice, coop_ofs, n_coop, n_full);
+        cut_list(slice, wi.tile_ofs, wi.n_tiles, n_full);
+    }
     const char* head_base = pool + (int64_t)kvh * kTile;
     const int64_t block_stride = (int64_t)n_kv * kTile;
 
@@ -177,8 +190,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     };
     // both lists, one after the other; `shift`: the shared list's ranges count row groups from the workgroup's first
     for (int list = 0; list < 2; ++list) {
-        const TileRef* tiles = plan.tiles + (list == 0 ? wg->coop_ofs : wi.tile_ofs);
-        const int n = list == 0 ? wg->n_coop : wi.n_tiles;
+        const TileRef* tiles = plan.tiles + (list == 0 ? coop_ofs : wi.tile_ofs);
+        const int n = list == 0 ? n_coop : wi.n_tiles;
         const int shift = list == 0 ? wi.grp_lo - wg->grp_base : 0;
         // (tiles of the shared list that no row of this wavefront sees are passed over)
         auto next = [&](int t) {
@@ -213,7 +226,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     }
     // a multi-candidate call's candidates: one more tile of at most 8 token rows per thread, each visible to the rows
     // whose mask names it (the unit that writes the rows directly adds them)
-    const bool with_cands = (wi.flags & kWaveDirect) && cand_mask != nullptr && (wave == 0 || !(wi.flags & kWaveSplit));
+    const bool with_cands = (wi.flags & kWaveDirect) && cand_mask != nullptr && (wave == 0 || !(wi.flags & kWaveSplit)) && slice.s == 0;
     if (with_cands) {
         const int64_t tok_stride = (int64_t)n_kv * D;
         for (int ru = wi.grp_lo / n_sl; ru <= (wi.grp_lo + wi.n_grp - 1) / n_sl; ++ru) {
@@ -271,8 +284,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
                 m = m_new;
             };
             for (int list = 0; list < 2; ++list) {
-                const TileRef* tiles = plan.tiles + (list == 0 ? wg->coop_ofs : wi.tile_ofs);
-                const int n = list == 0 ? wg->n_coop : wi.n_tiles;
+                const TileRef* tiles = plan.tiles + (list == 0 ? coop_ofs : wi.tile_ofs);
+                const int n = list == 0 ? n_coop : wi.n_tiles;
                 const int jl = list == 0 ? j + (wi.grp_lo - wg->grp_base) : j;
                 for (int t = 0; t < n; ++t) {
                     const int meta = tiles[t].meta, lo = meta & 1023, hi = (meta >> 10) & 1023;
@@ -342,6 +355,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
         s0.m = mx;
         s0.l = g4 == 0 ? lt : 0.0f;
     }
+    if constexpr (SPLIT)
+        if (!fold_slices<NT, J>(plan.split, slice, n_kv, kvh, wave, (wi.flags & kWaveSplit) ? 1 : 4, lane, st)) return;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         float lt = st[nt].l;
@@ -372,23 +387,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 hipError_t launch_attention_f32(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand, PartialBuf part,
                                 const void* cand_k, const void* cand_v, const uint8_t* mask, void* out, hipStream_t st) {
     int first = 0;
+    const bool split = plan.split.blocks != nullptr;
+    const int32_t* n_class = split ? plan.split.n_blocks_class : plan.n_wg_class;
     for (int cls = 0; cls < 3; ++cls) {
-        const int64_t n = (int64_t)plan.n_wg_class[cls] * s.n_kv;
+        const int64_t n = (int64_t)n_class[cls] * s.n_kv;
         if (n > 0x7fffffff || (cls == 0 && n > 0)) return hipErrorInvalidValue;  // (fp32 pools have no matrix units)
         if (n == 0) continue;
-#define APAR_LAUNCH(DV, NTV)                                                                                             \
-    hipLaunchKernelGGL((attention_f32<DV, NTV>), dim3((unsigned)n), dim3(256), 0, st, (const char*)pool, (const float*)q, \
-                       plan, first, n_cand, s.n_q, s.n_kv, s.group, s.scale_log2e, part, (const float*)cand_k,           \
-                       (const float*)cand_v, mask, (float*)out)
+#define APAR_LAUNCH(DV, NTV, SPLITV)                                                                                      \
+    hipLaunchKernelGGL((attention_f32<DV, NTV, SPLITV>), dim3((unsigned)n), dim3(256), 0, st, (const char*)pool,          \
+                       (const float*)q, plan, first, n_cand, s.n_q, s.n_kv, s.group, s.scale_log2e, part,                \
+                       (const float*)cand_k, (const float*)cand_v, mask, (float*)out)
         if (s.d == 64) {
-            if (cls == 1) APAR_LAUNCH(64, 2);
-            else APAR_LAUNCH(64, 1);
+            if (split) {
+                if (cls == 1) APAR_LAUNCH(64, 2, true);
+                else APAR_LAUNCH(64, 1, true);
+            } else {
+                if (cls == 1) APAR_LAUNCH(64, 2, false);
+                else APAR_LAUNCH(64, 1, false);
+            }
+        } else if (split) {
+            if (cls == 1) APAR_LAUNCH(128, 2, true);
+            else APAR_LAUNCH(128, 1, true);
         } else {
-            if (cls == 1) APAR_LAUNCH(128, 2);
-            else APAR_LAUNCH(128, 1);
+            if (cls == 1) APAR_LAUNCH(128, 2, false);
+            else APAR_LAUNCH(128, 1, false);
         }
 #undef APAR_LAUNCH
-        first += plan.n_wg_class[cls];
+        first += n_class[cls];
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
