@@ -606,7 +606,12 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     return APAR_OK;
 }
 
-// Mean attended rows per query token from which a bf16 prefill call goes to the 32x32 kernel by itself.
+// A bf16 prefill call goes to the 32x32 kernel by itself when its threads bring this many query rows each (query tokens
+// x q heads of a kv group, on average: one wavefront's worth), or when a query token attends to this many rows.
+// Measured (us, row tiles / matrix kernel): 360 threads of walks around 1000, 32 kv heads, m query tokens each: m = 1
+// 904 / 656, 32 1007 / 677, whole segments (90 on average) 1652 / 1224; walks around 200: m = 1 255 / 279, 16 301 / 291, 32 309 / 300,
+// whole 589 / 489; 8 kv heads (4 rows per token): m = 4 84 / 90, 8 87 / 92, 16 95 / 105, 32 156 / 128, whole 417 / 353.
+constexpr int64_t kMatrixPrefillRows = 32;
 constexpr int64_t kMatrixPrefillMeanWalk = 1024;
 
 // bf16 pools: the matrix-core prefill kernel.  One workgroup per (thread, chunk of 128 / group query tokens);
@@ -716,13 +721,13 @@ int prefill_common(apar_pool* p, const void* q, const apar_thread* ids, const in
     if (rows > INT32_MAX / 2) return APAR_ERR_UNSUPPORTED;
     PlanHost& ph = p->plan;
     int rc = APAR_OK;
-    // bf16 pools have two kernels.  The 32x32 matrix-core kernel pays off once the walk of a query token is long
-    // (its fixed cost per workgroup is spread over many super-blocks); short walks stay on the row-tile kernel,
-    // whose plan also reads a prefix shared by sibling threads once for all of them.
+    // bf16 pools have two kernels.  The 32x32 matrix-core kernel wants a wavefront's worth of rows per thread or a long
+    // walk to spread its fixed cost per workgroup over; a few rows with short walks stay on the row-tile kernel.
     p->last_prefill_kernel = APAR_PREFILL_ROW_TILES;
     if (!p->dry_run && p->shape.dtype == APAR_BF16 && !p->shape.fp8_sealed && 16 % p->shape.group == 0 &&
         (p->prefill_kernel == APAR_PREFILL_MATRIX ||
-         (p->prefill_kernel == APAR_PREFILL_AUTO && attended >= kMatrixPrefillMeanWalk * rows))) {
+         (p->prefill_kernel == APAR_PREFILL_AUTO &&
+          (rows * p->shape.group >= kMatrixPrefillRows * n || attended >= kMatrixPrefillMeanWalk * rows)))) {
         p->last_prefill_kernel = APAR_PREFILL_MATRIX;
         return prefill_bf16(p, views, rows, attended, q, out, stream, t0);
     }
