@@ -159,6 +159,24 @@ struct Shape {
     int64_t block_bytes;          // n_kv tiles
 };
 
+// One block an append call writes to.
+struct AppendBlock {
+    int32_t dst;
+    int32_t copy_of;          // the shared block whose rows before the first new one it takes over (copy on write), or -1
+    int32_t first;            // source row of the first new row, or, with a list of source rows, its place in the list
+    int32_t slots;            // new rows: slots [slots & 255, slots >> 8)
+};
+static_assert(sizeof(AppendBlock) == 16, "four words of the staged tables");
+constexpr int kAppendInlineWords = 480;
+template <bool INLINE>
+struct AppendTables {
+    const int32_t* words;
+};
+template <>
+struct AppendTables<true> {
+    int32_t words[kAppendInlineWords];
+};
+
 // Partial results: for partial row p, candidate c, q head h the slot is
 // (p * n_cand + c) * n_q + h; part_o holds d floats per slot, part_ml two (max, sum).
 struct PartialBuf {
@@ -187,11 +205,12 @@ constexpr int kSplitMaxCut = 1024;
 hipError_t fixed_workspace_of_device(int device, char** out);
 
 // ---- launchers (defined next to their kernels) ------------------------------
-hipError_t launch_append_rows(const Shape& s, void* pool, const void* k, const void* v, const int32_t* dst_codes,
-                              const int32_t* src_rows, int n_rows, hipStream_t st);
+// words: n_blocks AppendBlocks, the n_open that stay open first, then n_src source rows; on the host (at most kAppendInlineWords words, which go along
+// with the kernel's arguments) or on the device.  (Weak: the host side also links without the kernels.)
+hipError_t launch_append_blocks(const Shape& s, void* pool, const void* k, const void* v, const int32_t* words, bool on_host,
+                                int n_blocks, int n_open, int n_src, hipStream_t st) __attribute__((weak));
 hipError_t launch_block_copies(const Shape& s, void* pool, const int32_t* src_dst_pairs, int n_pairs,
                                hipStream_t st);
-hipError_t launch_seal_blocks(const Shape& s, void* pool, const int32_t* blocks, int n_blocks, hipStream_t st);
 // words[pairs[2 i]] = pairs[2 i + 1] for i < n_pairs (device pointers; `pairs` 8-byte aligned)
 hipError_t launch_scatter_words(int32_t* words, const int32_t* pairs, int n_pairs, hipStream_t st);
 hipError_t launch_read_rows(const Shape& s, const void* pool, const int32_t* src_codes, int n_rows, void* k_out,

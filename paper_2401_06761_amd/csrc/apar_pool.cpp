@@ -90,6 +90,8 @@ struct apar_pool {
     std::vector<int32_t> prefill_tables;
     std::vector<int32_t> scratch_codes, scratch_copies, scratch_seals, scratch_commit_src;
     std::vector<apar_thread> scratch_commit_ids;
+    std::vector<AppendBlock> append_blocks;
+    std::vector<int32_t> append_of, append_src, append_words;
     apar_plan_info last_plan{};
     PlanHost plan;  // the last plan, kept for the next call to carry over, for reuse of its storage and for inspection
     // the call that plan was made or last carried over for: its listed threads, its parameters, and how many
@@ -164,6 +166,21 @@ int32_t pop_block(apar_pool* p) {
     return b;
 }
 
+int grow_slot(StageSlot& s, size_t bytes) {
+    if (!s.ev) HIP_TRY(hipEventCreateWithFlags(&s.ev, hipEventDisableTiming));
+    if (s.host) HIP_TRY(hipHostFree(s.host));
+    if (s.dev) HIP_TRY(hipFree(s.dev));
+    s.host = s.dev = nullptr;
+    s.cap = 0;
+    const size_t cap = align_up(std::max(bytes + bytes / 2, (size_t)1 << 20), 4096);
+    HIP_TRY(hipHostMalloc((void**)&s.host, cap, hipHostMallocDefault));
+    HIP_TRY(hipMalloc((void**)&s.dev, cap));
+    // (the runtime sets a pair of buffers up at its first copy, some 30 us that a call would wait for)
+    HIP_TRY(hipMemcpy(s.dev, s.host, 256, hipMemcpyHostToDevice));
+    s.cap = cap;
+    return APAR_OK;
+}
+
 int acquire_stage(apar_pool* p, size_t bytes, StageSlot** out) {
     if (&p->stage[p->next_slot] == p->resident) p->next_slot = (p->next_slot + 1) % kStageSlots;
     StageSlot& s = p->stage[p->next_slot];
@@ -175,21 +192,13 @@ int acquire_stage(apar_pool* p, size_t bytes, StageSlot** out) {
         p->wait_in_call_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - w0).count();
         if (p->profiling) p->host_wait_ms += p->wait_in_call_ms;
     }
-    if (!s.ev) HIP_TRY(hipEventCreateWithFlags(&s.ev, hipEventDisableTiming));
     // Growing a slot frees device memory, which waits for the GPU to drain: a slot grows to what the largest
     // request so far would need, not just to this one, so that the slots of a loop whose calls alternate
     // between small and large tables (row codes, plan updates) stop growing after one round.
     p->stage_want = std::max(p->stage_want, bytes);
     if (s.cap < bytes) {
-        bytes = p->stage_want;
-        if (s.host) HIP_TRY(hipHostFree(s.host));
-        if (s.dev) HIP_TRY(hipFree(s.dev));
-        s.host = s.dev = nullptr;
-        s.cap = 0;
-        size_t cap = align_up(std::max(bytes + bytes / 2, (size_t)1 << 20), 4096);
-        HIP_TRY(hipHostMalloc((void**)&s.host, cap, hipHostMallocDefault));
-        HIP_TRY(hipMalloc((void**)&s.dev, cap));
-        s.cap = cap;
+        const int rc = grow_slot(s, p->stage_want);
+        if (rc != APAR_OK) return rc;
     }
     *out = &s;
     return APAR_OK;
@@ -265,42 +274,93 @@ int writes_are_private(const apar_pool* p, const std::vector<int32_t>& codes, co
     return APAR_OK;
 }
 
-// src_rows (may be null): which row of k, v each appended row is taken from.
+// Writes the call's rows: row i to codes[i], taken from row src_rows[i] of k, v (row i if src_rows is null), one
+// AppendBlock per block written to.  A block is written by one thread only, whose rows fill its slots in order, but the
+// thread may be listed in several places: the block's rows are contiguous in the call or get a list of source rows.
 int run_append(apar_pool* p, const std::vector<int32_t>& codes, const std::vector<int32_t>& copies,
-               const std::vector<int32_t>& seals, const std::vector<int32_t>* src_rows, const void* k, const void* v,
-               hipStream_t st) {
-    const size_t copy_bytes = align_up(copies.size() * sizeof(int32_t), 256);
-    const size_t code_bytes = align_up(codes.size() * sizeof(int32_t), 256);
-    const size_t seal_bytes = align_up(seals.size() * sizeof(int32_t), 256);
-    const size_t src_bytes = src_rows ? src_rows->size() * sizeof(int32_t) : 0;
-    const size_t total = copy_bytes + code_bytes + seal_bytes + src_bytes;
+               const std::vector<int32_t>* src_rows, const void* k, const void* v, hipStream_t st) {
+    std::vector<AppendBlock>& blocks = p->append_blocks;
+    std::vector<int32_t>& at = p->append_of;  // per block of the pool: its place in `blocks` (-1 between calls)
+    std::vector<int32_t>& src = p->append_src;
+    blocks.clear();
+    src.clear();
+    bool contiguous = src_rows == nullptr;
+    const int n = (int)codes.size();
+    for (int i = 0; i < n; ++i) {
+        const int32_t block = codes[i] / kBlockTokens, slot = codes[i] % kBlockTokens;
+        int32_t& b = at[block];
+        if (b < 0) {
+            b = (int32_t)blocks.size();
+            blocks.push_back(AppendBlock{block, -1, i, slot | (slot + 1) << 8});
+        } else {
+            AppendBlock& ab = blocks[b];
+            contiguous = contiguous && i == ab.first + (ab.slots >> 8) - (ab.slots & 255);
+            ab.slots += 1 << 8;
+        }
+    }
+    if (!contiguous) {  // source rows, block by block
+        int32_t ofs = 0;
+        for (AppendBlock& b : blocks) {
+            b.first = ofs;
+            ofs += (b.slots >> 8) - (b.slots & 255);
+        }
+        src.resize(n);
+        for (int i = 0; i < n; ++i) {
+            const AppendBlock& b = blocks[at[codes[i] / kBlockTokens]];
+            src[b.first + codes[i] % kBlockTokens - (b.slots & 255)] = src_rows ? (*src_rows)[i] : i;
+        }
+    }
+    // Copy on write: the copy takes its first rows from the shared block as it is written.  A shared block that its last
+    // holder fills and seals in this very call would change under its readers: then the copies are made first.
+    bool copies_first = false;
+    for (size_t i = 0; i + 1 < copies.size(); i += 2)
+        copies_first = copies_first || (at[copies[i]] >= 0 && blocks[at[copies[i]]].slots >> 8 == kBlockTokens);
+    if (!copies_first)
+        for (size_t i = 0; i + 1 < copies.size(); i += 2) blocks[at[copies[i + 1]]].copy_of = copies[i];
+    for (const AppendBlock& b : blocks) at[b.dst] = -1;
+    int n_open = (int)blocks.size();  // the blocks that are not sealed come first
+    if (p->shape.dtype != APAR_F32)
+        n_open = (int)(std::partition(blocks.begin(), blocks.end(), [](const AppendBlock& b) { return b.slots >> 8 < kBlockTokens; }) -
+                       blocks.begin());
+
+    const size_t words = blocks.size() * 4 + src.size();
+    const size_t copy_words = copies_first ? copies.size() : 0;
+    const bool inlined = words <= (size_t)kAppendInlineWords && copy_words == 0;
+    const int32_t* tables = (const int32_t*)blocks.data();
     StageSlot* s = nullptr;
-    int rc = acquire_stage(p, total, &s);
-    if (rc != APAR_OK) return rc;
-    if (!copies.empty()) memcpy(s->host, copies.data(), copies.size() * sizeof(int32_t));
-    memcpy(s->host + copy_bytes, codes.data(), codes.size() * sizeof(int32_t));
-    if (!seals.empty()) memcpy(s->host + copy_bytes + code_bytes, seals.data(), seals.size() * sizeof(int32_t));
-    if (src_bytes) memcpy(s->host + copy_bytes + code_bytes + seal_bytes, src_rows->data(), src_bytes);
-    if ((rc = upload(p, s, total, st)) != APAR_OK) return rc;
+    int rc = APAR_OK;
+    if (inlined) {
+        if (!src.empty()) {
+            p->append_words.assign(tables, tables + blocks.size() * 4);
+            p->append_words.insert(p->append_words.end(), src.begin(), src.end());
+            tables = p->append_words.data();
+        }
+    } else {
+        const size_t total = (words + copy_words) * sizeof(int32_t);
+        if ((rc = acquire_stage(p, total, &s)) != APAR_OK) return rc;
+        int32_t* host = (int32_t*)s->host;
+        memcpy(host, blocks.data(), blocks.size() * sizeof(AppendBlock));
+        if (!src.empty()) memcpy(host + blocks.size() * 4, src.data(), src.size() * sizeof(int32_t));
+        if (copy_words) memcpy(host + words, copies.data(), copy_words * sizeof(int32_t));
+        if ((rc = upload(p, s, total, st)) != APAR_OK) return rc;
+        tables = (const int32_t*)s->dev;
+    }
     EventPair ev;
     if (p->profiling) {
         if ((rc = new_event(p, &ev.a)) != APAR_OK || (rc = new_event(p, &ev.b)) != APAR_OK) return rc;
         HIP_TRY(hipEventRecord(ev.a, st));
     }
-    if (!copies.empty())
-        HIP_TRY(launch_block_copies(p->shape, p->kv, (const int32_t*)s->dev, (int)(copies.size() / 2), st));
-    HIP_TRY(launch_append_rows(p->shape, p->kv, k, v, (const int32_t*)(s->dev + copy_bytes),
-                               src_bytes ? (const int32_t*)(s->dev + copy_bytes + code_bytes + seal_bytes) : nullptr,
-                               (int)codes.size(), st));
-    if (!seals.empty())
-        HIP_TRY(launch_seal_blocks(p->shape, p->kv, (const int32_t*)(s->dev + copy_bytes + code_bytes), (int)seals.size(), st));
+    if (copy_words) HIP_TRY(launch_block_copies(p->shape, p->kv, tables + words, (int)(copy_words / 2), st));
+    HIP_TRY(launch_append_blocks(p->shape, p->kv, k, v, tables, inlined, (int)blocks.size(), n_open, (int)src.size(), st));
     if (p->profiling) {
         HIP_TRY(hipEventRecord(ev.b, st));
         p->append_events.push_back(ev);
         p->n_append_calls += 1;
     }
-    HIP_TRY(hipEventRecord(s->ev, st));
-    s->pending = true;
+    if (s) {
+        HIP_TRY(hipEventRecord(s->ev, st));
+        s->pending = true;
+    }
     return APAR_OK;
 }
 
@@ -835,7 +895,16 @@ int apar_pool_create(const apar_pool_config* cfg, void* kv_dev, size_t kv_bytes,
             rc = APAR_ERR_HIP;
         p->split_bytes = std::min(kSplitStateBytes, std::max((size_t)1 << 20, (size_t)(block * cfg->num_blocks) / 8));
         if (rc == APAR_OK && !hip_ok(hipMalloc((void**)&p->split_dev, p->split_bytes), "hipMalloc(split)")) rc = APAR_ERR_HIP;
+        // the staging slots at their smallest, so that a pool's first calls do not stop to allocate them (appends used to
+        // by the time of the first decode call)
+        for (StageSlot& s : p->stage)
+            if (rc == APAR_OK) rc = grow_slot(s, 0);
         if (rc != APAR_OK) {
+            for (StageSlot& s : p->stage) {
+                if (s.host) (void)hipHostFree(s.host);
+                if (s.dev) (void)hipFree(s.dev);
+                if (s.ev) (void)hipEventDestroy(s.ev);
+            }
             if (p->split_dev) (void)hipFree(p->split_dev);
             if (p->fixed_up) (void)hipEventDestroy(p->fixed_up);
             if (p->fixed_host) (void)hipHostFree(p->fixed_host);
@@ -857,6 +926,7 @@ int apar_pool_create(const apar_pool_config* cfg, void* kv_dev, size_t kv_bytes,
     p->free_stack.resize(cfg->num_blocks);
     for (int64_t i = 0; i < cfg->num_blocks; ++i) p->free_stack[i] = (int32_t)(cfg->num_blocks - 1 - i);
     p->seg_of.assign(cfg->num_blocks, -1);
+    if (!p->dry_run) p->append_of.assign(cfg->num_blocks, -1);
     *out = p;
     return APAR_OK;
 }
@@ -942,7 +1012,7 @@ int apar_append_kv(apar_pool* p, apar_thread thread, const void* k_dev, const vo
     if (p->check_writes && writes_are_private(p, codes, copies, seals) != APAR_OK) return APAR_ERR_INTERNAL;
     if (p->dry_run) return APAR_OK;
     DeviceGuard guard(p->device);
-    return run_append(p, codes, copies, seals, nullptr, k_dev, v_dev, (hipStream_t)hip_stream);
+    return run_append(p, codes, copies, nullptr, k_dev, v_dev, (hipStream_t)hip_stream);
 }
 
 // One row per entry of `threads` (a thread may repeat), row i taken from row src_rows[i] of k_dev, v_dev
@@ -990,7 +1060,7 @@ static int append_rows_of(apar_pool* p, const apar_thread* threads, int n, const
     if (p->check_writes && writes_are_private(p, codes, copies, seals) != APAR_OK) return APAR_ERR_INTERNAL;
     if (p->dry_run) return APAR_OK;
     DeviceGuard guard(p->device);
-    return run_append(p, codes, copies, seals, src_rows, k_dev, v_dev, (hipStream_t)hip_stream);
+    return run_append(p, codes, copies, src_rows, k_dev, v_dev, (hipStream_t)hip_stream);
 }
 
 int apar_append_kv_batch(apar_pool* p, const apar_thread* threads, int n, const void* k_dev, const void* v_dev,

@@ -17,64 +17,22 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
 }
 
 // ---------------------------------------------------------------------------
-// Row writes.  Row i of the call is taken from row src_rows[i] of k and v (from row
-// i when src_rows is null).  bf16: 32 lanes per (row, kv head), eight pairs per
-// workgroup; fp32: one wavefront per pair.
-// bf16 pools keep a block that is still filling in plain row-major form (K rows
-// then V rows, 256 contiguous bytes each), so an appended row is two full-line
-// writes per half; seal_blocks_bf16 rewrites a block into matrix-core order once
-// its sixteenth slot is written.
+// Appended rows, one pass per block: a wavefront takes one (block the call writes to, kv head).  The block's rows
+// [s0, s1) come from the call's k and v; where the block is the copy-on-write copy of a shared tail, rows [0, s0) come
+// from that.  A block that stays open is written row by row (256 or 512 contiguous bytes a half).  A block that is full
+// now (16-bit pools) is SEALED: its sixteen rows are gathered in LDS - those before s0 from the block itself or from the
+// block it copies - and written once, in matrix-core order.
+// Before, three kernels did this: block copies, row writes, and a pass that read full blocks back and rewrote them.
+// Their time against this kernel's (us, with the two events around them): prompts of 300, 1 k, 4 k, 8 k rows, 8 kv heads
+// 8.9, 10.0, 17.5, 28.3 -> 6.8, 7.8, 9.6, 14.2; one row each for 3.8 k threads, 32 heads, one in sixteen sealing 56 -> 58;
+// 5 and 1000 threads forked off a tail of 9 rows 11.2, 74 -> 8.7, 45, off one of 15 (copied and sealed) 10.8, 194 -> 6.9, 67.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void append_rows_bf16(char* __restrict__ pool, const uint16_t* __restrict__ k,
-                                                        const uint16_t* __restrict__ v,
-                                                        const int32_t* __restrict__ codes,
-                                                        const int32_t* __restrict__ src_rows, int n_rows, int n_kv,
-                                                        int64_t tile_bytes) {
-    const int64_t pair = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 5);  // (row, kv head), heads fastest
-    const int lane = threadIdx.x & 31;
-    if (pair >= (int64_t)n_rows * n_kv) return;
-    const int row = (int)(pair / n_kv), h = (int)(pair - (int64_t)row * n_kv);
-    const int32_t code = codes[row];
-    const int slot = code & 15;
-    char* tile = pool + ((int64_t)(code >> 4) * n_kv + h) * tile_bytes;
-    const int64_t from = src_rows ? src_rows[row] : row;
-    const uint16_t* src = (lane < 16 ? k : v) + (from * n_kv + h) * 128 + (lane & 15) * 8;
-    *reinterpret_cast<uint4*>(tile + (lane < 16 ? 0 : 4096) + slot * 256 + (lane & 15) * 16) =
-        *reinterpret_cast<const uint4*>(src);
-}
+// A tile half's rows in LDS: padded, so that sixteen lanes reading one piece of sixteen rows meet sixteen banks.
+constexpr int kSealRowStride = 272;
 
-// In-place row-major -> matrix-core order for blocks that just became full.
-// One workgroup per (block, kv head): the 8 KiB tile goes through LDS.
-__global__ __launch_bounds__(256) void seal_blocks_bf16(char* __restrict__ pool, const int32_t* __restrict__ blocks,
-                                                        int n_kv, int64_t tile_bytes) {
-    __shared__ __attribute__((aligned(16))) char raw[8192];
-    const int t = threadIdx.x;
-    char* tile = pool + ((int64_t)blocks[blockIdx.x] * n_kv + blockIdx.y) * tile_bytes;
-    reinterpret_cast<uint4*>(raw)[t] = reinterpret_cast<const uint4*>(tile)[t];
-    reinterpret_cast<uint4*>(raw)[256 + t] = reinterpret_cast<const uint4*>(tile)[256 + t];
-    __syncthreads();
-    // piece t of either half sits at byte t*16 of the half: load index r = t / 64, lane = t % 64
-    const int r = t >> 6, lane = t & 63, g = lane >> 4, c = lane & 15;
-    // K piece: K[token c][dims 32g + 8r .. +8]
-    const uint4 kp = *reinterpret_cast<const uint4*>(raw + c * 256 + (32 * g + 8 * r) * 2);
-    // V piece: V[tokens 4g..4g+3][dim 32r + c], then V[tokens 4g..4g+3][dim 32r + 16 + c]
-    const uint16_t* vr = reinterpret_cast<const uint16_t*>(raw + 4096);
-    uint32_t w[4];
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-        const int dim = 32 * r + 16 * hh + c;
-        w[2 * hh] = (uint32_t)vr[(4 * g + 0) * 128 + dim] | ((uint32_t)vr[(4 * g + 1) * 128 + dim] << 16);
-        w[2 * hh + 1] = (uint32_t)vr[(4 * g + 2) * 128 + dim] | ((uint32_t)vr[(4 * g + 3) * 128 + dim] << 16);
-    }
-    reinterpret_cast<uint4*>(tile)[t] = kp;
-    reinterpret_cast<uint4*>(tile)[256 + t] = make_uint4(w[0], w[1], w[2], w[3]);
-}
-
-// fp8 pools: a block that just became full is rewritten from bf16 rows into fp8 codes in matrix-core order,
-// with one power-of-two scale for its K half and one for its V half: the smallest power of two s for which
-// max |x| / s <= 448, the largest e4m3 magnitude (1 if the half is all zeros), so that the codes use the top
-// binade of the format.  Codes are rounded to nearest even by the hardware conversion.  One workgroup per
-// (block, kv head); the 8 KiB of rows go through LDS.
+// fp8 pools: the smallest power of two s for which max |x| / s <= 448, the largest e4m3 magnitude (1 if the half is
+// all zeros), so that the codes use the top binade of the format.  Codes are rounded to nearest even by the hardware
+// conversion.
 __device__ __forceinline__ float fp8_scale_for(float amax) {
     if (!(amax > 0.0f) || !(amax < INFINITY)) return 1.0f;
     int k;
@@ -83,72 +41,147 @@ __device__ __forceinline__ float fp8_scale_for(float amax) {
     return ldexpf(1.0f, e < -126 ? -126 : e);
 }
 
-__global__ __launch_bounds__(256) void seal_blocks_fp8(char* __restrict__ pool, const int32_t* __restrict__ blocks,
-                                                       int n_kv, int64_t tile_bytes) {
-    __shared__ __attribute__((aligned(16))) char raw[8192];
-    __shared__ float wave_max[2][4];
-    const int t = threadIdx.x;
-    char* tile = pool + ((int64_t)blocks[blockIdx.x] * n_kv + blockIdx.y) * tile_bytes;
-    const uint4 a = reinterpret_cast<const uint4*>(tile)[t], b = reinterpret_cast<const uint4*>(tile)[256 + t];
-    reinterpret_cast<uint4*>(raw)[t] = a;
-    reinterpret_cast<uint4*>(raw)[256 + t] = b;
-    // largest magnitude of either half (thread t holds 8 K elements in a and 8 V elements in b)
-    float mk = 0.0f, mv = 0.0f;
-    const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        mk = fmaxf(mk, fmaxf(fabsf(__uint_as_float(aw[i] << 16)), fabsf(__uint_as_float(aw[i] & 0xffff0000u))));
-        mv = fmaxf(mv, fmaxf(fabsf(__uint_as_float(bw[i] << 16)), fabsf(__uint_as_float(bw[i] & 0xffff0000u))));
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        mk = fmaxf(mk, __shfl_xor(mk, o, 64));
-        mv = fmaxf(mv, __shfl_xor(mv, o, 64));
-    }
-    if ((t & 63) == 0) wave_max[0][t >> 6] = mk, wave_max[1][t >> 6] = mv;
-    __syncthreads();
-    const float ks = fp8_scale_for(fmaxf(fmaxf(wave_max[0][0], wave_max[0][1]), fmaxf(wave_max[0][2], wave_max[0][3])));
-    const float vs = fp8_scale_for(fmaxf(fmaxf(wave_max[1][0], wave_max[1][1]), fmaxf(wave_max[1][2], wave_max[1][3])));
-    const float kinv = 1.0f / ks, vinv = 1.0f / vs;  // powers of two: exact
-    // thread t writes the 8 bytes of piece r of lane `lane` of each half: r = t / 64
-    const int r = t >> 6, lane = t & 63, g = lane >> 4, c = lane & 15;
-    const uint16_t* kr = reinterpret_cast<const uint16_t*>(raw) + c * 128 + 32 * g + 8 * r;  // K[token c][dims 32g + 8r ..]
-    const uint16_t* vr = reinterpret_cast<const uint16_t*>(raw + 4096);
-    float kx[8], vx[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) kx[i] = bf16_to_f32(kr[i]) * kinv;
+// One half of a tile, its sixteen rows in LDS, in matrix-core order (a lane's pieces r = 0..3; see the pool layout):
+// K[token c][dims 32g + 8r .. +8];  V[tokens 4g..4g+3][dim 32r + c], then [dim 32r + 16 + c].
+__device__ __forceinline__ void k_piece(const char* rows, int lane, int r, uint16_t (&x)[8]) {
+    *reinterpret_cast<uint4*>(x) = *reinterpret_cast<const uint4*>(rows + (lane & 15) * kSealRowStride + (32 * (lane >> 4) + 8 * r) * 2);
+}
+__device__ __forceinline__ void v_piece(const char* rows, int lane, int r, uint16_t (&x)[8]) {
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) vx[4 * hh + i] = bf16_to_f32(vr[(4 * g + i) * 128 + 32 * r + 16 * hh + c]) * vinv;
-    uint32_t kw[2], vw[2];
-#pragma unroll
-    for (int w = 0; w < 2; ++w) {
-        kw[w] = __builtin_amdgcn_cvt_pk_fp8_f32(kx[4 * w], kx[4 * w + 1], 0, false);
-        kw[w] = __builtin_amdgcn_cvt_pk_fp8_f32(kx[4 * w + 2], kx[4 * w + 3], kw[w], true);
-        vw[w] = __builtin_amdgcn_cvt_pk_fp8_f32(vx[4 * w], vx[4 * w + 1], 0, false);
-        vw[w] = __builtin_amdgcn_cvt_pk_fp8_f32(vx[4 * w + 2], vx[4 * w + 3], vw[w], true);
-    }
-    const int ofs = (r >> 1) * 1024 + lane * 16 + (r & 1) * 8;
-    *reinterpret_cast<uint2*>(tile + ofs) = make_uint2(kw[0], kw[1]);
-    *reinterpret_cast<uint2*>(tile + kFp8HalfBytes + ofs) = make_uint2(vw[0], vw[1]);
-    if (t == 0) *reinterpret_cast<float2*>(tile + kFp8ScaleOfs) = make_float2(ks, vs);
+        for (int i = 0; i < 4; ++i)
+            x[4 * hh + i] = *reinterpret_cast<const uint16_t*>(rows + (4 * (lane >> 4) + i) * kSealRowStride + (32 * r + 16 * hh + (lane & 15)) * 2);
 }
 
-__global__ __launch_bounds__(64) void append_rows_f32(char* __restrict__ pool, const float* __restrict__ k,
-                                                      const float* __restrict__ v, const int32_t* __restrict__ codes,
-                                                      const int32_t* __restrict__ src_rows, int n_kv, int d,
-                                                      int64_t tile_bytes) {
-    const int row = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-    const int32_t code = codes[row];
-    const int slot = code & 15;
-    float* tile = reinterpret_cast<float*>(pool + ((int64_t)(code >> 4) * n_kv + h) * tile_bytes);
-    const int64_t from = src_rows ? src_rows[row] : row;
-    const float* ksrc = k + (from * n_kv + h) * d;
-    const float* vsrc = v + (from * n_kv + h) * d;
-    for (int x = lane; x < d; x += 64) {
-        tile[slot * d + x] = ksrc[x];
-        tile[16 * d + slot * d + x] = vsrc[x];
+// fp8 codes of a piece under the inverse of the half's scale (a power of two: exact)
+__device__ __forceinline__ uint2 fp8_piece(const uint16_t (&x)[8], float inv) {
+    uint32_t w[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        w[i] = __builtin_amdgcn_cvt_pk_fp8_f32(bf16_to_f32(x[4 * i]) * inv, bf16_to_f32(x[4 * i + 1]) * inv, 0, false);
+        w[i] = __builtin_amdgcn_cvt_pk_fp8_f32(bf16_to_f32(x[4 * i + 2]) * inv, bf16_to_f32(x[4 * i + 3]) * inv, w[i], true);
+    }
+    return make_uint2(w[0], w[1]);
+}
+
+// ROW: bytes of one row of a half.  SEAL: 0 fp32 pools (nothing is sealed), 1 bf16, 2 fp8.  INLINE: the descriptors and
+// the source rows come with the kernel's arguments (the first one, so that they start the argument segment).
+// The blocks that stay open come first, n_open of them: the first workgroups write those, as many lanes as a row has
+// 16-byte pieces per (block, kv head); the others take the full ones, a wavefront per (block, kv head).
+template <int ROW, int SEAL, bool INLINE>
+__global__ __launch_bounds__(256) void append_blocks(AppendTables<INLINE> tables, char* __restrict__ pool, const char* __restrict__ k,
+                                                     const char* __restrict__ v, int n_blocks, int n_open, int n_src, int n_kv) {
+    // one half's rows per wavefront: the open blocks' workgroups want the occupancy
+    __shared__ __attribute__((aligned(16))) char lds[SEAL ? 4 : 1][SEAL ? 16 * kSealRowStride : 16];
+    constexpr int64_t kTile = 2 * 16 * ROW;
+    constexpr int kLanes = 2 * ROW / 16;      // lanes of one row: its K half, then its V half
+    auto block_at = [&](int at) -> AppendBlock {
+        if constexpr (INLINE) {
+            typedef const AppendBlock __attribute__((address_space(4))) * Blocks;
+            const auto* p = (Blocks)__builtin_amdgcn_kernarg_segment_ptr() + at;
+            return AppendBlock{p->dst, p->copy_of, p->first, p->slots};
+        } else {
+            return reinterpret_cast<const AppendBlock*>(tables.words)[at];
+        }
+    };
+    auto src_of = [&](int i) -> int {
+        if constexpr (INLINE) {
+            typedef const int32_t __attribute__((address_space(4))) * Words;
+            return ((Words)__builtin_amdgcn_kernarg_segment_ptr())[4 * n_blocks + i];
+        } else {
+            return tables.words[4 * n_blocks + i];
+        }
+    };
+    // 16 bytes of slot `slot` (before s1) of a block, at `ofs` of half `half` (one load, whose address is chosen: a branch
+    // around it would make every load wait where it is issued)
+    auto fetch = [&](const AppendBlock& b, int h, int half, int slot, int ofs) -> uint4 {
+        const int s0 = b.slots & 255, row = b.first + max(slot - s0, 0);
+        const int64_t from = n_src ? src_of(row) : row;
+        const char* fresh = (half ? v : k) + (from * n_kv + h) * ROW;
+        const char* old = pool + ((int64_t)(b.copy_of >= 0 ? b.copy_of : b.dst) * n_kv + h) * kTile + half * 16 * ROW + slot * ROW;
+        return *reinterpret_cast<const uint4*>((slot < s0 ? old : fresh) + ofs);
+    };
+    constexpr int kPairs = 256 / kLanes;
+    const int open_wgs = (int)(((int64_t)n_open * n_kv + kPairs - 1) / kPairs);
+    if ((int)blockIdx.x < open_wgs) {
+        const int pair = (int)blockIdx.x * kPairs + (int)threadIdx.x / kLanes;  // (open block, kv head), heads fastest
+        const int at = pair / n_kv, h = pair - at * n_kv;
+        if (at >= n_open) return;
+        const AppendBlock b = block_at(at);
+        const int l = (int)threadIdx.x % kLanes, half = l / (kLanes / 2), ofs = (l % (kLanes / 2)) * 16;
+        char* dst = pool + ((int64_t)b.dst * n_kv + h) * kTile + half * 16 * ROW + ofs;
+        const int s1 = b.slots >> 8;
+        int s = b.copy_of >= 0 ? 0 : b.slots & 255;
+        if (s + 1 == s1) {
+            *reinterpret_cast<uint4*>(dst + s * ROW) = fetch(b, h, half, s, ofs);
+            return;
+        }
+        for (; s < s1; s += 4) {  // four rows in flight
+            uint4 x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = fetch(b, h, half, min(s + i, s1 - 1), ofs);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (s + i < s1) *reinterpret_cast<uint4*>(dst + (s + i) * ROW) = x[i];
+        }
+        return;
+    }
+    if constexpr (SEAL != 0) {
+        const int lane = threadIdx.x & 63;
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        const int item = ((int)blockIdx.x - open_wgs) * 4 + wave;  // (full block, kv head), heads fastest
+        const int at = item / n_kv, h = item - at * n_kv;
+        if (at >= n_blocks - n_open) return;
+        const AppendBlock b = block_at(n_open + at);
+        constexpr int kRows = 64 / kLanes;    // rows a wavefront moves at once
+        const int l = lane % kLanes, half = l / (kLanes / 2), chunk = (l % (kLanes / 2)) * 16, sub = lane / kLanes;
+        char* tile = pool + ((int64_t)b.dst * n_kv + h) * kTile;
+        char* rows = lds[wave];
+        uint4 x[16 / kRows];
+#pragma unroll
+        for (int i = 0; i < 16 / kRows; ++i) x[i] = fetch(b, h, half, i * kRows + sub, chunk);
+        float scale[2] = {1.0f, 1.0f};
+        if constexpr (SEAL == 2) {
+            float top = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 16 / kRows; ++i) {
+                const uint32_t w[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    top = fmaxf(top, fmaxf(fabsf(__uint_as_float(w[e] << 16)), fabsf(__uint_as_float(w[e] & 0xffff0000u))));
+            }
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1)
+                if (o != kLanes / 2) top = fmaxf(top, __shfl_xor(top, o, 64));
+            const float other = __shfl_xor(top, kLanes / 2, 64);
+            scale[0] = fp8_scale_for(half ? other : top);
+            scale[1] = fp8_scale_for(half ? top : other);
+        }
+        // (every row is in registers by the time the first piece is written: the tile may be overwritten in place)
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+            __builtin_amdgcn_wave_barrier();
+            if (half == hf) {
+#pragma unroll
+                for (int i = 0; i < 16 / kRows; ++i) *reinterpret_cast<uint4*>(rows + (i * kRows + sub) * kSealRowStride + chunk) = x[i];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                __attribute__((aligned(16))) uint16_t e[8];
+                if (hf == 0) k_piece(rows, lane, r, e);
+                else v_piece(rows, lane, r, e);
+                if constexpr (SEAL == 2)
+                    *reinterpret_cast<uint2*>(tile + hf * kFp8HalfBytes + (r >> 1) * 1024 + lane * 16 + (r & 1) * 8) = fp8_piece(e, 1.0f / scale[hf]);
+                else
+                    *reinterpret_cast<uint4*>(tile + hf * 4096 + r * 1024 + lane * 16) = *reinterpret_cast<const uint4*>(e);
+            }
+        }
+        if constexpr (SEAL == 2)
+            if (lane == 0) *reinterpret_cast<float2*>(tile + kFp8ScaleOfs) = make_float2(scale[0], scale[1]);
     }
 }
 
@@ -355,42 +388,37 @@ hipError_t fixed_workspace_of_device(int device, char** out) {
     return hipSuccess;
 }
 
-hipError_t launch_append_rows(const Shape& s, void* pool, const void* k, const void* v, const int32_t* dst_codes,
-                              const int32_t* src_rows, int n_rows, hipStream_t st) {
-    if (n_rows <= 0) return hipSuccess;
-    // grid.x carries the rows: go through them in slices that fit the grid limits
-    const int kMaxRows = 1 << 20;
-    for (int r0 = 0; r0 < n_rows; r0 += kMaxRows) {
-        const int nr = n_rows - r0 < kMaxRows ? n_rows - r0 : kMaxRows;
-        dim3 grid(nr, s.n_kv);
-        // with a source index the rows are addressed from the arrays' start; without, slice by slice
-        const int64_t row_elems = src_rows ? 0 : (int64_t)s.n_kv * s.d;
-        const int32_t* from = src_rows ? src_rows + r0 : nullptr;
-        if (s.dtype == APAR_BF16) {
-            const unsigned n_wg = (unsigned)(((int64_t)nr * s.n_kv + 7) / 8);
-            hipLaunchKernelGGL(append_rows_bf16, dim3(n_wg), dim3(256), 0, st, (char*)pool,
-                               (const uint16_t*)k + r0 * row_elems, (const uint16_t*)v + r0 * row_elems,
-                               dst_codes + r0, from, nr, s.n_kv, s.tile_bytes);
-        } else {
-            hipLaunchKernelGGL(append_rows_f32, grid, dim3(64), 0, st, (char*)pool, (const float*)k + r0 * row_elems,
-                               (const float*)v + r0 * row_elems, dst_codes + r0, from, s.n_kv, s.d, s.tile_bytes);
-        }
+hipError_t launch_append_blocks(const Shape& s, void* pool, const void* k, const void* v, const int32_t* words, bool on_host,
+                                int n_blocks, int n_open, int n_src, hipStream_t st) {
+    if (n_blocks <= 0) return hipSuccess;
+    if (s.dtype == APAR_F32 && n_open != n_blocks) return hipErrorInvalidValue;  // (fp32 blocks are never sealed)
+    const int pairs = s.dtype == APAR_F32 && s.d == 128 ? 4 : 8;
+    const int64_t grid = ((int64_t)n_open * s.n_kv + pairs - 1) / pairs + ((int64_t)(n_blocks - n_open) * s.n_kv + 3) / 4;
+    if (grid > 0x7fffffff || (int64_t)n_blocks * s.n_kv > 0x7fffffff) return hipErrorInvalidValue;
+    AppendTables<false> ptr{words};
+    AppendTables<true> args;
+    if (on_host) {
+        if ((size_t)4 * n_blocks + n_src > sizeof(args.words) / sizeof(int32_t)) return hipErrorInvalidValue;
+        for (int i = 0; i < 4 * n_blocks + n_src; ++i) args.words[i] = words[i];
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_seal_blocks(const Shape& s, void* pool, const int32_t* blocks, int n_blocks, hipStream_t st) {
-    if (n_blocks <= 0 || s.dtype != APAR_BF16) return hipSuccess;
-    const int kSlice = 1 << 20;
-    for (int b0 = 0; b0 < n_blocks; b0 += kSlice) {
-        const int nb = n_blocks - b0 < kSlice ? n_blocks - b0 : kSlice;
-        if (s.fp8_sealed)
-            hipLaunchKernelGGL(seal_blocks_fp8, dim3(nb, s.n_kv), dim3(256), 0, st, (char*)pool, blocks + b0, s.n_kv,
-                               s.tile_bytes);
-        else
-            hipLaunchKernelGGL(seal_blocks_bf16, dim3(nb, s.n_kv), dim3(256), 0, st, (char*)pool, blocks + b0, s.n_kv,
-                               s.tile_bytes);
+#define APAR_APPEND(ROWV, SEALV)                                                                                           \
+    do {                                                                                                                   \
+        if (on_host)                                                                                                       \
+            hipLaunchKernelGGL((append_blocks<ROWV, SEALV, true>), dim3((unsigned)grid), dim3(256), 0, st, args,           \
+                               (char*)pool, (const char*)k, (const char*)v, n_blocks, n_open, n_src, s.n_kv);                      \
+        else                                                                                                               \
+            hipLaunchKernelGGL((append_blocks<ROWV, SEALV, false>), dim3((unsigned)grid), dim3(256), 0, st, ptr,           \
+                               (char*)pool, (const char*)k, (const char*)v, n_blocks, n_open, n_src, s.n_kv);                      \
+    } while (0)
+    if (s.dtype == APAR_F32) {
+        if (s.d == 64) APAR_APPEND(256, 0);
+        else APAR_APPEND(512, 0);
+    } else if (s.fp8_sealed) {
+        APAR_APPEND(256, 2);
+    } else {
+        APAR_APPEND(256, 1);
     }
+#undef APAR_APPEND
     return hipGetLastError();
 }
 
