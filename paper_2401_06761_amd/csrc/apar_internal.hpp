@@ -138,7 +138,32 @@ struct PlanDev {              // device pointers of one staged plan
     int32_t n_threads;
     int32_t rows_per_thread, rows_per_slice, n_slices;
     SplitPlan split;
+    const int32_t* inline_words; // small plans: the tables on the host, to go along with the kernel's arguments; every table
+    int32_t n_inline_words;      // pointer above (split.blocks, always there then, included) is its offset in bytes
 };
+
+// The first argument of the attention kernels; they take it from the head of the argument segment.
+constexpr int kPlanInlineWords = 832;
+template <bool INLINE>
+struct PlanWords {
+    const int32_t* unused;
+};
+template <>
+struct PlanWords<true> {
+    int32_t words[kPlanInlineWords];
+};
+#if defined(__HIP_DEVICE_COMPILE__)
+// A plan whose tables are the kernel's first argument.
+__device__ __forceinline__ void plan_from_arguments(PlanDev& plan) {
+    const char* base = (const char*)(const char __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr();
+    plan.wgs = (const WgDesc*)(base + (size_t)plan.wgs);
+    plan.tiles = (const TileRef*)(base + (size_t)plan.tiles);
+    plan.dfs_threads = (const int32_t*)(base + (size_t)plan.dfs_threads);
+    plan.split.blocks = (const SplitBlock*)(base + (size_t)plan.split.blocks);
+}
+#elif defined(__HIP__)
+__device__ inline void plan_from_arguments(PlanDev&) {}
+#endif
 
 struct PrefillWg {            // one workgroup of the bf16 prefill kernel: consecutive query tokens of one thread
     int32_t table_ofs;        // the thread's block table inside the staged tables
@@ -198,6 +223,7 @@ struct ClassStreams {
 // units x kv heads.
 constexpr size_t kSplitStateBytes = (size_t)32 << 20;
 constexpr int kSplitMaxCut = 1024;
+constexpr size_t kSplitCounterBytes = (size_t)kSplitMaxCut * 4 * sizeof(int32_t);
 
 // Where `device`'s copy of the library's static workspace (APAR_FIXED_PLAN_BYTES of plan tables followed by
 // APAR_FIXED_PARTIAL_BYTES of partial results and kSplitStateBytes of row states) lives.  `device` must be the current device.  The address is

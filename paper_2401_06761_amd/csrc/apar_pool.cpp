@@ -126,12 +126,15 @@ struct apar_pool {
     hipEvent_t fixed_up = nullptr;
     bool fixed_pending = false;
 
-    // row states of launches whose units are cut into slices; obtained at pool creation
+    // row states of launches whose units are cut into slices, behind the counters of slices that have arrived (zero
+    // between launches); obtained at pool creation
     char* split_dev = nullptr;
     size_t split_bytes = 0;
     std::vector<SplitBlock> split_blocks;  // of the plan as it was built
     int32_t n_split_class[3] = {0, 0, 0};
     size_t n_split_cut = 0;
+    std::vector<int32_t> inline_words;  // a small plan's tables, as they go along with the kernels' arguments
+    size_t inline_ofs[4] = {0, 0, 0, 0};
 
     bool profiling = false;
     std::vector<EventPair> decode_events, append_events;
@@ -425,6 +428,39 @@ void cut_into_slices(const PlanHost& ph, const Shape& s, size_t state_bytes, std
     n_cut = 0;
 }
 
+// Lays a small plan's tables out for the kernels' arguments: no upload, no staging slot and no event.  Only where nothing
+// is left to merge (the merge kernel reads staged tables).  Measured per call: one request of five threads, 32 heads
+// 22.5 -> 15.6 us, three threads on an fp32 pool 16.7 -> 9.4 us, a whole response (prompt, 16 steps of five threads) 435 -> 374 us.
+bool inline_plan(apar_pool* p, const PlanHost& ph) {
+    if (ph.any_partial || ph.n_wg_class[0] > 0) return false;
+    const size_t n_blocks = p->split_blocks.empty() ? ph.wgs.size() : p->split_blocks.size();
+    const size_t words = ph.wgs.size() * (sizeof(WgDesc) / 4) + n_blocks * (sizeof(SplitBlock) / 4) + ph.tiles.size() * (sizeof(TileRef) / 4) +
+                         ph.dfs_threads.size();
+    if (words > (size_t)kPlanInlineWords) return false;
+    p->inline_words.resize(words);
+    char* base = (char*)p->inline_words.data();
+    size_t at = 0;
+    auto put = [&](int k, const void* from, size_t bytes) {
+        p->inline_ofs[k] = at;
+        memcpy(base + at, from, bytes);
+        at += bytes;
+    };
+    put(0, ph.wgs.data(), ph.wgs.size() * sizeof(WgDesc));
+    if (p->split_blocks.empty()) {  // units as they are
+        p->inline_ofs[3] = at;
+        for (size_t k = 0; k < n_blocks; ++k) {
+            const SplitBlock b{(int32_t)k, 1 << 16, 0, 0};
+            memcpy(base + at, &b, sizeof b);
+            at += sizeof b;
+        }
+    } else {
+        put(3, p->split_blocks.data(), n_blocks * sizeof(SplitBlock));
+    }
+    put(1, ph.tiles.data(), ph.tiles.size() * sizeof(TileRef));
+    put(2, ph.dfs_threads.data(), ph.dfs_threads.size() * sizeof(int32_t));
+    return true;
+}
+
 // fixed: the plan and the partial results go to the device's static workspace, nothing is allocated, no
 // stream or event is created and profiling is off for the call.
 int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* cand_v, const uint8_t* mask,
@@ -520,9 +556,9 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     ofs[4] = align_up(ofs[3] + ph.path_ofs.size() * 4, 256);
     ofs[5] = align_up(ofs[4] + ph.path_ids.size() * 4, 256);
     ofs[6] = align_up(ofs[5] + p->split_blocks.size() * sizeof(SplitBlock), 256);
-    // (the counters of slices that have arrived are staged too, as zeros)
+    // (apar_decode_attention_fixed stages the counters of slices that have arrived too, as zeros)
     const size_t counter_bytes = p->n_split_cut * p->shape.n_kv * 4 * sizeof(int32_t);
-    const size_t staged = align_up(ofs[6] + counter_bytes, 256);
+    const size_t staged = ofs[6];
     bool cut = !p->split_blocks.empty();
     const size_t slots = (size_t)ph.n_partial_rows * n_cand * p->shape.n_q;
     StageSlot* s = nullptr;
@@ -531,10 +567,11 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     PartialBuf part = p->part;
     if (p->resident_behind) p->resident = nullptr;
     p->resident_behind = false;
+    const bool inlined = !fixed && inline_plan(p, ph);
     // a carried-over plan whose tables are still on the device from the previous call: only the words that
     // changed are sent, and written in place once the previous call's kernels are through
     // (small tables are staged whole instead: one copy, against a copy and a launch)
-    const bool in_place = carried && !fixed && p->resident && p->resident_bytes == staged && staged >= kCopyStreamMinBytes;
+    const bool in_place = carried && !fixed && !inlined && p->resident && p->resident_bytes == staged && staged >= kCopyStreamMinBytes;
     if (!in_place) p->resident = nullptr;
     if (in_place) {
         p->resident_behind = true;
@@ -571,14 +608,14 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
         dev = p->fixed_dev;
         part.o = (float*)(p->fixed_dev + kFixedPlanBytes);
         part.ml = part.o + cap_slots * p->shape.d;
-        cut = cut && staged <= kFixedPlanBytes;
-        fixed_bytes = cut ? staged : ofs[5];
-    } else {
+        cut = cut && staged + counter_bytes <= kFixedPlanBytes;
+        fixed_bytes = cut ? staged + counter_bytes : ofs[5];
+    } else if (!inlined) {
         if ((rc = acquire_stage(p, staged, &s)) != APAR_OK) return rc;
         host = s->host;
         dev = s->dev;
     }
-    if (!in_place) {
+    if (!in_place && !inlined) {
         memcpy(host + ofs[0], ph.wgs.data(), ph.wgs.size() * sizeof(WgDesc));
         memcpy(host + ofs[1], ph.tiles.data(), ph.tiles.size() * sizeof(TileRef));
         memcpy(host + ofs[2], ph.dfs_threads.data(), ph.dfs_threads.size() * 4);
@@ -586,7 +623,7 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
         if (!ph.path_ids.empty()) memcpy(host + ofs[4], ph.path_ids.data(), ph.path_ids.size() * 4);
         if (cut) {
             memcpy(host + ofs[5], p->split_blocks.data(), p->split_blocks.size() * sizeof(SplitBlock));
-            memset(host + ofs[6], 0, counter_bytes);
+            if (fixed) memset(host + staged, 0, counter_bytes);
         }
     }
 
@@ -604,8 +641,8 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
         part = p->part;
     }
 
-    if (in_place) {
-        // (already there)
+    if (in_place || inlined) {
+        // (already there, or on its way with the kernels)
     } else if (fixed) {
         HIP_TRY(hipMemcpyAsync(dev, host, fixed_bytes, hipMemcpyHostToDevice, st));
         HIP_TRY(hipEventRecord(p->fixed_up, st));
@@ -629,8 +666,21 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     if (cut) {
         pd.split.blocks = (const SplitBlock*)(dev + ofs[5]);
         for (int k = 0; k < 3; ++k) pd.split.n_blocks_class[k] = p->n_split_class[k];
-        pd.split.arrived = (int32_t*)(dev + ofs[6]);
-        pd.split.state = (float*)(fixed ? p->fixed_dev + kFixedPlanBytes + kFixedPartBytes : p->split_dev);
+        pd.split.arrived = (int32_t*)(fixed ? dev + staged : p->split_dev);
+        pd.split.state = (float*)(fixed ? p->fixed_dev + kFixedPlanBytes + kFixedPartBytes : p->split_dev + kSplitCounterBytes);
+    }
+
+    if (inlined) {
+        pd.wgs = (const WgDesc*)p->inline_ofs[0];
+        pd.tiles = (const TileRef*)p->inline_ofs[1];
+        pd.dfs_threads = (const int32_t*)p->inline_ofs[2];
+        pd.path_ofs = pd.path_ids = nullptr;  // (nothing to merge)
+        pd.split.blocks = (const SplitBlock*)p->inline_ofs[3];
+        for (int k = 0; k < 3; ++k) pd.split.n_blocks_class[k] = cut ? p->n_split_class[k] : ph.n_wg_class[k];
+        pd.split.arrived = (int32_t*)p->split_dev;
+        pd.split.state = (float*)(p->split_dev + kSplitCounterBytes);
+        pd.inline_words = p->inline_words.data();
+        pd.n_inline_words = (int32_t)p->inline_words.size();
     }
 
     EventPair ev;
@@ -894,7 +944,9 @@ int apar_pool_create(const apar_pool_config* cfg, void* kv_dev, size_t kv_bytes,
         if (rc == APAR_OK && !hip_ok(hipEventCreateWithFlags(&p->fixed_up, hipEventDisableTiming), "hipEventCreate"))
             rc = APAR_ERR_HIP;
         p->split_bytes = std::min(kSplitStateBytes, std::max((size_t)1 << 20, (size_t)(block * cfg->num_blocks) / 8));
-        if (rc == APAR_OK && !hip_ok(hipMalloc((void**)&p->split_dev, p->split_bytes), "hipMalloc(split)")) rc = APAR_ERR_HIP;
+        if (rc == APAR_OK && (!hip_ok(hipMalloc((void**)&p->split_dev, kSplitCounterBytes + p->split_bytes), "hipMalloc(split)") ||
+                              !hip_ok(hipMemset(p->split_dev, 0, kSplitCounterBytes), "hipMemset(split)")))
+            rc = APAR_ERR_HIP;  // (the copies that set the staging slots up follow it and are waited for)
         // the staging slots at their smallest, so that a pool's first calls do not stop to allocate them (appends used to
         // by the time of the first decode call)
         for (StageSlot& s : p->stage)

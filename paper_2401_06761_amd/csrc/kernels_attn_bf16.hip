@@ -51,6 +51,7 @@
 // common path.
 #include <hip/hip_runtime.h>
 
+#include <cstring>
 #include <type_traits>
 
 #include "apar_internal.hpp"
@@ -216,8 +217,9 @@ constexpr int kOpenScratch = 16 * kOpenRowStride;   // one wavefront's row-major
 // NT = 16-row tiles per wavefront (1 or 2 are instantiated): a workgroup carries up to 64 * NT query rows.
 // F8: full blocks hold fp8 codes and two scales (APAR_BF16_FP8KV pools).
 // SPLIT: several workgroups per unit, each with a slice of its tile lists (attn_split.hpp).
-template <int NT, bool F8, bool SPLIT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3 : 2))) void attention_bf16(const char* __restrict__ pool, const uint16_t* __restrict__ q,
+// INLINE (with SPLIT): the plan's tables come with the kernel's arguments.
+template <int NT, bool F8, bool SPLIT, bool INLINE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3 : 2))) void attention_bf16(PlanWords<INLINE>, const char* __restrict__ pool, const uint16_t* __restrict__ q,
                                                       PlanDev plan, int wg_first, int n_cand, int n_q, int n_kv,
                                                       int group, float scale_log2e, PartialBuf part,
                                                       const uint16_t* __restrict__ cand_k,
@@ -233,6 +235,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int g4 = lane >> 4, c = lane & 15;
     const int kvh = blockIdx.x % n_kv;
+    if constexpr (INLINE) plan_from_arguments(plan);
     Slice slice;
     if constexpr (SPLIT) {
         slice = slice_of_block(plan.split, wg_first, n_kv);
@@ -908,7 +911,8 @@ hipError_t launch_attention_bf16(const Shape& s, const void* pool, const void* q
     // the last one present runs on the caller's stream and the other beside it on a side stream that waits
     // for the caller's stream first and that the caller's stream then waits for.
     int first[3], last = -1, n_present = 0;
-    const bool split = plan.split.blocks != nullptr;
+    if (plan.n_inline_words > kPlanInlineWords) return hipErrorInvalidValue;
+    const bool split = plan.split.blocks != nullptr || plan.inline_words;
     const int32_t* n_class = split ? plan.split.n_blocks_class : plan.n_wg_class;  // (matrix units are never cut)
     for (int cls = 0, f = 0; cls < 3; ++cls) {
         first[cls] = f;
@@ -942,25 +946,30 @@ hipError_t launch_attention_bf16(const Shape& s, const void* pool, const void* q
             if ((e = hipStreamWaitEvent(on, cs.fork, 0)) != hipSuccess) return e;
         }
         const unsigned n_wg = (unsigned)count * (unsigned)s.n_kv;
-#define APAR_LAUNCH(NTV, F8V, SPLITV)                                                                                   \
-    hipLaunchKernelGGL((attention_bf16<NTV, F8V, SPLITV>), dim3(n_wg), dim3(256), 0, on, (const char*)pool, (const uint16_t*)q, \
-                       plan, first[cls], n_cand, s.n_q, s.n_kv, s.group, s.scale_log2e, part,                           \
-                       (const uint16_t*)cand_k, (const uint16_t*)cand_v, mask, (uint16_t*)out)
-        if (s.fp8_sealed) {
-            if (split) {
-                if (cls == 1) APAR_LAUNCH(2, true, true);
-                else APAR_LAUNCH(1, true, true);
-            } else {
-                if (cls == 1) APAR_LAUNCH(2, true, false);
-                else APAR_LAUNCH(1, true, false);
-            }
+#define APAR_LAUNCH(NTV, F8V, SPLITV, INLINEV, WORDS)                                                                   \
+    hipLaunchKernelGGL((attention_bf16<NTV, F8V, SPLITV, INLINEV>), dim3(n_wg), dim3(256), 0, on, WORDS,                 \
+                       (const char*)pool, (const uint16_t*)q, plan, first[cls], n_cand, s.n_q, s.n_kv, s.group,          \
+                       s.scale_log2e, part, (const uint16_t*)cand_k, (const uint16_t*)cand_v, mask, (uint16_t*)out)
+#define APAR_LAUNCH_F8(SPLITV, INLINEV, WORDS)                          \
+    do {                                                                \
+        if (s.fp8_sealed) {                                             \
+            if (cls == 1) APAR_LAUNCH(2, true, SPLITV, INLINEV, WORDS); \
+            else APAR_LAUNCH(1, true, SPLITV, INLINEV, WORDS);          \
+        } else {                                                        \
+            if (cls == 1) APAR_LAUNCH(2, false, SPLITV, INLINEV, WORDS);\
+            else APAR_LAUNCH(1, false, SPLITV, INLINEV, WORDS);         \
+        }                                                               \
+    } while (0)
+        if (plan.inline_words) {
+            PlanWords<true> words;
+            memcpy(words.words, plan.inline_words, (size_t)plan.n_inline_words * sizeof(int32_t));
+            APAR_LAUNCH_F8(true, true, words);
         } else if (split) {
-            if (cls == 1) APAR_LAUNCH(2, false, true);
-            else APAR_LAUNCH(1, false, true);
+            APAR_LAUNCH_F8(true, false, PlanWords<false>{});
         } else {
-            if (cls == 1) APAR_LAUNCH(2, false, false);
-            else APAR_LAUNCH(1, false, false);
+            APAR_LAUNCH_F8(false, false, PlanWords<false>{});
         }
+#undef APAR_LAUNCH_F8
 #undef APAR_LAUNCH
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (cls != last && side_by_side) {

@@ -29,6 +29,8 @@
 // one, over the blocks each of them sees.
 #include <hip/hip_runtime.h>
 
+#include <cstring>
+
 #include "apar_internal.hpp"
 #include "attn_split.hpp"
 
@@ -100,10 +102,11 @@ __device__ __forceinline__ void accumulate(const f32x4 (&v)[4][D / 64], Row<D>& 
             st.o[jj] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[i][jj / 4][jj % 4], p[i], st.o[jj], 0, 0, 0);
 }
 
-// NT = 16-row tiles per wavefront; SPLIT: several workgroups per unit, each with a slice of its lists (attn_split.hpp).
-template <int D, int NT, bool SPLIT>
+// NT = 16-row tiles per wavefront; SPLIT: several workgroups per unit, each with a slice of its lists (attn_split.hpp);
+// INLINE (with SPLIT): the plan's tables come with the kernel's arguments.
+template <int D, int NT, bool SPLIT, bool INLINE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attention_f32(
-    const char* __restrict__ pool, const float* __restrict__ q, PlanDev plan, int wg_first, int n_cand, int n_q, int n_kv,
+    PlanWords<INLINE>, const char* __restrict__ pool, const float* __restrict__ q, PlanDev plan, int wg_first, int n_cand, int n_q, int n_kv,
     int group, float scale_log2e, PartialBuf part, const float* __restrict__ cand_k, const float* __restrict__ cand_v,
     const uint8_t* __restrict__ cand_mask, float* __restrict__ out) {
     constexpr int J = D / 16;
@@ -114,6 +117,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int g4 = lane >> 4, c = lane & 15;
     const int kvh = blockIdx.x % n_kv;
+    if constexpr (INLINE) plan_from_arguments(plan);
     Slice slice;
     if constexpr (SPLIT) {
         slice = slice_of_block(plan.split, wg_first, n_kv);
@@ -387,31 +391,37 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 hipError_t launch_attention_f32(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand, PartialBuf part,
                                 const void* cand_k, const void* cand_v, const uint8_t* mask, void* out, hipStream_t st) {
     int first = 0;
-    const bool split = plan.split.blocks != nullptr;
+    if (plan.n_inline_words > kPlanInlineWords) return hipErrorInvalidValue;
+    const bool split = plan.split.blocks != nullptr || plan.inline_words;
     const int32_t* n_class = split ? plan.split.n_blocks_class : plan.n_wg_class;
     for (int cls = 0; cls < 3; ++cls) {
         const int64_t n = (int64_t)n_class[cls] * s.n_kv;
         if (n > 0x7fffffff || (cls == 0 && n > 0)) return hipErrorInvalidValue;  // (fp32 pools have no matrix units)
         if (n == 0) continue;
-#define APAR_LAUNCH(DV, NTV, SPLITV)                                                                                      \
-    hipLaunchKernelGGL((attention_f32<DV, NTV, SPLITV>), dim3((unsigned)n), dim3(256), 0, st, (const char*)pool,          \
-                       (const float*)q, plan, first, n_cand, s.n_q, s.n_kv, s.group, s.scale_log2e, part,                \
-                       (const float*)cand_k, (const float*)cand_v, mask, (float*)out)
-        if (s.d == 64) {
-            if (split) {
-                if (cls == 1) APAR_LAUNCH(64, 2, true);
-                else APAR_LAUNCH(64, 1, true);
-            } else {
-                if (cls == 1) APAR_LAUNCH(64, 2, false);
-                else APAR_LAUNCH(64, 1, false);
-            }
+#define APAR_LAUNCH(DV, NTV, SPLITV, INLINEV, WORDS)                                                                      \
+    hipLaunchKernelGGL((attention_f32<DV, NTV, SPLITV, INLINEV>), dim3((unsigned)n), dim3(256), 0, st, WORDS,             \
+                       (const char*)pool, (const float*)q, plan, first, n_cand, s.n_q, s.n_kv, s.group, s.scale_log2e,    \
+                       part, (const float*)cand_k, (const float*)cand_v, mask, (float*)out)
+#define APAR_LAUNCH_D(SPLITV, INLINEV, WORDS)                         \
+    do {                                                              \
+        if (s.d == 64) {                                              \
+            if (cls == 1) APAR_LAUNCH(64, 2, SPLITV, INLINEV, WORDS); \
+            else APAR_LAUNCH(64, 1, SPLITV, INLINEV, WORDS);          \
+        } else {                                                      \
+            if (cls == 1) APAR_LAUNCH(128, 2, SPLITV, INLINEV, WORDS);\
+            else APAR_LAUNCH(128, 1, SPLITV, INLINEV, WORDS);         \
+        }                                                             \
+    } while (0)
+        if (plan.inline_words) {
+            PlanWords<true> words;
+            memcpy(words.words, plan.inline_words, (size_t)plan.n_inline_words * sizeof(int32_t));
+            APAR_LAUNCH_D(true, true, words);
         } else if (split) {
-            if (cls == 1) APAR_LAUNCH(128, 2, true);
-            else APAR_LAUNCH(128, 1, true);
+            APAR_LAUNCH_D(true, false, PlanWords<false>{});
         } else {
-            if (cls == 1) APAR_LAUNCH(128, 2, false);
-            else APAR_LAUNCH(128, 1, false);
+            APAR_LAUNCH_D(false, false, PlanWords<false>{});
         }
+#undef APAR_LAUNCH_D
 #undef APAR_LAUNCH
         first += n_class[cls];
         const hipError_t e = hipGetLastError();
