@@ -78,14 +78,15 @@ __device__ __forceinline__ bool fold_slices(const SplitPlan& sp, const Slice& sl
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         const int at = base + nt * kTileBytes;
-        float mx = -INFINITY;
-        for (int s = 0; s < sl.n; ++s)
-            mx = fmaxf(mx, __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(state, at + s * step + J * 1024 + lane * 8, 0, kAgent)));
+        // One pass, the reference moving along (a pass for the largest one first is another latency per slice), three
+        // slices in flight.  Against two passes and two slices: one request, 8 kv heads, 2 k - 8 k tokens 14.4 -> 11.9 us,
+        // 9 k - 30 k tokens 33.8 -> 29.7, 12 threads 15.4 -> 14.7.
+        float m = -INFINITY;
         float l = 0.0f;
         f32x4 o[J];
 #pragma unroll
         for (int jj = 0; jj < J; ++jj) o[jj] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll(NT == 1 ? 2 : 1)
+#pragma unroll(NT == 1 ? 3 : 1)
         for (int s = 0; s < sl.n; ++s) {
             const int as = at + s * step;
             const f32x2 ml = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(state, as + J * 1024 + lane * 8, 0, kAgent));
@@ -94,12 +95,15 @@ __device__ __forceinline__ bool fold_slices(const SplitPlan& sp, const Slice& sl
             for (int jj = 0; jj < J; ++jj)
                 os[jj] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(state, as + (jj * 64 + lane) * 16, 0, kAgent));
             // (a slice that saw nothing of the row left m = -inf and zeros)
-            const float a = mx == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(ml[0] - mx);
-            l += a * ml[1];
+            const float mx = fmaxf(m, ml[0]);
+            const float a = mx == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m - mx);
+            const float b = mx == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(ml[0] - mx);
+            l = a * l + b * ml[1];
 #pragma unroll
-            for (int jj = 0; jj < J; ++jj) o[jj] += a * os[jj];
+            for (int jj = 0; jj < J; ++jj) o[jj] = a * o[jj] + b * os[jj];
+            m = mx;
         }
-        st[nt].m = mx;
+        st[nt].m = m;
         st[nt].l = l;
 #pragma unroll
         for (int jj = 0; jj < J; ++jj) st[nt].o[jj] = o[jj];
