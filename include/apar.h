@@ -495,7 +495,8 @@ APAR_API int apar_set_inline_shared(apar_pool* pool, int on);
  * group size that divides 16, otherwise the call stays on ROW_TILES).  AUTO (default) takes MATRIX when
  * the threads bring 32 query rows each (query tokens x q heads per kv head) or more on average, or a query token
  * attends to 1024 rows or more on average.  Both give the same result to rounding.
- * fp32 pools ignore the knob.  apar_last_prefill_kernel tells which one the most recent call ran (0: none). */
+ * fp8 pools take the matrix kernel under AUTO, by the same rule, and ROW_TILES otherwise; fp32 pools ignore the knob.
+ * apar_last_prefill_kernel tells which one the most recent call ran (0: none). */
 enum { APAR_PREFILL_AUTO = 0, APAR_PREFILL_ROW_TILES = 1, APAR_PREFILL_MATRIX = 2 };
 APAR_API int apar_set_prefill_kernel(apar_pool* pool, int which);
 APAR_API int apar_last_prefill_kernel(apar_pool* pool);

@@ -716,11 +716,13 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     return APAR_OK;
 }
 
-// A bf16 prefill call goes to the 32x32 kernel by itself when its threads bring this many query rows each (query tokens
+// A prefill call on a bf16 or fp8 pool goes to the 32x32 kernel by itself when its threads bring this many query rows each (query tokens
 // x q heads of a kv group, on average: one wavefront's worth), or when a query token attends to this many rows.
 // Measured (us, row tiles / matrix kernel): 360 threads of walks around 1000, 32 kv heads, m query tokens each: m = 1
 // 904 / 656, 32 1007 / 677, whole segments (90 on average) 1652 / 1224; walks around 200: m = 1 255 / 279, 16 301 / 291, 32 309 / 300,
 // whole 589 / 489; 8 kv heads (4 rows per token): m = 4 84 / 90, 8 87 / 92, 16 95 / 105, 32 156 / 128, whole 417 / 353.
+// fp8 pools, whole segments: walks of 300, 900, 3300, 32 kv heads 730 / 694, 378 / 360, 457 / 418; two prompts of 100 to 400
+// tokens, 8 kv heads 81 / 37, six of 1 k to 8 k 2254 / 1974 (whole call).
 constexpr int64_t kMatrixPrefillRows = 32;
 constexpr int64_t kMatrixPrefillMeanWalk = 1024;
 
@@ -831,11 +833,12 @@ int prefill_common(apar_pool* p, const void* q, const apar_thread* ids, const in
     if (rows > INT32_MAX / 2) return APAR_ERR_UNSUPPORTED;
     PlanHost& ph = p->plan;
     int rc = APAR_OK;
-    // bf16 pools have two kernels.  The 32x32 matrix-core kernel wants a wavefront's worth of rows per thread or a long
+    // 16-bit pools have two kernels.  The 32x32 matrix-core kernel wants a wavefront's worth of rows per thread or a long
     // walk to spread its fixed cost per workgroup over; a few rows with short walks stay on the row-tile kernel.
     p->last_prefill_kernel = APAR_PREFILL_ROW_TILES;
-    if (!p->dry_run && p->shape.dtype == APAR_BF16 && !p->shape.fp8_sealed && 16 % p->shape.group == 0 &&
-        (p->prefill_kernel == APAR_PREFILL_MATRIX ||
+    // (an fp8 pool takes the matrix kernel by AUTO only)
+    if (!p->dry_run && p->shape.dtype == APAR_BF16 && 16 % p->shape.group == 0 &&
+        ((p->prefill_kernel == APAR_PREFILL_MATRIX && !p->shape.fp8_sealed) ||
          (p->prefill_kernel == APAR_PREFILL_AUTO &&
           (rows * p->shape.group >= kMatrixPrefillRows * n || attended >= kMatrixPrefillMeanWalk * rows)))) {
         p->last_prefill_kernel = APAR_PREFILL_MATRIX;
@@ -947,10 +950,10 @@ int apar_pool_create(const apar_pool_config* cfg, void* kv_dev, size_t kv_bytes,
         if (rc == APAR_OK && (!hip_ok(hipMalloc((void**)&p->split_dev, kSplitCounterBytes + p->split_bytes), "hipMalloc(split)") ||
                               !hip_ok(hipMemset(p->split_dev, 0, kSplitCounterBytes), "hipMemset(split)")))
             rc = APAR_ERR_HIP;  // (the copies that set the staging slots up follow it and are waited for)
-        // the staging slots at their smallest, so that a pool's first calls do not stop to allocate them (appends used to
-        // by the time of the first decode call)
-        for (StageSlot& s : p->stage)
-            if (rc == APAR_OK) rc = grow_slot(s, 0);
+        // two staging slots at their smallest, so that a pool's first decode call does not stop to set them up (the appends
+        // before it, whose tables go along with their kernels, do not use them)
+        for (int k = 0; k < 2; ++k)
+            if (rc == APAR_OK) rc = grow_slot(p->stage[k], 0);
         if (rc != APAR_OK) {
             for (StageSlot& s : p->stage) {
                 if (s.host) (void)hipHostFree(s.host);

@@ -1,4 +1,4 @@
-// Attention shaped for the matrix cores (bf16 pools): 32x32 products, 128 query rows per workgroup.
+// Attention shaped for the matrix cores (16-bit pools): 32x32 products, 128 query rows per workgroup.
 //
 // Two kernels share one walk:
 //   * prefill_bf16: a workgroup takes up to 128 query rows of ONE thread - consecutive query tokens x the
@@ -62,6 +62,18 @@ __device__ __forceinline__ uint32_t pack_pair(float lo, float hi) {  // round to
 // 256 consecutive bytes.
 __device__ __forceinline__ int v_operand_offset(int r, int hf, int c, int h) { return ((((r * 2 + hf) * 2 + h) * 16) + c) * 16; }
 
+// fp8 codes in x[0], x[1] times the half's power-of-two scale -> the half's four bf16 pieces x[0..3].
+__device__ __forceinline__ void widen(u32x4 (&x)[4], float scale) {
+    const u32x4 raw[2] = {x[0], x[1]};
+#pragma unroll
+    for (int rp = 0; rp < 2; ++rp)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            x[2 * rp + (w >> 1)][2 * (w & 1)] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[rp][w], scale, false));
+            x[2 * rp + (w >> 1)][2 * (w & 1) + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[rp][w], scale, true));
+        }
+}
+
 // What a wavefront brings to the walk.  `len` token slots are filled along the walk's block list
 // (entry i of the list is table[i * table_stride]); the lane's row sees slots 0 .. pos.
 struct Walk {
@@ -81,6 +93,8 @@ struct Walk {
 
 // Runs the walk; leaves the lane's share of O^T (dims 32 jj + 8 (i / 4) + 4 h + i % 4 of row n in o[jj][i]),
 // the row's reference m and this lane's half of the row's sum l.
+// F8: full blocks hold fp8 codes and two scales; they are widened when they are staged, so that LDS holds the bf16 tile.
+template <bool F8>
 __device__ __forceinline__ void walk_blocks(const Walk& wk, char* lds, f32x16 (&o)[4], float& m, float& l) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -110,12 +124,20 @@ __device__ __forceinline__ void walk_blocks(const Walk& wk, char* lds, f32x16 (&
     const int n_grp = (n_blk + 3) / 4;
     // this wavefront stages block `wave` of every group
     u32x4 sk[4], sv[4];
+    f32x2 ssc = {1.0f, 1.0f};  // fp8 pools: the scales of the block in flight
     auto fetch = [&](int g) {
         // a group's last blocks may lie past the walk's last block: they are masked, re-read the last one
         const int blk = min(4 * g + wave, n_blk - 1);
         const int fill = min(16, wk.len - blk * 16);
         const char* tile = head_base + wk.table[blk * wk.table_stride] * block_stride;
-        if (fill == 16) {
+        if (F8 && fill == 16) {
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                sk[r] = *reinterpret_cast<const u32x4*>(tile + r * 1024 + lane * 16);
+                sv[r] = *reinterpret_cast<const u32x4*>(tile + kFp8HalfBytes + r * 1024 + lane * 16);
+            }
+            ssc = *reinterpret_cast<const f32x2*>(tile + kFp8ScaleOfs);
+        } else if (fill == 16) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 sk[r] = *reinterpret_cast<const u32x4*>(tile + r * 1024 + lane * 16);
@@ -136,6 +158,11 @@ __device__ __forceinline__ void walk_blocks(const Walk& wk, char* lds, f32x16 (&
         const int blk = min(4 * g + wave, n_blk - 1);
         const bool sealed = wk.len - blk * 16 >= 16;
         char* dst = buf + wave * kTileBytes;
+        if (F8 && sealed) {
+            // two 16-byte loads hold a half's four pieces at one byte per element (a code times a power of two: exact)
+            widen(sk, ssc[0]);
+            widen(sv, ssc[1]);
+        }
         // K: as it lies in HBM (either layout keeps piece r of lane l at r * 1024 + l * 16)
 #pragma unroll
         for (int r = 0; r < 4; ++r) *reinterpret_cast<u32x4*>(dst + r * 1024 + lane * 16) = sk[r];
@@ -262,6 +289,7 @@ __device__ __forceinline__ void walk_blocks(const Walk& wk, char* lds, f32x16 (&
 
 }
 
+template <bool F8>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void prefill_bf16(
     const char* __restrict__ pool, const uint16_t* __restrict__ q, const PrefillWg* __restrict__ wgs,
     const int32_t* __restrict__ tables, int n_q, int n_kv, int group, float scale_log2e, uint16_t* __restrict__ out) {
@@ -294,7 +322,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     wk.scale_log2e = scale_log2e;
     f32x16 o[4];
     float m, l;
-    walk_blocks(wk, lds, o, m, l);
+    walk_blocks<F8>(wk, lds, o, m, l);
 
     // Normalise and write.  The rows go through LDS (the walk ended with a barrier) so that a store instruction writes
     // four whole rows of 256 bytes: a lane holds its row in runs of four dims, and stores of 8 bytes per lane, 16 per
@@ -366,7 +394,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     wk.scale_log2e = scale_log2e;
     f32x16 o[4];
     float m, l;
-    walk_blocks(wk, lds, o, m, l);
+    walk_blocks<false>(wk, lds, o, m, l);
 
     // the row's state goes out as a partial result
     const float lt = l + __shfl_xor(l, 32, 64);
@@ -393,8 +421,12 @@ hipError_t launch_prefill_bf16(const Shape& s, const void* pool, const void* q, 
     if (n_wg <= 0) return hipSuccess;
     const int64_t grid = (int64_t)n_wg * s.n_kv;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(prefill_bf16, dim3((unsigned)grid), dim3(256), 0, st, (const char*)pool, (const uint16_t*)q, wgs,
-                       tables, s.n_q, s.n_kv, s.group, s.scale_log2e, (uint16_t*)out);
+    if (s.fp8_sealed)
+        hipLaunchKernelGGL(prefill_bf16<true>, dim3((unsigned)grid), dim3(256), 0, st, (const char*)pool, (const uint16_t*)q, wgs,
+                           tables, s.n_q, s.n_kv, s.group, s.scale_log2e, (uint16_t*)out);
+    else
+        hipLaunchKernelGGL(prefill_bf16<false>, dim3((unsigned)grid), dim3(256), 0, st, (const char*)pool, (const uint16_t*)q, wgs,
+                           tables, s.n_q, s.n_kv, s.group, s.scale_log2e, (uint16_t*)out);
     return hipGetLastError();
 }
 
