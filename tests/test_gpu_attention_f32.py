@@ -76,3 +76,31 @@ def test_a_threads_infinities_stay_its_own(d, fan, bad):
                 assert not np.isfinite(got[2]).all()
             rows = [r for r in range(2 * len(live)) if r != 5]
             assert_close(got2[rows], want2[rows], "f32", where)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_rows_at_any_four_byte_address(d):
+    """fp32 rows are loaded and stored 16 bytes at a time; callers may hand over any float's address."""
+    import torch
+
+    w = manual_tree([-1, 0, 0], [21, 9, 30], HeadConfig(2, 2, d, "f32"), seed=4)
+    dense = DenseThreads(2, 2, d)
+    with pool_for(w, blocks_upper_bound(w)) as pool:
+        pool.kv.fill_(0xFF)
+        live, _ = replay_trace(w, pool, None, dense)
+        rng = np.random.default_rng(3)
+        k, v = (rng.standard_normal((len(live), 2, d)).astype(np.float32) for _ in "kv")
+
+        def shifted(x):
+            flat = torch.zeros(x.size + 1, dtype=torch.float32, device="cuda:0")
+            flat[1:] = torch.from_numpy(x.reshape(-1)).cuda()
+            return flat[1:].view(x.shape)
+
+        ap.apar_append_kv_batch(pool.handle, live, shifted(k), shifted(v))
+        for i, t in enumerate(live):
+            dense.append(t, k[i:i + 1], v[i:i + 1])
+        q = step_q(w, 0, len(live))
+        out = shifted(np.zeros_like(q))
+        ap.apar_decode_attention(pool.handle, shifted(q), live, out)
+        torch.cuda.synchronize()
+        assert_close(to_host(out), dense.decode(q, live), "f32")
