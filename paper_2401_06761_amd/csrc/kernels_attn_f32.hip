@@ -25,8 +25,8 @@
 // With its heaviest units cut into slices (attn_split.hpp) the first of these takes 137 us, error 3.1e-7.
 //
 // A row that does not see a block meets it with probability 0, and 0 times an infinity or a NaN is a NaN.  Blocks of
-// other threads must not do that to a row: a wavefront whose results are not all finite takes its rows again, one by
-// one, over the blocks each of them sees.
+// other threads must not do that to a row: a wavefront takes those of its rows that did not come out finite again, one
+// by one, over the blocks each of them sees.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
@@ -265,12 +265,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
         for (int jj = 0; jj < J; ++jj)
 #pragma unroll
             for (int i = 0; i < 4; ++i) fine = fine && fabsf(st[nt].o[jj][i]) < INFINITY;
-        if (__builtin_amdgcn_ballot_w64(my_j[nt] >= 0 && !fine) == 0) continue;
+        const uint64_t off = __builtin_amdgcn_ballot_w64(my_j[nt] >= 0 && !fine);
+        if (off == 0) continue;
+        const uint32_t bad = (uint32_t)(off | off >> 16 | off >> 32 | off >> 48) & 0xffffu;  // by column: any of a row's four lanes
         float* rows = lds[wave];
         for (int col = 0; col < 16; ++col) {
             int j, listed, cc;
             int64_t qrow, slot;
-            if (!row_of(nt, col, j, listed, cc, qrow, slot)) continue;
+            if (!((bad >> col) & 1u) || !row_of(nt, col, j, listed, cc, qrow, slot)) continue;
             constexpr int E = D / 64;
             float qv[E], acc[E], m = -INFINITY, l = 0.0f;
 #pragma unroll
@@ -281,7 +283,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
                 for (int e = 0; e < E; ++e) dot += qv[e] * krow[lane + 64 * e];
                 const float sc = wave_sum(dot) * scale_log2e;
                 const float m_new = fmaxf(m, sc);
-                const float alpha = exp2f(m - m_new), pr = exp2f(sc - m_new);
+                // a logit of -inf weighs nothing, also before any other (a NaN stays one, through pr)
+                const float alpha = m_new == -INFINITY ? 1.0f : exp2f(m - m_new), pr = sc == -INFINITY ? 0.0f : exp2f(sc - m_new);
                 l = l * alpha + pr;
 #pragma unroll
                 for (int e = 0; e < E; ++e) acc[e] = acc[e] * alpha + pr * vrow[lane + 64 * e];
@@ -314,7 +317,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (my_j[nt] >= 0) {
+        if ((bad >> c) & 1u) {
 #pragma unroll
             for (int jj = 0; jj < J; ++jj)
 #pragma unroll

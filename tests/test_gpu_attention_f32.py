@@ -104,3 +104,44 @@ def test_rows_at_any_four_byte_address(d):
         ap.apar_decode_attention(pool.handle, shifted(q), live, out)
         torch.cuda.synchronize()
         assert_close(to_host(out), dense.decode(q, live), "f32")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("root", [40, 2100])
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_logits_of_minus_infinity_beside_a_threads_infinities(d, root, bad):
+    """Every sixteenth cached row, from the first on, has a logit of -inf for every query (weight 0), and one thread's V
+    holds infinities or NaN: its siblings are what they are without it, on a short walk and on one that is cut into slices."""
+    import torch
+
+    n_leaf, hkv = 4, 2
+    heads = HeadConfig(hkv, hkv, d, "f32")
+    rng = np.random.default_rng(root + d)
+    k, v = (rng.standard_normal((root, hkv, d)).astype(np.float32) for _ in "kv")
+    k[::16, :, 7] = -np.inf
+    dense = DenseThreads(hkv, hkv, d)
+    w = manual_tree([-1], [1], heads, seed=1)
+    with pool_for(w, root // 16 + 16) as pool:
+        pool.kv.fill_(0xFF)
+        t = ap.apar_thread_create(pool.handle)
+        assert t == dense.create()
+        ap.apar_append_kv(pool.handle, t, to_dev(k, "f32"), to_dev(v, "f32"), root)
+        dense.append(t, k, v)
+        live = ap.apar_fork(pool.handle, t, n_leaf)
+        assert list(live) == list(dense.fork(t, n_leaf))
+        k1, v1 = (rng.standard_normal((n_leaf, hkv, d)).astype(np.float32) for _ in "kv")
+        v1[2, :, 5] = bad
+        ap.apar_append_kv_batch(pool.handle, live, to_dev(k1, "f32"), to_dev(v1, "f32"))
+        for i, x in enumerate(live):
+            dense.append(x, k1[i:i + 1], v1[i:i + 1])
+        q = rng.standard_normal((n_leaf, hkv, d)).astype(np.float32)
+        q[:, :, 7] = 1.0 + np.abs(q[:, :, 7])
+        want = dense.decode(q, live)
+        others = [0, 1, 3]
+        for call in (ap.apar_decode_attention, ap.apar_decode_attention_fixed):
+            out = torch.empty_like(to_dev(q, "f32"))
+            call(pool.handle, to_dev(q, "f32"), live, out)
+            torch.cuda.synchronize()
+            got = to_host(out)
+            assert_close(got[others], want[others], "f32", call.__name__)
+            assert not np.isfinite(got[2]).all()
