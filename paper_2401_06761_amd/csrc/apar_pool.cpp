@@ -47,8 +47,10 @@ struct StageSlot {
     hipEvent_t ev = nullptr;   // recorded after the kernels that read the slot
     hipEvent_t up = nullptr;   // recorded after the slot's upload
     bool pending = false;
+    bool own = false;          // the pair was allocated when the slot grew (else it is a part of the pool's workspace)
 };
 constexpr int kStageSlots = 4;
+constexpr size_t kStageBytes = (size_t)1 << 20;  // what a slot holds to begin with
 constexpr size_t kCopyStreamMinBytes = 256 << 10;  // uploads from this size on run on the pool's copy stream
 
 struct EventPair {
@@ -119,15 +121,21 @@ struct apar_pool {
     ClassStreams class_streams;
     hipStream_t copy_stream = nullptr;  // uploads of plans and row codes run here, beside the caller's stream
 
-    // apar_decode_attention_fixed: this device's copy of the static workspace, a pinned host buffer the plan
-    // is staged in, and the event after its upload; all three obtained at pool creation
+    // Obtained at pool creation, an allocation each: pinned host memory (the buffer apar_decode_attention_fixed stages its
+    // plan in, then the host halves of the staging slots), and device memory (counters and row states of launches whose
+    // units are cut into slices, then the device halves of the staging slots).
+    char* work_host = nullptr;
+    char* work_dev = nullptr;
+
+    // apar_decode_attention_fixed: this device's copy of the static workspace, the pinned host buffer the plan
+    // is staged in, and the event after its upload
     char* fixed_dev = nullptr;
     char* fixed_host = nullptr;
     hipEvent_t fixed_up = nullptr;
     bool fixed_pending = false;
 
     // row states of launches whose units are cut into slices, behind the counters of slices that have arrived (zero
-    // between launches); obtained at pool creation
+    // between launches)
     char* split_dev = nullptr;
     size_t split_bytes = 0;
     std::vector<SplitBlock> split_blocks;  // of the plan as it was built
@@ -170,18 +178,52 @@ int32_t pop_block(apar_pool* p) {
 }
 
 int grow_slot(StageSlot& s, size_t bytes) {
-    if (!s.ev) HIP_TRY(hipEventCreateWithFlags(&s.ev, hipEventDisableTiming));
-    if (s.host) HIP_TRY(hipHostFree(s.host));
-    if (s.dev) HIP_TRY(hipFree(s.dev));
+    if (s.own && s.host) HIP_TRY(hipHostFree(s.host));
+    if (s.own && s.dev) HIP_TRY(hipFree(s.dev));
     s.host = s.dev = nullptr;
     s.cap = 0;
-    const size_t cap = align_up(std::max(bytes + bytes / 2, (size_t)1 << 20), 4096);
+    s.own = true;
+    const size_t cap = align_up(std::max(bytes + bytes / 2, kStageBytes), 4096);
     HIP_TRY(hipHostMalloc((void**)&s.host, cap, hipHostMallocDefault));
     HIP_TRY(hipMalloc((void**)&s.dev, cap));
-    // (the runtime sets a pair of buffers up at its first copy, some 30 us that a call would wait for)
-    HIP_TRY(hipMemcpy(s.dev, s.host, 256, hipMemcpyHostToDevice));
     s.cap = cap;
     return APAR_OK;
+}
+
+// Everything a pool's calls work in besides the pool: all staging slots, so that no call of a loop stops to set one up
+// (measured, one after the other: the third and fourth call of a new pool took 60 to 80 us on the host against 17), in one
+// pinned and one device allocation (a slot each: 250 -> 290 us for a small pool).  One copy clears the counters and
+// takes the pair of allocations through its first transfer.
+int set_up_workspace(apar_pool* p, size_t pool_bytes) {
+    if (!hip_ok(fixed_workspace_of_device(p->device, &p->fixed_dev), "hipGetSymbolAddress(scratch)")) return APAR_ERR_HIP;
+    HIP_TRY(hipEventCreateWithFlags(&p->fixed_up, hipEventDisableTiming));
+    for (StageSlot& s : p->stage) HIP_TRY(hipEventCreateWithFlags(&s.ev, hipEventDisableTiming));
+    p->split_bytes = std::min(kSplitStateBytes, std::max((size_t)1 << 20, pool_bytes / 8));
+    const size_t split = kSplitCounterBytes + p->split_bytes;
+    HIP_TRY(hipHostMalloc((void**)&p->work_host, kFixedPlanBytes + kStageSlots * kStageBytes, hipHostMallocDefault));
+    HIP_TRY(hipMalloc((void**)&p->work_dev, split + kStageSlots * kStageBytes));
+    p->fixed_host = p->work_host;
+    p->split_dev = p->work_dev;
+    for (int k = 0; k < kStageSlots; ++k) {
+        p->stage[k].host = p->work_host + kFixedPlanBytes + k * kStageBytes;
+        p->stage[k].dev = p->work_dev + split + k * kStageBytes;
+        p->stage[k].cap = kStageBytes;
+    }
+    memset(p->work_host, 0, kSplitCounterBytes);
+    HIP_TRY(hipMemcpy(p->work_dev, p->work_host, kSplitCounterBytes, hipMemcpyHostToDevice));
+    return APAR_OK;
+}
+
+void release_workspace(apar_pool* p) {
+    for (StageSlot& s : p->stage) {
+        if (s.own && s.host) (void)hipHostFree(s.host);
+        if (s.own && s.dev) (void)hipFree(s.dev);
+        if (s.ev) (void)hipEventDestroy(s.ev);
+        if (s.up) (void)hipEventDestroy(s.up);
+    }
+    if (p->work_host) (void)hipHostFree(p->work_host);
+    if (p->work_dev) (void)hipFree(p->work_dev);
+    if (p->fixed_up) (void)hipEventDestroy(p->fixed_up);
 }
 
 int acquire_stage(apar_pool* p, size_t bytes, StageSlot** out) {
@@ -937,32 +979,10 @@ int apar_pool_create(const apar_pool_config* cfg, void* kv_dev, size_t kv_bytes,
         hipPointerAttribute_t attr;
         if (hipPointerGetAttributes(&attr, kv_dev) == hipSuccess) p->device = attr.device;
         else (void)hipGetLastError();
-        // what apar_decode_attention_fixed needs and may not obtain itself: the address of this device's copy of
-        // the static workspace, a pinned buffer to stage its plan in and the event that follows the upload
         DeviceGuard guard(p->device);
-        int rc = APAR_OK;
-        if (!hip_ok(fixed_workspace_of_device(p->device, &p->fixed_dev), "hipGetSymbolAddress(scratch)")) rc = APAR_ERR_HIP;
-        if (rc == APAR_OK && !hip_ok(hipHostMalloc((void**)&p->fixed_host, kFixedPlanBytes, hipHostMallocDefault), "hipHostMalloc"))
-            rc = APAR_ERR_HIP;
-        if (rc == APAR_OK && !hip_ok(hipEventCreateWithFlags(&p->fixed_up, hipEventDisableTiming), "hipEventCreate"))
-            rc = APAR_ERR_HIP;
-        p->split_bytes = std::min(kSplitStateBytes, std::max((size_t)1 << 20, (size_t)(block * cfg->num_blocks) / 8));
-        if (rc == APAR_OK && (!hip_ok(hipMalloc((void**)&p->split_dev, kSplitCounterBytes + p->split_bytes), "hipMalloc(split)") ||
-                              !hip_ok(hipMemset(p->split_dev, 0, kSplitCounterBytes), "hipMemset(split)")))
-            rc = APAR_ERR_HIP;  // (the copies that set the staging slots up follow it and are waited for)
-        // two staging slots at their smallest, so that a pool's first decode call does not stop to set them up (the appends
-        // before it, whose tables go along with their kernels, do not use them)
-        for (int k = 0; k < 2; ++k)
-            if (rc == APAR_OK) rc = grow_slot(p->stage[k], 0);
+        const int rc = set_up_workspace(p, (size_t)(block * cfg->num_blocks));
         if (rc != APAR_OK) {
-            for (StageSlot& s : p->stage) {
-                if (s.host) (void)hipHostFree(s.host);
-                if (s.dev) (void)hipFree(s.dev);
-                if (s.ev) (void)hipEventDestroy(s.ev);
-            }
-            if (p->split_dev) (void)hipFree(p->split_dev);
-            if (p->fixed_up) (void)hipEventDestroy(p->fixed_up);
-            if (p->fixed_host) (void)hipHostFree(p->fixed_host);
+            release_workspace(p);
             delete p;
             return rc;
         }
@@ -995,16 +1015,8 @@ int apar_pool_destroy(apar_pool* p) {
     DeviceGuard guard(p->device);
     int rc = APAR_OK;
     if (!hip_ok(hipDeviceSynchronize(), "hipDeviceSynchronize")) rc = APAR_ERR_HIP;
-    for (StageSlot& s : p->stage) {
-        if (s.host) (void)hipHostFree(s.host);
-        if (s.dev) (void)hipFree(s.dev);
-        if (s.ev) (void)hipEventDestroy(s.ev);
-        if (s.up) (void)hipEventDestroy(s.up);
-    }
+    release_workspace(p);
     if (p->copy_stream) (void)hipStreamDestroy(p->copy_stream);
-    if (p->fixed_host) (void)hipHostFree(p->fixed_host);
-    if (p->fixed_up) (void)hipEventDestroy(p->fixed_up);
-    if (p->split_dev) (void)hipFree(p->split_dev);
     if (p->part.o) (void)hipFree(p->part.o);
     if (p->part.ml) (void)hipFree(p->part.ml);
     auto drop = [](hipEvent_t e) {

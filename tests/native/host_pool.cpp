@@ -1,0 +1,163 @@
+// The host side of a pool that launches, against a HIP runtime that runs on the host: allocations are counted and can be
+// refused, copies happen at once, kernels only look at what they were handed.  Built and run by
+// tests/test_pool_resources.py, which names the check to run.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "apar_internal.hpp"
+
+#define CHECK(c)                                                              \
+    do {                                                                      \
+        if (!(c)) {                                                           \
+            std::fprintf(stderr, "check failed: %s (line %d)\n", #c, __LINE__); \
+            std::exit(1);                                                     \
+        }                                                                     \
+    } while (0)
+
+// ---- the runtime ------------------------------------------------------------------------------------
+static std::map<char*, size_t> g_dev, g_host;      // live allocations
+static int g_allocs = 0, g_refuse = -1;            // allocations so far; the one to refuse (-1: none)
+static bool g_refuse_rest = false;                 // ... and all after it
+static int g_waits = 0, g_objects = 0;             // calls that wait for the device; live events and streams
+static hipError_t g_last = hipSuccess;
+
+static hipError_t failed(hipError_t e) { return g_last = e; }
+static hipError_t allocate(std::map<char*, size_t>& live, void** out, size_t size) {
+    const int n = g_allocs++;
+    if (n == g_refuse || (g_refuse_rest && g_refuse >= 0 && n > g_refuse)) return failed(hipErrorOutOfMemory);
+    char* p = (char*)std::aligned_alloc(256, (size + 255) / 256 * 256);
+    std::memset(p, 0xa5, size);
+    live[p] = size;
+    *out = p;
+    return hipSuccess;
+}
+static hipError_t release(std::map<char*, size_t>& live, void* p) {
+    if (!p) return hipSuccess;
+    g_waits += 1;
+    CHECK(live.erase((char*)p) == 1);
+    std::free(p);
+    return hipSuccess;
+}
+static bool on_device(const void* p, size_t bytes) {
+    auto it = g_dev.upper_bound((char*)p);
+    return it != g_dev.begin() && (--it, (char*)p + bytes <= it->first + it->second);
+}
+extern "C" {
+hipError_t hipMalloc(void** p, size_t size) { return allocate(g_dev, p, size); }
+hipError_t hipFree(void* p) { return release(g_dev, p); }
+hipError_t hipHostMalloc(void** p, size_t size, unsigned int) { return allocate(g_host, p, size); }
+hipError_t hipHostFree(void* p) { return release(g_host, p); }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { g_waits += 1; std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemset(void* d, int v, size_t n) { std::memset(d, v, n); return hipSuccess; }
+hipError_t hipDeviceSynchronize() { g_waits += 1; return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { g_objects += 1; *e = (hipEvent_t)std::malloc(1); return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { return hipEventCreateWithFlags(e, 0); }
+hipError_t hipEventDestroy(hipEvent_t e) { g_objects -= 1; std::free((void*)e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) { CHECK(e != nullptr); return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }  // (a slot's last kernels: done by then)
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0.0f; return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { g_objects += 1; *s = (hipStream_t)std::malloc(1); return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) { g_objects -= 1; std::free((void*)s); return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetLastError() { const hipError_t e = g_last; g_last = hipSuccess; return e; }
+const char* hipGetErrorString(hipError_t) { return "refused"; }
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void*) { *a = hipPointerAttribute_t{}; return hipSuccess; }
+}
+
+// ---- the kernels ------------------------------------------------------------------------------------
+static apar::PlanDev g_plan;  // of the last decode or row-tile prefill call
+static std::vector<apar::SplitBlock> g_blocks;
+static char* g_fixed = nullptr;
+namespace apar {
+hipError_t fixed_workspace_of_device(int, char** out) {
+    if (!g_fixed) g_fixed = (char*)std::aligned_alloc(256, (size_t)APAR_FIXED_PLAN_BYTES + APAR_FIXED_PARTIAL_BYTES);
+    *out = g_fixed;
+    return hipSuccess;
+}
+hipError_t launch_append_blocks(const Shape&, void*, const void*, const void*, const int32_t*, bool, int, int, int, hipStream_t) { return hipGetLastError(); }
+hipError_t launch_block_copies(const Shape&, void*, const int32_t*, int, hipStream_t) { return hipGetLastError(); }
+hipError_t launch_read_rows(const Shape&, const void*, const int32_t* codes, int n, void*, void*, hipStream_t) {
+    CHECK(on_device(codes, (size_t)n * 4));
+    return hipGetLastError();
+}
+hipError_t launch_scatter_words(int32_t*, const int32_t*, int, hipStream_t) { return hipGetLastError(); }
+// Every cut unit's states and counters lie in memory of their own, and no unit is cut without room for them.
+hipError_t launch_attention_partial(const Shape& s, const void*, const void*, const PlanDev& plan, int, PartialBuf, const void*, const void*,
+                                    const uint8_t*, void*, ClassStreams&, hipStream_t) {
+    g_plan = plan;
+    g_blocks.clear();
+    if (plan.split.blocks) {
+        const char* base = plan.inline_words ? (const char*)plan.inline_words : nullptr;
+        const SplitBlock* b = (const SplitBlock*)(base + (size_t)plan.split.blocks);
+        const WgDesc* wgs = (const WgDesc*)(base + (size_t)plan.wgs);
+        g_blocks.assign(b, b + plan.split.n_blocks_class[0] + plan.split.n_blocks_class[1] + plan.split.n_blocks_class[2]);
+        for (const SplitBlock& x : g_blocks) {
+            const int n = x.slice >> 16, tiles = (wgs[x.wg].w[0].flags & kWaveSplit ? 1 : 4) * (wgs[x.wg].row_tiles & 255);
+            if (n == 1) continue;
+            const size_t tile = (size_t)(s.d / 4 + 2) * 64 * 4;
+            CHECK(on_device((char*)plan.split.state + (size_t)x.state * s.n_kv * tile, (size_t)n * tiles * s.n_kv * tile));
+            const int32_t* counters = plan.split.arrived + (size_t)x.cut * s.n_kv * 4;
+            CHECK(on_device(counters, (size_t)s.n_kv * 16));
+            for (int i = 0; i < s.n_kv * 4; ++i) CHECK(counters[i] == 0);
+        }
+    }
+    return hipGetLastError();
+}
+hipError_t launch_prefill_bf16(const Shape&, const void*, const void*, const PrefillWg*, const int32_t*, int, void*, hipStream_t) { return hipGetLastError(); }
+hipError_t launch_merge(const Shape&, const PlanDev&, PartialBuf, const void*, const void*, const void*, const uint8_t*, int, void*, hipStream_t) {
+    return hipGetLastError();
+}
+}  // namespace apar
+
+// ---- checks -----------------------------------------------------------------------------------------
+static char g_kv[256] __attribute__((aligned(256)));  // (no kernel runs: the pool's memory is never touched)
+static void* const kRows = g_kv;
+
+static int create(int n_q, int n_kv, int dtype, int64_t blocks, apar_pool** p) {
+    apar_pool_config c{};
+    c.n_q_heads = n_q, c.n_kv_heads = n_kv, c.head_dim = 128, c.block_size = 16, c.dtype = dtype, c.max_threads = 1 << 20, c.num_blocks = blocks;
+    return apar_pool_create(&c, g_kv, (size_t)1 << 60, p);
+}
+static apar_thread thread_of(apar_pool* p, int n) {
+    apar_thread t;
+    CHECK(apar_thread_create(p, &t) == APAR_OK && apar_append_kv(p, t, kRows, kRows, n, nullptr) == APAR_OK);
+    return t;
+}
+
+// Once a pool is there, its first calls neither allocate nor wait, whichever staging slot they come to.
+static void staging() {
+    apar_pool* p;
+    CHECK(create(8, 8, APAR_BF16, 4000, &p) == APAR_OK);
+    std::vector<apar_thread> ids;
+    for (int i = 0; i < 120; ++i) ids.push_back(thread_of(p, 100 + i));
+    const int allocs = g_allocs, waits = g_waits;
+    for (int step = 0; step < 9; ++step) {
+        CHECK(apar_decode_attention(p, kRows, ids.data(), (int)ids.size(), kRows, nullptr) == APAR_OK);
+        CHECK(g_plan.inline_words == nullptr);  // (staged)
+        CHECK(apar_read_kv_rows(p, ids[0], 0, 100, kRows, kRows, nullptr) == APAR_OK);
+        CHECK(apar_append_kv_batch(p, ids.data(), (int)ids.size(), kRows, kRows, nullptr) == APAR_OK);
+    }
+    CHECK(g_allocs == allocs && g_waits == waits);
+    // a larger request takes memory of its own, and still does not wait the first time
+    const apar_thread big = thread_of(p, 40000);
+    CHECK(apar_read_kv_rows(p, big, 0, 40000, kRows, kRows, nullptr) == APAR_OK);
+    std::vector<int32_t> m(1, 40000);
+    CHECK(g_waits == waits);
+    CHECK(apar_pool_destroy(p) == APAR_OK);
+    CHECK(g_dev.empty() && g_host.empty() && g_objects == 0);
+}
+
+int main(int argc, char** argv) {
+    const std::map<std::string, void (*)()> checks = {{"staging", staging}};
+    CHECK(argc == 2 && checks.count(argv[1]));
+    checks.at(argv[1])();
+    std::printf("ok: %s\n", argv[1]);
+    return 0;
+}
