@@ -194,16 +194,28 @@ int grow_slot(StageSlot& s, size_t bytes) {
 // (measured, one after the other: the third and fourth call of a new pool took 60 to 80 us on the host against 17), in one
 // pinned and one device allocation (a slot each: 250 -> 290 us for a small pool).  One copy clears the counters and
 // takes the pair of allocations through its first transfer.
+// A pool does without all of this but the buffer of apar_decode_attention_fixed, whose calls may not allocate: where memory
+// is short, slots are set up by the calls that need them and no unit is cut.
 int set_up_workspace(apar_pool* p, size_t pool_bytes) {
     if (!hip_ok(fixed_workspace_of_device(p->device, &p->fixed_dev), "hipGetSymbolAddress(scratch)")) return APAR_ERR_HIP;
     HIP_TRY(hipEventCreateWithFlags(&p->fixed_up, hipEventDisableTiming));
     for (StageSlot& s : p->stage) HIP_TRY(hipEventCreateWithFlags(&s.ev, hipEventDisableTiming));
-    p->split_bytes = std::min(kSplitStateBytes, std::max((size_t)1 << 20, pool_bytes / 8));
-    const size_t split = kSplitCounterBytes + p->split_bytes;
-    HIP_TRY(hipHostMalloc((void**)&p->work_host, kFixedPlanBytes + kStageSlots * kStageBytes, hipHostMallocDefault));
-    HIP_TRY(hipMalloc((void**)&p->work_dev, split + kStageSlots * kStageBytes));
+    if (hipHostMalloc((void**)&p->work_host, kFixedPlanBytes + kStageSlots * kStageBytes, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        HIP_TRY(hipHostMalloc((void**)&p->work_host, kFixedPlanBytes, hipHostMallocDefault));
+        p->fixed_host = p->work_host;
+        return APAR_OK;
+    }
     p->fixed_host = p->work_host;
+    const size_t state_bytes = std::min(kSplitStateBytes, std::max((size_t)1 << 20, pool_bytes / 8));
+    const size_t split = kSplitCounterBytes + state_bytes;
+    if (hipMalloc((void**)&p->work_dev, split + kStageSlots * kStageBytes) != hipSuccess) {
+        (void)hipGetLastError();
+        p->work_dev = nullptr;
+        return APAR_OK;
+    }
     p->split_dev = p->work_dev;
+    p->split_bytes = state_bytes;
     for (int k = 0; k < kStageSlots; ++k) {
         p->stage[k].host = p->work_host + kFixedPlanBytes + k * kStageBytes;
         p->stage[k].dev = p->work_dev + split + k * kStageBytes;
@@ -434,6 +446,7 @@ void cut_into_slices(const PlanHost& ph, const Shape& s, size_t state_bytes, std
     out.clear();
     n_class[0] = n_class[1] = n_class[2] = 0;
     n_cut = 0;
+    if (state_bytes == 0) return;
     auto cost = [](const WgDesc& wg) {
         return wg.n_coop + std::max(std::max(wg.w[0].n_tiles, wg.w[1].n_tiles), std::max(wg.w[2].n_tiles, wg.w[3].n_tiles));
     };

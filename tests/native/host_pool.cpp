@@ -1,6 +1,7 @@
 // The host side of a pool that launches, against a HIP runtime that runs on the host: allocations are counted and can be
 // refused, copies happen at once, kernels only look at what they were handed.  Built and run by
 // tests/test_pool_resources.py, which names the check to run.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -154,8 +155,31 @@ static void staging() {
     CHECK(g_dev.empty() && g_host.empty() && g_objects == 0);
 }
 
+// What a pool works in besides its blocks is only needed by some calls: whichever allocation is refused, alone or with
+// all after it, creation succeeds as long as the buffer of the entry point that may not allocate is there.
+static void creation() {
+    for (int rest = 0; rest < 2; ++rest)
+        for (int k = 0; k < 4; ++k) {
+            apar_pool* p = nullptr;
+            g_allocs = 0, g_refuse = k, g_refuse_rest = rest != 0;
+            const int rc = create(8, 8, APAR_BF16, 4000, &p);
+            const bool refused = g_allocs > k;
+            g_refuse = -1;
+            CHECK(rc == (rest && k == 0 ? APAR_ERR_HIP : APAR_OK) && (rc == APAR_OK) == (p != nullptr));
+            if (p) {
+                const apar_thread t = thread_of(p, 1600);
+                CHECK(apar_decode_attention(p, kRows, &t, 1, kRows, nullptr) == APAR_OK);  // (a long walk: cut where there is room)
+                int slices = 0;
+                for (const apar::SplitBlock& b : g_blocks) slices = std::max(slices, b.slice >> 16);
+                CHECK((slices > 1) == !refused);
+                CHECK(apar_read_kv_rows(p, t, 0, 1600, kRows, kRows, nullptr) == APAR_OK);
+            }
+            CHECK(apar_pool_destroy(p) == APAR_OK && g_dev.empty() && g_host.empty() && g_objects == 0);
+        }
+}
+
 int main(int argc, char** argv) {
-    const std::map<std::string, void (*)()> checks = {{"staging", staging}};
+    const std::map<std::string, void (*)()> checks = {{"staging", staging}, {"creation", creation}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();
     std::printf("ok: %s\n", argv[1]);
