@@ -217,9 +217,9 @@ APAR_API int apar_decode_attention_spec(apar_pool* pool, const void* q_dev, cons
  * library allocates, every kernel runs on `hip_stream` itself, and the call creates no stream or
  * event and is never profiled.  It calls no hipMalloc, hipFree, hipHostMalloc or any other
  * allocating routine (what it needs besides - the workspace's address on the pool's device, a
- * pinned staging buffer of APAR_FIXED_PLAN_BYTES and one event - apar_pool_create obtained).  A unit that
- * is cut into several workgroups leaves its rows' states in the workspace too; where the tables of that do not
- * fit any more the units stay whole (same result to rounding).
+ * pinned staging buffer of APAR_FIXED_PLAN_BYTES, one event and the room for the rows' states of units cut
+ * into several workgroups - apar_pool_create obtained).  Where the tables of such a cut do not fit any more
+ * the units stay whole (same result to rounding).
  * Limits: the staged plan (128 bytes per workgroup, 8 per block read, 8 per listed thread and 4
  * per partial result to merge) must fit APAR_FIXED_PLAN_BYTES, and the partial results
  * ((head_dim + 2) floats per (partial row, q head); none when every sharing subtree fits one work

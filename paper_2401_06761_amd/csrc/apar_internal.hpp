@@ -226,7 +226,7 @@ constexpr int kSplitMaxCut = 1024;
 constexpr size_t kSplitCounterBytes = (size_t)kSplitMaxCut * 4 * sizeof(int32_t);
 
 // Where `device`'s copy of the library's static workspace (APAR_FIXED_PLAN_BYTES of plan tables followed by
-// APAR_FIXED_PARTIAL_BYTES of partial results and kSplitStateBytes of row states) lives.  `device` must be the current device.  The address is
+// APAR_FIXED_PARTIAL_BYTES of partial results) lives.  `device` must be the current device.  The address is
 // asked for once per device and kept.
 hipError_t fixed_workspace_of_device(int device, char** out);
 

@@ -611,8 +611,6 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     ofs[4] = align_up(ofs[3] + ph.path_ofs.size() * 4, 256);
     ofs[5] = align_up(ofs[4] + ph.path_ids.size() * 4, 256);
     ofs[6] = align_up(ofs[5] + p->split_blocks.size() * sizeof(SplitBlock), 256);
-    // (apar_decode_attention_fixed stages the counters of slices that have arrived too, as zeros)
-    const size_t counter_bytes = p->n_split_cut * p->shape.n_kv * 4 * sizeof(int32_t);
     const size_t staged = ofs[6];
     bool cut = !p->split_blocks.empty();
     const size_t slots = (size_t)ph.n_partial_rows * n_cand * p->shape.n_q;
@@ -663,8 +661,8 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
         dev = p->fixed_dev;
         part.o = (float*)(p->fixed_dev + kFixedPlanBytes);
         part.ml = part.o + cap_slots * p->shape.d;
-        cut = cut && staged + counter_bytes <= kFixedPlanBytes;
-        fixed_bytes = cut ? staged + counter_bytes : ofs[5];
+        cut = cut && staged <= kFixedPlanBytes;
+        fixed_bytes = cut ? staged : ofs[5];
     } else if (!inlined) {
         if ((rc = acquire_stage(p, staged, &s)) != APAR_OK) return rc;
         host = s->host;
@@ -676,10 +674,7 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
         memcpy(host + ofs[2], ph.dfs_threads.data(), ph.dfs_threads.size() * 4);
         memcpy(host + ofs[3], ph.path_ofs.data(), ph.path_ofs.size() * 4);
         if (!ph.path_ids.empty()) memcpy(host + ofs[4], ph.path_ids.data(), ph.path_ids.size() * 4);
-        if (cut) {
-            memcpy(host + ofs[5], p->split_blocks.data(), p->split_blocks.size() * sizeof(SplitBlock));
-            if (fixed) memset(host + staged, 0, counter_bytes);
-        }
+        if (cut) memcpy(host + ofs[5], p->split_blocks.data(), p->split_blocks.size() * sizeof(SplitBlock));
     }
 
     // partial-result buffer
@@ -721,9 +716,9 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     if (cut) {
         pd.split.blocks = (const SplitBlock*)(dev + ofs[5]);
         for (int k = 0; k < 3; ++k) pd.split.n_blocks_class[k] = p->n_split_class[k];
-        pd.split.arrived = (int32_t*)(fixed ? dev + staged : p->split_dev);
-        pd.split.state = (float*)(fixed ? p->fixed_dev + kFixedPlanBytes + kFixedPartBytes : p->split_dev + kSplitCounterBytes);
     }
+    pd.split.arrived = (int32_t*)p->split_dev;  // (no room: nothing is cut and nothing reads either)
+    pd.split.state = p->split_dev ? (float*)(p->split_dev + kSplitCounterBytes) : nullptr;
 
     if (inlined) {
         pd.wgs = (const WgDesc*)p->inline_ofs[0];
@@ -732,8 +727,6 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
         pd.path_ofs = pd.path_ids = nullptr;  // (nothing to merge)
         pd.split.blocks = (const SplitBlock*)p->inline_ofs[3];
         for (int k = 0; k < 3; ++k) pd.split.n_blocks_class[k] = cut ? p->n_split_class[k] : ph.n_wg_class[k];
-        pd.split.arrived = (int32_t*)p->split_dev;
-        pd.split.state = (float*)(p->split_dev + kSplitCounterBytes);
         pd.inline_words = p->inline_words.data();
         pd.n_inline_words = (int32_t)p->inline_words.size();
     }

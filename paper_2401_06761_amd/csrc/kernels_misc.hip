@@ -362,13 +362,13 @@ __global__ __launch_bounds__(256) void merge_rows(PlanDev plan, PartialBuf part,
 }  // namespace
 
 // ---------------------------------------------------------------------------
-// Fixed workspace of apar_decode_attention_fixed: the plan tables, the partial results and the row states of
-// units cut into slices of one call live in this array instead of in memory the library allocates.  Every GPU the library runs on holds its own
+// Fixed workspace of apar_decode_attention_fixed: the plan tables and the partial results of one call live
+// in this array instead of in memory the library allocates.  Every GPU the library runs on holds its own
 // copy of the array, at its own address, until the process ends.  In host code the array's name is only a
 // handle of the symbol, not a device address: the address comes from hipGetSymbolAddress, once per device
 // with that device current, and that pointer is what kernels and copies are given.
 // ---------------------------------------------------------------------------
-static __device__ __align__(256) unsigned char scratch[(size_t)APAR_FIXED_PLAN_BYTES + (size_t)APAR_FIXED_PARTIAL_BYTES + kSplitStateBytes];
+static __device__ __align__(256) unsigned char scratch[(size_t)APAR_FIXED_PLAN_BYTES + (size_t)APAR_FIXED_PARTIAL_BYTES];
 
 namespace {
 constexpr int kMaxDevices = 64;

@@ -178,8 +178,25 @@ static void creation() {
         }
 }
 
+// The entry point that may not allocate cuts as the other does, its states in the pool's own memory: the workspace that is
+// part of the device image holds tables and partial results, nothing after them.
+static void fixed() {
+    apar_pool* p;
+    CHECK(create(8, 8, APAR_BF16, 4000, &p) == APAR_OK);
+    const apar_thread t = thread_of(p, 1600);
+    for (int k = 0; k < 2; ++k) {
+        CHECK(apar_decode_attention(p, kRows, &t, 1, kRows, nullptr) == APAR_OK);
+        const std::vector<apar::SplitBlock> as = g_blocks;
+        const int allocs = g_allocs;
+        CHECK(apar_decode_attention_fixed(p, kRows, &t, 1, kRows, nullptr) == APAR_OK);  // (where the states lie: at the launch)
+        CHECK(g_allocs == allocs && as.size() > 1 && as.size() == g_blocks.size());
+        for (size_t i = 0; i < as.size(); ++i) CHECK(std::memcmp(&as[i], &g_blocks[i], sizeof as[i]) == 0);
+    }
+    CHECK(apar_pool_destroy(p) == APAR_OK);
+}
+
 int main(int argc, char** argv) {
-    const std::map<std::string, void (*)()> checks = {{"staging", staging}, {"creation", creation}};
+    const std::map<std::string, void (*)()> checks = {{"staging", staging}, {"creation", creation}, {"fixed", fixed}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();
     std::printf("ok: %s\n", argv[1]);
