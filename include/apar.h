@@ -493,8 +493,9 @@ APAR_API int apar_set_inline_shared(apar_pool* pool, int on);
  * under a prefill plan (16-row tiles; a prefix shared by sibling threads is read once for all of them),
  * MATRIX the 32x32 matrix-core kernel (one workgroup per thread and chunk of 128 query rows; needs a
  * group size that divides 16, otherwise the call stays on ROW_TILES).  AUTO (default) takes MATRIX when
- * the threads bring 32 query rows each (query tokens x q heads per kv head) or more on average, or a query token
- * attends to 1024 rows or more on average.  Both give the same result to rounding.
+ * most of the rows walked are walked for threads with more than 64 query rows (query tokens x q heads per kv head),
+ * on bf16 pools also for large calls and where a query token attends to 1024 rows or more on average.
+ * Both give the same result to rounding.
  * fp8 pools take the matrix kernel under AUTO, by the same rule, and ROW_TILES otherwise; fp32 pools ignore the knob.
  * apar_last_prefill_kernel tells which one the most recent call ran (0: none). */
 enum { APAR_PREFILL_AUTO = 0, APAR_PREFILL_ROW_TILES = 1, APAR_PREFILL_MATRIX = 2 };

@@ -764,15 +764,36 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     return APAR_OK;
 }
 
-// A prefill call on a bf16 or fp8 pool goes to the 32x32 kernel by itself when its threads bring this many query rows each (query tokens
-// x q heads of a kv group, on average: one wavefront's worth), or when a query token attends to this many rows.
-// Measured (us, row tiles / matrix kernel): 360 threads of walks around 1000, 32 kv heads, m query tokens each: m = 1
-// 904 / 656, 32 1007 / 677, whole segments (90 on average) 1652 / 1224; walks around 200: m = 1 255 / 279, 16 301 / 291, 32 309 / 300,
-// whole 589 / 489; 8 kv heads (4 rows per token): m = 4 84 / 90, 8 87 / 92, 16 95 / 105, 32 156 / 128, whole 417 / 353.
-// fp8 pools, whole segments: walks of 300, 900, 3300, 32 kv heads 730 / 694, 378 / 360, 457 / 418; two prompts of 100 to 400
-// tokens, 8 kv heads 81 / 37, six of 1 k to 8 k 2254 / 1974 (whole call).
-constexpr int64_t kMatrixPrefillRows = 32;
+// Whether a prefill call on a bf16 or fp8 pool goes to the 32x32 kernel by itself.  That kernel gives a workgroup up to 128
+// query rows (tokens x q heads of a kv group) of one thread; a row-tile workgroup with one row tile per wavefront holds 64.
+//  - Threads of more than 64 rows are faster there, the others on the row tiles: what decides is the rows that the
+//    workgroups of either kind walk, so that one long prompt does not take hundreds of short threads with it.
+//    Measured (us, row tiles / matrix kernel; 362 threads, walks around 300, bf16): group 1, 59 and 69 rows 302 / 305, 527 / 421;
+//    group 4, 64 and 80 rows 110 / 122, 166 / 130; group 16, 64 and 80 rows 50 / 55, 64 / 57; fp8 pools: group 1 338 / 436,
+//    494 / 451, group 4 101 / 128, 169 / 135; walks around 950, group 4: bf16 218 / 225, 317 / 249, fp8 189 / 252, 318 / 264.
+//    360 threads of one row and walks of 300 beside a prompt of 2000, group 8: bf16 124 / 93, fp8 130 / 101; walks of 900
+//    beside it: group 4 188 / 205, group 1 439 / 620.  (fp8 pools, group 8 or more, 112 to 128 rows per thread: 2 to 7 % slower.)
+//  - bf16 pools: from 32 rows per workgroup on, a large call (kMatrixPrefillWalked rows walked by all its workgroups, kv
+//    heads counted) is faster there all the same: group 1, 48 rows, 362 threads of walks around 400, 700, 1050 (4.6, 8, 12 M)
+//    410 / 390, 670 / 560, 1015 / 773; group 4, 48 rows, 891 threads (2.9, 5, 7.5 M) 233 / 266, 377 / 371, 573 / 488;
+//    and calls whose query tokens attend to kMatrixPrefillMeanWalk rows on average go there (group 1, one token each, 360 threads,
+//    around 1000 rows: 904 / 656).  fp8 pools: neither (362 threads, group 4, around 1050 rows, 32 and 64 rows 189 / 226, 189 / 252).
+constexpr int64_t kMatrixPrefillRows = 64, kMatrixPrefillMinRows = 32;
+constexpr int64_t kMatrixPrefillWalked = 4500000;
 constexpr int64_t kMatrixPrefillMeanWalk = 1024;
+bool prefill_on_matrix(const Shape& s, const std::vector<PrefillThreadView>& views, int64_t rows, int64_t attended) {
+    const int64_t chunk = 128 / s.group;
+    int64_t wgs = 0, wide = 0, narrow = 0;
+    for (const PrefillThreadView& t : views) {
+        const int64_t w = (t.m + chunk - 1) / chunk;  // workgroups; each walks to its last token
+        wgs += w;
+        ((int64_t)t.m * s.group > kMatrixPrefillRows ? wide : narrow) += w * (t.len - t.m) + chunk * (w - 1) * w / 2 + t.m;
+    }
+    if (wide >= narrow) return true;
+    if (s.fp8_sealed) return false;
+    return attended >= kMatrixPrefillMeanWalk * rows ||
+           (rows * s.group >= kMatrixPrefillMinRows * wgs && (wide + narrow) * s.n_kv >= kMatrixPrefillWalked);
+}
 
 // bf16 pools: the matrix-core prefill kernel.  One workgroup per (thread, chunk of 128 / group query tokens);
 // the threads' block tables are staged next to the workgroup descriptors.
@@ -881,14 +902,11 @@ int prefill_common(apar_pool* p, const void* q, const apar_thread* ids, const in
     if (rows > INT32_MAX / 2) return APAR_ERR_UNSUPPORTED;
     PlanHost& ph = p->plan;
     int rc = APAR_OK;
-    // 16-bit pools have two kernels.  The 32x32 matrix-core kernel wants a wavefront's worth of rows per thread or a long
-    // walk to spread its fixed cost per workgroup over; a few rows with short walks stay on the row-tile kernel.
     p->last_prefill_kernel = APAR_PREFILL_ROW_TILES;
     // (an fp8 pool takes the matrix kernel by AUTO only)
     if (!p->dry_run && p->shape.dtype == APAR_BF16 && 16 % p->shape.group == 0 &&
         ((p->prefill_kernel == APAR_PREFILL_MATRIX && !p->shape.fp8_sealed) ||
-         (p->prefill_kernel == APAR_PREFILL_AUTO &&
-          (rows * p->shape.group >= kMatrixPrefillRows * n || attended >= kMatrixPrefillMeanWalk * rows)))) {
+         (p->prefill_kernel == APAR_PREFILL_AUTO && prefill_on_matrix(p->shape, views, rows, attended)))) {
         p->last_prefill_kernel = APAR_PREFILL_MATRIX;
         return prefill_bf16(p, views, rows, attended, q, out, stream, t0);
     }

@@ -195,8 +195,37 @@ static void fixed() {
     CHECK(apar_pool_destroy(p) == APAR_OK);
 }
 
+// Which kernel a prefill call goes to by itself: the faster one of calls that were measured on both.
+static void prefill() {
+    struct Call { int dtype, n_q, n_kv, threads, len, m, long_m, kernel; };  // long_m: one prompt of that many tokens besides
+    const int T = APAR_PREFILL_ROW_TILES, M = APAR_PREFILL_MATRIX;
+    const Call calls[] = {
+        {APAR_BF16_FP8KV, 32, 32, 362, 380, 48, 0, T},  {APAR_BF16_FP8KV, 32, 32, 362, 380, 90, 0, M},  // 318 / 433, 507 / 479 us
+        {APAR_BF16_FP8KV, 32, 4, 891, 380, 6, 0, T},    {APAR_BF16_FP8KV, 32, 4, 891, 380, 10, 0, M},   // 110 / 152, 167 / 163
+        {APAR_BF16_FP8KV, 32, 8, 362, 1100, 16, 0, T},  {APAR_BF16_FP8KV, 32, 8, 362, 1100, 20, 0, M},  // 189 / 252, 318 / 264
+        {APAR_BF16, 32, 8, 362, 300, 16, 0, T},         {APAR_BF16, 32, 8, 362, 300, 24, 0, M},         // 95 / 105, 150 / 113
+        {APAR_BF16, 32, 16, 179, 700, 24, 0, T},        {APAR_BF16, 32, 16, 179, 700, 40, 0, M},        // 150 / 163, 223 / 180
+        {APAR_BF16, 32, 32, 179, 380, 48, 0, T},        {APAR_BF16, 32, 32, 891, 700, 48, 0, M},        // 196 / 204, 1836 / 1351
+        {APAR_BF16, 32, 32, 362, 300, 1, 0, T},         {APAR_BF16, 32, 32, 362, 1100, 1, 0, M},        // 254 / 282, 793 / 614
+        {APAR_BF16, 32, 32, 360, 901, 1, 2000, T},      {APAR_BF16, 32, 4, 360, 301, 1, 2000, M},       // 439 / 620, 124 / 93
+        {APAR_BF16_FP8KV, 32, 4, 360, 301, 1, 2000, M}, {APAR_BF16, 32, 8, 360, 901, 1, 2000, T},       // 130 / 101, 188 / 205
+    };
+    for (const Call& c : calls) {
+        apar_pool* p;
+        CHECK(create(c.n_q, c.n_kv, c.dtype, 70000, &p) == APAR_OK);
+        std::vector<apar_thread> ids;
+        for (int i = 0; i < c.threads; ++i) ids.push_back(thread_of(p, c.len));
+        std::vector<int32_t> m(ids.size(), c.m);
+        if (c.long_m) ids.push_back(thread_of(p, c.long_m)), m.push_back(c.long_m);
+        CHECK(apar_prefill_attention(p, kRows, ids.data(), m.data(), (int)ids.size(), kRows, nullptr) == APAR_OK);
+        if (apar_last_prefill_kernel(p) != c.kernel) std::fprintf(stderr, "call %d\n", (int)(&c - calls));
+        CHECK(apar_last_prefill_kernel(p) == c.kernel);
+        CHECK(apar_pool_destroy(p) == APAR_OK);
+    }
+}
+
 int main(int argc, char** argv) {
-    const std::map<std::string, void (*)()> checks = {{"staging", staging}, {"creation", creation}, {"fixed", fixed}};
+    const std::map<std::string, void (*)()> checks = {{"staging", staging}, {"creation", creation}, {"fixed", fixed}, {"prefill", prefill}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();
     std::printf("ok: %s\n", argv[1]);
