@@ -24,11 +24,12 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
 // block it copies - and written once, in matrix-core order.
 // Before, three kernels did this: block copies, row writes, and a pass that read full blocks back and rewrote them.
 // Their time against this kernel's (us, with the two events around them): prompts of 300, 1 k, 4 k, 8 k rows, 8 kv heads
-// 8.9, 10.0, 17.5, 28.3 -> 6.8, 7.8, 9.6, 14.2; one row each for 3.8 k threads, 32 heads, one in sixteen sealing 56 -> 58;
+// 8.9, 10.0, 17.5, 28.3 -> 6.8, 7.8, 9.6, 14.2; one row each for 3.8 k threads, 32 heads, one in sixteen sealing 56 -> 47;
 // 5 and 1000 threads forked off a tail of 9 rows 11.2, 74 -> 8.7, 45, off one of 15 (copied and sealed) 10.8, 194 -> 6.9, 67.
 // ---------------------------------------------------------------------------
 // A tile half's rows in LDS: padded, so that sixteen lanes reading one piece of sixteen rows meet sixteen banks.
 constexpr int kSealRowStride = 272;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // fp8 pools: the smallest power of two s for which max |x| / s <= 448, the largest e4m3 magnitude (1 if the half is
 // all zeros), so that the codes use the top binade of the format.  Codes are rounded to nearest even by the hardware
@@ -67,8 +68,12 @@ __device__ __forceinline__ uint2 fp8_piece(const uint16_t (&x)[8], float inv) {
 
 // ROW: bytes of one row of a half.  SEAL: 0 fp32 pools (nothing is sealed), 1 bf16, 2 fp8.  INLINE: the descriptors and
 // the source rows come with the kernel's arguments (the first one, so that they start the argument segment).
-// The blocks that stay open come first, n_open of them: the first workgroups write those, as many lanes as a row has
-// 16-byte pieces per (block, kv head); the others take the full ones, a wavefront per (block, kv head).
+// In the tables the blocks that stay open come first, n_open of them.  The first workgroups take the full ones, a wavefront per
+// (block, kv head), so that the launch does not end on them; the others write the open ones, as many lanes as a row has
+// 16-byte pieces per (block, kv head).  A full block's earlier rows are read with non-temporal loads, other rows (the caller's,
+// shared tails) with plain ones.  Measured, us: 3.8 k threads, 32 heads, one row each, one block in sixteen full: full blocks
+// last 59.6, first 56.4, non-temporal loads for their own rows 47.0; for every row 51.4, and 1000 copies of a tail of 9
+// rows 76 instead of 44.
 template <int ROW, int SEAL, bool INLINE>
 __global__ __launch_bounds__(256) void append_blocks(AppendTables<INLINE> tables, char* __restrict__ pool, const char* __restrict__ k,
                                                      const char* __restrict__ v, int n_blocks, int n_open, int n_src, int n_kv) {
@@ -93,19 +98,19 @@ __global__ __launch_bounds__(256) void append_blocks(AppendTables<INLINE> tables
             return tables.words[4 * n_blocks + i];
         }
     };
-    // 16 bytes of slot `slot` (before s1) of a block, at `ofs` of half `half` (one load, whose address is chosen: a branch
-    // around it would make every load wait where it is issued)
-    auto fetch = [&](const AppendBlock& b, int h, int half, int slot, int ofs) -> uint4 {
+    // where 16 bytes of slot `slot` (before s1) of a block come from, at `ofs` of half `half` (one load, whose address is
+    // chosen: a branch around it would make every load wait where it is issued)
+    auto source = [&](const AppendBlock& b, int h, int half, int slot, int ofs) -> const u32x4* {
         const int s0 = b.slots & 255, row = b.first + max(slot - s0, 0);
         const int64_t from = n_src ? src_of(row) : row;
         const char* fresh = (half ? v : k) + (from * n_kv + h) * ROW;
         const char* old = pool + ((int64_t)(b.copy_of >= 0 ? b.copy_of : b.dst) * n_kv + h) * kTile + half * 16 * ROW + slot * ROW;
-        return *reinterpret_cast<const uint4*>((slot < s0 ? old : fresh) + ofs);
+        return reinterpret_cast<const u32x4*>((slot < s0 ? old : fresh) + ofs);
     };
     constexpr int kPairs = 256 / kLanes;
-    const int open_wgs = (int)(((int64_t)n_open * n_kv + kPairs - 1) / kPairs);
-    if ((int)blockIdx.x < open_wgs) {
-        const int pair = (int)blockIdx.x * kPairs + (int)threadIdx.x / kLanes;  // (open block, kv head), heads fastest
+    const int full_wgs = SEAL ? (int)(((int64_t)(n_blocks - n_open) * n_kv + 3) / 4) : 0;
+    if ((int)blockIdx.x >= full_wgs) {
+        const int pair = ((int)blockIdx.x - full_wgs) * kPairs + (int)threadIdx.x / kLanes;  // (open block, kv head), heads fastest
         const int at = pair / n_kv, h = pair - at * n_kv;
         if (at >= n_open) return;
         const AppendBlock b = block_at(at);
@@ -114,23 +119,23 @@ __global__ __launch_bounds__(256) void append_blocks(AppendTables<INLINE> tables
         const int s1 = b.slots >> 8;
         int s = b.copy_of >= 0 ? 0 : b.slots & 255;
         if (s + 1 == s1) {
-            *reinterpret_cast<uint4*>(dst + s * ROW) = fetch(b, h, half, s, ofs);
+            *reinterpret_cast<u32x4*>(dst + s * ROW) = *source(b, h, half, s, ofs);
             return;
         }
         for (; s < s1; s += 4) {  // four rows in flight
-            uint4 x[4];
+            u32x4 x[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) x[i] = fetch(b, h, half, min(s + i, s1 - 1), ofs);
+            for (int i = 0; i < 4; ++i) x[i] = *source(b, h, half, min(s + i, s1 - 1), ofs);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                if (s + i < s1) *reinterpret_cast<uint4*>(dst + (s + i) * ROW) = x[i];
+                if (s + i < s1) *reinterpret_cast<u32x4*>(dst + (s + i) * ROW) = x[i];
         }
         return;
     }
     if constexpr (SEAL != 0) {
         const int lane = threadIdx.x & 63;
         const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-        const int item = ((int)blockIdx.x - open_wgs) * 4 + wave;  // (full block, kv head), heads fastest
+        const int item = (int)blockIdx.x * 4 + wave;  // (full block, kv head), heads fastest
         const int at = item / n_kv, h = item - at * n_kv;
         if (at >= n_blocks - n_open) return;
         const AppendBlock b = block_at(n_open + at);
@@ -138,9 +143,14 @@ __global__ __launch_bounds__(256) void append_blocks(AppendTables<INLINE> tables
         const int l = lane % kLanes, half = l / (kLanes / 2), chunk = (l % (kLanes / 2)) * 16, sub = lane / kLanes;
         char* tile = pool + ((int64_t)b.dst * n_kv + h) * kTile;
         char* rows = lds[wave];
-        uint4 x[16 / kRows];
+        u32x4 x[16 / kRows];
+        if (b.copy_of < 0 && (b.slots & 255) > 0) {  // its own rows so far, laid out anew: not read again as they are
 #pragma unroll
-        for (int i = 0; i < 16 / kRows; ++i) x[i] = fetch(b, h, half, i * kRows + sub, chunk);
+            for (int i = 0; i < 16 / kRows; ++i) x[i] = __builtin_nontemporal_load(source(b, h, half, i * kRows + sub, chunk));
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16 / kRows; ++i) x[i] = *source(b, h, half, i * kRows + sub, chunk);
+        }
         float scale[2] = {1.0f, 1.0f};
         if constexpr (SEAL == 2) {
             float top = 0.0f;
@@ -164,7 +174,7 @@ __global__ __launch_bounds__(256) void append_blocks(AppendTables<INLINE> tables
             __builtin_amdgcn_wave_barrier();
             if (half == hf) {
 #pragma unroll
-                for (int i = 0; i < 16 / kRows; ++i) *reinterpret_cast<uint4*>(rows + (i * kRows + sub) * kSealRowStride + chunk) = x[i];
+                for (int i = 0; i < 16 / kRows; ++i) *reinterpret_cast<u32x4*>(rows + (i * kRows + sub) * kSealRowStride + chunk) = x[i];
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
