@@ -232,9 +232,9 @@ hipError_t fixed_workspace_of_device(int device, char** out);
 
 // ---- launchers (defined next to their kernels) ------------------------------
 // words: n_blocks AppendBlocks, the n_open that stay open first, then n_src source rows; on the host (at most kAppendInlineWords words, which go along
-// with the kernel's arguments) or on the device.  (Weak: the host side also links without the kernels.)
+// with the kernel's arguments) or on the device.
 hipError_t launch_append_blocks(const Shape& s, void* pool, const void* k, const void* v, const int32_t* words, bool on_host,
-                                int n_blocks, int n_open, int n_src, hipStream_t st) __attribute__((weak));
+                                int n_blocks, int n_open, int n_src, hipStream_t st);
 hipError_t launch_block_copies(const Shape& s, void* pool, const int32_t* src_dst_pairs, int n_pairs,
                                hipStream_t st);
 // words[pairs[2 i]] = pairs[2 i + 1] for i < n_pairs (device pointers; `pairs` 8-byte aligned)

@@ -16,9 +16,8 @@
 
 namespace apar {
 hipError_t fixed_workspace_of_device(int, char** out) { static char nothing[256]; *out = nothing; return hipSuccess; }
-hipError_t launch_append_rows(const Shape&, void*, const void*, const void*, const int32_t*, const int32_t*, int, hipStream_t) { std::abort(); }
+hipError_t launch_append_blocks(const Shape&, void*, const void*, const void*, const int32_t*, bool, int, int, int, hipStream_t) { std::abort(); }
 hipError_t launch_block_copies(const Shape&, void*, const int32_t*, int, hipStream_t) { std::abort(); }
-hipError_t launch_seal_blocks(const Shape&, void*, const int32_t*, int, hipStream_t) { std::abort(); }
 hipError_t launch_read_rows(const Shape&, const void*, const int32_t*, int, void*, void*, hipStream_t) { std::abort(); }
 hipError_t launch_scatter_words(int32_t*, const int32_t*, int, hipStream_t) { std::abort(); }
 hipError_t launch_attention_partial(const Shape&, const void*, const void*, const PlanDev&, int, PartialBuf, const void*, const void*,

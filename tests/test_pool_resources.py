@@ -29,6 +29,18 @@ def test_host_side(host_pool, check):
     assert ran.returncode == 0 and ran.stdout == f"ok: {check}\n", ran.stdout + ran.stderr
 
 
+def test_the_host_side_names_every_launcher_it_needs(tmp_path):
+    """A library built without a kernel's file must not link: no launcher is a symbol that may stay undefined."""
+    cxx, nm = shutil.which("g++"), shutil.which("nm")
+    if cxx is None or nm is None or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
+        pytest.skip("no g++, no nm or no HIP headers")
+    csrc, obj = os.path.join(ROOT, "paper_2401_06761_amd", "csrc"), str(tmp_path / "apar_pool.o")
+    subprocess.run([cxx, "-std=c++17", "-c", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + os.path.join(ROOT, "include"), "-I" + csrc,
+                    os.path.join(csrc, "apar_pool.cpp"), "-o", obj], check=True, capture_output=True)
+    launchers = [l.split() for l in subprocess.run([nm, "-C", obj], check=True, capture_output=True, text=True).stdout.splitlines() if "apar::launch_" in l]
+    assert len(launchers) >= 6 and all(kind == "U" for kind, *_ in launchers), launchers
+
+
 @pytest.mark.gpu
 def test_first_staged_calls_return_before_the_work_they_wait_behind():
     """A new pool's first four staged calls (there are four staging slots), on a stream with work ahead of them, are
