@@ -219,10 +219,10 @@ struct ClassStreams {
                           // no stream or event is ever created (for the entry point that must not allocate)
 };
 
-// Room for the row states of a launch some of whose units are cut into slices (attn_split.hpp), and the most such
-// units x kv heads.
+// Room for the row states of a launch some of whose units are cut into slices (attn_split.hpp): 256 shares of the work are
+// fewer than 512 slices x kv heads, of at most 8 row tiles of 8.5 KiB.  kSplitMaxCut: the most cut units x kv heads.
 constexpr size_t kSplitStateBytes = (size_t)32 << 20;
-constexpr int kSplitMaxCut = 1024;
+constexpr int kSplitMaxCut = 512;
 constexpr size_t kSplitCounterBytes = (size_t)kSplitMaxCut * 4 * sizeof(int32_t);
 
 // Where `device`'s copy of the library's static workspace (APAR_FIXED_PLAN_BYTES of plan tables followed by

@@ -140,7 +140,6 @@ struct apar_pool {
     size_t split_bytes = 0;
     std::vector<SplitBlock> split_blocks;  // of the plan as it was built
     int32_t n_split_class[3] = {0, 0, 0};
-    size_t n_split_cut = 0;
     std::vector<int32_t> inline_words;  // a small plan's tables, as they go along with the kernels' arguments
     size_t inline_ofs[4] = {0, 0, 0, 0};
 
@@ -428,29 +427,32 @@ bool same_params(const PlanParams& a, const PlanParams& b) {
 }
 
 // Which units of a decode plan are cut into slices (attn_split.hpp), and the launch's workgroups in order.  A unit's cost
-// is the tiles a wavefront of it walks.  With T = total cost / shares, but at least kSplitMinTiles, units of more than T
+// is the tiles a wavefront of it walks.  With T = total cost / shares, but at least kSliceMinTiles, units of more than T
 // tiles become slices of about T; where no unit does, `out` stays empty and the launch has one workgroup per unit.
 // Measured (us per call, uncut / 256 / 512 / 1024 shares; trees of two fork levels, 32 q heads):
 //   bf16, 32 kv heads:  1 request 36 / 24 / 24 / 24,  4: 88 / 44 / 44 / 47,  16: 182 / 170 / 162 / 162,  32: 251 / 252 / 266 / 258
 //   bf16, 8 kv heads:   1 request 41 / 22 / 22 / 22,  4: 98 / 67 / 70 / 70,  16: 136 / 96 / 97 / 96
 //   one thread family of 32 k tokens, 8 kv heads: 106 / 58 / 59 / 63;  five candidates, 16 requests: 189 / 189 / 221 / 222
 //   fp32, 12 requests, 8 kv heads: 356 / 165 / 137 / 139 (its wavefronts are busy with products, not waiting)
-// Slices of 4, 2 and 1 tiles instead of kSplitMinTiles: 25, 32 and 32 against 22 us for one request with 8 kv heads.
-// Slices are worth their states and their fold only where they shorten the longest walk by more than kSplitMinGain
+// Slices of 4, 2 and 1 tiles instead of kSliceMinTiles: 25, 32 and 32 against 22 us for one request with 8 kv heads.
+// Slices are worth their states and their fold only where they shorten the longest walk by more than kSliceMinGain
 // tiles (26 requests, 8 kv heads, units of 19 to 27 tiles: 46 us uncut, 49 us with every unit cut in two).  Their room is an
-// eighth of the pool, at most kSplitStateBytes.
-constexpr int kSplitShares = 256, kSplitSharesF32 = 512;
-constexpr int kSplitMinTiles = 6, kSplitMinGain = 16;
-void cut_into_slices(const PlanHost& ph, const Shape& s, size_t state_bytes, std::vector<SplitBlock>& out, int32_t (&n_class)[3],
-                     size_t& n_cut) {
+// eighth of the pool, at least 1 MiB and at most kSplitStateBytes; where it is short, T grows until the states fit (by a quarter
+// at a time: a pass over the units each, nothing is built) or nothing is worth cutting any more.
+constexpr int kSliceShares = 256, kSliceSharesF32 = 512;
+constexpr int kSliceMinTiles = 6, kSliceMinGain = 16;
+// (a unit that is cut costs more than T >= total * n_kv / shares, so cut units x kv heads stay below the shares)
+static_assert(kSliceShares <= kSplitMaxCut && kSliceSharesF32 <= kSplitMaxCut, "a counter per cut unit, kv head and wavefront");
+void cut_into_slices(const PlanHost& ph, const Shape& s, size_t state_bytes, std::vector<SplitBlock>& out, int32_t (&n_class)[3]) {
     out.clear();
     n_class[0] = n_class[1] = n_class[2] = 0;
-    n_cut = 0;
     if (state_bytes == 0) return;
     auto cost = [](const WgDesc& wg) {
         return wg.n_coop + std::max(std::max(wg.w[0].n_tiles, wg.w[1].n_tiles), std::max(wg.w[2].n_tiles, wg.w[3].n_tiles));
     };
-    const size_t first = (size_t)ph.n_wg_class[0];
+    // 16-row tiles of state that a slice of the unit leaves
+    auto state_of = [](const WgDesc& wg) { return ((wg.w[0].flags & kWaveSplit) ? 1 : 4) * (wg.row_tiles & 255); };
+    const size_t first = (size_t)ph.n_wg_class[0];  // (matrix units stay whole)
     int64_t total = 0;
     int longest = 0;
     for (size_t k = first; k < ph.wgs.size(); ++k) {
@@ -458,29 +460,29 @@ void cut_into_slices(const PlanHost& ph, const Shape& s, size_t state_bytes, std
         total += c;
         longest = std::max(longest, c);
     }
-    const int64_t shares = s.dtype == APAR_F32 ? kSplitSharesF32 : kSplitShares;
-    int64_t tiles = std::max<int64_t>(kSplitMinTiles, (total * s.n_kv + shares - 1) / shares);
-    const int64_t tile_bytes = (int64_t)(s.d / 4 + 2) * 64 * sizeof(float);
-    for (; longest > tiles + kSplitMinGain; tiles += (tiles + 3) / 4) {
-        out.clear();
-        n_class[0] = (int32_t)first;
-        n_class[1] = n_class[2] = 0;
-        n_cut = 0;
+    const int64_t shares = s.dtype == APAR_F32 ? kSliceSharesF32 : kSliceShares;
+    int64_t tiles = std::max<int64_t>(kSliceMinTiles, (total * s.n_kv + shares - 1) / shares);
+    auto slices_of = [&](size_t k) { return k < first ? 1 : (int)std::min<int64_t>(64, (cost(ph.wgs[k]) + tiles - 1) / tiles); };
+    const int64_t room = (int64_t)state_bytes / (s.n_kv * (int64_t)(s.d / 4 + 2) * 64 * (int64_t)sizeof(float));
+    for (;; tiles += (tiles + 3) / 4) {
+        if (longest <= tiles + kSliceMinGain) return;
         int64_t state = 0;
-        for (size_t k = 0; k < ph.wgs.size(); ++k) {
-            const WgDesc& wg = ph.wgs[k];
-            const int n = k < first ? 1 : (int)std::min<int64_t>(64, (cost(wg) + tiles - 1) / tiles);
-            for (int j = 0; j < n; ++j) out.push_back(SplitBlock{(int32_t)k, j | n << 16, (int32_t)state, (int32_t)n_cut});
-            if (k >= first) n_class[(wg.row_tiles & 255) == 2 ? 1 : 2] += n;
-            if (n > 1) {
-                state += (int64_t)n * ((wg.w[0].flags & kWaveSplit) ? 1 : 4) * (wg.row_tiles & 255);
-                n_cut += 1;
-            }
-        }
-        if (state * s.n_kv * tile_bytes <= (int64_t)state_bytes && (int64_t)n_cut * s.n_kv <= kSplitMaxCut) return;
+        for (size_t k = first; k < ph.wgs.size(); ++k)
+            if (const int n = slices_of(k); n > 1) state += (int64_t)n * state_of(ph.wgs[k]);
+        if (state <= room) break;
     }
-    out.clear();
-    n_cut = 0;
+    n_class[0] = (int32_t)first;
+    int32_t state = 0, n_cut = 0;
+    for (size_t k = 0; k < ph.wgs.size(); ++k) {
+        const WgDesc& wg = ph.wgs[k];
+        const int n = slices_of(k);
+        for (int j = 0; j < n; ++j) out.push_back(SplitBlock{(int32_t)k, j | n << 16, state, n_cut});
+        if (k >= first) n_class[(wg.row_tiles & 255) == 2 ? 1 : 2] += n;
+        if (n > 1) {
+            state += n * state_of(wg);
+            n_cut += 1;
+        }
+    }
 }
 
 // Lays a small plan's tables out for the kernels' arguments: no upload, no staging slot and no event.  Only where nothing
@@ -601,7 +603,7 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     DeviceGuard guard(p->device);
     hipStream_t st = (hipStream_t)stream;
 
-    if (!carried) cut_into_slices(ph, p->shape, p->split_bytes, p->split_blocks, p->n_split_class, p->n_split_cut);  // (a carried plan keeps its cut)
+    if (!carried) cut_into_slices(ph, p->shape, p->split_bytes, p->split_blocks, p->n_split_class);  // (a carried plan keeps its cut)
     // stage the tables in one copy
     size_t ofs[7];
     ofs[0] = 0;

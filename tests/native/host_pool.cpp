@@ -99,6 +99,14 @@ hipError_t launch_attention_partial(const Shape& s, const void*, const void*, co
         const SplitBlock* b = (const SplitBlock*)(base + (size_t)plan.split.blocks);
         const WgDesc* wgs = (const WgDesc*)(base + (size_t)plan.wgs);
         g_blocks.assign(b, b + plan.split.n_blocks_class[0] + plan.split.n_blocks_class[1] + plan.split.n_blocks_class[2]);
+        int state = 0, cut = 0;
+        for (const SplitBlock& x : g_blocks) {  // a unit's slices in a row, its states and counters behind those of the unit before
+            const int at = (int)(&x - g_blocks.data()), n_of = x.slice >> 16, s_of = x.slice & 0xffff;
+            CHECK(s_of < n_of && x.state == state && x.cut == cut);
+            CHECK(at == 0 ? x.wg == 0 && s_of == 0 : s_of == 0 ? x.wg == g_blocks[at - 1].wg + 1 : x.wg == g_blocks[at - 1].wg && s_of == (g_blocks[at - 1].slice & 0xffff) + 1);
+            if (n_of > 1 && s_of == n_of - 1) state += n_of * (wgs[x.wg].w[0].flags & kWaveSplit ? 1 : 4) * (wgs[x.wg].row_tiles & 255), cut += 1;
+        }
+        CHECK(g_blocks.empty() || ((g_blocks.back().slice & 0xffff) == (g_blocks.back().slice >> 16) - 1 && g_blocks.back().wg == plan.n_wg - 1));
         for (const SplitBlock& x : g_blocks) {
             const int n = x.slice >> 16, tiles = (wgs[x.wg].w[0].flags & kWaveSplit ? 1 : 4) * (wgs[x.wg].row_tiles & 255);
             if (n == 1) continue;
@@ -195,6 +203,33 @@ static void fixed() {
     CHECK(apar_pool_destroy(p) == APAR_OK);
 }
 
+// Units are cut as far as there is room for their states, down to not at all, and always completely (at the launch).
+static int longest_cut(int n_q, int n_kv, int dtype, int64_t blocks, int root, int kids, int kid_len) {
+    apar_pool* p;
+    CHECK(create(n_q, n_kv, dtype, blocks, &p) == APAR_OK);
+    const apar_thread t = thread_of(p, root);
+    std::vector<apar_thread> ids(kids + 1);
+    CHECK(apar_fork(p, t, kids, ids.data()) == APAR_OK);
+    ids[kids] = t;
+    for (int i = 0; i < kids; ++i) CHECK(apar_append_kv(p, ids[i], kRows, kRows, kid_len > 1 ? kid_len + i % 30 : 1, nullptr) == APAR_OK);
+    CHECK(apar_decode_attention(p, kRows, ids.data(), kids + 1, kRows, nullptr) == APAR_OK);
+    int slices = 1;
+    for (const apar::SplitBlock& b : g_blocks) slices = std::max(slices, b.slice >> 16);
+    const int rc = apar_decode_attention_fixed(p, kRows, ids.data(), kids + 1, kRows, nullptr);
+    CHECK(rc == APAR_OK || rc == APAR_ERR_WORKSPACE_LIMIT);
+    CHECK(apar_pool_destroy(p) == APAR_OK);
+    return slices;
+}
+static void slices() {
+    for (int dtype : {APAR_F32, APAR_BF16})
+        for (int n_kv : {1, 4, 32})
+            for (int kids : {1, 5, 40, 150})
+                for (int root : {40, 640, 6000}) longest_cut(n_kv * 4, n_kv, dtype, 200000, root, kids, 17);
+    // seventy leaves below 640 rows, 16 kv heads: room for all, for fewer slices than that, for none
+    const int all = longest_cut(16, 16, APAR_BF16, 100000, 640, 70, 16), some = longest_cut(16, 16, APAR_BF16, 290, 640, 70, 16);
+    CHECK(all > some && some > 1 && longest_cut(16, 16, APAR_BF16, 114, 640, 70, 1) == 1);
+}
+
 // Which kernel a prefill call goes to by itself: the faster one of calls that were measured on both.
 static void prefill() {
     struct Call { int dtype, n_q, n_kv, threads, len, m, long_m, kernel; };  // long_m: one prompt of that many tokens besides
@@ -225,7 +260,7 @@ static void prefill() {
 }
 
 int main(int argc, char** argv) {
-    const std::map<std::string, void (*)()> checks = {{"staging", staging}, {"creation", creation}, {"fixed", fixed}, {"prefill", prefill}};
+    const std::map<std::string, void (*)()> checks = {{"staging", staging}, {"creation", creation}, {"fixed", fixed}, {"prefill", prefill}, {"slices", slices}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();
     std::printf("ok: %s\n", argv[1]);
