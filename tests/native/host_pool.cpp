@@ -201,6 +201,28 @@ static void fixed() {
         for (size_t i = 0; i < as.size(); ++i) CHECK(std::memcmp(&as[i], &g_blocks[i], sizeof as[i]) == 0);
     }
     CHECK(apar_pool_destroy(p) == APAR_OK);
+    // one long thread beside so many short ones that the tables come to the limit: cut, then whole, then refused
+    int seen[3] = {0, 0, 0};
+    for (int n = 22000; n < 32000; n += 2000) {
+        CHECK(create(1, 1, APAR_BF16, 40000, &p) == APAR_OK);
+        std::vector<apar_thread> ids(1, thread_of(p, 16000));
+        apar_thread u;
+        for (int i = 0; i < n; ++i) {
+            CHECK(apar_thread_create(p, &u) == APAR_OK);
+            ids.push_back(u);
+        }
+        CHECK(apar_append_kv_batch(p, ids.data() + 1, n, kRows, kRows, nullptr) == APAR_OK);
+        const int rc = apar_decode_attention_fixed(p, kRows, ids.data(), n + 1, kRows, nullptr);
+        CHECK(rc == APAR_OK || rc == APAR_ERR_WORKSPACE_LIMIT);
+        const int at = rc != APAR_OK ? 2 : g_blocks.empty() ? 1 : 0;
+        for (int later = at + 1; later < 3; ++later) CHECK(seen[later] == 0);
+        seen[at] += 1;
+        if (rc == APAR_OK) {  // (the other entry point cuts)
+            CHECK(apar_decode_attention(p, kRows, ids.data(), n + 1, kRows, nullptr) == APAR_OK && !g_blocks.empty());
+        }
+        CHECK(apar_pool_destroy(p) == APAR_OK);
+    }
+    CHECK(seen[0] && seen[1] && seen[2]);
 }
 
 // Units are cut as far as there is room for their states, down to not at all, and always completely (at the launch).

@@ -121,7 +121,7 @@ def test_logits_of_minus_infinity_beside_a_threads_infinities(d, root, bad):
     k[::16, :, 7] = -np.inf
     dense = DenseThreads(hkv, hkv, d)
     w = manual_tree([-1], [1], heads, seed=1)
-    with pool_for(w, root // 16 + 16) as pool:
+    with pool_for(w, 2 * (root // 16) + 16) as pool:
         pool.kv.fill_(0xFF)
         t = ap.apar_thread_create(pool.handle)
         assert t == dense.create()
@@ -134,14 +134,20 @@ def test_logits_of_minus_infinity_beside_a_threads_infinities(d, root, bad):
         ap.apar_append_kv_batch(pool.handle, live, to_dev(k1, "f32"), to_dev(v1, "f32"))
         for i, x in enumerate(live):
             dense.append(x, k1[i:i + 1], v1[i:i + 1])
+        # and one whose own rows make slices of their own, an infinity or NaN among them
+        k2, v2 = (rng.standard_normal((root, hkv, d)).astype(np.float32) for _ in "kv")
+        k2[root // 3, :, 9] = bad
+        v2[root // 2, :, 9] = bad
+        ap.apar_append_kv(pool.handle, live[3], to_dev(k2, "f32"), to_dev(v2, "f32"), root)
+        dense.append(live[3], k2, v2)
         q = rng.standard_normal((n_leaf, hkv, d)).astype(np.float32)
         q[:, :, 7] = 1.0 + np.abs(q[:, :, 7])
         want = dense.decode(q, live)
-        others = [0, 1, 3]
+        others = [0, 1]
         for call in (ap.apar_decode_attention, ap.apar_decode_attention_fixed):
             out = torch.empty_like(to_dev(q, "f32"))
             call(pool.handle, to_dev(q, "f32"), live, out)
             torch.cuda.synchronize()
             got = to_host(out)
             assert_close(got[others], want[others], "f32", call.__name__)
-            assert not np.isfinite(got[2]).all()
+            assert not np.isfinite(got[2]).all() and not np.isfinite(got[3]).all()

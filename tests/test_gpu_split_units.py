@@ -60,3 +60,47 @@ def test_slices_against_the_oracle(dtype, d, n_q, n_kv, shape):
             ap.apar_decode_attention_spec(h, to_dev(q, dtype), to_dev(ck, dtype), to_dev(cv, dtype), torch.from_numpy(masks).cuda(), c, live, out)
             torch.cuda.synchronize()
             assert_close(to_host(out), dense.decode_spec(q, ck, cv, masks, live), dtype, f"candidates, chunk {chunk}")
+
+
+@pytest.mark.parametrize("blocks", [400, 290, 114])
+def test_short_rooms(blocks):
+    """Row states have an eighth of the pool: seventy leaves below 640 rows on 16 kv heads leave too many for the smaller
+    pools, whose units are cut into fewer slices or not at all."""
+    import torch
+
+    lens = [640] + [1] * 70
+    w = manual_tree([-1] + [0] * 70, lens, HeadConfig(16, 16, 128, "bf16"), seed=5)
+    dense = DenseThreads(16, 16, 128)
+    with pool_for(w, blocks) as pool:
+        pool.kv.fill_(0xFF)
+        live, _ = replay_trace(w, pool, None, dense)
+        q = step_q(w, 0, len(live))
+        for call in (ap.apar_decode_attention, ap.apar_decode_attention_fixed, ap.apar_decode_attention):
+            out = torch.full_like(to_dev(q, "bf16"), 3.0)
+            call(pool.handle, to_dev(q, "bf16"), live, out)
+            torch.cuda.synchronize()
+            assert_close(to_host(out), dense.decode(q, live), "bf16", f"{call.__name__}, {blocks} blocks")
+
+
+def test_fixed_entry_point_leaves_units_whole_where_the_tables_do_not_fit():
+    """26 k one-row threads bring the tables to the fixed workspace's limit: the long thread beside them is cut by the other
+    entry point only."""
+    import torch
+
+    n, long = 26000, 16000
+    rng = np.random.default_rng(8)
+    with ap.Pool(1, 1, 128, "bf16", n + long // 16 + 8, max_threads=n + 8) as pool:
+        h = pool.handle
+        live = [ap.apar_thread_create(h) for _ in range(n + 1)]
+        k, v, k1, v1 = (to_dev(rng.standard_normal((m, 1, 128)).astype(np.float32), "bf16") for m in (long, long, n, n))
+        ap.apar_append_kv(h, live[0], k, v)
+        ap.apar_append_kv_batch(h, live[1:], k1, v1)
+        q = to_dev(rng.standard_normal((n + 1, 1, 128)).astype(np.float32), "bf16")
+        outs = [torch.full_like(q, 3.0) for _ in range(2)]
+        ap.apar_decode_attention(h, q, live, outs[0])
+        ap.apar_decode_attention_fixed(h, q, live, outs[1])
+        torch.cuda.synchronize()
+        want = torch.softmax(q[0].double() @ k[:, 0].double().T / 128 ** 0.5, dim=-1) @ v[:, 0].double()
+        for out in outs:
+            assert_close(to_host(out[:1]), want[None].cpu().numpy(), "bf16", "the long thread")
+            assert torch.equal(out[1:], v1)  # (one row each: its value)
