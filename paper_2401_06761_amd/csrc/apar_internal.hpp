@@ -207,7 +207,12 @@ struct AppendTables<true> {
 struct PartialBuf {
     float* o;
     float* ml;
+    int32_t stream;  // this call's are more than the memory-side cache holds: written with non-temporal stores
 };
+// Measured (bf16; attention + merge, us, plain / non-temporal stores; partial rows x 32 heads of 520 bytes each):
+// 20 rows (32 k tokens, 4 threads) 33.6 + 8.0 / 33.6 + 9.4, 1547 rows (26 MB) 247 + 10 / 249 + 12, 13 k rows (218 MB)
+// 1827 + 41 / 1813 + 49, 50 k rows (831 MB) 3758 + 179 / 3675 + 173; 1600 rows of matrix units 186 + 10 / 188 + 11.
+constexpr size_t kStreamPartialBytes = (size_t)256 << 20;
 
 // Side streams on which the attention kernels of different row-tile classes run next to each
 // other (each class alone would leave most of the chip idle during its tail).  Created on first

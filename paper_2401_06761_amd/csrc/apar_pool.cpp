@@ -702,6 +702,7 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     } else if ((rc = upload(p, s, staged, st)) != APAR_OK) {
         return rc;
     }
+    part.stream = slots * (size_t)(p->shape.d + 2) * sizeof(float) > kStreamPartialBytes;
     PlanDev pd{};
     pd.wgs = (const WgDesc*)(dev + ofs[0]);
     pd.tiles = (const TileRef*)(dev + ofs[1]);

@@ -886,11 +886,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3
                 if (row >= 0) __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(out + row * 128) + c);
             }
         } else if (my_j[nt] != 0x7fff) {
-            // (plain stores: 64 bytes per row and store, which the L2 puts together)
             float* dst = part.o + slot * 128 + 4 * g4;
+            if (part.stream) {
+                asm volatile("" ::: "memory");  // (before and after: else the two branches' stores become one, without the hint)
 #pragma unroll
-            for (int jj = 0; jj < 8; ++jj)
-                *reinterpret_cast<f32x4*>(dst + 16 * jj) = st[nt].o[jj];
+                for (int jj = 0; jj < 8; ++jj) __builtin_nontemporal_store(st[nt].o[jj], reinterpret_cast<f32x4*>(dst + 16 * jj));
+                asm volatile("" ::: "memory");
+            } else {  // 64 bytes per row and store, which the L2 puts together, and the merge kernel finds them there
+#pragma unroll
+                for (int jj = 0; jj < 8; ++jj) *reinterpret_cast<f32x4*>(dst + 16 * jj) = st[nt].o[jj];
+            }
             if (g4 == 0) {
                 part.ml[slot * 2] = st[nt].m;
                 part.ml[slot * 2 + 1] = lt;

@@ -28,6 +28,8 @@
 // wavefront's first limit is applied without masks, one wholly above its last limit is skipped.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "apar_internal.hpp"
 
 namespace apar {
@@ -401,13 +403,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     if (!wk.row_ok) return;
     const int64_t slot = ((int64_t)(wg->w[0].part_base + tr) * n_cand + cc) * n_q + hq;
     float* dst = part.o + slot * 128 + 4 * h;
+    auto write = [&](auto stream) {
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj)
+        for (int jj = 0; jj < 4; ++jj)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const f32x4 v = {o[jj][4 * j + 0], o[jj][4 * j + 1], o[jj][4 * j + 2], o[jj][4 * j + 3]};
-            *reinterpret_cast<f32x4*>(dst + 32 * jj + 8 * j) = v;
-        }
+            for (int j = 0; j < 4; ++j) {
+                const f32x4 v = {o[jj][4 * j + 0], o[jj][4 * j + 1], o[jj][4 * j + 2], o[jj][4 * j + 3]};
+                f32x4* to = reinterpret_cast<f32x4*>(dst + 32 * jj + 8 * j);
+                if constexpr (decltype(stream)::value) __builtin_nontemporal_store(v, to);
+                else *to = v;
+            }
+    };
+    if (part.stream) {
+        asm volatile("" ::: "memory");  // (before and after: else the two branches' stores become one, without the hint)
+        write(std::true_type{});
+        asm volatile("" ::: "memory");
+    } else {
+        write(std::false_type{});
+    }
     if (h == 0) {
         part.ml[slot * 2] = m;
         part.ml[slot * 2 + 1] = lt;

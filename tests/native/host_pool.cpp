@@ -75,6 +75,7 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void*) { *a =
 // ---- the kernels ------------------------------------------------------------------------------------
 static apar::PlanDev g_plan;  // of the last decode or row-tile prefill call
 static std::vector<apar::SplitBlock> g_blocks;
+static apar::PartialBuf g_part;
 static char* g_fixed = nullptr;
 namespace apar {
 hipError_t fixed_workspace_of_device(int, char** out) {
@@ -90,9 +91,10 @@ hipError_t launch_read_rows(const Shape&, const void*, const int32_t* codes, int
 }
 hipError_t launch_scatter_words(int32_t*, const int32_t*, int, hipStream_t) { return hipGetLastError(); }
 // Every cut unit's states and counters lie in memory of their own, and no unit is cut without room for them.
-hipError_t launch_attention_partial(const Shape& s, const void*, const void*, const PlanDev& plan, int, PartialBuf, const void*, const void*,
+hipError_t launch_attention_partial(const Shape& s, const void*, const void*, const PlanDev& plan, int, PartialBuf part, const void*, const void*,
                                     const uint8_t*, void*, ClassStreams&, hipStream_t) {
     g_plan = plan;
+    g_part = part;
     g_blocks.clear();
     if (plan.split.blocks) {
         const char* base = plan.inline_words ? (const char*)plan.inline_words : nullptr;
@@ -252,6 +254,22 @@ static void slices() {
     CHECK(all > some && some > 1 && longest_cut(16, 16, APAR_BF16, 114, 640, 70, 1) == 1);
 }
 
+// Partial results are streamed where the call's are more than the memory-side cache holds.
+static void partials() {
+    for (int n : {200, 3200}) {
+        apar_pool* p;
+        CHECK(create(32, 8, APAR_BF16, 100000, &p) == APAR_OK);
+        CHECK(apar_set_chunk_blocks(p, 2) == APAR_OK);
+        std::vector<apar_thread> ids;
+        for (int i = 0; i < n; ++i) ids.push_back(thread_of(p, 200));
+        CHECK(apar_decode_attention(p, kRows, ids.data(), n, kRows, nullptr) == APAR_OK);
+        apar_plan_info info;
+        CHECK(apar_last_plan_info(p, &info) == APAR_OK && info.n_partial_rows > n);
+        CHECK((g_part.stream != 0) == (info.n_partial_rows * 32 * 520 > (int64_t)256 << 20) && (g_part.stream != 0) == (n == 3200));
+        CHECK(apar_pool_destroy(p) == APAR_OK);
+    }
+}
+
 // Which kernel a prefill call goes to by itself: the faster one of calls that were measured on both.
 static void prefill() {
     struct Call { int dtype, n_q, n_kv, threads, len, m, long_m, kernel; };  // long_m: one prompt of that many tokens besides
@@ -282,7 +300,7 @@ static void prefill() {
 }
 
 int main(int argc, char** argv) {
-    const std::map<std::string, void (*)()> checks = {{"staging", staging}, {"creation", creation}, {"fixed", fixed}, {"prefill", prefill}, {"slices", slices}};
+    const std::map<std::string, void (*)()> checks = {{"staging", staging}, {"creation", creation}, {"fixed", fixed}, {"prefill", prefill}, {"slices", slices}, {"partials", partials}};
     CHECK(argc == 2 && checks.count(argv[1]));
     checks.at(argv[1])();
     std::printf("ok: %s\n", argv[1]);

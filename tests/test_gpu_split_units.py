@@ -104,3 +104,27 @@ def test_fixed_entry_point_leaves_units_whole_where_the_tables_do_not_fit():
         for out in outs:
             assert_close(to_host(out[:1]), want[None].cpu().numpy(), "bf16", "the long thread")
             assert torch.equal(out[1:], v1)  # (one row each: its value)
+
+
+def test_partial_results_beyond_the_memory_side_cache():
+    """More than 256 MiB of partial results (written with other stores than fewer): the merged rows are those of the same
+    threads attended whole."""
+    import torch
+
+    n, length = 5500, 40
+    with ap.Pool(32, 8, 128, "bf16", n * 3 + 8, max_threads=n + 8) as pool:
+        h = pool.handle
+        k, v = (torch.randn(length, n, 8, 128, device="cuda:0").bfloat16() for _ in "kv")
+        live = [ap.apar_thread_create(h) for _ in range(n)]
+        for i in range(length):
+            ap.apar_append_kv_batch(h, live, k[i], v[i])
+        q = torch.randn(n, 32, 128, device="cuda:0").bfloat16()
+        outs = []
+        for chunk in (1, 512):
+            ap.apar_set_chunk_blocks(h, chunk)
+            outs.append(torch.full_like(q, 3.0))
+            ap.apar_decode_attention(h, q, live, outs[-1])
+            rows = ap.apar_last_plan_info(h).n_partial_rows
+            assert rows * 32 * 130 * 4 > 256 << 20 if chunk == 1 else rows == 0
+        torch.cuda.synchronize()
+        assert_close(to_host(outs[0]), to_host(outs[1]), "bf16")

@@ -23,7 +23,7 @@ def host_pool(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["staging", "creation", "fixed", "prefill", "slices"])
+@pytest.mark.parametrize("check", ["staging", "creation", "fixed", "prefill", "slices", "partials"])
 def test_host_side(host_pool, check):
     ran = subprocess.run([host_pool, check], capture_output=True, text=True, timeout=120)
     assert ran.returncode == 0 and ran.stdout == f"ok: {check}\n", ran.stdout + ran.stderr
