@@ -490,9 +490,9 @@ APAR_API int apar_set_matrix_units(apar_pool* pool, int min_rows, int min_blocks
  * result per (chunk, thread) and its children are tried again. */
 APAR_API int apar_set_inline_shared(apar_pool* pool, int on);
 /* Tuning knob: which kernel apar_prefill_attention runs on a bf16 pool.  ROW_TILES is the decode kernel
- * under a prefill plan (16-row tiles; a prefix shared by sibling threads is read once for all of them),
- * MATRIX the 32x32 matrix-core kernel (one workgroup per thread and chunk of 128 query rows; needs a
- * group size that divides 16, otherwise the call stays on ROW_TILES).  AUTO (default) takes MATRIX when
+ * under a prefill plan (16-row tiles; one workgroup per thread and chunk of 64 or 128 query rows), MATRIX the
+ * 32x32 matrix-core kernel (one workgroup per thread and chunk of 128 query rows; needs a group size that
+ * divides 16, otherwise the call stays on ROW_TILES).  AUTO (default) takes MATRIX when
  * most of the rows walked are walked for threads with more than 64 query rows (query tokens x q heads per kv head),
  * on bf16 pools also for large calls and where a query token attends to 1024 rows or more on average.
  * Both give the same result to rounding.

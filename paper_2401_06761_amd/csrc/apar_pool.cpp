@@ -771,9 +771,10 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
 // query rows (tokens x q heads of a kv group) of one thread; a row-tile workgroup with one row tile per wavefront holds 64.
 //  - Threads of more than 64 rows are faster there, the others on the row tiles: what decides is the rows that the
 //    workgroups of either kind walk, so that one long prompt does not take hundreds of short threads with it.
-//    Measured (us, row tiles / matrix kernel; 362 threads, walks around 300, bf16): group 1, 59 and 69 rows 302 / 305, 527 / 421;
-//    group 4, 64 and 80 rows 110 / 122, 166 / 130; group 16, 64 and 80 rows 50 / 55, 64 / 57; fp8 pools: group 1 338 / 436,
-//    494 / 451, group 4 101 / 128, 169 / 135; walks around 950, group 4: bf16 218 / 225, 317 / 249, fp8 189 / 252, 318 / 264.
+//    Measured (us, row tiles / matrix kernel; 362 threads, walks around 400): bf16 group 2, 63 and 78 rows 206 / 219, 285 / 241;
+//    group 4, 64 and 80 rows 110 / 122, 166 / 130; group 16, 64 and 80 rows 50 / 55, 64 / 57; fp8 pools group 1, 59 and 69 rows
+//    338 / 436, 494 / 451, group 4, 64 and 80 rows 101 / 128, 169 / 135; walks around 1050, group 4: bf16 218 / 225, 317 / 249,
+//    fp8 189 / 252, 318 / 264.
 //    360 threads of one row and walks of 300 beside a prompt of 2000, group 8: bf16 124 / 93, fp8 130 / 101; walks of 900
 //    beside it: group 4 188 / 205, group 1 439 / 620.  (fp8 pools, group 8 or more, 112 to 128 rows per thread: 2 to 7 % slower.)
 //  - bf16 pools: from 32 rows per workgroup on, a large call (kMatrixPrefillWalked rows walked by all its workgroups, kv
