@@ -24,6 +24,7 @@ thread_local std::string g_last_hip_error;
 bool hip_ok(hipError_t e, const char* what) {
     if (e == hipSuccess) return true;
     g_last_hip_error = std::string(what) + ": " + hipGetErrorString(e);
+    (void)hipGetLastError();  // (reported here: the next launch's check must not find it)
     return false;
 }
 #define HIP_TRY(expr)                                  \
@@ -135,9 +136,10 @@ struct apar_pool {
     bool fixed_pending = false;
 
     // row states of launches whose units are cut into slices, behind the counters of slices that have arrived (zero
-    // between launches)
+    // between launches once split_clear: a clear has run or is enqueued before any launch to come)
     char* split_dev = nullptr;
     size_t split_bytes = 0;
+    bool split_clear = false;
     std::vector<SplitBlock> split_blocks;  // of the plan as it was built
     int32_t n_split_class[3] = {0, 0, 0};
     std::vector<int32_t> inline_words;  // a small plan's tables, as they go along with the kernels' arguments
@@ -191,37 +193,34 @@ int grow_slot(StageSlot& s, size_t bytes) {
 
 // Everything a pool's calls work in besides the pool: all staging slots, so that no call of a loop stops to set one up
 // (measured, one after the other: the third and fourth call of a new pool took 60 to 80 us on the host against 17), in one
-// pinned and one device allocation (a slot each: 250 -> 290 us for a small pool).  One copy clears the counters and
-// takes the pair of allocations through its first transfer.
+// pinned and one device allocation.  Nothing is enqueued, so that creating a pool waits for nobody's work: the first launch
+// with a cut unit clears the counters.
 // A pool does without all of this but the buffer of apar_decode_attention_fixed, whose calls may not allocate: where memory
 // is short, slots are set up by the calls that need them and no unit is cut.
 int set_up_workspace(apar_pool* p, size_t pool_bytes) {
     if (!hip_ok(fixed_workspace_of_device(p->device, &p->fixed_dev), "hipGetSymbolAddress(scratch)")) return APAR_ERR_HIP;
-    HIP_TRY(hipEventCreateWithFlags(&p->fixed_up, hipEventDisableTiming));
-    for (StageSlot& s : p->stage) HIP_TRY(hipEventCreateWithFlags(&s.ev, hipEventDisableTiming));
-    if (hipHostMalloc((void**)&p->work_host, kFixedPlanBytes + kStageSlots * kStageBytes, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        HIP_TRY(hipHostMalloc((void**)&p->work_host, kFixedPlanBytes, hipHostMallocDefault));
-        p->fixed_host = p->work_host;
-        return APAR_OK;
-    }
-    p->fixed_host = p->work_host;
     const size_t state_bytes = std::min(kSplitStateBytes, std::max((size_t)1 << 20, pool_bytes / 8));
     const size_t split = kSplitCounterBytes + state_bytes;
-    if (hipMalloc((void**)&p->work_dev, split + kStageSlots * kStageBytes) != hipSuccess) {
+    if (hipMalloc((void**)&p->work_dev, split + kStageSlots * kStageBytes) == hipSuccess) {
+        p->split_dev = p->work_dev;
+        p->split_bytes = state_bytes;
+    } else {
         (void)hipGetLastError();
         p->work_dev = nullptr;
-        return APAR_OK;
     }
-    p->split_dev = p->work_dev;
-    p->split_bytes = state_bytes;
-    for (int k = 0; k < kStageSlots; ++k) {
-        p->stage[k].host = p->work_host + kFixedPlanBytes + k * kStageBytes;
-        p->stage[k].dev = p->work_dev + split + k * kStageBytes;
-        p->stage[k].cap = kStageBytes;
+    if (hipHostMalloc((void**)&p->work_host, kFixedPlanBytes + kStageSlots * kStageBytes, hipHostMallocDefault) == hipSuccess) {
+        for (int k = 0; p->work_dev && k < kStageSlots; ++k) {
+            p->stage[k].host = p->work_host + kFixedPlanBytes + k * kStageBytes;
+            p->stage[k].dev = p->work_dev + split + k * kStageBytes;
+            p->stage[k].cap = kStageBytes;
+        }
+    } else {
+        (void)hipGetLastError();
+        HIP_TRY(hipHostMalloc((void**)&p->work_host, kFixedPlanBytes, hipHostMallocDefault));
     }
-    memset(p->work_host, 0, kSplitCounterBytes);
-    HIP_TRY(hipMemcpy(p->work_dev, p->work_host, kSplitCounterBytes, hipMemcpyHostToDevice));
+    p->fixed_host = p->work_host;
+    HIP_TRY(hipEventCreateWithFlags(&p->fixed_up, hipEventDisableTiming));
+    for (StageSlot& s : p->stage) HIP_TRY(hipEventCreateWithFlags(&s.ev, hipEventDisableTiming));
     return APAR_OK;
 }
 
@@ -741,6 +740,13 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
             (rc = new_event(p, &ev.c)) != APAR_OK)
             return rc;
         HIP_TRY(hipEventRecord(ev.a, st));
+    }
+    if (cut && !p->split_clear) {
+        HIP_TRY(launch_clear_words((int32_t*)p->split_dev, (int)(kSplitCounterBytes / sizeof(int32_t)), st));
+        // (a call that is being captured runs its own clear when it is replayed; nothing is cleared before that)
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
+        else p->split_clear = capture == hipStreamCaptureStatusNone;
     }
     ClassStreams one_stream;
     one_stream.serial = true;

@@ -456,6 +456,17 @@ hipError_t launch_scatter_words(int32_t* words, const int32_t* pairs, int n_pair
     return hipGetLastError();
 }
 
+__global__ __launch_bounds__(256) void clear_words(int32_t* __restrict__ words, int n) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) words[i] = 0;
+}
+
+hipError_t launch_clear_words(int32_t* words, int n, hipStream_t st) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(clear_words, dim3((n + 255) / 256), dim3(256), 0, st, words, n);
+    return hipGetLastError();
+}
+
 hipError_t launch_read_rows(const Shape& s, const void* pool, const int32_t* src_codes, int n_rows, void* k_out,
                             void* v_out, hipStream_t st) {
     if (n_rows <= 0) return hipSuccess;

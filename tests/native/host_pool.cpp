@@ -24,6 +24,7 @@ static std::map<char*, size_t> g_dev, g_host;      // live allocations
 static int g_allocs = 0, g_refuse = -1;            // allocations so far; the one to refuse (-1: none)
 static bool g_refuse_rest = false;                 // ... and all after it
 static int g_waits = 0, g_objects = 0;             // calls that wait for the device; live events and streams
+static bool g_capturing = false;
 static hipError_t g_last = hipSuccess;
 
 static hipError_t failed(hipError_t e) { return g_last = e; }
@@ -54,7 +55,7 @@ hipError_t hipHostMalloc(void** p, size_t size, unsigned int) { return allocate(
 hipError_t hipHostFree(void* p) { return release(g_host, p); }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { g_waits += 1; std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
-hipError_t hipMemset(void* d, int v, size_t n) { std::memset(d, v, n); return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) { *s = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone; return hipSuccess; }
 hipError_t hipDeviceSynchronize() { g_waits += 1; return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { g_objects += 1; *e = (hipEvent_t)std::malloc(1); return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) { return hipEventCreateWithFlags(e, 0); }
@@ -76,6 +77,7 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void*) { *a =
 static apar::PlanDev g_plan;  // of the last decode or row-tile prefill call
 static std::vector<apar::SplitBlock> g_blocks;
 static apar::PartialBuf g_part;
+static int g_clears = 0;  // launches that cleared counters
 static char* g_fixed = nullptr;
 namespace apar {
 hipError_t fixed_workspace_of_device(int, char** out) {
@@ -90,6 +92,12 @@ hipError_t launch_read_rows(const Shape&, const void*, const int32_t* codes, int
     return hipGetLastError();
 }
 hipError_t launch_scatter_words(int32_t*, const int32_t*, int, hipStream_t) { return hipGetLastError(); }
+hipError_t launch_clear_words(int32_t* words, int n, hipStream_t) {
+    CHECK(on_device(words, (size_t)n * 4));
+    std::memset(words, 0, (size_t)n * 4);
+    g_clears += 1;
+    return hipGetLastError();
+}
 // Every cut unit's states and counters lie in memory of their own, and no unit is cut without room for them.
 hipError_t launch_attention_partial(const Shape& s, const void*, const void*, const PlanDev& plan, int, PartialBuf part, const void*, const void*,
                                     const uint8_t*, void*, ClassStreams&, hipStream_t) {
@@ -134,7 +142,9 @@ static void* const kRows = g_kv;
 static int create(int n_q, int n_kv, int dtype, int64_t blocks, apar_pool** p) {
     apar_pool_config c{};
     c.n_q_heads = n_q, c.n_kv_heads = n_kv, c.head_dim = 128, c.block_size = 16, c.dtype = dtype, c.max_threads = 1 << 20, c.num_blocks = blocks;
-    return apar_pool_create(&c, g_kv, (size_t)1 << 60, p);
+    const int waits = g_waits, rc = apar_pool_create(&c, g_kv, (size_t)1 << 60, p);
+    CHECK(rc != APAR_OK || g_waits == waits);
+    return rc;
 }
 static apar_thread thread_of(apar_pool* p, int n) {
     apar_thread t;
@@ -173,15 +183,15 @@ static void creation() {
             apar_pool* p = nullptr;
             g_allocs = 0, g_refuse = k, g_refuse_rest = rest != 0;
             const int rc = create(8, 8, APAR_BF16, 4000, &p);
-            const bool refused = g_allocs > k;
+            const bool room = k > 0;  // (the device allocation comes first)
             g_refuse = -1;
-            CHECK(rc == (rest && k == 0 ? APAR_ERR_HIP : APAR_OK) && (rc == APAR_OK) == (p != nullptr));
+            CHECK(rc == (rest && k <= 1 ? APAR_ERR_HIP : APAR_OK) && (rc == APAR_OK) == (p != nullptr));
             if (p) {
                 const apar_thread t = thread_of(p, 1600);
                 CHECK(apar_decode_attention(p, kRows, &t, 1, kRows, nullptr) == APAR_OK);  // (a long walk: cut where there is room)
                 int slices = 0;
                 for (const apar::SplitBlock& b : g_blocks) slices = std::max(slices, b.slice >> 16);
-                CHECK((slices > 1) == !refused);
+                CHECK((slices > 1) == room);
                 CHECK(apar_read_kv_rows(p, t, 0, 1600, kRows, kRows, nullptr) == APAR_OK);
             }
             CHECK(apar_pool_destroy(p) == APAR_OK && g_dev.empty() && g_host.empty() && g_objects == 0);
@@ -202,6 +212,15 @@ static void fixed() {
         CHECK(g_allocs == allocs && as.size() > 1 && as.size() == g_blocks.size());
         for (size_t i = 0; i < as.size(); ++i) CHECK(std::memcmp(&as[i], &g_blocks[i], sizeof as[i]) == 0);
     }
+    CHECK(apar_pool_destroy(p) == APAR_OK);
+    // the counters are cleared once, but not by a call that is only recorded: its clear belongs to the graph
+    CHECK(create(8, 8, APAR_BF16, 4000, &p) == APAR_OK);
+    const apar_thread u0 = thread_of(p, 1600);
+    g_clears = 0, g_capturing = true;
+    for (int k = 0; k < 2; ++k) CHECK(apar_decode_attention_fixed(p, kRows, &u0, 1, kRows, nullptr) == APAR_OK && g_clears == k + 1);
+    g_capturing = false;
+    for (int k = 0; k < 2; ++k) CHECK(apar_decode_attention_fixed(p, kRows, &u0, 1, kRows, nullptr) == APAR_OK && g_clears == 3);
+    CHECK(apar_decode_attention(p, kRows, &u0, 1, kRows, nullptr) == APAR_OK && g_clears == 3);
     CHECK(apar_pool_destroy(p) == APAR_OK);
     // one long thread beside so many short ones that the tables come to the limit: cut, then whole, then refused
     int seen[3] = {0, 0, 0};

@@ -84,4 +84,6 @@ def test_first_staged_calls_return_before_the_work_they_wait_behind():
         ahead.record()
         calls(pool, live, q, k)
         assert not ahead.query()
+        with ap.Pool(8, 8, 128, "bf16", 1400) as another:  # (nor does creating one; destroying one does)
+            assert another.handle and not ahead.query()
         torch.cuda.synchronize()
