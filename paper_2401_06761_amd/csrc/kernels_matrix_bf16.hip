@@ -20,12 +20,21 @@
 // index of the second product is permuted the same way, so probabilities never move between lanes.
 //
 // The four wavefronts share the path through LDS in groups of two super-blocks (four KV blocks, double
-// buffered, one barrier per group): each wavefront fetches one block of the group while the previous
-// group is consumed.  K is staged as it lies in HBM - operand order for a sealed block, row-major for a
-// still open one (only the last block of a walk can be) - and read back with the matching address
-// pattern; V is rearranged on its way into LDS so that an operand (8 token slots of one dim) is one
-// 16-byte read.  Masks only matter at the end of a row's range: a super-block wholly below a
-// wavefront's first limit is applied without masks, one wholly above its last limit is skipped.
+// buffered, one barrier per group): each wavefront has one block of the next group on its way to LDS, without
+// registers in between, while a group is consumed.  Blocks lie in LDS in operand order, as sealed blocks do in
+// HBM; a still open one (only the last block of a walk can be) is put into that order once it has landed, and the
+// codes of a full fp8 block are widened on their way.
+//
+// What bounds it: a super-block is 512 cycles of products and some 450 of vector instructions (16 exp2 are 256 of
+// them) on the same SIMD, and with one phase after the other a wavefront pair needs 1250 cycles per super-block.  So a
+// wavefront's own vector work is issued between its products: the probabilities of one super-block between the K.Q^T
+// products of the next one, the maximum over those between the V^T.P^T products, and LDS operands are read beside
+// either, into registers that have just become free (218 registers, two wavefronts per SIMD).  Six prompts of 1 k to 8 k
+// tokens, 8 kv heads of 4 (1.75 TFLOP): 1.90 -> 1.64 ms, matrix pipe busy 57 % of the time instead of 41 % at a clock that
+// falls from 1.94 to 1.79 GHz; own segments of 982 threads, 32 heads, walks of 529: 1.80 -> 1.65 ms.  The direct loads alone,
+// phases one after the other as before, take half of that.
+// Masks only matter at the end of a row's range: a super-block wholly below a wavefront's first limit is applied
+// without masks, one wholly above its last limit is skipped.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -59,10 +68,10 @@ __device__ __forceinline__ uint32_t pack_pair(float lo, float hi) {  // round to
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
 }
 
-// Where the V operand of (matrix row block r = dims 32r.., dim 16 * hf + c, lane half h) lives inside a staged V
-// half: 16 bytes = token slots 4h..4h+3 then 8+4h..8+4h+3 of that dim.  The sixteen lanes of one c run read
-// 256 consecutive bytes.
-__device__ __forceinline__ int v_operand_offset(int r, int hf, int c, int h) { return ((((r * 2 + hf) * 2 + h) * 16) + c) * 16; }
+__device__ __forceinline__ float other_half(float x) {  // the value of lane ^ 32
+    const u32x2 r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
+    return __builtin_bit_cast(float, (threadIdx.x & 32) ? r.x : r.y);
+}
 
 // fp8 codes in x[0], x[1] times the half's power-of-two scale -> the half's four bf16 pieces x[0..3].
 __device__ __forceinline__ void widen(u32x4 (&x)[4], float scale) {
@@ -93,19 +102,50 @@ struct Walk {
     float scale_log2e;
 };
 
-// Runs the walk; leaves the lane's share of O^T (dims 32 jj + 8 (i / 4) + 4 h + i % 4 of row n in o[jj][i]),
-// the row's reference m and this lane's half of the row's sum l.
+// Memory to LDS without a register in between: the lane's 16 bytes at from + ofs go to LDS address lds + 16 lane; dma_half
+// brings the three KiB after that too.  Statements of their own rather than the builtin: the compiler takes that one for an
+// access that either counter may count, and then has every operand read from LDS wait for all others.  Whoever requests
+// waits for vmcnt(0) before anybody reads.  (M0 is used by nothing else here; the wait states cover a scalar register
+// that a vector instruction has just written.)
+__device__ __forceinline__ void dma_piece(const char* from, uint32_t ofs, uint32_t lds) {
+    asm volatile(
+        "s_mov_b32 m0, %0\n\t"
+        "s_nop 4\n\t"
+        "global_load_lds_dwordx4 %1, %2"
+        :
+        : "s"(lds), "v"(ofs), "s"(from)
+        : "memory");
+}
+__device__ __forceinline__ void dma_half(const char* from, uint32_t ofs, uint32_t lds) {
+    asm volatile(
+        "s_mov_b32 m0, %0\n\t"
+        "s_nop 4\n\t"
+        "global_load_lds_dwordx4 %1, %2\n\t"
+        "global_load_lds_dwordx4 %1, %2 offset:1024\n\t"
+        "global_load_lds_dwordx4 %1, %2 offset:2048\n\t"
+        "global_load_lds_dwordx4 %1, %2 offset:3072"
+        :
+        : "s"(lds), "v"(ofs), "s"(from)
+        : "memory");
+}
+
+// Runs the walk; leaves the lane's share of O^T (dims 32 jj + 16 (j % 2) + 8 (j / 2) + 4 h + i of row n in
+// o[jj][4 j + i]), the row's reference m and this lane's half of the row's sum l.
 // F8: full blocks hold fp8 codes and two scales; they are widened when they are staged, so that LDS holds the bf16 tile.
 template <bool F8>
 __device__ __forceinline__ void walk_blocks(const Walk& wk, char* lds, f32x16 (&o)[4], float& m, float& l) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int n = lane & 31, h = lane >> 5;   // column (query row) and half of the 32x32 products
-    const int g4 = lane >> 4, c = lane & 15;  // the (token group, column) view of a sealed block's 16-byte pieces
+    // For the paths that only open blocks take: what is derived from it is not kept in registers over the walk.
+    auto recomputed_lane = [&]() {
+        int x = lane;
+        asm volatile("" : "+v"(x));
+        return x;
+    };
     const char* head_base = wk.head_base;
     const int64_t block_stride = wk.block_stride;
-    const bool wave_ok = wk.wave_ok, row_ok = wk.row_ok;
-    const int w_first = wk.w_first, w_last = wk.w_last, pos = wk.pos;
+    const int w_first = wk.w_first, pos = wk.pos;
     const float scale_log2e = wk.scale_log2e;
 
     // Q as the B operand: lane (n, h) holds dims 8 (2 s + h) .. + 8 of its row for product step s
@@ -113,25 +153,30 @@ __device__ __forceinline__ void walk_blocks(const Walk& wk, char* lds, f32x16 (&
     {
         const u32x4* qp = reinterpret_cast<const u32x4*>(wk.q_row);
 #pragma unroll
-        for (int s = 0; s < 8; ++s) qv[s].u = row_ok ? qp[2 * s + h] : u32x4{0u, 0u, 0u, 0u};
+        for (int s = 0; s < 8; ++s) qv[s].u = wk.row_ok ? qp[2 * s + h] : u32x4{0u, 0u, 0u, 0u};
     }
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[jj][i] = 0.0f;
     m = -INFINITY, l = 0.0f;
+    float bias = -INFINITY;  // -m, or -inf as long as the row has seen nothing
 
     // groups of four blocks (64 token slots)
     const int n_blk = wk.n_blk;
     const int n_grp = (n_blk + 3) / 4;
-    // this wavefront stages block `wave` of every group
-    u32x4 sk[4], sv[4];
-    f32x2 ssc = {1.0f, 1.0f};  // fp8 pools: the scales of the block in flight
-    auto fetch = [&](int g) {
-        // a group's last blocks may lie past the walk's last block: they are masked, re-read the last one
+    const int n_sb = wk.wave_ok ? (wk.w_last >> 5) + 1 : 0;  // super-blocks that some row of the wavefront sees
+    // This wavefront stages block `wave` of every group (a group's last blocks may lie past the walk's last block: they
+    // are masked, re-read the last one): request() when the group before is about to be consumed, land() when it has been.
+    // Sealed blocks lie in LDS as they lie in HBM, and so do open ones once they have landed.
+    const uint32_t lds_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+    u32x4 sk[2], sv[2];        // fp8 pools: the codes of a full block in flight,
+    f32x2 ssc = {1.0f, 1.0f};  // and its scales
+    auto request = [&](int g) {
         const int blk = min(4 * g + wave, n_blk - 1);
         const int fill = min(16, wk.len - blk * 16);
-        const char* tile = head_base + wk.table[blk * wk.table_stride] * block_stride;
+        const char* tile = head_base + __builtin_amdgcn_readfirstlane(wk.table[blk * wk.table_stride]) * block_stride;
+        const uint32_t to = lds_addr + (g & 1) * kBufBytes + wave * kTileBytes;
         if (F8 && fill == 16) {
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
@@ -140,155 +185,190 @@ __device__ __forceinline__ void walk_blocks(const Walk& wk, char* lds, f32x16 (&
             }
             ssc = *reinterpret_cast<const f32x2*>(tile + kFp8ScaleOfs);
         } else if (fill == 16) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                sk[r] = *reinterpret_cast<const u32x4*>(tile + r * 1024 + lane * 16);
-                sv[r] = *reinterpret_cast<const u32x4*>(tile + kHalf + r * 1024 + lane * 16);
-            }
+            dma_half(tile, lane * 16, to);
+            dma_half(tile + kHalf, lane * 16, to + kHalf);
         } else {
             // the walk's last block is still open: row-major.  Piece r of this lane belongs to token row
             // 4r + g4; rows past the fill count re-read row 0 (finite values under probability 0)
+            const int ln = recomputed_lane();
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int trow = 4 * r + g4 < fill ? 4 * r + g4 : 0;
-                sk[r] = *reinterpret_cast<const u32x4*>(tile + trow * 256 + c * 16);
-                sv[r] = *reinterpret_cast<const u32x4*>(tile + kHalf + trow * 256 + c * 16);
+                const int trow = 4 * r + (ln >> 4) < fill ? 4 * r + (ln >> 4) : 0;
+                dma_piece(tile, trow * 256 + (ln & 15) * 16, to + r * 1024);
+                dma_piece(tile + kHalf, trow * 256 + (ln & 15) * 16, to + kHalf + r * 1024);
             }
         }
     };
-    auto stage = [&](int g, char* buf) {
+    // (the caller has waited for this wavefront's requests)
+    auto land = [&](int g) {
         const int blk = min(4 * g + wave, n_blk - 1);
         const bool sealed = wk.len - blk * 16 >= 16;
-        char* dst = buf + wave * kTileBytes;
+        char* dst = lds + (g & 1) * kBufBytes + wave * kTileBytes;
         if (F8 && sealed) {
             // two 16-byte loads hold a half's four pieces at one byte per element (a code times a power of two: exact)
-            widen(sk, ssc[0]);
-            widen(sv, ssc[1]);
+            u32x4 x[4] = {sk[0], sk[1], sk[0], sk[1]};
+            widen(x, ssc[0]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) *reinterpret_cast<u32x4*>(dst + r * 1024 + lane * 16) = x[r];
+            x[0] = sv[0], x[1] = sv[1];
+            widen(x, ssc[1]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) *reinterpret_cast<u32x4*>(dst + kHalf + r * 1024 + lane * 16) = x[r];
+        } else if (!sealed) {
+            // piece r of this lane = slot 4r + g4, dims 8c .. 8c + 7 of the open block: put where a sealed one has them
+            const int ln = recomputed_lane();
+            u32x4 x[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x[r] = *reinterpret_cast<const u32x4*>(dst + r * 1024 + ln * 16);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) *reinterpret_cast<u32x4*>(dst + bf16_k_offset(4 * r + (ln >> 4), 8 * (ln & 15))) = x[r];
+            dst += kHalf;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) x[r] = *reinterpret_cast<const u32x4*>(dst + r * 1024 + ln * 16);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    *reinterpret_cast<uint16_t*>(dst + bf16_v_offset(4 * r + (ln >> 4), 8 * (ln & 15) + e)) = (uint16_t)(x[r][e >> 1] >> (16 * (e & 1)));
         }
-        // K: as it lies in HBM (either layout keeps piece r of lane l at r * 1024 + l * 16)
+    };
+    // every wavefront's requests have landed, and everyone has read what it needs of the group before
+    auto hand_over = [&](int g) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+        land(g);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+
+    // Operands of the super-block whose two blocks lie at `at`.  K: lane (n as token slot, h) reads dims 8 (2 s + h) .. + 8 of
+    // slot n % 16 of block n / 16.  V: lane (n as matrix row, h) reads slots 4h .. 4h + 3, then 8 + 4h .. 8 + 4h + 3, of one
+    // dim; which of the 32 dims a matrix row stands for is chosen so that eight chunks of 16 bytes - two dims each -
+    // serve sixteen lanes (the sixteen lanes of dims c = 0..15 instead would meet in half the banks, twice).
+    const int k_lane = (n >> 4) * kTileBytes + (n & 15) * 16 + h * 1024;
+    const int v_lane = kHalf + (h * 16 + (n & 7) + 8 * (n >> 4)) * 16 + 8 * ((n >> 3) & 1);
+    Op ka[8], va[8];
+    float top = -INFINITY;  // the largest of the lane's logits of the super-block to come, unscaled
+    auto load_k = [&](const char* at, int k) {
+        ka[k].u = *reinterpret_cast<const u32x4*>(at + k_lane + (k & 1) * 2048 + (k >> 1) * 256);
+    };
+    auto load_v = [&](const char* at, int k) {  // k = 4 block + jj
+        const char* p = at + v_lane + (k >> 2) * kTileBytes + (k & 3) * 1024;
+        const u32x2 lo = *reinterpret_cast<const u32x2*>(p), hi = *reinterpret_cast<const u32x2*>(p + 512);
+        va[k].u = u32x4{lo.x, lo.y, hi.x, hi.y};
+    };
+    // slot t0 + 8 (i / 4) + 4 h + i % 4 is visible up to the row's pos; only super-blocks near the rows' limits need it
+    auto mask = [&](f32x16& s, int t0) {
+        if (t0 + 31 > w_first) {
+            const int room = pos - t0 - 4 * h;  // visible iff 8 (i / 4) + i % 4 <= room
 #pragma unroll
-        for (int r = 0; r < 4; ++r) *reinterpret_cast<u32x4*>(dst + r * 1024 + lane * 16) = sk[r];
-        dst += kHalf;
-        if (sealed) {
-            // V, sealed: piece r of lane (g4, c) = slots 4g4..4g4+3 of dim 32r + c, then of dim 32r + 16 + c
+            for (int i = 0; i < 16; ++i) s[i] = (8 * (i >> 2) + (i & 3) <= room) ? s[i] : -INFINITY;
+        }
+    };
+    // If some row ran away from its reference (always so on a row's first super-block): move every row's reference to its
+    // running maximum (the two lanes of a row agree on it) and rescale.
+    auto settle = [&]() {
+        const float t = top * scale_log2e;
+        if (__builtin_amdgcn_ballot_w64(t > m + kSlack) != 0) {
+            const float mx = fmaxf(t, other_half(t));
+            const float m_new = fmaxf(m, mx);
+            const float alpha = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - m_new);
+            l *= alpha;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const u32x2 lo = {sv[r].x, sv[r].y}, hi = {sv[r].z, sv[r].w};
-                *reinterpret_cast<u32x2*>(dst + v_operand_offset(r, 0, c, g4 & 1) + 8 * (g4 >> 1)) = lo;
-                *reinterpret_cast<u32x2*>(dst + v_operand_offset(r, 1, c, g4 & 1) + 8 * (g4 >> 1)) = hi;
+            for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o[jj][i] *= alpha;
+            m = m_new;
+            bias = m != -INFINITY ? -m : -INFINITY;
+        }
+    };
+    // Probabilities of the super-block whose logits are s, among the K.Q^T products of the one after it (logits sn, first
+    // slot t0n), then the V^T.P^T products among the maximum over sn.  The order is fixed: a wavefront's vector instructions
+    // run beside its own products only if they are issued between them.  (After a wavefront's last super-block sn comes from
+    // whatever is staged and nobody looks at it: eight products too many per walk, between vector instructions.)
+    auto weigh = [&](const f32x16& s, f32x16& sn, int t0n, auto beside_k, auto beside_v) {
+        Op pb[2];
+        float x0 = __builtin_fmaf(s[0], scale_log2e, bias), x1 = __builtin_fmaf(s[1], scale_log2e, bias);
+        float sum0 = 0.0f, sum1 = 0.0f, p0 = 0.0f, p1 = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sn[i] = 0.0f;
+#pragma unroll
+        for (int step = 0; step < 8; ++step) {
+            sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[step].b8, qv[step].b8, sn, 0, 0, 0);
+            beside_k(step);
+            const float e0 = __builtin_amdgcn_exp2f(x0), e1 = __builtin_amdgcn_exp2f(x1);
+            if (step < 7) {
+                x0 = __builtin_fmaf(s[2 * step + 2], scale_log2e, bias);
+                x1 = __builtin_fmaf(s[2 * step + 3], scale_log2e, bias);
             }
-        } else {
-            // V, open: piece r of this lane = slot 4r + g4, dims 8c .. 8c + 7
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int slot = 4 * r + g4;
-                const uint32_t w[4] = {sv[r].x, sv[r].y, sv[r].z, sv[r].w};
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int dim = 8 * c + e;
-                    const uint16_t val = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-                    *reinterpret_cast<uint16_t*>(dst + v_operand_offset(dim >> 5, (dim >> 4) & 1, dim & 15, (slot >> 2) & 1) +
-                                                 8 * (slot >> 3) + 2 * (slot & 3)) = val;
-                }
+            if (step > 0) {
+                sum0 += p0;
+                sum1 += p1;
+                uint32_t w = pack_pair(p0, p1);
+                asm volatile("" : "+v"(w), "+v"(sum0), "+v"(sum1));  // (else they sink below the branch that masks sn)
+                pb[(step - 1) >> 2].u[(step - 1) & 3] = w;
             }
+            p0 = e0, p1 = e1;
+            asm volatile("" : "+v"(p0), "+v"(p1));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        l += (sum0 + p0) + (sum1 + p1);
+        pb[1].u[3] = pack_pair(p0, p1);
+        mask(sn, t0n);
+        top = fmaxf(sn[0], sn[1]);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            o[k & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[k].b8, pb[k >> 2].b8, o[k & 3], 0, 0, 0);
+            beside_v(k);
+            if (k > 0) top = fmaxf(fmaxf(top, sn[2 * k]), sn[2 * k + 1]);
+            asm volatile("" : "+v"(top));
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
 
-    fetch(0);
-    stage(0, lds);
-    if (n_grp > 1) fetch(1);
-    __syncthreads();
-    for (int g = 0; g < n_grp; ++g) {
-        const char* buf = lds + (g & 1) * kBufBytes;
+    request(0);
+    hand_over(0);
+    if (n_grp > 1) request(1);
+    f32x16 s0, s1;
+    int g = 0;
+    if (n_sb > 0) {
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-            const int t0 = 64 * g + 32 * sub;  // first token slot of the super-block
-            if (!(wave_ok && t0 <= w_last)) continue;
-            // ---- S^T = K . Q^T -------------------------------------------------------------------
-            f32x16 s;
+        for (int k = 0; k < 8; ++k) load_k(lds, k);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[i] = 0.0f;
-            {
-                // lane (n as token slot m, h): block m / 16 of the super-block, slot m % 16 of it
-                const int j = 2 * sub + (n >> 4);
-                const int blk = min(4 * g + j, n_blk - 1);
-                const bool sealed = wk.len - blk * 16 >= 16;
-                const char* kb = buf + j * kTileBytes;
-                const int slot = n & 15;
-                // all eight operands are requested before the first product waits for one
-                Op a[8];
+        for (int i = 0; i < 16; ++i) s0[i] = 0.0f;
 #pragma unroll
-                for (int step = 0; step < 8; ++step) {
-                    const int piece = 2 * step + h;  // dims 8 piece .. + 8
-                    const int ofs = sealed ? (piece & 3) * 1024 + ((piece >> 2) * 16 + slot) * 16 : slot * 256 + piece * 16;
-                    a[step].u = *reinterpret_cast<const u32x4*>(kb + ofs);
-                }
-                __builtin_amdgcn_sched_barrier(0);
+        for (int s = 0; s < 8; ++s) s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[s].b8, qv[s].b8, s0, 0, 0, 0);
+        mask(s0, 0);
+        top = s0[0];
 #pragma unroll
-                for (int step = 0; step < 8; ++step) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[step].b8, qv[step].b8, s, 0, 0, 0);
+        for (int i = 1; i < 16; ++i) top = fmaxf(top, s0[i]);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) load_k(lds + 2 * kTileBytes, k);
+        // Group by group; at the top of the loop s0 holds the logits of the group's first super-block and ka the K operands
+        // of its second one.  Operands are read from LDS beside products, into registers that have just become free.
+        for (; 2 * g < n_sb; ++g) {
+            const char* buf = lds + (g & 1) * kBufBytes;
+            const char* other = lds + ((g + 1) & 1) * kBufBytes;
+            settle();
+            weigh(s0, s1, 64 * g + 32, [&](int k) { load_v(buf, k); }, [&](int k) { load_v(buf + 2 * kTileBytes, k); });
+            if (2 * g + 1 >= n_sb) break;
+            if (g + 1 < n_grp) {
+                hand_over(g + 1);
+                if (g + 2 < n_grp) request(g + 2);
             }
-            // the V operands travel from LDS while the softmax runs
-            Op va[2][4];
 #pragma unroll
-            for (int T = 0; T < 2; ++T)
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj)  // lane (n as dim 32 jj + n, h)
-                    va[T][jj].u = *reinterpret_cast<const u32x4*>(buf + (2 * sub + T) * kTileBytes + kHalf +
-                                                                  v_operand_offset(jj, n >> 4, n & 15, h));
-            __builtin_amdgcn_sched_barrier(0);
-            // ---- mask near the rows' limits: slot t0 + 8 (i / 4) + 4 h + i % 4 is visible up to the row's pos
-            if (t0 + 31 > w_first) {
-                const int room = row_ok ? pos - t0 - 4 * h : -1;  // visible iff 8 (i / 4) + i % 4 <= room
-#pragma unroll
-                for (int i = 0; i < 16; ++i) s[i] = (8 * (i >> 2) + (i & 3) <= room) ? s[i] : -INFINITY;
-            }
-            // ---- online softmax ------------------------------------------------------------------
-            float top = s[0];
-#pragma unroll
-            for (int i = 1; i < 16; ++i) top = fmaxf(top, s[i]);
-            top = row_ok ? top * scale_log2e : -INFINITY;
-            if (__builtin_amdgcn_ballot_w64(top > m + kSlack) != 0) {
-                // some row ran away from its reference (always so on a row's first super-block): move every
-                // row's reference to its running maximum (the two lanes of a row agree on it) and rescale
-                const float mx = fmaxf(top, __shfl_xor(top, 32, 64));
-                const float m_new = fmaxf(m, mx);
-                const float alpha = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - m_new);
-                l *= alpha;
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) o[jj][i] *= alpha;
-                m = m_new;
-            }
-            const float bias = (row_ok && m != -INFINITY) ? -m : -INFINITY;
-            float p[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], scale_log2e, bias));
-            float sum = 0.0f;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) sum += p[i];
-            l += sum;
-            // ---- O^T += V^T . P^T: block T of the super-block uses elements 8T .. 8T + 7 ---------------
-#pragma unroll
-            for (int T = 0; T < 2; ++T) {
-                Op b;
-                b.u.x = pack_pair(p[8 * T + 0], p[8 * T + 1]);
-                b.u.y = pack_pair(p[8 * T + 2], p[8 * T + 3]);
-                b.u.z = pack_pair(p[8 * T + 4], p[8 * T + 5]);
-                b.u.w = pack_pair(p[8 * T + 6], p[8 * T + 7]);
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) o[jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[T][jj].b8, b.b8, o[jj], 0, 0, 0);
-            }
+            for (int k = 0; k < 8; ++k) load_k(other, k);
+            settle();
+            weigh(s1, s0, 64 * g + 64, [](int) {}, [&](int k) { load_k(other + 2 * kTileBytes, k); });
         }
-        // hand over: the next group (in registers) goes into the other buffer, which everyone finished
-        // reading before the barrier that ended the previous iteration
-        if (g + 1 < n_grp) {
-            stage(g + 1, lds + ((g + 1) & 1) * kBufBytes);
-            if (g + 2 < n_grp) fetch(g + 2);
-        }
-        __syncthreads();
     }
-
+    for (; g + 1 < n_grp; ++g) {  // a wavefront without rows, or whose rows end before the walk does, goes on staging
+        hand_over(g + 1);
+        if (g + 2 < n_grp) request(g + 2);
+    }
+    __syncthreads();
 }
 
 template <bool F8>
@@ -330,7 +410,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     // four whole rows of 256 bytes: a lane holds its row in runs of four dims, and stores of 8 bytes per lane, 16 per
     // row, leave the L2 as partial lines (80 requests, 480 segments of 107 tokens, walks of 300, 32 heads, 0.85 GB of
     // queries and outputs: 1580 us with non-temporal stores of 8 bytes, 678 with plain ones, 650 this way).
-    const float lt = l + __shfl_xor(l, 32, 64);
+    const float lt = l + other_half(l);
     const float inv = 1.0f / lt;
     constexpr int kStride = 256 + 16;  // padded: the rows of a column of lanes start in different banks
     char* rows = lds + wave * 32 * kStride;
@@ -341,7 +421,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
             u32x2 pk;
             pk.x = pack_pair(o[jj][4 * j + 0] * inv, o[jj][4 * j + 1] * inv);
             pk.y = pack_pair(o[jj][4 * j + 2] * inv, o[jj][4 * j + 3] * inv);
-            *reinterpret_cast<u32x2*>(rows + n * kStride + (32 * jj + 8 * j + 4 * h) * 2) = pk;
+            *reinterpret_cast<u32x2*>(rows + n * kStride + (32 * jj + 16 * (j & 1) + 8 * (j >> 1) + 4 * h) * 2) = pk;
         }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -399,7 +479,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     walk_blocks<false>(wk, lds, o, m, l);
 
     // the row's state goes out as a partial result
-    const float lt = l + __shfl_xor(l, 32, 64);
+    const float lt = l + other_half(l);
     if (!wk.row_ok) return;
     const int64_t slot = ((int64_t)(wg->w[0].part_base + tr) * n_cand + cc) * n_q + hq;
     float* dst = part.o + slot * 128 + 4 * h;
@@ -409,7 +489,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const f32x4 v = {o[jj][4 * j + 0], o[jj][4 * j + 1], o[jj][4 * j + 2], o[jj][4 * j + 3]};
-                f32x4* to = reinterpret_cast<f32x4*>(dst + 32 * jj + 8 * j);
+                f32x4* to = reinterpret_cast<f32x4*>(dst + 32 * jj + 16 * (j & 1) + 8 * (j >> 1));
                 if constexpr (decltype(stream)::value) __builtin_nontemporal_store(v, to);
                 else *to = v;
             }
