@@ -242,7 +242,15 @@ hipError_t launch_append_blocks(const Shape& s, void* pool, const void* k, const
                                 int n_blocks, int n_open, int n_src, hipStream_t st);
 hipError_t launch_block_copies(const Shape& s, void* pool, const int32_t* src_dst_pairs, int n_pairs,
                                hipStream_t st);
-// words[pairs[2 i]] = pairs[2 i + 1] for i < n_pairs (device pointers; `pairs` 8-byte aligned)
+// Staged tables, from pinned host memory to the device (both 16-byte aligned, and padded to 16 bytes), by a kernel.
+#if defined(__HIP__)
+hipError_t copy_staged(void* dev, const void* host, size_t bytes, hipStream_t st);
+#else  // a build of the host side alone has no kernels
+inline hipError_t copy_staged(void* dev, const void* host, size_t bytes, hipStream_t st) {
+    return hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, st);
+}
+#endif
+// words[pairs[2 i]] = pairs[2 i + 1] for i < n_pairs (words on the device, pairs in pinned host memory, 8-byte aligned)
 hipError_t launch_scatter_words(int32_t* words, const int32_t* pairs, int n_pairs, hipStream_t st);
 // words[i] = 0 for i < n
 hipError_t launch_clear_words(int32_t* words, int n, hipStream_t st);

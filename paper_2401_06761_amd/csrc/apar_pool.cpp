@@ -264,10 +264,12 @@ int acquire_stage(apar_pool* p, size_t bytes, StageSlot** out) {
 // attention, typically) instead of queueing behind it.  The slot is free by construction: acquire_stage waited
 // for the kernels that last read it.
 int upload(apar_pool* p, StageSlot* s, size_t bytes, hipStream_t st) {
-    // Small tables go on the caller's stream: the hop to the copy stream and back costs more than it hides when a
-    // step is a few launches long (a serving loop at a few hundred threads: 0.18 ms per step with the hop, 0.12 without).
+    // Small tables go on the caller's stream, copied by a kernel: the hop to the copy stream and back costs more than it hides
+    // when a step is a few launches long (a serving loop at a few hundred threads: 0.18 ms per step with the hop, 0.12
+    // without), and a copy by the runtime keeps the kernels behind it waiting (64 requests, 32 heads 234 -> 218 us per
+    // decode call; one thread family of 32 k tokens 54 -> 39; figures per size beside copy_words).
     if (bytes < kCopyStreamMinBytes) {
-        HIP_TRY(hipMemcpyAsync(s->dev, s->host, bytes, hipMemcpyHostToDevice, st));
+        HIP_TRY(copy_staged(s->dev, s->host, bytes, st));
         return APAR_OK;
     }
     if (!p->copy_stream) HIP_TRY(hipStreamCreateWithFlags(&p->copy_stream, hipStreamNonBlocking));
@@ -623,13 +625,15 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     p->resident_behind = false;
     const bool inlined = !fixed && inline_plan(p, ph);
     // a carried-over plan whose tables are still on the device from the previous call: only the words that
-    // changed are sent, and written in place once the previous call's kernels are through
-    // (small tables are staged whole instead: one copy, against a copy and a launch)
-    const bool in_place = carried && !fixed && !inlined && p->resident && p->resident_bytes == staged && staged >= kCopyStreamMinBytes;
+    // changed are sent, and written in place once the previous call's kernels are through (one launch, as a copy of the whole
+    // tables is: a step of 64 requests, 32 heads, one row per thread and call 0.386 -> 0.380 ms; a serving loop with at most 64
+    // requests 1.45 -> 1.49 M output tokens per second)
+    const bool in_place = carried && !fixed && !inlined && p->resident && p->resident_bytes == staged;
     if (!in_place) p->resident = nullptr;
     if (in_place) {
         p->resident_behind = true;
         StageSlot* res = p->resident;
+        if (res->pending) HIP_TRY(hipStreamWaitEvent(st, res->ev, 0));  // (a no-op on the stream of the previous call)
         const size_t n_pairs = ph.dirty_wg_words.size() + ph.dirty_tile_words.size();
         if (n_pairs > 0) {
             StageSlot* ps = nullptr;
@@ -640,9 +644,7 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
             const int32_t wg_base = (int32_t)(ofs[0] / 4), tile_base = (int32_t)(ofs[1] / 4);
             for (int32_t w : ph.dirty_wg_words) *pairs++ = wg_base + w, *pairs++ = wg_words[w];
             for (int32_t w : ph.dirty_tile_words) *pairs++ = tile_base + w, *pairs++ = tile_words[w];
-            if ((rc = upload(p, ps, n_pairs * 2 * sizeof(int32_t), st)) != APAR_OK) return rc;
-            if (res->pending) HIP_TRY(hipStreamWaitEvent(st, res->ev, 0));  // (a no-op on the stream of the previous call)
-            HIP_TRY(launch_scatter_words((int32_t*)res->dev, (const int32_t*)ps->dev, (int)n_pairs, st));
+            HIP_TRY(launch_scatter_words((int32_t*)res->dev, (const int32_t*)ps->host, (int)n_pairs, st));
             HIP_TRY(hipEventRecord(ps->ev, st));
             ps->pending = true;
         }
@@ -695,7 +697,7 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     if (in_place || inlined) {
         // (already there, or on its way with the kernels)
     } else if (fixed) {
-        HIP_TRY(hipMemcpyAsync(dev, host, fixed_bytes, hipMemcpyHostToDevice, st));
+        HIP_TRY(copy_staged(dev, host, fixed_bytes, st));
         HIP_TRY(hipEventRecord(p->fixed_up, st));
         p->fixed_pending = true;
     } else if ((rc = upload(p, s, staged, st)) != APAR_OK) {

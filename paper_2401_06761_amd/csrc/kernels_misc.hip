@@ -441,8 +441,24 @@ hipError_t launch_block_copies(const Shape& s, void* pool, const int32_t* pairs,
     return hipGetLastError();
 }
 
-// words[pairs[2 i]] = pairs[2 i + 1]: brings staged plan tables up to date word by word.  Pairs that name the
-// same word carry the same value.
+// Bound by the host's memory over PCIe, and below some 100 KB by the launch.  A copy by the runtime goes to a DMA engine from
+// 16 KiB on, which the kernels behind it wait some 20 us for (kernel to kernel beside a kernel of 70 us, copy by the runtime /
+// this kernel: 4 and 16 KiB 4.9 / 5.1 us, 64 KiB 20.1 / 5.9, 200 KB 22.6 / 8.7, 1 MB 36.9 / 27.8).
+__global__ __launch_bounds__(256) void copy_words(uint4* __restrict__ to, const uint4* __restrict__ from, int n) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) to[i] = from[i];
+}
+
+hipError_t copy_staged(void* dev, const void* host, size_t bytes, hipStream_t st) {
+    if (bytes == 0) return hipSuccess;
+    const size_t n = (bytes + 15) / 16;
+    if (n > 0x7fffffff - 255 || ((uintptr_t)dev | (uintptr_t)host) % 16 != 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(copy_words, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (uint4*)dev, (const uint4*)host, (int)n);
+    return hipGetLastError();
+}
+
+// words[pairs[2 i]] = pairs[2 i + 1]: brings staged plan tables up to date word by word, out of pinned host memory (a
+// copy of its own first would be one more launch).  Pairs that name the same word carry the same value.
 __global__ __launch_bounds__(256) void scatter_words(int32_t* __restrict__ words, const int32_t* __restrict__ pairs, int n) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
