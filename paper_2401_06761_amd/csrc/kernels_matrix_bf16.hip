@@ -225,11 +225,20 @@ __device__ __forceinline__ void walk_blocks(const Walk& wk, char* lds, f32x16 (&
             dst += kHalf;
 #pragma unroll
             for (int r = 0; r < 4; ++r) x[r] = *reinterpret_cast<const u32x4*>(dst + r * 1024 + ln * 16);
+            // V: lanes c, 16 + c, 32 + c, 48 + c hold four slots of the same eight dims and swap words until each has all four
+            // slots of two dims (thirty-two 2-byte stores per lane otherwise, eight lanes of each into the same bank)
+            const int g4 = ln >> 4, c = ln & 15;
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    *reinterpret_cast<uint16_t*>(dst + bf16_v_offset(4 * r + (ln >> 4), 8 * (ln & 15) + e)) = (uint16_t)(x[r][e >> 1] >> (16 * (e & 1)));
+            for (int r = 0; r < 4; ++r) {
+                const u32x2 a = __builtin_amdgcn_permlane32_swap(x[r][0], x[r][2], false, false);
+                const u32x2 b = __builtin_amdgcn_permlane32_swap(x[r][1], x[r][3], false, false);
+                const u32x2 t01 = __builtin_amdgcn_permlane16_swap(a.x, b.x, false, false);  // word g4 of slots 4r, 4r + 1
+                const u32x2 t23 = __builtin_amdgcn_permlane16_swap(a.y, b.y, false, false);  // ... 4r + 2, 4r + 3
+                const u32x2 even = {(t01.x & 0xffffu) | (t01.y << 16), (t23.x & 0xffffu) | (t23.y << 16)};
+                const u32x2 odd = {(t01.x >> 16) | (t01.y & 0xffff0000u), (t23.x >> 16) | (t23.y & 0xffff0000u)};
+                *reinterpret_cast<u32x2*>(dst + bf16_v_offset(4 * r, 8 * c + 2 * g4)) = even;
+                *reinterpret_cast<u32x2*>(dst + bf16_v_offset(4 * r, 8 * c + 2 * g4 + 1)) = odd;
+            }
         }
     };
     // every wavefront's requests have landed, and everyone has read what it needs of the group before
