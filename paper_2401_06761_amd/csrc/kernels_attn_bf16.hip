@@ -217,31 +217,21 @@ constexpr int kOpenScratch = 16 * kOpenRowStride;   // one wavefront's row-major
 // NT = 16-row tiles per wavefront (1 or 2 are instantiated): a workgroup carries up to 64 * NT query rows.
 // F8: full blocks hold fp8 codes and two scales (APAR_BF16_FP8KV pools).
 // SPLIT: several workgroups per unit, each with a slice of its tile lists (attn_split.hpp).
-// INLINE (with SPLIT): the plan's tables come with the kernel's arguments.
-template <int NT, bool F8, bool SPLIT, bool INLINE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3 : 2))) void attention_bf16(PlanWords<INLINE>, const char* __restrict__ pool, const uint16_t* __restrict__ q,
-                                                      PlanDev plan, int wg_first, int n_cand, int n_q, int n_kv,
-                                                      int group, float scale_log2e, PartialBuf part,
-                                                      const uint16_t* __restrict__ cand_k,
-                                                      const uint16_t* __restrict__ cand_v,
-                                                      const uint8_t* __restrict__ cand_mask,
-                                                      uint16_t* __restrict__ out) {
-    // four staged tiles during the shared phase; then one V-transpose scratch per wavefront; last, three
-    // wavefronts' row states when a unit is split
-    __shared__ __attribute__((aligned(16))) char lds[4 * kTileBytes];
-    static_assert(4 * kTileBytes >= 3 * 16 * 130 * 4 && 4 * kTileBytes >= 4 * kOpenScratch && kOpenRowStride >= 256, "LDS areas overlap in time");
+// lds: four staged tiles during the shared phase; then one V-transpose scratch per wavefront; last, three wavefronts' row
+// states when a unit is split
+constexpr int kAttnLds = 4 * kTileBytes;
+static_assert(kAttnLds >= 3 * 16 * 130 * 4 && kAttnLds >= 4 * kOpenScratch && kOpenRowStride >= 256, "LDS areas overlap in time");
+template <int NT, bool F8, bool SPLIT>
+__device__ __forceinline__ void attend_unit(char* lds, const Slice& slice, const char* __restrict__ pool, const uint16_t* __restrict__ q,
+                                            const PlanDev& plan, int n_cand, int n_q, int n_kv, int group, float scale_log2e,
+                                            const PartialBuf& part, const uint16_t* __restrict__ cand_k,
+                                            const uint16_t* __restrict__ cand_v, const uint8_t* __restrict__ cand_mask,
+                                            uint16_t* __restrict__ out) {
     char(*stage)[kTileBytes] = reinterpret_cast<char(*)[kTileBytes]>(lds);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int g4 = lane >> 4, c = lane & 15;
     const int kvh = blockIdx.x % n_kv;
-    if constexpr (INLINE) plan_from_arguments(plan);
-    Slice slice;
-    if constexpr (SPLIT) {
-        slice = slice_of_block(plan.split, wg_first, n_kv);
-    } else {
-        slice.wg = wg_first + blockIdx.x / n_kv;
-    }
     const WgDesc* wg = plan.wgs + slice.wg;
     WaveItem wi = wg->w[wave];
     int n_coop = wg->n_coop, coop_ofs = wg->coop_ofs, coop_full = wg->row_tiles >> 8;
@@ -904,6 +894,59 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3
     }
 }
 
+template <bool SPLIT, bool INLINE>
+__device__ __forceinline__ Slice unit_of_block(PlanDev& plan, int wg_first, int n_kv) {
+    if constexpr (INLINE) plan_from_arguments(plan);
+    Slice slice;
+    if constexpr (SPLIT) {
+        slice = slice_of_block(plan.split, wg_first, n_kv);
+    } else {
+        slice.wg = wg_first + blockIdx.x / n_kv;
+    }
+    return slice;
+}
+
+// Units of one row-tile class.  INLINE (with SPLIT): the plan's tables come with the kernel's arguments.
+template <int NT, bool F8, bool SPLIT, bool INLINE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3 : 2))) void attention_bf16(
+    PlanWords<INLINE>, const char* __restrict__ pool, const uint16_t* __restrict__ q, PlanDev plan, int wg_first, int n_cand, int n_q, int n_kv,
+    int group, float scale_log2e, PartialBuf part, const uint16_t* __restrict__ cand_k, const uint16_t* __restrict__ cand_v,
+    const uint8_t* __restrict__ cand_mask, uint16_t* __restrict__ out) {
+    __shared__ __attribute__((aligned(16))) char lds[kAttnLds];
+    const Slice slice = unit_of_block<SPLIT, INLINE>(plan, wg_first, n_kv);
+    attend_unit<NT, F8, SPLIT>(lds, slice, pool, q, plan, n_cand, n_q, n_kv, group, scale_log2e, part, cand_k, cand_v, cand_mask, out);
+}
+
+// Units of both classes in one launch (238 registers: the chip holds two workgroups per compute unit).
+template <bool F8, bool SPLIT, bool INLINE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attention_bf16_both(
+    PlanWords<INLINE>, const char* __restrict__ pool, const uint16_t* __restrict__ q, PlanDev plan, int wg_first, int n_cand, int n_q, int n_kv,
+    int group, float scale_log2e, PartialBuf part, const uint16_t* __restrict__ cand_k, const uint16_t* __restrict__ cand_v,
+    const uint8_t* __restrict__ cand_mask, uint16_t* __restrict__ out) {
+    __shared__ __attribute__((aligned(16))) char lds[kAttnLds];
+    const Slice slice = unit_of_block<SPLIT, INLINE>(plan, wg_first, n_kv);
+    if ((plan.wgs[slice.wg].row_tiles & 255) == 2)
+        attend_unit<2, F8, SPLIT>(lds, slice, pool, q, plan, n_cand, n_q, n_kv, group, scale_log2e, part, cand_k, cand_v, cand_mask, out);
+    else
+        attend_unit<1, F8, SPLIT>(lds, slice, pool, q, plan, n_cand, n_q, n_kv, group, scale_log2e, part, cand_k, cand_v, cand_mask, out);
+}
+
+// Whether a call with units of both row-tile classes runs them in one launch (n_wg workgroups) rather than in two side by
+// side on two streams.  Two launches cost an event, two waits and the second stream's start, 15 to 20 us, and each ends
+// on a tail of its own; one launch holds two workgroups per compute unit where the one-row-tile class alone would hold
+// three.  Measured, us per call, two launches / one (workgroups):
+//   bf16   8 kv heads (64) 68.7 / 48.9, (128) 71.5 / 53.5, (264) 113 / 102, (512) 134 / 121, (520) 157 / 160, (570) 154 / 157,
+//          (620) 174 / 171, (690) 198 / 178, (1048) 254 / 232, (2096) 501 / 471, (4184) 931 / 899, (8328) 3178 / 3183;
+//          32 kv heads (128, five candidates) 72 / 56, (2048, three) 496 / 472, (2048, two) 570 / 449, (4000) 1296 / 1194
+//   fp8    8 kv heads (128) 123 / 99, (136) 80 / 73, (520) 119 / 137, (570) 126 / 143, (690) 146 / 148, (1024) 188 / 173,
+//          (1048) 177 / 166, (1472) 244 / 226, (2096) 331 / 340, (3270) 467 / 507; 32 kv heads (2048) 390 / 385
+// So: where all are resident at once, and again where the few of a second round no longer stand out; fp8 pools, whose
+// wavefronts live on how many of them have tiles in flight, up to four rounds.
+constexpr int64_t kResident = 2 * 256;
+bool one_launch(int64_t n_wg, bool fp8) {
+    return n_wg <= kResident || (fp8 ? n_wg >= 3 * kResident / 2 && n_wg <= 4 * kResident : n_wg >= 6 * kResident / 5);
+}
+
 }  // namespace
 
 hipError_t launch_attention_bf16(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand,
@@ -912,7 +955,8 @@ hipError_t launch_attention_bf16(const Shape& s, const void* pool, const void* q
     // workgroups are sorted by class: [matrix units | 2 row tiles per wavefront | 1], heaviest first in each.
     // Matrix units go first, alone, on the caller's stream: their workgroups need 64 KB of LDS and most of a
     // SIMD's registers, and beside a kernel of small workgroups they wait until that kernel has drained
-    // (measured: a 100 us launch took as long as the 800 us launch beside it).  Of the two row-tile classes
+    // (measured: a 100 us launch took as long as the 800 us launch beside it).  Two row-tile classes go in one
+    // launch where that was measured faster (one_launch); elsewhere
     // the last one present runs on the caller's stream and the other beside it on a side stream that waits
     // for the caller's stream first and that the caller's stream then waits for.
     int first[3], last = -1, n_present = 0;
@@ -929,7 +973,8 @@ hipError_t launch_attention_bf16(const Shape& s, const void* pool, const void* q
     if (n_class[0] > 0 && (e = launch_attention_units_bf16(s, pool, q, plan, first[0], n_class[0], n_cand, part, st)) != hipSuccess)
         return e;
     if (last < 0) return hipSuccess;
-    const bool side_by_side = n_present > 1 && !cs.serial;
+    const bool both = n_present > 1 && one_launch((int64_t)(n_class[1] + n_class[2]) * s.n_kv, s.fp8_sealed != 0);
+    const bool side_by_side = n_present > 1 && !cs.serial && !both;
     if (side_by_side) {
         if (!cs.fork) {
             if ((e = hipEventCreateWithFlags(&cs.fork, hipEventDisableTiming)) != hipSuccess) return e;
@@ -943,27 +988,28 @@ hipError_t launch_attention_bf16(const Shape& s, const void* pool, const void* q
     int side = 0;
     bool used[2] = {false, false};
     for (int cls = 1; cls < 3; ++cls) {
-        const int count = n_class[cls];
-        if (count == 0) continue;
+        const int count = both ? n_class[1] + n_class[2] : n_class[cls];
+        if (count == 0 || (both && cls == 2)) continue;
         hipStream_t on = st;
         if (cls != last && side_by_side) {
             on = cs.aux[side];
             if ((e = hipStreamWaitEvent(on, cs.fork, 0)) != hipSuccess) return e;
         }
         const unsigned n_wg = (unsigned)count * (unsigned)s.n_kv;
-#define APAR_LAUNCH(NTV, F8V, SPLITV, INLINEV, WORDS)                                                                   \
-    hipLaunchKernelGGL((attention_bf16<NTV, F8V, SPLITV, INLINEV>), dim3(n_wg), dim3(256), 0, on, WORDS,                 \
+#define APAR_LAUNCH(KERNEL, WORDS)                                                                                      \
+    hipLaunchKernelGGL(KERNEL, dim3(n_wg), dim3(256), 0, on, WORDS,                                                      \
                        (const char*)pool, (const uint16_t*)q, plan, first[cls], n_cand, s.n_q, s.n_kv, s.group,          \
                        s.scale_log2e, part, (const uint16_t*)cand_k, (const uint16_t*)cand_v, mask, (uint16_t*)out)
+#define APAR_LAUNCH_CLASS(F8V, SPLITV, INLINEV, WORDS)                                        \
+    do {                                                                                      \
+        if (both) APAR_LAUNCH((attention_bf16_both<F8V, SPLITV, INLINEV>), WORDS);            \
+        else if (cls == 1) APAR_LAUNCH((attention_bf16<2, F8V, SPLITV, INLINEV>), WORDS);     \
+        else APAR_LAUNCH((attention_bf16<1, F8V, SPLITV, INLINEV>), WORDS);                   \
+    } while (0)
 #define APAR_LAUNCH_F8(SPLITV, INLINEV, WORDS)                          \
     do {                                                                \
-        if (s.fp8_sealed) {                                             \
-            if (cls == 1) APAR_LAUNCH(2, true, SPLITV, INLINEV, WORDS); \
-            else APAR_LAUNCH(1, true, SPLITV, INLINEV, WORDS);          \
-        } else {                                                        \
-            if (cls == 1) APAR_LAUNCH(2, false, SPLITV, INLINEV, WORDS);\
-            else APAR_LAUNCH(1, false, SPLITV, INLINEV, WORDS);         \
-        }                                                               \
+        if (s.fp8_sealed) APAR_LAUNCH_CLASS(true, SPLITV, INLINEV, WORDS);  \
+        else APAR_LAUNCH_CLASS(false, SPLITV, INLINEV, WORDS);          \
     } while (0)
         if (plan.inline_words) {
             PlanWords<true> words;
@@ -975,6 +1021,7 @@ hipError_t launch_attention_bf16(const Shape& s, const void* pool, const void* q
             APAR_LAUNCH_F8(false, false, PlanWords<false>{});
         }
 #undef APAR_LAUNCH_F8
+#undef APAR_LAUNCH_CLASS
 #undef APAR_LAUNCH
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (cls != last && side_by_side) {
