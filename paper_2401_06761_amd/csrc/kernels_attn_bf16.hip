@@ -220,7 +220,8 @@ constexpr int kOpenScratch = 16 * kOpenRowStride;   // one wavefront's row-major
 // lds: four staged tiles during the shared phase; then one V-transpose scratch per wavefront; last, three wavefronts' row
 // states when a unit is split
 constexpr int kAttnLds = 4 * kTileBytes;
-static_assert(kAttnLds >= 3 * 16 * 130 * 4 && kAttnLds >= 4 * kOpenScratch && kOpenRowStride >= 256, "LDS areas overlap in time");
+constexpr int kSplitState = 8 * 1024 + 512;  // eight accumulator quads, reference and share of the sum per lane
+static_assert(kAttnLds >= 3 * kSplitState && kAttnLds >= 4 * kOpenScratch && kOpenRowStride >= 256, "LDS areas overlap in time");
 template <int NT, bool F8, bool SPLIT>
 __device__ __forceinline__ void attend_unit(char* lds, const Slice& slice, const char* __restrict__ pool, const uint16_t* __restrict__ q,
                                             const PlanDev& plan, int n_cand, int n_q, int n_kv, int group, float scale_log2e,
@@ -756,47 +757,40 @@ __device__ __forceinline__ void attend_unit(char* lds, const Slice& slice, const
 
     // ---- results ------------------------------------------------------------------------------
     if (NT == 1 && (wi.flags & kWaveSplit)) {
-        // the four wavefronts hold the same rows over different tiles: fold 1..3 into 0 through LDS
+        // the four wavefronts hold the same rows over different tiles: fold 1..3 into 0 through LDS, every register of a
+        // wavefront as 1 KiB in the order of its lanes (row by row instead, sixteen lanes met in one bank: 4.4 us of the 14.6
+        // that one request of five threads took)
         RowState& s0 = st[0];
-        float lt = s0.l;
-        lt += __shfl_xor(lt, 16, 64);
-        lt += __shfl_xor(lt, 32, 64);
-        float* so = reinterpret_cast<float*>(lds);           // [3][16 rows][128]
-        float* sml = so + 3 * 16 * 128;                       // [3][16 rows][2]
         __syncthreads();  // every wavefront is done with its transpose scratch, which this area overlaps
         if (wave > 0) {
-            float* dst = so + ((wave - 1) * 16 + c) * 128 + 4 * g4;
+            char* to = lds + (wave - 1) * kSplitState;
 #pragma unroll
-            for (int jj = 0; jj < 8; ++jj) *reinterpret_cast<f32x4*>(dst + 16 * jj) = s0.o[jj];
-            if (g4 == 0) {
-                sml[((wave - 1) * 16 + c) * 2] = s0.m;
-                sml[((wave - 1) * 16 + c) * 2 + 1] = lt;
-            }
+            for (int jj = 0; jj < 8; ++jj) *reinterpret_cast<f32x4*>(to + (jj * 64 + lane) * 16) = s0.o[jj];
+            *reinterpret_cast<f32x2*>(to + 8 * 1024 + lane * 8) = f32x2{s0.m, s0.l};
         }
         __syncthreads();
         if (wave > 0) return;
-        float mw[3], lw[3], mx = s0.m;
+        f32x2 ml[3];
+        float mx = s0.m;
 #pragma unroll
         for (int w2 = 0; w2 < 3; ++w2) {
-            mw[w2] = sml[(w2 * 16 + c) * 2];
-            lw[w2] = sml[(w2 * 16 + c) * 2 + 1];
-            mx = fmaxf(mx, mw[w2]);
+            ml[w2] = *reinterpret_cast<const f32x2*>(lds + w2 * kSplitState + 8 * 1024 + lane * 8);
+            mx = fmaxf(mx, ml[w2].x);
         }
         // a wavefront that saw no tile of a row left m = -inf and sums of zero for it
         const float a0 = (s0.m == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(s0.m - mx);
-        lt *= a0;
+        s0.l *= a0;
 #pragma unroll
         for (int jj = 0; jj < 8; ++jj) s0.o[jj] *= a0;
 #pragma unroll
         for (int w2 = 0; w2 < 3; ++w2) {
-            const float aw = (mw[w2] == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(mw[w2] - mx);
-            lt += aw * lw[w2];
-            const float* src = so + (w2 * 16 + c) * 128 + 4 * g4;
+            const float aw = (ml[w2].x == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(ml[w2].x - mx);
+            s0.l += aw * ml[w2].y;
 #pragma unroll
-            for (int jj = 0; jj < 8; ++jj) s0.o[jj] += aw * *reinterpret_cast<const f32x4*>(src + 16 * jj);
+            for (int jj = 0; jj < 8; ++jj)
+                s0.o[jj] += aw * *reinterpret_cast<const f32x4*>(lds + w2 * kSplitState + (jj * 64 + lane) * 16);
         }
         s0.m = mx;
-        s0.l = g4 == 0 ? lt : 0.0f;  // back to one share per lane: the four lanes of a row add up to the sum
         __builtin_amdgcn_wave_barrier();
     }
 
