@@ -519,6 +519,13 @@ bool inline_plan(apar_pool* p, const PlanHost& ph) {
     return true;
 }
 
+// What an open tile costs a wavefront of the 16-bit kernel: its V half takes a turn through LDS and nothing is in flight
+// meanwhile (one request of five threads, 32 heads: 1.3 us per open tile, 0.6 per full one, 12.6 us for the wavefront that has
+// all five against 10.0 for the others).  On fp32 pools every tile is alike.
+// Counted as one, two and three: one request 15.0 / 13.5 / 13.7 us, 16 requests 58.5 / 54.8 / 54.7, 64 with 8 heads
+// 65.2 / 60.9 / 60.5, two requests 22.5 / 13.3 / 12.6 (whose wavefronts were long enough to be cut into slices).
+constexpr int kOpenTileCost = 2;
+
 // fixed: the plan and the partial results go to the device's static workspace, nothing is allocated, no
 // stream or event is created and profiling is off for the call.
 int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* cand_v, const uint8_t* mask,
@@ -555,6 +562,7 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     prm.matrix_min_rows = (p->shape.dtype == APAR_BF16 && !p->shape.fp8_sealed) ? p->matrix_min_rows : 0;
     prm.matrix_min_blocks = p->matrix_min_blocks;
     prm.inline_shared = p->inline_shared;
+    prm.open_cost = p->shape.dtype == APAR_F32 ? 1 : kOpenTileCost;
     // Decode calls of a loop list the same threads step after step - each a few rows longer, a few replaced
     // by a thread forked from them - and the plan of the previous call then only needs its tails brought up
     // to date.  A table never changes before its last block, and a thread forked since the previous call

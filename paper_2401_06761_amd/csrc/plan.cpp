@@ -671,14 +671,26 @@ int build_plan(const PlanThreadView* threads, int n, const int32_t* refcount, in
             WgDesc wg{};
             wg.grp_base = it.grp_lo;
             wg.row_tiles = 1;
+            // Cut by cost: an open tile - all of them are at the end - counts as open_cost full ones.  The last wavefront
+            // takes every open tile where they are a quarter of the list at most (a carried plan finds them there).
+            const int32_t n_open = it.n_tiles - item_full;
+            const int64_t whole = item_full + (int64_t)n_open * prm.open_cost;
+            const bool all_last = item_full >= (int32_t)((int64_t)it.n_tiles * 3 / 4);
+            const bool only_open = all_last && whole * 3 / 4 >= item_full;  // the last wavefront has its share in open tiles alone
+            auto cut = [&](int j) {
+                if (j == 4) return it.n_tiles;
+                if (only_open) return (int32_t)((int64_t)item_full * j / 3);
+                const int64_t at = whole * j / 4;
+                return at <= item_full ? (int32_t)at : item_full + (int32_t)((at - item_full) / prm.open_cost);
+            };
             for (int j = 0; j < 4; ++j) {
-                const int32_t b = (int32_t)((int64_t)it.n_tiles * j / 4), e = (int32_t)((int64_t)it.n_tiles * (j + 1) / 4);
+                const int32_t b = cut(j), e = cut(j + 1);
                 wg.w[j] = WaveItem{it.tile_ofs + b, e - b, it.grp_lo, it.n_grp, it.part_base, it.flags | kWaveSplit};
                 wg.n_full[j] = std::max(0, std::min(e, item_full) - b);
             }
-            // the item's open tiles, and the entries left free behind them, belong to the last quarter (if they all do)
+            // the item's open tiles, and the entries left free behind them, belong to the last wavefront (if they all do)
             ph.item_wg[slot[k]] = (int32_t)ph.wgs.size();
-            ph.item_slot[slot[k]] = item_full >= (int32_t)((int64_t)it.n_tiles * 3 / 4) ? 3 : -1;
+            ph.item_slot[slot[k]] = all_last ? 3 : -1;
             ph.wgs.push_back(wg);
         }
         for (; k < slot.size(); k += 4) {

@@ -95,6 +95,7 @@ struct PlanParams {
                                 // read the shared segments above their threads, instead of standing alone with partial results
     int32_t matrix_min_rows = 0;    // stand-alone segments with at least this many query rows (0: never) ...
     int32_t matrix_min_blocks = 0;  // ... and at least this many blocks become matrix units
+    int32_t open_cost = 1;          // a tile that is not full, in full tiles, where a list is cut four ways
 };
 
 struct PrefillThreadView {  // one listed thread of a prefill call
