@@ -214,6 +214,9 @@ __device__ __forceinline__ void v_operands_from_rows(const char* vrows, int stri
 constexpr int kOpenRowStride = 272;                 // padded, so the four token groups hit different LDS banks
 constexpr int kOpenScratch = 16 * kOpenRowStride;   // one wavefront's row-major V half
 
+// The scale of a full fp8 tile's half, by a scalar load (full blocks are not written while a kernel reads them).
+__device__ __forceinline__ float scale_at(const char* p) { return *(const float __attribute__((address_space(4)))*)p; }
+
 // NT = 16-row tiles per wavefront (1 or 2 are instantiated): a workgroup carries up to 64 * NT query rows.
 // F8: full blocks hold fp8 codes and two scales (APAR_BF16_FP8KV pools).
 // SPLIT: several workgroups per unit, each with a slice of its tile lists (attn_split.hpp).
@@ -560,7 +563,7 @@ __device__ __forceinline__ void attend_unit(char* lds, const Slice& slice, const
         if constexpr (F8) {
 #pragma unroll
             for (int rp = 0; rp < 2; ++rp) k8[rp] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p + rp * 1024));
-            k8s = *reinterpret_cast<const float*>(tile + kFp8ScaleOfs);
+            k8s = scale_at(tile + kFp8ScaleOfs);
         } else {
 #pragma unroll
             for (int r = 0; r < 4; ++r) k[r].u = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p + r * 1024));
@@ -571,7 +574,7 @@ __device__ __forceinline__ void attend_unit(char* lds, const Slice& slice, const
             const char* p = tile + kFp8HalfBytes + lane * 16;
 #pragma unroll
             for (int rp = 0; rp < 2; ++rp) v8[rp] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p + rp * 1024));
-            v8s = *reinterpret_cast<const float*>(tile + kFp8ScaleOfs + 4);
+            v8s = scale_at(tile + kFp8ScaleOfs + 4);
         } else {
             const u32x4* p = reinterpret_cast<const u32x4*>(tile + 4096) + lane;
 #pragma unroll
@@ -629,13 +632,13 @@ __device__ __forceinline__ void attend_unit(char* lds, const Slice& slice, const
                 if (want_k) {
 #pragma unroll
                     for (int rp = 0; rp < 2; ++rp) kk[rp] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p + rp * 1024));
-                    ks = *reinterpret_cast<const float*>(tile + kFp8ScaleOfs);
+                    ks = scale_at(tile + kFp8ScaleOfs);
                 }
                 if (want_v) {
 #pragma unroll
                     for (int rp = 0; rp < 2; ++rp)
                         vv[rp] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p + kFp8HalfBytes + rp * 1024));
-                    vs = *reinterpret_cast<const float*>(tile + kFp8ScaleOfs + 4);
+                    vs = scale_at(tile + kFp8ScaleOfs + 4);
                 }
             };
             // tile j, whose codes are in (kk, vv); then (refill): tile j + 2 into the same registers
@@ -919,6 +922,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     const uint8_t* __restrict__ cand_mask, uint16_t* __restrict__ out) {
     __shared__ __attribute__((aligned(16))) char lds[kAttnLds];
     const Slice slice = unit_of_block<SPLIT, INLINE>(plan, wg_first, n_kv);
+    tables_unwritten(plan);
     if ((plan.wgs[slice.wg].row_tiles & 255) == 2)
         attend_unit<2, F8, SPLIT>(lds, slice, pool, q, plan, n_cand, n_q, n_kv, group, scale_log2e, part, cand_k, cand_v, cand_mask, out);
     else

@@ -396,6 +396,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     } else {
         slice.wg = blockIdx.x / n_kv;
     }
+    tables_unwritten(plan);
     if ((plan.wgs[slice.wg].row_tiles & 255) == 2)
         attend_unit<D, 2, SPLIT>(lds, slice, pool, q, plan, n_cand, n_q, n_kv, group, scale_log2e, part, cand_k, cand_v, cand_mask, out);
     else

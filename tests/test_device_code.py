@@ -1,0 +1,50 @@
+"""What the compiler makes of the row-tile kernels: those that run units of either row-tile class read a plan's tables and fp8 scales as the
+kernels of one class do, by scalar loads, and no 16-bit kernel needs scratch memory."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2401_06761_amd import build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """Per kernel of kernels_attn_bf16.hip, (mangled template arguments, vector loads of one or two words, bytes of scratch)."""
+    try:
+        hipcc = build.hipcc()
+    except RuntimeError:
+        pytest.skip("no hipcc")
+    asm = str(tmp_path_factory.mktemp("asm") / "attn.s")
+    csrc = os.path.join(ROOT, "paper_2401_06761_amd", "csrc")
+    done = subprocess.run([hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                           "-I" + os.path.join(ROOT, "include"), "-I" + csrc, "-x", "hip", "--cuda-device-only", "-S",
+                           os.path.join(csrc, "kernels_attn_bf16.hip"), "-o", asm], capture_output=True, text=True, timeout=300)
+    assert done.returncode == 0, done.stderr[-3000:]
+    text = open(asm).read()
+    found = {}
+    for name in re.findall(r"^\s*\.amdhsa_kernel (\S+)", text, re.M):
+        body = re.search(rf"^{re.escape(name)}:.*?^\.Lfunc_end", text, re.S | re.M).group(0)
+        scratch = re.search(rf"\.amdhsa_kernel {re.escape(name)}.*?private_segment_fixed_size (\d+)", text, re.S).group(1)
+        found[name] = (len(re.findall(r"^\s+global_load_dword(?:x2)? ", body, re.M)), int(scratch))
+    return found
+
+
+def _one(kernels, pattern):
+    return next(v for k, v in kernels.items() if pattern in k)
+
+
+@pytest.mark.parametrize("f8,split,inline", [(0, 0, 0), (0, 1, 0), (0, 1, 1), (1, 0, 0), (1, 1, 0), (1, 1, 1)])
+def test_kernels_of_both_classes_load_as_those_of_one_do(kernels, f8, split, inline):
+    rest = f"ELb{f8}ELb{split}ELb{inline}EE"
+    both = _one(kernels, f"attention_bf16_bothILb{f8}ELb{split}ELb{inline}EE")
+    one, two = (_one(kernels, f"attention_bf16ILi{nt}{rest}") for nt in (1, 2))
+    # (the words of a list that each lane reads for itself are vector loads in all of them)
+    assert both[0] <= one[0] + two[0]
+
+
+def test_no_kernel_needs_scratch(kernels):
+    assert len(kernels) == 18 and all(scratch == 0 for _, scratch in kernels.values()), kernels
