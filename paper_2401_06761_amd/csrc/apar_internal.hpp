@@ -230,16 +230,6 @@ struct PartialBuf {
 // 1827 + 41 / 1813 + 49, 50 k rows (831 MB) 3758 + 179 / 3675 + 173; 1600 rows of matrix units 186 + 10 / 188 + 11.
 constexpr size_t kStreamPartialBytes = (size_t)256 << 20;
 
-// Side streams on which the attention kernels of different row-tile classes run next to each
-// other (each class alone would leave most of the chip idle during its tail).  Created on first
-// use by the launcher, released by the pool; all at the default priority.
-struct ClassStreams {
-    hipStream_t aux[2] = {nullptr, nullptr};
-    hipEvent_t fork = nullptr, join[2] = {nullptr, nullptr};
-    bool serial = false;  // true: every class is launched on the caller's stream, one after the other, and
-                          // no stream or event is ever created (for the entry point that must not allocate)
-};
-
 // Room for the row states of a launch some of whose units are cut into slices (attn_split.hpp): 256 shares of the work are
 // fewer than 512 slices x kv heads, of at most 8 row tiles of 8.5 KiB.  kSplitMaxCut: the most cut units x kv heads.
 constexpr size_t kSplitStateBytes = (size_t)32 << 20;
@@ -274,10 +264,10 @@ hipError_t launch_read_rows(const Shape& s, const void* pool, const int32_t* src
                             void* v_out, hipStream_t st);
 hipError_t launch_attention_partial(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand,
                                     PartialBuf part, const void* cand_k, const void* cand_v, const uint8_t* mask,
-                                    void* out, ClassStreams& cs, hipStream_t st);
+                                    void* out, hipStream_t st);
 hipError_t launch_attention_bf16(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand,
                                  PartialBuf part, const void* cand_k, const void* cand_v, const uint8_t* mask,
-                                 void* out, ClassStreams& cs, hipStream_t st);
+                                 void* out, hipStream_t st);
 hipError_t launch_attention_f32(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand,
                                 PartialBuf part, const void* cand_k, const void* cand_v, const uint8_t* mask, void* out,
                                 hipStream_t st);

@@ -119,7 +119,6 @@ struct apar_pool {
     bool resident_behind = false;
     PartialBuf part{};
     size_t part_slots_cap = 0;
-    ClassStreams class_streams;
     hipStream_t copy_stream = nullptr;  // uploads of plans and row codes run here, beside the caller's stream
 
     // Obtained at pool creation, an allocation each: pinned host memory (the buffer apar_decode_attention_fixed stages its
@@ -758,10 +757,7 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
         if (hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
         else p->split_clear = capture == hipStreamCaptureStatusNone;
     }
-    ClassStreams one_stream;
-    one_stream.serial = true;
-    HIP_TRY(launch_attention_partial(p->shape, p->kv, q, pd, n_cand, part, cand_k, cand_v, mask, out,
-                                     fixed ? one_stream : p->class_streams, st));
+    HIP_TRY(launch_attention_partial(p->shape, p->kv, q, pd, n_cand, part, cand_k, cand_v, mask, out, st));
     if (profiling) HIP_TRY(hipEventRecord(ev.b, st));
     if (ph.any_partial)
         HIP_TRY(launch_merge(p->shape, pd, part, q, cand_k, cand_v, mask, n_cand, out, st));
@@ -968,8 +964,7 @@ int prefill_common(apar_pool* p, const void* q, const apar_thread* ids, const in
             return rc;
         HIP_TRY(hipEventRecord(ev.a, st));
     }
-    HIP_TRY(launch_attention_partial(p->shape, p->kv, q, pd, 1, p->part, nullptr, nullptr, nullptr, out,
-                                     p->class_streams, st));
+    HIP_TRY(launch_attention_partial(p->shape, p->kv, q, pd, 1, p->part, nullptr, nullptr, nullptr, out, st));
     if (p->profiling) {
         HIP_TRY(hipEventRecord(ev.b, st));
         HIP_TRY(hipEventRecord(ev.c, st));
@@ -1069,9 +1064,6 @@ int apar_pool_destroy(apar_pool* p) {
     for (EventPair& e : p->decode_events) drop(e.a), drop(e.b), drop(e.c);
     for (EventPair& e : p->append_events) drop(e.a), drop(e.b), drop(e.c);
     for (hipEvent_t e : p->spare_events) drop(e);
-    drop(p->class_streams.fork), drop(p->class_streams.join[0]), drop(p->class_streams.join[1]);
-    for (hipStream_t a : p->class_streams.aux)
-        if (a) (void)hipStreamDestroy(a);
     delete p;
     return rc;
 }

@@ -914,7 +914,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 3
     attend_unit<NT, F8, SPLIT>(lds, slice, pool, q, plan, n_cand, n_q, n_kv, group, scale_log2e, part, cand_k, cand_v, cand_mask, out);
 }
 
-// Units of both classes in one launch (238 registers: the chip holds two workgroups per compute unit).
+// Units of both classes in one launch (217 to 240 registers: the chip holds two workgroups per compute unit, where units of one
+// row tile alone would have three).  Two launches side by side cost an event, two waits and the second stream's start, and each
+// ends on a tail of its own.  Measured, us per call, two launches / one (workgroups of the two classes):
+//   bf16   8 kv heads (16 + 1016) 176 / 134, (96 + 4032) 564 / 475, (48 + 8160) 979 / 888, (792 + 3600) 711 / 664, 84 requests of two
+//          fork levels 207 / 168, 128 requests of group 8 246 / 211, 1024 of group 4 3136 / 3060; 32 kv heads (32 + 2016) 301 / 226,
+//          (32 + 8160) 810 / 645, (832 + 7360) 1854 / 1753; two candidates (64 requests) 583 / 441, three 502 / 469, (100) 339 / 339;
+//          five (2368 + 2112) 915 / 868, (9536 + 576) 3278 / 3261, (29408 + 192) 11680 / 11720
+//   fp8    8 kv heads (16 + 1016) 127 / 80, (96 + 4032) 342 / 262, (48 + 8160) 557 / 489, (792 + 3600) 460 / 413; 32 kv heads (32 + 2016)
+//          232 / 166, (32 + 8160) 487 / 367, (832 + 7360) 1461 / 1340; two candidates (224 + 3968) 276 / 199
 template <bool F8, bool SPLIT, bool INLINE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attention_bf16_both(
     PlanWords<INLINE>, const char* __restrict__ pool, const uint16_t* __restrict__ q, PlanDev plan, int wg_first, int n_cand, int n_q, int n_kv,
@@ -929,108 +937,52 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
         attend_unit<1, F8, SPLIT>(lds, slice, pool, q, plan, n_cand, n_q, n_kv, group, scale_log2e, part, cand_k, cand_v, cand_mask, out);
 }
 
-// Whether a call with units of both row-tile classes runs them in one launch (n_wg workgroups) rather than in two side by
-// side on two streams.  Two launches cost an event, two waits and the second stream's start, 15 to 20 us, and each ends
-// on a tail of its own; one launch holds two workgroups per compute unit where the one-row-tile class alone would hold
-// three.  Measured, us per call, two launches / one (workgroups):
-//   bf16   8 kv heads (64) 68.7 / 48.9, (128) 71.5 / 53.5, (264) 113 / 102, (512) 134 / 121, (520) 157 / 160, (570) 154 / 157,
-//          (620) 174 / 171, (690) 198 / 178, (1048) 254 / 232, (2096) 501 / 471, (4184) 931 / 899, (8328) 3178 / 3183;
-//          32 kv heads (128, five candidates) 72 / 56, (2048, three) 496 / 472, (2048, two) 570 / 449, (4000) 1296 / 1194
-//   fp8    8 kv heads (128) 123 / 99, (136) 80 / 73, (520) 119 / 137, (570) 126 / 143, (690) 146 / 148, (1024) 188 / 173,
-//          (1048) 177 / 166, (1472) 244 / 226, (2096) 331 / 340, (3270) 467 / 507; 32 kv heads (2048) 390 / 385
-// So: where all are resident at once, and again where the few of a second round no longer stand out; fp8 pools, whose
-// wavefronts live on how many of them have tiles in flight, up to four rounds.
-constexpr int64_t kResident = 2 * 256;
-bool one_launch(int64_t n_wg, bool fp8) {
-    return n_wg <= kResident || (fp8 ? n_wg >= 3 * kResident / 2 && n_wg <= 4 * kResident : n_wg >= 6 * kResident / 5);
-}
-
 }  // namespace
 
 hipError_t launch_attention_bf16(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand,
                                  PartialBuf part, const void* cand_k, const void* cand_v, const uint8_t* mask,
-                                 void* out, ClassStreams& cs, hipStream_t st) {
+                                 void* out, hipStream_t st) {
     // workgroups are sorted by class: [matrix units | 2 row tiles per wavefront | 1], heaviest first in each.
-    // Matrix units go first, alone, on the caller's stream: their workgroups need 64 KB of LDS and most of a
+    // Matrix units go first, alone: their workgroups need 64 KB of LDS and most of a
     // SIMD's registers, and beside a kernel of small workgroups they wait until that kernel has drained
-    // (measured: a 100 us launch took as long as the 800 us launch beside it).  Two row-tile classes go in one
-    // launch where that was measured faster (one_launch); elsewhere
-    // the last one present runs on the caller's stream and the other beside it on a side stream that waits
-    // for the caller's stream first and that the caller's stream then waits for.
-    int first[3], last = -1, n_present = 0;
+    // (measured: a 100 us launch took as long as the 800 us launch beside it).
     if (plan.n_inline_words > kPlanInlineWords) return hipErrorInvalidValue;
     const bool split = plan.split.blocks != nullptr || plan.inline_words;
     const int32_t* n_class = split ? plan.split.n_blocks_class : plan.n_wg_class;  // (matrix units are never cut)
-    for (int cls = 0, f = 0; cls < 3; ++cls) {
-        first[cls] = f;
-        f += n_class[cls];
-        if (cls > 0 && n_class[cls] > 0) last = cls, ++n_present;
-        if ((int64_t)n_class[cls] * s.n_kv > 0x7fffffff) return hipErrorInvalidValue;
-    }
+    const int first = n_class[0];
+    const int64_t n_wg = ((int64_t)n_class[1] + n_class[2]) * s.n_kv;
+    if (n_wg > 0x7fffffff) return hipErrorInvalidValue;
     hipError_t e;
-    if (n_class[0] > 0 && (e = launch_attention_units_bf16(s, pool, q, plan, first[0], n_class[0], n_cand, part, st)) != hipSuccess)
-        return e;
-    if (last < 0) return hipSuccess;
-    const bool both = n_present > 1 && one_launch((int64_t)(n_class[1] + n_class[2]) * s.n_kv, s.fp8_sealed != 0);
-    const bool side_by_side = n_present > 1 && !cs.serial && !both;
-    if (side_by_side) {
-        if (!cs.fork) {
-            if ((e = hipEventCreateWithFlags(&cs.fork, hipEventDisableTiming)) != hipSuccess) return e;
-        }
-        for (int k = 0; k < 2; ++k) {
-            if (!cs.aux[k] && (e = hipStreamCreateWithFlags(&cs.aux[k], hipStreamNonBlocking)) != hipSuccess) return e;
-            if (!cs.join[k] && (e = hipEventCreateWithFlags(&cs.join[k], hipEventDisableTiming)) != hipSuccess) return e;
-        }
-        if ((e = hipEventRecord(cs.fork, st)) != hipSuccess) return e;
-    }
-    int side = 0;
-    bool used[2] = {false, false};
-    for (int cls = 1; cls < 3; ++cls) {
-        const int count = both ? n_class[1] + n_class[2] : n_class[cls];
-        if (count == 0 || (both && cls == 2)) continue;
-        hipStream_t on = st;
-        if (cls != last && side_by_side) {
-            on = cs.aux[side];
-            if ((e = hipStreamWaitEvent(on, cs.fork, 0)) != hipSuccess) return e;
-        }
-        const unsigned n_wg = (unsigned)count * (unsigned)s.n_kv;
+    if (first > 0 && (e = launch_attention_units_bf16(s, pool, q, plan, 0, first, n_cand, part, st)) != hipSuccess) return e;
+    if (n_wg == 0) return hipSuccess;
 #define APAR_LAUNCH(KERNEL, WORDS)                                                                                      \
-    hipLaunchKernelGGL(KERNEL, dim3(n_wg), dim3(256), 0, on, WORDS,                                                      \
-                       (const char*)pool, (const uint16_t*)q, plan, first[cls], n_cand, s.n_q, s.n_kv, s.group,          \
+    hipLaunchKernelGGL(KERNEL, dim3((unsigned)n_wg), dim3(256), 0, st, WORDS,                                            \
+                       (const char*)pool, (const uint16_t*)q, plan, first, n_cand, s.n_q, s.n_kv, s.group,               \
                        s.scale_log2e, part, (const uint16_t*)cand_k, (const uint16_t*)cand_v, mask, (uint16_t*)out)
-#define APAR_LAUNCH_CLASS(F8V, SPLITV, INLINEV, WORDS)                                        \
-    do {                                                                                      \
-        if (both) APAR_LAUNCH((attention_bf16_both<F8V, SPLITV, INLINEV>), WORDS);            \
-        else if (cls == 1) APAR_LAUNCH((attention_bf16<2, F8V, SPLITV, INLINEV>), WORDS);     \
-        else APAR_LAUNCH((attention_bf16<1, F8V, SPLITV, INLINEV>), WORDS);                   \
+#define APAR_LAUNCH_CLASS(F8V, SPLITV, INLINEV, WORDS)                                                  \
+    do {                                                                                                \
+        if (n_class[1] == 0) APAR_LAUNCH((attention_bf16<1, F8V, SPLITV, INLINEV>), WORDS);             \
+        else if (n_class[2] == 0) APAR_LAUNCH((attention_bf16<2, F8V, SPLITV, INLINEV>), WORDS);        \
+        else APAR_LAUNCH((attention_bf16_both<F8V, SPLITV, INLINEV>), WORDS);                           \
     } while (0)
-#define APAR_LAUNCH_F8(SPLITV, INLINEV, WORDS)                          \
-    do {                                                                \
+#define APAR_LAUNCH_F8(SPLITV, INLINEV, WORDS)                              \
+    do {                                                                    \
         if (s.fp8_sealed) APAR_LAUNCH_CLASS(true, SPLITV, INLINEV, WORDS);  \
-        else APAR_LAUNCH_CLASS(false, SPLITV, INLINEV, WORDS);          \
+        else APAR_LAUNCH_CLASS(false, SPLITV, INLINEV, WORDS);              \
     } while (0)
-        if (plan.inline_words) {
-            PlanWords<true> words;
-            memcpy(words.words, plan.inline_words, (size_t)plan.n_inline_words * sizeof(int32_t));
-            APAR_LAUNCH_F8(true, true, words);
-        } else if (split) {
-            APAR_LAUNCH_F8(true, false, PlanWords<false>{});
-        } else {
-            APAR_LAUNCH_F8(false, false, PlanWords<false>{});
-        }
+    if (plan.inline_words) {
+        PlanWords<true> words;
+        memcpy(words.words, plan.inline_words, (size_t)plan.n_inline_words * sizeof(int32_t));
+        APAR_LAUNCH_F8(true, true, words);
+    } else if (split) {
+        APAR_LAUNCH_F8(true, false, PlanWords<false>{});
+    } else {
+        APAR_LAUNCH_F8(false, false, PlanWords<false>{});
+    }
 #undef APAR_LAUNCH_F8
 #undef APAR_LAUNCH_CLASS
 #undef APAR_LAUNCH
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (cls != last && side_by_side) {
-            if ((e = hipEventRecord(cs.join[side], on)) != hipSuccess) return e;
-            used[side] = true;
-            ++side;
-        }
-    }
-    for (int k = 0; k < 2; ++k)
-        if (used[k] && (e = hipStreamWaitEvent(st, cs.join[k], 0)) != hipSuccess) return e;
-    return hipSuccess;
+    return hipGetLastError();
 }
 
 }  // namespace apar

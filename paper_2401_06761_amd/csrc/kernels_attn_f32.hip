@@ -380,9 +380,12 @@ __device__ __forceinline__ void attend_unit(float (&lds)[4][16 * D + 32], const 
     }
 }
 
-// Units of both row-tile classes in one launch (either way two wavefronts per SIMD; one launch after the other: twelve trees,
-// 8 kv heads 118 -> 103 us, eight of 300 rows, group 8, 111 -> 94, four candidates 93 -> 69).  INLINE (with SPLIT): the plan's tables
-// come with the kernel's arguments.
+// Units of either row-tile class, in one launch (one launch after the other: twelve trees, 8 kv heads 118 -> 94 us, eight of 300
+// rows, group 8, 111 -> 79, four candidates 96 -> 63).  It holds as many wavefronts as the two-tile class needs registers for: two per
+// SIMD (d = 128) or three (d = 64), where the one-tile class alone would have three at most and four.  Calls of that class do not
+// gain by a kernel of their own (us, by it / by this one; workgroups): d = 64 (3008) 131 / 130, (1576) 102 / 103, (1200) 24.3 / 25.0,
+// (768) 63.5 / 63.5, 100 requests of two fork levels 79 / 71; d = 128 (3008) 254 / 253, (1576) 195 / 195, (480) 56 / 56, (192) 47 / 47: their
+// wavefronts are busy with products.  INLINE (with SPLIT): the plan's tables come with the kernel's arguments.
 template <int D, bool SPLIT, bool INLINE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attention_f32(
     PlanWords<INLINE>, const char* __restrict__ pool, const float* __restrict__ q, PlanDev plan, int n_cand, int n_q, int n_kv,

@@ -498,10 +498,10 @@ hipError_t launch_read_rows(const Shape& s, const void* pool, const int32_t* src
 
 hipError_t launch_attention_partial(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand,
                                     PartialBuf part, const void* cand_k, const void* cand_v, const uint8_t* mask,
-                                    void* out, ClassStreams& cs, hipStream_t st) {
+                                    void* out, hipStream_t st) {
     if (plan.n_wg <= 0) return hipSuccess;
     if (s.dtype == APAR_BF16)
-        return launch_attention_bf16(s, pool, q, plan, n_cand, part, cand_k, cand_v, mask, out, cs, st);
+        return launch_attention_bf16(s, pool, q, plan, n_cand, part, cand_k, cand_v, mask, out, st);
     return launch_attention_f32(s, pool, q, plan, n_cand, part, cand_k, cand_v, mask, out, st);
 }
 

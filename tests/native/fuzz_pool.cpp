@@ -22,7 +22,7 @@ hipError_t launch_read_rows(const Shape&, const void*, const int32_t*, int, void
 hipError_t launch_scatter_words(int32_t*, const int32_t*, int, hipStream_t) { std::abort(); }
 hipError_t launch_clear_words(int32_t*, int, hipStream_t) { std::abort(); }
 hipError_t launch_attention_partial(const Shape&, const void*, const void*, const PlanDev&, int, PartialBuf, const void*, const void*,
-                                    const uint8_t*, void*, ClassStreams&, hipStream_t) { std::abort(); }
+                                    const uint8_t*, void*, hipStream_t) { std::abort(); }
 hipError_t launch_prefill_bf16(const Shape&, const void*, const void*, const PrefillWg*, const int32_t*, int, void*, hipStream_t) { std::abort(); }
 hipError_t launch_attention_units_bf16(const Shape&, const void*, const void*, const PlanDev&, int, int, int, PartialBuf, hipStream_t) { std::abort(); }
 hipError_t launch_merge(const Shape&, const PlanDev&, PartialBuf, const void*, const void*, const void*, const uint8_t*, int, void*,

@@ -100,7 +100,7 @@ hipError_t launch_clear_words(int32_t* words, int n, hipStream_t) {
 }
 // Every cut unit's states and counters lie in memory of their own, and no unit is cut without room for them.
 hipError_t launch_attention_partial(const Shape& s, const void*, const void*, const PlanDev& plan, int, PartialBuf part, const void*, const void*,
-                                    const uint8_t*, void*, ClassStreams&, hipStream_t) {
+                                    const uint8_t*, void*, hipStream_t) {
     g_plan = plan;
     g_part = part;
     g_blocks.clear();
