@@ -105,8 +105,8 @@ struct Walk {
 // Memory to LDS without a register in between: the lane's 16 bytes at from + ofs go to LDS address lds + 16 lane; dma_half
 // brings the three KiB after that too.  Statements of their own rather than the builtin: the compiler takes that one for an
 // access that either counter may count, and then has every operand read from LDS wait for all others.  Whoever requests
-// waits for vmcnt(0) before anybody reads.  (M0 is used by nothing else here; the wait states cover a scalar register
-// that a vector instruction has just written.)
+// waits for vmcnt(0) before anybody reads.  (The wait states cover a scalar register that a vector instruction has just
+// written.)
 __device__ __forceinline__ void dma_piece(const char* from, uint32_t ofs, uint32_t lds) {
     asm volatile(
         "s_mov_b32 m0, %0\n\t"
@@ -114,7 +114,7 @@ __device__ __forceinline__ void dma_piece(const char* from, uint32_t ofs, uint32
         "global_load_lds_dwordx4 %1, %2"
         :
         : "s"(lds), "v"(ofs), "s"(from)
-        : "memory");
+        : "memory", "m0");
 }
 __device__ __forceinline__ void dma_half(const char* from, uint32_t ofs, uint32_t lds) {
     asm volatile(
@@ -126,7 +126,7 @@ __device__ __forceinline__ void dma_half(const char* from, uint32_t ofs, uint32_
         "global_load_lds_dwordx4 %1, %2 offset:3072"
         :
         : "s"(lds), "v"(ofs), "s"(from)
-        : "memory");
+        : "memory", "m0");
 }
 
 // Runs the walk; leaves the lane's share of O^T (dims 32 jj + 16 (j % 2) + 8 (j / 2) + 4 h + i of row n in

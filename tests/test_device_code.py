@@ -48,3 +48,15 @@ def test_kernels_of_both_classes_load_as_those_of_one_do(kernels, f8, split, inl
 
 def test_no_kernel_needs_scratch(kernels):
     assert len(kernels) == 18 and all(scratch == 0 for _, scratch in kernels.values()), kernels
+
+
+def test_statements_say_that_they_write_m0():
+    """Inline assembly that sets M0 names it among what it overwrites: the compiler may keep a value of its own there."""
+    csrc = os.path.join(ROOT, "paper_2401_06761_amd", "csrc")
+    setting = 0
+    for name in sorted(os.listdir(csrc)):
+        for body in re.findall(r"\basm(?:\s+volatile)?\s*\((.*?)\);", open(os.path.join(csrc, name)).read(), re.S):
+            if re.search(r"\bs_mov_b32 m0\b", body):
+                setting += 1
+                assert '"m0"' in body.rsplit(":", 1)[1], (name, body)
+    assert setting >= 2
