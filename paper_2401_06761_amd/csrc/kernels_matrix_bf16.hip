@@ -220,11 +220,13 @@ __device__ __forceinline__ void walk_blocks(const Walk& wk, char* lds, f32x16 (&
             u32x4 x[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) x[r] = *reinterpret_cast<const u32x4*>(dst + r * 1024 + ln * 16);
+            asm volatile("" ::: "memory");  // (lanes read and write each other's pieces)
 #pragma unroll
             for (int r = 0; r < 4; ++r) *reinterpret_cast<u32x4*>(dst + bf16_k_offset(4 * r + (ln >> 4), 8 * (ln & 15))) = x[r];
             dst += kHalf;
 #pragma unroll
             for (int r = 0; r < 4; ++r) x[r] = *reinterpret_cast<const u32x4*>(dst + r * 1024 + ln * 16);
+            asm volatile("" ::: "memory");  // (lanes read and write each other's pieces)
             // V: lanes c, 16 + c, 32 + c, 48 + c hold four slots of the same eight dims and swap words until each has all four
             // slots of two dims (thirty-two 2-byte stores per lane otherwise, eight lanes of each into the same bank)
             const int g4 = ln >> 4, c = ln & 15;
