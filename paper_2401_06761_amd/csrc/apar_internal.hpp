@@ -179,6 +179,8 @@ __device__ __forceinline__ void tables_unwritten(PlanDev& plan) {
 #elif defined(__HIP__)
 __device__ inline void plan_from_arguments(PlanDev&) {}
 __device__ inline void tables_unwritten(PlanDev&) {}
+template <class T>
+__device__ inline const T* unwritten(const T* p) { return p; }
 #endif
 
 struct PrefillWg {            // one workgroup of the bf16 prefill kernel: consecutive query tokens of one thread

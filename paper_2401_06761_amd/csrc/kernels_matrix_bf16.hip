@@ -472,7 +472,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     Walk wk;
     wk.head_base = pool + (int64_t)kvh * kTileBytes;
     wk.block_stride = (int64_t)n_kv * kTileBytes;
-    wk.table = &tiles[0].blk;
+    wk.table = unwritten(&tiles[0].blk);
     wk.table_stride = sizeof(TileRef) / sizeof(int32_t);
     wk.n_blk = n_blk;
     wk.len = (n_blk - 1) * 16 + last_fill;

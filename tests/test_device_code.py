@@ -1,5 +1,5 @@
-"""What the compiler makes of the row-tile kernels: those that run units of either row-tile class read a plan's tables and fp8 scales as the
-kernels of one class do, by scalar loads, and no 16-bit kernel needs scratch memory."""
+"""What the compiler makes of the 16-bit kernels: those that run units of either row-tile class read a plan's tables and fp8
+scales as the kernels of one class do, by scalar loads, and none needs scratch memory."""
 import os
 import re
 import subprocess
@@ -11,18 +11,17 @@ from paper_2401_06761_amd import build
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """Per kernel of kernels_attn_bf16.hip, (mangled template arguments, vector loads of one or two words, bytes of scratch)."""
+def _compiled(tmp_path_factory, source):
+    """Per kernel of a source, by its mangled name: vector loads of one or two words, bytes of scratch."""
     try:
         hipcc = build.hipcc()
     except RuntimeError:
         pytest.skip("no hipcc")
-    asm = str(tmp_path_factory.mktemp("asm") / "attn.s")
+    asm = str(tmp_path_factory.mktemp("asm") / "kernels.s")
     csrc = os.path.join(ROOT, "paper_2401_06761_amd", "csrc")
     done = subprocess.run([hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                            "-I" + os.path.join(ROOT, "include"), "-I" + csrc, "-x", "hip", "--cuda-device-only", "-S",
-                           os.path.join(csrc, "kernels_attn_bf16.hip"), "-o", asm], capture_output=True, text=True, timeout=300)
+                           os.path.join(csrc, source), "-o", asm], capture_output=True, text=True, timeout=300)
     assert done.returncode == 0, done.stderr[-3000:]
     text = open(asm).read()
     found = {}
@@ -31,6 +30,11 @@ def kernels(tmp_path_factory):
         scratch = re.search(rf"\.amdhsa_kernel {re.escape(name)}.*?private_segment_fixed_size (\d+)", text, re.S).group(1)
         found[name] = (len(re.findall(r"^\s+global_load_dword(?:x2)? ", body, re.M)), int(scratch))
     return found
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    return _compiled(tmp_path_factory, "kernels_attn_bf16.hip")
 
 
 def _one(kernels, pattern):
@@ -48,6 +52,13 @@ def test_kernels_of_both_classes_load_as_those_of_one_do(kernels, f8, split, inl
 
 def test_no_kernel_needs_scratch(kernels):
     assert len(kernels) == 18 and all(scratch == 0 for _, scratch in kernels.values()), kernels
+
+
+def test_matrix_kernels(tmp_path_factory):
+    found = _compiled(tmp_path_factory, "kernels_matrix_bf16.hip")
+    assert len(found) == 3 and all(scratch == 0 for _, scratch in found.values()), found
+    # a unit's workgroup reads its list of blocks by scalar loads: left are a lane's thread and the last block's fill count
+    assert _one(found, "attention_units_bf16")[0] <= 2
 
 
 def test_statements_say_that_they_write_m0():
