@@ -420,12 +420,6 @@ int run_append(apar_pool* p, const std::vector<int32_t>& codes, const std::vecto
     return APAR_OK;
 }
 
-bool same_params(const PlanParams& a, const PlanParams& b) {
-    return a.rows_per_thread == b.rows_per_thread && a.max_unit_tiles == b.max_unit_tiles && a.allow_direct == b.allow_direct &&
-           a.fuse == b.fuse && a.inline_shared == b.inline_shared && a.matrix_min_rows == b.matrix_min_rows &&
-           a.matrix_min_blocks == b.matrix_min_blocks;
-}
-
 // Which units of a decode plan are cut into slices (attn_split.hpp), and the launch's workgroups in order.  A unit's cost
 // is the tiles a wavefront of it walks.  With T = total cost / shares, but at least kSliceMinTiles, units of more than T
 // tiles become slices of about T; where no unit does, `out` stays empty and the launch has one workgroup per unit.
@@ -568,7 +562,7 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     // started from a copy of its parent's table as it was then or later, so "position by position the same
     // thread or one forked from it since" is all that has to hold for patch_plan to apply.
     bool carried = false;
-    if (p->plan_reuse && ph.reusable && (size_t)n == p->plan_ids.size() && same_params(prm, p->plan_prm)) {
+    if (p->plan_reuse && ph.reusable && (size_t)n == p->plan_ids.size() && prm == p->plan_prm) {
         bool same = true;
         for (int i = 0; i < n && same; ++i) {
             int32_t t = ids[i];

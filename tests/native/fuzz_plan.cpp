@@ -3,7 +3,8 @@
 // thread's table is its root path's blocks, refcounts count the live holders, internal nodes end on block
 // boundaries - are planned under random geometry and policy parameters; the plan is checked for coverage:
 // every row group of every listed thread must be shown exactly the blocks of its thread's table, once, and
-// every index in the plan must lie inside its array (the sanitizers watch the builder's own accesses).
+// every index in the plan must lie inside its array (the sanitizers watch the builder's own accesses), and every list says
+// how many of its tiles are full.
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -92,6 +93,7 @@ static int one(int seed) {
         prm.matrix_min_rows = mrows[rng() % 4];
         const int mblk[] = {1, 3, 128};
         prm.matrix_min_blocks = mblk[rng() % 3];
+        prm.open_cost = rnd(1, 3);
         CHECK(build_plan(views.data(), n, refcount.data(), seg_of.data(), prm, ph) == 0);
         for (int32_t x : seg_of) CHECK(x == -1);
         const int n_sl = (prm.rows_per_thread + 15) / 16;
@@ -117,6 +119,9 @@ static int one(int seed) {
                     for (int t = 0; t < wi.n_tiles; ++t) show(ph.tiles[wi.tile_ofs + t], wi.grp_lo, g, err);
                 }
                 CHECK(!err);
+                // a list's full tiles come first, and as many as the descriptor says
+                const int n_full = std::min(wg.n_full[k], wi.n_tiles);
+                for (int t = 0; t < wi.n_tiles; ++t) CHECK((((ph.tiles[wi.tile_ofs + t].meta >> 20) & 31) == 16) == (t < n_full));
             }
         }
         CHECK((int)ph.dfs_threads.size() == n);
@@ -143,8 +148,28 @@ static int one(int seed) {
     return 0;
 }
 
+// A plan built under other parameters is not carried over: every one of them counts.
+static int parameters(int seed) {
+    const PlanParams a{4, 512, true, true, true, 256, 128, 2};
+    CHECK(a == a);
+    for (int k = 0; k < 8; ++k) {
+        PlanParams b = a;
+        if (k == 0) b.rows_per_thread = 5;
+        if (k == 1) b.max_unit_tiles = 5;
+        if (k == 2) b.allow_direct = false;
+        if (k == 3) b.fuse = false;
+        if (k == 4) b.inline_shared = false;
+        if (k == 5) b.matrix_min_rows = 5;
+        if (k == 6) b.matrix_min_blocks = 5;
+        if (k == 7) b.open_cost = 3;
+        CHECK(!(a == b));
+    }
+    return 0;
+}
+
 int main(int argc, char** argv) {
     const int first = argc > 1 ? std::atoi(argv[1]) : 0, count = argc > 2 ? std::atoi(argv[2]) : 200;
+    if (parameters(-1)) return 1;
     for (int seed = first; seed < first + count; ++seed)
         if (one(seed)) return 1;
     std::printf("ok: %d forests\n", count);
