@@ -265,8 +265,8 @@ int acquire_stage(apar_pool* p, size_t bytes, StageSlot** out) {
 int upload(apar_pool* p, StageSlot* s, size_t bytes, hipStream_t st) {
     // Small tables go on the caller's stream, copied by a kernel: the hop to the copy stream and back costs more than it hides
     // when a step is a few launches long (a serving loop at a few hundred threads: 0.18 ms per step with the hop, 0.12
-    // without), and a copy by the runtime keeps the kernels behind it waiting (64 requests, 32 heads 234 -> 218 us per
-    // decode call; one thread family of 32 k tokens 54 -> 39; figures per size beside copy_words).
+    // without), and a copy by the runtime keeps the kernels behind it waiting (a new plan every call: 64 requests, 32
+    // heads 307 -> 295 us, one thread family of 32 k tokens 52 -> 41; figures per size beside copy_words).
     if (bytes < kCopyStreamMinBytes) {
         HIP_TRY(copy_staged(s->dev, s->host, bytes, st));
         return APAR_OK;
@@ -515,8 +515,10 @@ bool inline_plan(apar_pool* p, const PlanHost& ph) {
 // What an open tile costs a wavefront of the 16-bit kernel: its V half takes a turn through LDS and nothing is in flight
 // meanwhile (one request of five threads, 32 heads: 1.3 us per open tile, 0.6 per full one, 12.6 us for the wavefront that has
 // all five against 10.0 for the others).  On fp32 pools every tile is alike.
-// Counted as one, two and three: one request 15.0 / 13.5 / 13.7 us, 16 requests 58.5 / 54.8 / 54.7, 64 with 8 heads
-// 65.2 / 60.9 / 60.5, two requests 22.5 / 13.3 / 12.6 (whose wavefronts were long enough to be cut into slices).
+// Counted as one, two and three: one request 15.9 / 14.2 / 14.6 us, four requests 27.9 / 25.3 / 25.6, 64 with 8 heads
+// 65.5 / 61.1 / 60.9, two requests 22.4 / 13.3 / 12.7 (whose wavefronts were long enough to be cut into slices).  fp8 pools, whose full
+// tiles have to be widened and whose open ones have not: 15.5 / 14.8 / 13.4, 29.7 / 27.1 / 24.2, 48.0 / 44.8 / 42.9, 25.9 / 14.8 / 12.2, 64
+// requests with 32 heads 131 / 127 / 121 (there three is the better count still).
 constexpr int kOpenTileCost = 2;
 
 // fixed: the plan and the partial results go to the device's static workspace, nothing is allocated, no
@@ -775,19 +777,20 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
 
 // Whether a prefill call on a bf16 or fp8 pool goes to the 32x32 kernel by itself.  That kernel gives a workgroup up to 128
 // query rows (tokens x q heads of a kv group) of one thread; a row-tile workgroup with one row tile per wavefront holds 64.
-//  - Threads of more than 64 rows are faster there, the others on the row tiles: what decides is the rows that the
+//  - Threads of more than 64 rows are faster there, the others mostly on the row tiles: what decides is the rows that the
 //    workgroups of either kind walk, so that one long prompt does not take hundreds of short threads with it.
-//    Measured (us, row tiles / matrix kernel; 362 threads, walks around 400): bf16 group 2, 63 and 78 rows 206 / 219, 285 / 241;
-//    group 4, 64 and 80 rows 110 / 122, 166 / 130; group 16, 64 and 80 rows 50 / 55, 64 / 57; fp8 pools group 1, 59 and 69 rows
-//    338 / 436, 494 / 451, group 4, 64 and 80 rows 101 / 128, 169 / 135; walks around 1050, group 4: bf16 218 / 225, 317 / 249,
-//    fp8 189 / 252, 318 / 264.
-//    360 threads of one row and walks of 300 beside a prompt of 2000, group 8: bf16 124 / 93, fp8 130 / 101; walks of 900
-//    beside it: group 4 188 / 205, group 1 439 / 620.  (fp8 pools, group 8 or more, 112 to 128 rows per thread: 2 to 7 % slower.)
+//    Measured (us, row tiles / matrix kernel; 362 threads, six to a shared prefix, walks around 400): bf16 group 2, 62 and 78 rows
+//    164 / 184, 258 / 202; group 4, 64 and 80 rows 90 / 94, 134 / 99; fp8 pools group 1, 59 and 69 rows 305 / 345, 477 / 375, group 4,
+//    64 and 80 rows 88 / 98, 137 / 103, group 8, 112 rows 82 / 66; walks around 1050, group 4: bf16 181 / 184, 282 / 203, fp8
+//    170 / 184, 277 / 204.  360 threads of one row and walks of 300 beside a prompt of 2000, group 8: bf16 88 / 71, fp8 91 / 75.
+//    Where the line lies on the slower side: group 16, 64 rows 48 / 36; fp8 group 8, 48 rows 124 / 110; one row and walks of 900
+//    beside a prompt of 2000, group 4 179 / 154, group 1 556 / 477; 8 to 40 requests of 48 rows, group 4, by 6 to 9 %.
 //  - bf16 pools: from 32 rows per workgroup on, a large call (kMatrixPrefillWalked rows walked by all its workgroups, kv
-//    heads counted) is faster there all the same: group 1, 48 rows, 362 threads of walks around 400, 700, 1050 (4.6, 8, 12 M)
-//    410 / 390, 670 / 560, 1015 / 773; group 4, 48 rows, 891 threads (2.9, 5, 7.5 M) 233 / 266, 377 / 371, 573 / 488;
-//    and calls whose query tokens attend to kMatrixPrefillMeanWalk rows on average go there (group 1, one token each, 360 threads,
-//    around 1000 rows: 904 / 656).  fp8 pools: neither (362 threads, group 4, around 1050 rows, 32 and 64 rows 189 / 226, 189 / 252).
+//    heads counted) goes there all the same, which is even or a little faster: group 1, 48 rows, 362 threads of walks around 400,
+//    700, 1050 (4.6, 8, 12 M) 325 / 343, 492 / 484, 693 / 672; group 4, 48 rows, 891 threads (2.9, 5, 7.5 M) 197 / 218, 307 / 320,
+//    440 / 437, group 1, 891 threads, walks around 700 1224 / 1172; and calls whose query tokens attend to kMatrixPrefillMeanWalk rows
+//    on average go there (group 1, one token each, 362 threads, around 1100 rows: 499 / 523 where six share a prefix, 1080 / 1077 where
+//    nobody does).  fp8 pools: neither (362 threads, group 4, around 1050 rows, 32 and 64 rows 170 / 156, 170 / 184).
 constexpr int64_t kMatrixPrefillRows = 64, kMatrixPrefillMinRows = 32;
 constexpr int64_t kMatrixPrefillWalked = 4500000;
 constexpr int64_t kMatrixPrefillMeanWalk = 1024;

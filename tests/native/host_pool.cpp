@@ -289,20 +289,21 @@ static void partials() {
     }
 }
 
-// Which kernel a prefill call goes to by itself: the faster one of calls that were measured on both.
+// Which kernel a prefill call goes to by itself, on either side of the rule's lines (us on the row tiles / the matrix kernel, where
+// six threads share a prefix).
 static void prefill() {
     struct Call { int dtype, n_q, n_kv, threads, len, m, long_m, kernel; };  // long_m: one prompt of that many tokens besides
     const int T = APAR_PREFILL_ROW_TILES, M = APAR_PREFILL_MATRIX;
     const Call calls[] = {
-        {APAR_BF16_FP8KV, 32, 32, 362, 380, 48, 0, T},  {APAR_BF16_FP8KV, 32, 32, 362, 380, 90, 0, M},  // 318 / 433, 507 / 479 us
-        {APAR_BF16_FP8KV, 32, 4, 891, 380, 6, 0, T},    {APAR_BF16_FP8KV, 32, 4, 891, 380, 10, 0, M},   // 110 / 152, 167 / 163
-        {APAR_BF16_FP8KV, 32, 8, 362, 1100, 16, 0, T},  {APAR_BF16_FP8KV, 32, 8, 362, 1100, 20, 0, M},  // 189 / 252, 318 / 264
-        {APAR_BF16, 32, 8, 362, 300, 16, 0, T},         {APAR_BF16, 32, 8, 362, 300, 24, 0, M},         // 95 / 105, 150 / 113
-        {APAR_BF16, 32, 16, 179, 700, 24, 0, T},        {APAR_BF16, 32, 16, 179, 700, 40, 0, M},        // 150 / 163, 223 / 180
-        {APAR_BF16, 32, 32, 179, 380, 48, 0, T},        {APAR_BF16, 32, 32, 891, 700, 48, 0, M},        // 196 / 204, 1836 / 1351
-        {APAR_BF16, 32, 32, 362, 300, 1, 0, T},         {APAR_BF16, 32, 32, 362, 1100, 1, 0, M},        // 254 / 282, 793 / 614
-        {APAR_BF16, 32, 32, 360, 901, 1, 2000, T},      {APAR_BF16, 32, 4, 360, 301, 1, 2000, M},       // 439 / 620, 124 / 93
-        {APAR_BF16_FP8KV, 32, 4, 360, 301, 1, 2000, M}, {APAR_BF16, 32, 8, 360, 901, 1, 2000, T},       // 130 / 101, 188 / 205
+        {APAR_BF16_FP8KV, 32, 32, 362, 380, 48, 0, T},  {APAR_BF16_FP8KV, 32, 32, 362, 380, 90, 0, M},  // 301 / 325, 503 / 365
+        {APAR_BF16_FP8KV, 32, 4, 891, 380, 6, 0, T},    {APAR_BF16_FP8KV, 32, 4, 891, 380, 10, 0, M},   // 124 / 110, 169 / 124
+        {APAR_BF16_FP8KV, 32, 8, 362, 1100, 16, 0, T},  {APAR_BF16_FP8KV, 32, 8, 362, 1100, 20, 0, M},  // 183 / 197, 290 / 215
+        {APAR_BF16, 32, 8, 362, 300, 16, 0, T},         {APAR_BF16, 32, 8, 362, 300, 24, 0, M},         // 76 / 79, 115 / 84
+        {APAR_BF16, 32, 16, 179, 700, 24, 0, T},        {APAR_BF16, 32, 16, 179, 700, 40, 0, M},        // 121 / 123, 197 / 142
+        {APAR_BF16, 32, 32, 179, 380, 48, 0, T},        {APAR_BF16, 32, 32, 891, 700, 48, 0, M},        // 151 / 160, 1224 / 1172
+        {APAR_BF16, 32, 32, 362, 300, 1, 0, T},         {APAR_BF16, 32, 32, 362, 1100, 1, 0, M},        // 166 / 215, 499 / 523
+        {APAR_BF16, 32, 32, 360, 901, 1, 2000, T},      {APAR_BF16, 32, 4, 360, 301, 1, 2000, M},       // 556 / 477, 89 / 71
+        {APAR_BF16_FP8KV, 32, 4, 360, 301, 1, 2000, M}, {APAR_BF16, 32, 8, 360, 901, 1, 2000, T},       // 91 / 75, 179 / 154
     };
     for (const Call& c : calls) {
         apar_pool* p;
