@@ -558,3 +558,17 @@ def test_empty_calls_are_no_ops_and_gather_checks_its_arguments():
             ap.apar_append_kv_gather(h, [99], [0], None, None)
         assert e.value.status == -2
         assert ap.apar_thread_len(h, t) == 5
+
+
+@pytest.mark.parametrize("kind", ["list", "tuple", "int32", "read-only", "int64", "strided"])
+def test_thread_ids_are_taken_from_any_sequence(kind):
+    with ap.Pool(4, 2, 64, "f32", 8, dry_run=True) as pool:
+        h = pool.handle
+        ids = [ap.apar_thread_create(h) for _ in range(4)]
+        seq = {"list": ids[1:3], "tuple": tuple(ids[1:3]), "int32": np.array(ids[1:3], np.int32), "int64": np.array(ids[1:3], np.int64),
+               "read-only": np.frombuffer(np.array(ids[1:3], np.int32).tobytes(), np.int32), "strided": np.array(ids, np.int32)[1::2][:2]}[kind]
+        kept = [int(t) for t in seq]
+        ap.apar_append_kv_batch(h, seq, None, None)
+        assert [int(t) for t in seq] == kept and [ap.apar_thread_len(h, t) for t in ids] == [1 if t in kept else 0 for t in ids]
+        with pytest.raises(ValueError):
+            ap.apar_append_kv_batch(h, np.zeros((2, 1), np.int32), None, None)
