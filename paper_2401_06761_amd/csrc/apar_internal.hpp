@@ -137,6 +137,7 @@ struct PlanDev {              // device pointers of one staged plan
     int32_t n_wg_class[3];       // matrix units, workgroups with 2 and with 1 row tiles per wavefront, stored in that order
     int32_t n_threads;
     int32_t rows_per_thread, rows_per_slice, n_slices;
+    int32_t few;                 // 16-bit pools: the units go to the kernel for few workgroups
     SplitPlan split;
     const int32_t* inline_words; // small plans: the tables on the host, to go along with the kernel's arguments; every table
     int32_t n_inline_words;      // pointer above (split.blocks, always there then, included) is its offset in bytes
@@ -270,6 +271,8 @@ hipError_t launch_attention_partial(const Shape& s, const void* pool, const void
 hipError_t launch_attention_bf16(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand,
                                  PartialBuf part, const void* cand_k, const void* cand_v, const uint8_t* mask,
                                  void* out, hipStream_t st);
+hipError_t launch_attention_few_bf16(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand, PartialBuf part,
+                                     const void* cand_k, const void* cand_v, const uint8_t* mask, void* out, hipStream_t st);
 hipError_t launch_attention_f32(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand,
                                 PartialBuf part, const void* cand_k, const void* cand_v, const uint8_t* mask, void* out,
                                 hipStream_t st);

@@ -105,6 +105,7 @@ struct apar_pool {
     int64_t plan_copies_then = 0;  // copy-on-write copies the pool had made by then
     bool plan_reuse = true;
     int64_t n_plans_built = 0, n_plans_carried = 0;
+    bool few_units = false;            // the plan's units go to the kernel for few workgroups
     int32_t plan_geom[3] = {1, 1, 1};  // rows per thread, rows per slice, slices of the last plan
 
     StageSlot stage[kStageSlots];
@@ -420,6 +421,24 @@ int run_append(apar_pool* p, const std::vector<int32_t>& codes, const std::vecto
     return APAR_OK;
 }
 
+// Calls of few workgroups on 16-bit pools: units without shared lists, one row tile per wavefront, no more workgroups than compute
+// units (uncut).  They go to a kernel of their own (attend_few) whose wavefronts have a SIMD each, and the planner prefers such
+// units (PlanParams::few_units).  Measured, us per call (start of this change / general plan and that kernel / units of 16 rows and
+// that kernel / with the slices below): one request of 5 threads, group 4 14.4 / 13.9 / 9.6 / 8.2, group 1 11.7 / 9.8 / 9.8 / 8.4, two fork levels,
+// group 4 17.4 / 16.9 / 12.4 / 9.0; four requests, group 4 19.1 / 18.5 / 15.7 / 11.7, group 1 21.4 / 18.8 / 18.7 / 17.9; 16 requests,
+// group 4 28.5 / 28.0 / 24.7 / 24.6, of 2 k tokens on fp8 44.0 / 40.0 / 29.2 / 29.1.
+// A tree of more rows than a unit holds is read by several units, from L2 at best.  General plan / units of 16 rows, by the MiB
+// that are read again (group 8, and 4 where said): 62 (one request of 4 k) 20.3 / 15.3, 97 22.9 / 15.6, 91 (group 4) 30.2 / 28.9, 130 32.7 / 29.9,
+// 135 24.1 / 21.8, 153 (group 4) 43.0 / 45.8, 167 32.0 / 31.9, 208 29.5 / 32.3, 351 52.0 / 81.7.
+constexpr int64_t kFewAgainBytes = (int64_t)144 << 20;
+constexpr int32_t kFewWorkgroups = 256;
+bool few_units(const PlanHost& ph, const Shape& s) {
+    if (s.dtype != APAR_BF16 || ph.n_wg_class[0] > 0 || ph.n_wg_class[1] > 0 || ph.wgs.size() * s.n_kv > (size_t)kFewWorkgroups) return false;
+    for (const WgDesc& wg : ph.wgs)
+        if (wg.n_coop > 0) return false;
+    return true;
+}
+
 // Which units of a decode plan are cut into slices (attn_split.hpp), and the launch's workgroups in order.  A unit's cost
 // is the tiles a wavefront of it walks.  With T = total cost / shares, but at least kSliceMinTiles, units of more than T
 // tiles become slices of about T; where no unit does, `out` stays empty and the launch has one workgroup per unit.
@@ -435,9 +454,15 @@ int run_append(apar_pool* p, const std::vector<int32_t>& codes, const std::vecto
 // at a time: a pass over the units each, nothing is built) or nothing is worth cutting any more.
 constexpr int kSliceShares = 256, kSliceSharesF32 = 512;
 constexpr int kSliceMinTiles = 6, kSliceMinGain = 16;
+// Calls of few workgroups: shorter slices pay, since every wavefront folds a quarter of them, but only as long as there are no
+// more workgroups than compute units (two on one share its 50 bytes per cycle).  Shares / least tiles / least gain, us per call:
+//   256 / 6 / 16, 128 / 4 / 5, 192 / 4 / 5, 224 / 4 / 5: one request of 5 threads, 32 heads 9.7, 8.7, 8.4, 8.6, 8 heads 9.7, 8.6, 8.2, 8.5; two
+//   requests 14.1, 12.1, 10.8, 11.0; four 18.7, 15.1, 17.8, 20.4; eight, 8 heads 19.4, 17.0, 16.3, 21.0; 32 k tokens, 8 heads 34.3, 32.4, 31.7,
+//   32.8; three requests of 7 k to 11 k 116, 87, 90, 115; eight of 4 k on fp8, 8 heads 28.9, 28.4, 26.0, 29.4.
+constexpr int kFewShares = 192, kFewMinTiles = 4, kFewMinGain = 5;
 // (a unit that is cut costs more than T >= total * n_kv / shares, so cut units x kv heads stay below the shares)
-static_assert(kSliceShares <= kSplitMaxCut && kSliceSharesF32 <= kSplitMaxCut, "a counter per cut unit, kv head and wavefront");
-void cut_into_slices(const PlanHost& ph, const Shape& s, size_t state_bytes, std::vector<SplitBlock>& out, int32_t (&n_class)[3]) {
+static_assert(kSliceShares <= kSplitMaxCut && kSliceSharesF32 <= kSplitMaxCut && kFewWorkgroups <= kSplitMaxCut, "a counter per cut unit, kv head and wavefront");
+void cut_into_slices(const PlanHost& ph, const Shape& s, bool few, size_t state_bytes, std::vector<SplitBlock>& out, int32_t (&n_class)[3]) {
     out.clear();
     n_class[0] = n_class[1] = n_class[2] = 0;
     if (state_bytes == 0) return;
@@ -454,16 +479,19 @@ void cut_into_slices(const PlanHost& ph, const Shape& s, size_t state_bytes, std
         total += c;
         longest = std::max(longest, c);
     }
-    const int64_t shares = s.dtype == APAR_F32 ? kSliceSharesF32 : kSliceShares;
-    int64_t tiles = std::max<int64_t>(kSliceMinTiles, (total * s.n_kv + shares - 1) / shares);
+    const int64_t shares = s.dtype == APAR_F32 ? kSliceSharesF32 : few ? kFewShares : kSliceShares;
+    int64_t tiles = std::max<int64_t>(few ? kFewMinTiles : kSliceMinTiles, (total * s.n_kv + shares - 1) / shares);
     auto slices_of = [&](size_t k) { return k < first ? 1 : (int)std::min<int64_t>(64, (cost(ph.wgs[k]) + tiles - 1) / tiles); };
     const int64_t room = (int64_t)state_bytes / (s.n_kv * (int64_t)(s.d / 4 + 2) * 64 * (int64_t)sizeof(float));
     for (;; tiles += (tiles + 3) / 4) {
-        if (longest <= tiles + kSliceMinGain) return;
-        int64_t state = 0;
-        for (size_t k = first; k < ph.wgs.size(); ++k)
-            if (const int n = slices_of(k); n > 1) state += (int64_t)n * state_of(ph.wgs[k]);
-        if (state <= room) break;
+        if (longest <= tiles + (few ? kFewMinGain : kSliceMinGain)) return;
+        int64_t state = 0, blocks = 0;
+        for (size_t k = first; k < ph.wgs.size(); ++k) {
+            const int n = slices_of(k);
+            blocks += n;
+            if (n > 1) state += (int64_t)n * state_of(ph.wgs[k]);
+        }
+        if (state <= room && (!few || blocks * s.n_kv <= kFewWorkgroups)) break;
     }
     n_class[0] = (int32_t)first;
     int32_t state = 0, n_cut = 0;
@@ -558,6 +586,9 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     prm.matrix_min_blocks = p->matrix_min_blocks;
     prm.inline_shared = p->inline_shared;
     prm.open_cost = p->shape.dtype == APAR_F32 ? 1 : kOpenTileCost;
+    prm.few_units = p->shape.dtype == APAR_BF16 ? kFewWorkgroups / p->shape.n_kv : 0;
+    prm.few_again = (int32_t)(kFewAgainBytes / (p->shape.n_kv * (p->shape.fp8_sealed ? 4096 : 8192)));
+    prm.few_open_cost = p->shape.fp8_sealed ? 2 : 1;  // (twice the bytes of a full one)
     // Decode calls of a loop list the same threads step after step - each a few rows longer, a few replaced
     // by a thread forked from them - and the plan of the previous call then only needs its tails brought up
     // to date.  A table never changes before its last block, and a thread forked since the previous call
@@ -607,7 +638,10 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     DeviceGuard guard(p->device);
     hipStream_t st = (hipStream_t)stream;
 
-    if (!carried) cut_into_slices(ph, p->shape, p->split_bytes, p->split_blocks, p->n_split_class);  // (a carried plan keeps its cut)
+    if (!carried) {  // (a carried plan keeps its cut)
+        p->few_units = few_units(ph, p->shape);
+        cut_into_slices(ph, p->shape, p->few_units, p->split_bytes, p->split_blocks, p->n_split_class);
+    }
     // stage the tables in one copy
     size_t ofs[7];
     ofs[0] = 0;
@@ -726,6 +760,8 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     }
     pd.split.arrived = (int32_t*)p->split_dev;  // (no room: nothing is cut and nothing reads either)
     pd.split.state = p->split_dev ? (float*)(p->split_dev + kSplitCounterBytes) : nullptr;
+
+    pd.few = p->few_units;
 
     if (inlined) {
         pd.wgs = (const WgDesc*)p->inline_ofs[0];

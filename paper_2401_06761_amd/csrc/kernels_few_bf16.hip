@@ -1,0 +1,328 @@
+// Decode attention over bf16 KV tiles: launches of few workgroups.
+//
+// Units without shared lists, one row tile, no more workgroups than the chip has compute units (PlanDev::few): what a call takes
+// is one wavefront's chain of latencies, and every wavefront has a SIMD's registers to itself.  What the chain was made of (one
+// request of five threads, 32 heads, cycles of 26 k): descriptor and queries 3.5 k, a tile 1180 with one in flight, an open tile
+// 1600 (its K gathered sixteen bytes a row), fold by one wavefront and output 4.5 k.  So here two tiles (three of fp8 codes) are
+// on their way at any time, open tiles among them: every tile is fetched the same way, KiB by KiB, and an open one's rows are
+// put into operand order through LDS.  The four wavefronts of a divided list fold and write a quarter of the dims each.
+// One compute unit takes 50 bytes per cycle however many loads are on their way: 640 cycles per tile and wavefront.
+#include <hip/hip_runtime.h>
+
+#include <cstring>
+#include <type_traits>
+
+#include "attn_bf16.hpp"
+
+namespace apar {
+
+namespace {
+
+struct FewLds {
+    static constexpr int kStates = 4 * kOpenScratch;  // (apart from the scratch: nobody waits before leaving a state)
+    static constexpr int kBytes = kStates + 4 * kSplitState;
+};
+
+struct FewWalk {
+    const char* head_base;
+    int64_t block_stride;
+    float scale_log2e;
+    int my_j;       // row group of this lane's row, or 0x7fff
+    char* scratch;  // kOpenScratch bytes of LDS
+    int lane;
+};
+
+// A tile on its way: its rows or operand pieces (CODES: the codes of a full fp8 tile).
+template <bool CODES>
+struct FewTile {
+    Frag k[4], v[4];
+    u32x4 k8[CODES ? 2 : 1], v8[CODES ? 2 : 1];
+    float ks, vs;
+    int meta;
+
+    __device__ __forceinline__ void fetch_k(const FewWalk& w, const char* tile, int rows) {
+        if constexpr (CODES) {
+#pragma unroll
+            for (int r = 0; r < 2; ++r) k8[r] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(tile + w.lane * 16 + r * 1024));
+            ks = scale_at(tile + kFp8ScaleOfs);
+        } else {
+            fetch_half(w, tile, rows, k);
+        }
+    }
+    __device__ __forceinline__ void fetch_v(const FewWalk& w, const char* tile, int rows) {
+        if constexpr (CODES) {
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+                v8[r] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(tile + kFp8HalfBytes + w.lane * 16 + r * 1024));
+            vs = scale_at(tile + kFp8ScaleOfs + 4);
+        } else {
+            fetch_half(w, tile + 4096, rows, v);
+        }
+    }
+    // The half's KiB r: the operands' piece r of a full tile, token rows 4r .. 4r + 3 of an open one (rows that are not filled: row 0).
+    __device__ __forceinline__ static void fetch_half(const FewWalk& w, const char* half, int rows, Frag (&f)[4]) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t at = 4 * r + (w.lane >> 4) < rows ? r * 1024 + w.lane * 16 : (w.lane & 15) * 16;
+            f[r].u = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(half + at));
+        }
+    }
+    __device__ __forceinline__ static void rows_to_lds(const FewWalk& w, const Frag (&f)[4]) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) *reinterpret_cast<u32x4*>(w.scratch + (4 * r + (w.lane >> 4)) * kOpenRowStride + (w.lane & 15) * 16) = f[r].u;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    // Takes the tile; meanwhile the next one for these registers, `rows` rows of it, is fetched (rows = 1: there is none, and a row of
+    // the list's last tile comes instead, so that no load lies behind a branch).
+    template <bool MORE>
+    __device__ __forceinline__ void take(const FewWalk& w, RowState& st, const char* next, int next_meta, int rows) {
+        const int g4 = w.lane >> 4, c = w.lane & 15;
+        const int lo = meta & 1023, hi = (meta >> 10) & 1023, valid = (meta >> 20) & 31;
+        const bool causal = meta >> 30, open = !CODES && valid < kBlockTokens;
+        if constexpr (CODES) {
+            fp8_operands(k8, ks, k);
+        } else if (open) {
+            rows_to_lds(w, k);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) k[r].u = *reinterpret_cast<const u32x4*>(w.scratch + c * kOpenRowStride + g4 * 64 + r * 16);
+            __builtin_amdgcn_wave_barrier();
+        }
+        f32x4 s = products(k, st);
+        if constexpr (MORE) fetch_k(w, next, rows);
+        if (open || causal) {
+            const int first = (meta >> 25) & 31;
+            const int limit = causal ? min(valid, max(0, first + w.my_j - lo)) : valid;
+            mask_tokens(s, (1u << limit) - 1u, g4);
+        }
+        const bool in_range = w.my_j >= lo && w.my_j < hi;
+        move_reference(st, s, in_range, w.scale_log2e);
+        if constexpr (CODES) {
+            fp8_operands(v8, vs, v);
+        } else if (open) {
+            rows_to_lds(w, v);
+            v_operands_from_rows(w.scratch, kOpenRowStride, g4, c, v);
+            __builtin_amdgcn_wave_barrier();
+        }
+        weigh_values(v, st, s, in_range, w.scale_log2e);
+        if constexpr (MORE) fetch_v(w, next, rows);
+        meta = next_meta;
+    }
+};
+
+template <bool CODES>
+struct FewList {
+    static constexpr int kSets = CODES ? 3 : 2;
+    FewTile<CODES> set[kSets];
+    const TileRef* list;
+    int n;
+
+    __device__ __forceinline__ void start(const FewWalk& w) {
+        if (n <= 0) return;
+        TileRef ref[kSets];
+#pragma unroll
+        for (int i = 0; i < kSets; ++i) ref[i] = list[min(i, n - 1)];
+#pragma unroll
+        for (int i = 0; i < kSets; ++i) {
+            const char* tile = w.head_base + ref[i].blk * w.block_stride;
+            const int rows = i < n ? (ref[i].meta >> 20) & 31 : 1;
+            set[i].meta = ref[i].meta;
+            __builtin_amdgcn_sched_barrier(0);  // in this order, which the loop keeps
+            set[i].fetch_k(w, tile, rows);
+            __builtin_amdgcn_sched_barrier(0);
+            set[i].fetch_v(w, tile, rows);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __device__ __forceinline__ void walk(const FewWalk& w, RowState& st) {
+        if (n <= 0) return;
+        int t = 0;
+        for (; t + kSets <= n; t += kSets) {
+#pragma unroll
+            for (int i = 0; i < kSets; ++i) {
+                const TileRef ref = list[min(t + kSets + i, n - 1)];
+                set[i].template take<true>(w, st, w.head_base + ref.blk * w.block_stride, ref.meta, t + kSets + i < n ? (ref.meta >> 20) & 31 : 1);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i + 1 < kSets; ++i)
+            if (t + i < n) set[i].template take<false>(w, st, nullptr, 0, 0);
+    }
+};
+
+template <bool F8, bool SPLIT>
+__device__ __forceinline__ void attend_few(char* lds, const Slice& slice, const char* __restrict__ pool, const uint16_t* __restrict__ q,
+                                           const PlanDev& plan, int n_cand, int n_q, int n_kv, int group, float scale_log2e,
+                                           const PartialBuf& part, const uint16_t* __restrict__ cand_k, const uint16_t* __restrict__ cand_v,
+                                           const uint8_t* __restrict__ cand_mask, uint16_t* __restrict__ out) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int g4 = lane >> 4, c = lane & 15;
+    const int kvh = blockIdx.x % n_kv;
+    const WgDesc* wg = plan.wgs + slice.wg;
+    WaveItem wi = wg->w[wave];
+    int own_full = min(wg->n_full[wave], wi.n_tiles);
+    if constexpr (SPLIT) cut_list(slice, wi.tile_ofs, wi.n_tiles, own_full);
+    if (wi.n_grp == 0) return;  // (never one of the four wavefronts of a divided list)
+    const TileRef* mine = plan.tiles + wi.tile_ofs;
+
+    // column c is row `within` of the wavefront's row group c / rps
+    const int rps = plan.rows_per_slice, n_sl = plan.n_slices;
+    const int jc = c / rps, within = c - jc * rps;
+    const int grp = wi.grp_lo + jc, rank = grp / n_sl, rr = (grp - rank * n_sl) * rps + within;
+    const bool ok = jc < 16 / rps && jc < wi.n_grp && rr < plan.rows_per_thread;
+    const int listed = ok ? (plan.dfs_threads ? plan.dfs_threads[rank] : rank) : 0;
+    const int cc = ok ? rr / group : 0, hq = kvh * group + (ok ? rr - cc * group : 0);
+    const int64_t qrow = ((int64_t)listed * n_cand + cc) * n_q + hq;
+    RowState st[1];
+    st[0].m = -INFINITY;
+    st[0].l = 0.0f;
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj) st[0].o[jj] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    {
+        const u32x4* qp = reinterpret_cast<const u32x4*>(q + qrow * 128 + g4 * 32);
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) st[0].q[kk].u = qp[kk];  // (a column without a row: some row's queries, for no tile)
+    }
+    char* scratch = lds + wave * kOpenScratch;
+    const FewWalk walk{pool + (int64_t)kvh * kTileBytes, (int64_t)n_kv * kTileBytes, scale_log2e, ok ? jc : 0x7fff, scratch, lane};
+    if constexpr (F8) {  // full tiles are codes, open ones rows
+        FewList<true> codes;
+        FewList<false> rows;
+        codes.list = mine, codes.n = own_full;
+        rows.list = mine + own_full, rows.n = wi.n_tiles - own_full;
+        codes.start(walk);
+        rows.start(walk);
+        codes.walk(walk, st[0]);
+        rows.walk(walk, st[0]);
+    } else {
+        FewList<false> tiles;
+        tiles.list = mine, tiles.n = wi.n_tiles;
+        tiles.start(walk);
+        tiles.walk(walk, st[0]);
+    }
+    const bool divided = wi.flags & kWaveSplit;
+    if ((wi.flags & kWaveDirect) && cand_mask != nullptr && (!SPLIT || slice.s == 0) && (!divided || wave == 0))
+        attend_candidates<1>(st, scratch, plan, wi, cand_k, cand_v, cand_mask, {walk.my_j}, within, n_cand, n_kv, kvh, group, scale_log2e);
+
+    auto write = [&](auto quads, int j0, float l_all) {  // quads j0 .. of the lane's row
+        constexpr int J = decltype(quads)::value;
+        if (!ok) return;
+        if (wi.flags & kWaveDirect) {
+            const float inv = 1.0f / l_all;
+            uint16_t* dst = out + qrow * 128 + 4 * g4;
+#pragma unroll
+            for (int jj = 0; jj < J; ++jj) {
+                u32x2 pk;
+                pk.x = pack_bf16_pair(st[0].o[jj][0] * inv, st[0].o[jj][1] * inv);
+                pk.y = pack_bf16_pair(st[0].o[jj][2] * inv, st[0].o[jj][3] * inv);
+                *reinterpret_cast<u32x2*>(dst + 16 * (j0 + jj)) = pk;
+            }
+        } else {
+            const int64_t slot = ((int64_t)(wi.part_base + rank - wi.grp_lo / n_sl) * n_cand + cc) * n_q + hq;
+#pragma unroll
+            for (int jj = 0; jj < J; ++jj) *reinterpret_cast<f32x4*>(part.o + slot * 128 + 4 * g4 + 16 * (j0 + jj)) = st[0].o[jj];
+            if (g4 == 0 && j0 == 0) {
+                part.ml[slot * 2] = st[0].m;
+                part.ml[slot * 2 + 1] = l_all;
+            }
+        }
+    };
+    auto sum_of_row = [&](float l) {
+        l += __shfl_xor(l, 16, 64);
+        return l + __shfl_xor(l, 32, 64);
+    };
+    if (!divided) {
+        if constexpr (SPLIT)
+            if (!fold_slices<1, 8>(plan.split, slice, n_kv, kvh, wave, 4, lane, st)) return;
+        write(std::integral_constant<int, 8>{}, 0, sum_of_row(st[0].l));
+        return;
+    }
+    // the four wavefronts hold the same rows over different tiles: every one folds two of the eight accumulator quads
+    char* states = lds + FewLds::kStates;
+    {
+        char* to = states + wave * kSplitState;
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) *reinterpret_cast<f32x4*>(to + (jj * 64 + lane) * 16) = st[0].o[jj];
+        *reinterpret_cast<f32x2*>(to + 8 * 1024 + lane * 8) = f32x2{st[0].m, st[0].l};
+    }
+    // (not __syncthreads: it would wait for the rows fetched past the lists' ends)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const int j0 = 2 * wave;
+    f32x2 ml[4];
+    f32x4 o[4][2];
+#pragma unroll
+    for (int w2 = 0; w2 < 4; ++w2) {
+        const char* from = states + w2 * kSplitState;
+        ml[w2] = *reinterpret_cast<const f32x2*>(from + 8 * 1024 + lane * 8);
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) o[w2][jj] = *reinterpret_cast<const f32x4*>(from + ((j0 + jj) * 64 + lane) * 16);
+    }
+    const float mx = fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x));
+    st[0].m = mx;
+    st[0].l = 0.0f;
+#pragma unroll
+    for (int jj = 0; jj < 2; ++jj) st[0].o[jj] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int w2 = 0; w2 < 4; ++w2) {
+        // a wavefront that saw no tile of a row left m = -inf and sums of zero for it
+        const float a = ml[w2].x == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(ml[w2].x - mx);
+        st[0].l += a * ml[w2].y;
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) st[0].o[jj] += a * o[w2][jj];
+    }
+    if constexpr (SPLIT)
+        if (!fold_slices<1, 2, 8>(plan.split, slice, n_kv, kvh, wave, 1, lane, st, j0)) return;
+    write(std::integral_constant<int, 2>{}, j0, sum_of_row(st[0].l));
+}
+
+// Launches of few workgroups (attend_few): one wavefront per SIMD.
+template <bool F8, bool SPLIT, bool INLINE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attention_bf16_few(
+    PlanWords<INLINE>, const char* __restrict__ pool, const uint16_t* __restrict__ q, PlanDev plan, int n_cand, int n_q, int n_kv,
+    int group, float scale_log2e, PartialBuf part, const uint16_t* __restrict__ cand_k, const uint16_t* __restrict__ cand_v,
+    const uint8_t* __restrict__ cand_mask, uint16_t* __restrict__ out) {
+    __shared__ __attribute__((aligned(16))) char lds[FewLds::kBytes];
+    const Slice slice = unit_of_block<SPLIT, INLINE>(plan, 0, n_kv);
+    tables_unwritten(plan);
+    attend_few<F8, SPLIT>(lds, slice, pool, q, plan, n_cand, n_q, n_kv, group, scale_log2e, part, cand_k, cand_v, cand_mask, out);
+}
+
+}  // namespace
+
+hipError_t launch_attention_few_bf16(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand, PartialBuf part,
+                                     const void* cand_k, const void* cand_v, const uint8_t* mask, void* out, hipStream_t st) {
+    if (plan.n_inline_words > kPlanInlineWords) return hipErrorInvalidValue;
+    const bool split = plan.split.blocks != nullptr || plan.inline_words;
+    const int32_t* n_class = split ? plan.split.n_blocks_class : plan.n_wg_class;
+    const int64_t n_wg = (int64_t)n_class[2] * s.n_kv;
+    if (n_class[0] > 0 || n_class[1] > 0 || n_wg > 0x7fffffff) return hipErrorInvalidValue;
+    if (n_wg == 0) return hipSuccess;
+#define APAR_LAUNCH(KERNEL, WORDS)                                                                           \
+    hipLaunchKernelGGL(KERNEL, dim3((unsigned)n_wg), dim3(256), 0, st, WORDS, (const char*)pool,             \
+                       (const uint16_t*)q, plan, n_cand, s.n_q, s.n_kv, s.group, s.scale_log2e, part,        \
+                       (const uint16_t*)cand_k, (const uint16_t*)cand_v, mask, (uint16_t*)out)
+#define APAR_LAUNCH_F8(SPLITV, INLINEV, WORDS)                                                               \
+    do {                                                                                                     \
+        if (s.fp8_sealed) APAR_LAUNCH((attention_bf16_few<true, SPLITV, INLINEV>), WORDS);                   \
+        else APAR_LAUNCH((attention_bf16_few<false, SPLITV, INLINEV>), WORDS);                               \
+    } while (0)
+    if (plan.inline_words) {
+        PlanWords<true> words;
+        memcpy(words.words, plan.inline_words, (size_t)plan.n_inline_words * sizeof(int32_t));
+        APAR_LAUNCH_F8(true, true, words);
+    } else if (split) {
+        APAR_LAUNCH_F8(true, false, PlanWords<false>{});
+    } else {
+        APAR_LAUNCH_F8(false, false, PlanWords<false>{});
+    }
+#undef APAR_LAUNCH_F8
+#undef APAR_LAUNCH
+    return hipGetLastError();
+}
+
+}  // namespace apar

@@ -54,10 +54,16 @@ constexpr int B = kBlockTokens;
 
 inline int32_t make_meta(int lo, int hi, int valid) { return lo | (hi << 10) | (valid << 20); }
 
+// The widest tree that a call of few units may hold, in units of 16 rows - each of them reads the tree's shared segments - and the
+// most tiles its units may list: half a MiB, so that such a plan fits the static workspace.
+constexpr int kFewTreeUnits = 4;
+constexpr int64_t kFewTiles = 65536;
+
 struct Builder {
     PlanHost& ph;
     const PlanParams& prm;
     int n_sl, rps, cap;  // slices per thread, rows per slice, row groups per wavefront
+    bool few = false;    // units of 16 rows only (PlanParams::few_units)
     // per segment: first partial row it produces itself (stand-alone: n_chunks * n_shr rows; unit root
     // that is not direct: n_shr rows), and how many chunks
     std::vector<int32_t> part0, n_chunks;
@@ -242,6 +248,84 @@ struct Builder {
             for (int32_t m : range_segs) clipped(m);
     }
 
+    // A unit of at most 16 rows in a call of few units: its tiles are dealt out to the four wavefronts, which all hold its rows.
+    // Open tiles go round; full ones level the lists.  A thread's own last blocks stay with one wavefront, whose list has room for
+    // its next ones.
+    void emit_few(const UnitSpec& u, int groups, int32_t pbase, int32_t flags) {
+        const int32_t grp0 = u.r_lo * n_sl;
+        int n_full[4] = {0, 0, 0, 0}, n_open[4] = {0, 0, 0, 0}, n_tails[4] = {0, 0, 0, 0};
+        int64_t load[4] = {0, 0, 0, 0};
+        std::vector<int32_t>& visit = ph.order;  // segment, row groups, wavefront of its last block
+        visit.clear();
+        int64_t full = 0;
+        for_unit_segments(u, [&](int32_t m, int lo, int hi) {
+            const PlanHost::Segment& sg = ph.segs[m];
+            const bool open = sg.last_valid < B;
+            int k = -1;
+            if (open || is_tail(sg)) {
+                k = 3;
+                for (int j = 2; j >= 0; --j)
+                    if (load[j] < load[k] || (load[j] == load[k] && n_tails[j] < n_tails[k])) k = j;
+                n_open[k] += open ? 1 : 0;
+                n_tails[k] += is_tail(sg) ? 1 : 0;
+                load[k] += open ? prm.few_open_cost : 0;
+            }
+            full += sg.n_blk - (open ? 1 : 0);
+            visit.insert(visit.end(), {m, lo, hi, k});
+        });
+        // full tiles to the emptiest lists: every list is raised to one level
+        for (int64_t left = full; left > 0;) {
+            int64_t low = load[0], next = INT64_MAX;
+            for (int k = 1; k < 4; ++k) low = std::min(low, load[k]);
+            int n_low = 0;
+            for (int k = 0; k < 4; ++k) {
+                if (load[k] == low) ++n_low;
+                else next = std::min(next, load[k]);
+            }
+            const int64_t rise = next == INT64_MAX ? std::max<int64_t>(1, left / n_low) : std::min(next - low, std::max<int64_t>(1, left / n_low));
+            for (int k = 0; k < 4 && left > 0; ++k)
+                if (load[k] == low) {
+                    const int64_t take = std::min(rise, left);
+                    load[k] += take, n_full[k] += (int)take, left -= take;
+                }
+        }
+        const size_t base = ph.tiles.size();
+        size_t total = 0, ofs[4];
+        for (int k = 0; k < 4; ++k) {
+            ofs[k] = base + total;
+            total += (size_t)n_full[k] + n_open[k] + (size_t)n_tails[k] * PlanHost::kTailSlack;
+        }
+        ph.tiles.resize(base + total);
+        int k_full = 0, at_full = 0, at_open[4] = {0, 0, 0, 0};
+        for (size_t i = 0; i < visit.size(); i += 4) {
+            const PlanHost::Segment& sg = ph.segs[visit[i]];
+            const int lo = visit[i + 1], hi = visit[i + 2], k = visit[i + 3];
+            const bool open = sg.last_valid < B;
+            const int np = sg.n_blk - (open ? 1 : 0);
+            const int32_t meta = make_meta(lo, hi, B);
+            for (int b = 0; b < np; ++b) {
+                while (at_full == n_full[k_full]) ++k_full, at_full = 0;
+                ph.tiles[ofs[k_full] + at_full++] = TileRef{sg.blocks[b], meta};
+            }
+            if (open) ph.tiles[ofs[k] + n_full[k] + at_open[k]++] = TileRef{sg.blocks[np], make_meta(lo, hi, sg.last_valid)};
+            if (is_tail(sg)) note_tail(sg, ph.wide_items.size(), k, lo, hi);
+        }
+        PlanHost::WideItem wi{};
+        wi.wg.coop_ofs = (int32_t)base;
+        wi.wg.grp_base = grp0;
+        wi.wg.row_tiles = 1;
+        int longest = 0;
+        for (int k = 0; k < 4; ++k) {
+            const int32_t cnt = n_full[k] + n_open[k];
+            wi.wg.w[k] = WaveItem{(int32_t)ofs[k], cnt, grp0, groups, pbase, flags | kWaveSplit};
+            wi.wg.n_full[k] = n_full[k];
+            longest = std::max(longest, (int)cnt);
+        }
+        wi.cost = longest;
+        wi.family = u.family;
+        push_wide(wi);
+    }
+
     // Returns the unit's first partial-result row (-1 for a direct unit).
     int32_t emit_unit(const UnitSpec& u) {
         const int groups = u.n_thr * n_sl;
@@ -255,6 +339,10 @@ struct Builder {
         }
         const int32_t flags = u.direct ? kWaveDirect : 0;
         const int32_t grp0 = u.r_lo * n_sl;
+        if (few && u.root < 0) {
+            emit_few(u, groups, pbase, flags);
+            return pbase;
+        }
         if (groups <= cap) {
             const int32_t ofs = (int32_t)ph.tiles.size();
             ph.open_tmp.clear();
@@ -419,7 +507,7 @@ struct Builder {
     int32_t next_stamp = 0;
     bool emit_by_rank(int32_t rid) {
         const PlanHost::Segment& r = ph.segs[rid];
-        const int per_unit = std::max(1, 4 * kMaxRowTiles * cap / n_sl);  // threads
+        const int per_unit = few ? cap : std::max(1, 4 * kMaxRowTiles * cap / n_sl);  // threads
         const int n_units = (r.n_shr + per_unit - 1) / per_unit;
         const int64_t block_cap = (int64_t)4 * prm.max_unit_tiles;
         if (seg_mark.size() != ph.segs.size()) seg_mark.assign(ph.segs.size(), -1);
@@ -560,6 +648,19 @@ int build_plan(const PlanThreadView* threads, int n, const int32_t* refcount, in
         ph.tails.assign(n, none);
     }
     const int cap = bld.cap, n_sl = bld.n_sl;
+    if (prm.few_units > 0 && n_sl == 1 && prm.fuse && prm.inline_shared && prm.allow_direct) {
+        int64_t units = 0, tiles = 0, again = 0;
+        bool wide = false;
+        for (const PlanHost::Segment& s : segs)
+            if (s.parent < 0) {
+                const int of_tree = (s.n_shr + cap - 1) / cap;
+                units += of_tree;
+                tiles += (int64_t)of_tree * s.tiles_sub;
+                again += (int64_t)(of_tree - 1) * s.tiles_sub;
+                wide = wide || of_tree > kFewTreeUnits;
+            }
+        bld.few = !wide && units <= prm.few_units && tiles <= kFewTiles && again <= prm.few_again;
+    }
     for (int32_t m = 0; m < n_seg; ++m) {
         PlanHost::Segment& s = segs[m];
         ph.unique_blocks += s.n_blk;
@@ -574,8 +675,8 @@ int build_plan(const PlanThreadView* threads, int n, const int32_t* refcount, in
         }
         s.n_above = par >= 0 ? segs[par].n_above + bld.n_chunks[par] : 0;
         const int groups = s.n_shr * n_sl;
-        const bool few_rows = groups <= 4 * kMaxRowTiles * cap;
-        if (prm.fuse && few_rows && s.tiles_sub <= (int64_t)(groups <= cap ? 1 : 4) * prm.max_unit_tiles) {
+        const bool few_rows = groups <= (bld.few ? 1 : 4 * kMaxRowTiles) * cap;
+        if (prm.fuse && few_rows && s.tiles_sub <= (int64_t)(groups <= cap && !bld.few ? 1 : 4) * prm.max_unit_tiles) {
             s.unit = m;  // a unit is named after its root segment
             bld.emit_fused(m);
             continue;

@@ -1,0 +1,90 @@
+"""Plans of calls with few units (16-bit pools): trees of up to four units of 16 rows are cut by rank into units without shared
+lists, whose tiles are level over the four wavefronts; wider trees, many trees and trees that would be read too often go the
+general way, as every tree does with the knob that cuts by rank switched off.  Every plan shows every row its blocks, and a
+decode loop carries it over."""
+import numpy as np
+import pytest
+
+import paper_2401_06761_amd as ap
+
+from harness import check_plan_covers_tables
+
+
+def grow(h, prompt, leaves):
+    root = ap.apar_thread_create(h)
+    ap.apar_append_kv(h, root, None, None, prompt)
+    live = ap.apar_fork(h, root, len(leaves))
+    ap.apar_free_thread(h, root)
+    for t, n in zip(live, leaves):
+        ap.apar_append_kv(h, t, None, None, n)
+    return live
+
+
+def workgroups(h):
+    return np.asarray(ap.apar_last_plan_export(h, ap.APAR_PLAN_WORKGROUPS)).reshape(-1, 32)
+
+
+# kv heads, q heads per kv head, (prompt, leaves) per tree, whether the call is one of few units
+CALLS = [
+    (2, 1, [(300, [20 + k for k in range(17)])], True),           # 17 rows: two units
+    (2, 1, [(300, [5] * 64)], True),
+    (2, 1, [(300, [5] * 65)], False),                              # five units
+    (8, 4, [(100, [30] * 5), (17, [1, 16, 17, 40, 8, 90])], True),
+    (8, 16, [(64, [9, 16, 33])], True),
+    (8, 5, [(64, [9, 16, 33, 1, 70])], True),
+    (8, 1, [(40, [10] * 20)] * 16, True),                          # 32 units x 8 heads
+    (8, 1, [(40, [10] * 20)] * 17, False),
+    (8, 8, [(16 * 600, [40] * 8)], True),                          # read four times: 3 x 600 tiles x 64 KiB
+    (8, 8, [(16 * 900, [40] * 8)], False),
+    (1, 1, [(16 * 2100, [1] * 18)], False),                        # more tiles than a unit may list
+]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "bf16_fp8kv", "f32"])
+@pytest.mark.parametrize("n_kv,group,trees,few", CALLS)
+def test_plans_of_few_units(dtype, n_kv, group, trees, few):
+    if dtype == "bf16_fp8kv" and trees[0][0] > 16 * 700:
+        few = trees[0][0] <= 16 * 2048  # (half the bytes are read again)
+    blocks = sum(p // 16 + 2 + sum(n // 16 + 2 for n in leaves) for p, leaves in trees)
+    with ap.Pool(n_kv * group, n_kv, 128, dtype, blocks, max_threads=2048, dry_run=True) as pool:
+        h = pool.handle
+        live = [t for prompt, leaves in trees for t in grow(h, prompt, leaves)]
+        ap.apar_decode_attention(h, None, live, None)
+        check_plan_covers_tables(h, live, n_kv, group)
+        wgs = workgroups(h)
+        cap = 16 // group
+        units = sum(-(-len(leaves) // cap) for _, leaves in trees)
+        narrow = all(wg[1] == 0 and wg[3] & 255 == 1 for wg in wgs)
+        if dtype != "f32" and few:
+            assert narrow and len(wgs) == units and len(wgs) * n_kv <= 256
+            for wg in wgs:
+                tiles, full = [wg[5 + 6 * k] for k in range(4)], wg[28:32]
+                assert all(wg[9 + 6 * k] & 2 for k in range(4)) and max(tiles) - min(tiles) <= 1 + max(t - f for t, f in zip(tiles, full))
+        else:
+            assert not narrow or len(wgs) != units
+        ap.apar_set_inline_shared(h, False)  # nothing is cut by rank
+        ap.apar_decode_attention(h, None, live, None)
+        check_plan_covers_tables(h, live, n_kv, group)
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_a_loop_carries_them(seed):
+    rng = np.random.default_rng(seed)
+    n_kv, group = int(rng.choice([1, 2, 8])), int(rng.choice([1, 2, 4, 8]))
+    with ap.Pool(n_kv * group, n_kv, 128, "bf16", 4096, max_threads=1 << 20, dry_run=True) as pool:
+        h = pool.handle
+        live = []
+        for _ in range(int(rng.integers(1, 5))):
+            live += grow(h, int(rng.integers(1, 400)), [int(x) for x in rng.integers(1, 60, size=int(rng.integers(16 // group + 1, 64 // group + 1)))])
+        for step in range(60):
+            if step:
+                ap.apar_append_kv_batch(h, live, None, None)
+                pos = int(rng.integers(0, len(live)))
+                (child,) = ap.apar_fork(h, live[pos], 1)  # a thread finishes and one forked from it carries on in its place
+                ap.apar_free_thread(h, live[pos])
+                live[pos] = child
+            ap.apar_decode_attention(h, None, live, None)
+            check_plan_covers_tables(h, live, n_kv, group)
+            assert all(wg[1] == 0 and wg[3] & 255 == 1 for wg in workgroups(h))
+        built, carried = ap.apar_plan_counts(h)
+        assert built + carried == 60 and built <= 2

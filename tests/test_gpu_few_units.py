@@ -1,0 +1,68 @@
+"""Calls of few workgroups (16-bit pools), which have a kernel of their own: list lengths around the tiles that kernel keeps on
+their way, full, open and no tiles per wavefront, one to sixteen rows per unit, trees of two to four units, slices from two to
+the most, against the dense oracle; the entry point that allocates nothing gives the same bits."""
+import numpy as np
+import pytest
+
+import paper_2401_06761_amd as ap
+from apar_workloads import HeadConfig, draw_candidate_tree, manual_tree, mask_rows_from_parents, spec_step_qkv, step_q
+from oracle import DenseThreads
+
+from harness import assert_close, blocks_upper_bound, pool_for, replay_trace, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+# q heads, kv heads, (prompt, leaves) of every tree
+CALLS = {
+    "one_block": (1, 1, [(1, [1])]),
+    "tiles_1_to_9": (2, 2, [(16 * n + n % 3, [1]) for n in range(1, 10)]),
+    "full_tiles_only": (2, 2, [(16 * n, [16]) for n in (15, 16, 17, 24, 31)]),
+    "open_tiles_only": (2, 2, [(1, [1] * 15), (3, [2] * 13 + [15])]),
+    "rows_1_15_16": (1, 1, [(300, [7]), (250, list(range(1, 16))), (280, list(range(10, 26)))]),
+    "units_of_a_tree": (8, 2, [(200, [5, 16, 17, 31, 32]), (90, [40] * 9), (33, list(range(20, 36)))]),
+    "group_16": (16, 1, [(150, [3, 16, 33, 20])]),
+    "group_5": (5, 1, [(210, [1 + 9 * k for k in range(10)])]),
+    "slices": (2, 2, [(2500, [1, 20, 33])]),
+    "most_slices": (1, 1, [(11000, [40] * 17)]),
+    "as_many_as_compute_units": (32, 32, [(60 + 9 * k, [4 + k] * 4) for k in range(8)]),
+}
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "bf16_fp8kv"])
+@pytest.mark.parametrize("call", list(CALLS))
+def test_against_the_oracle(dtype, call):
+    import torch
+
+    n_q, n_kv, trees = CALLS[call]
+    parents, lens = [], []
+    for prompt, leaves in trees:
+        root = len(parents)
+        parents += [-1] + [root] * len(leaves)
+        lens += [prompt] + leaves
+    w = manual_tree(parents, lens, HeadConfig(n_q, n_kv, 128, dtype), seed=9)
+    dense = DenseThreads(n_q, n_kv, 128)
+    with pool_for(w, blocks_upper_bound(w)) as pool:
+        pool.kv.fill_(0xFF)
+        h = pool.handle
+        live, _ = replay_trace(w, pool, None, dense)
+        q = step_q(w, 0, len(live))
+        outs = [torch.full_like(to_dev(q, dtype), 3.0) for _ in range(3)]
+        ap.apar_decode_attention(h, to_dev(q, dtype), live, outs[0])
+        ap.apar_decode_attention(h, to_dev(q, dtype), live, outs[1])
+        ap.apar_decode_attention_fixed(h, to_dev(q, dtype), live, outs[2])
+        torch.cuda.synchronize()
+        wgs = np.asarray(ap.apar_last_plan_export(h, ap.APAR_PLAN_WORKGROUPS)).reshape(-1, 32)
+        assert all(wg[1] == 0 and wg[3] & 255 == 1 for wg in wgs) and len(wgs) * n_kv <= 256
+        assert_close(to_host(outs[0]), dense.decode(q, live), dtype)
+        assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+        c = 3
+        if c * n_q // n_kv > 16 or dtype == "bf16_fp8kv":
+            return
+        q, ck, cv = spec_step_qkv(w, 1, len(live), c)
+        rng = np.random.default_rng(1)
+        masks = np.array([mask_rows_from_parents(draw_candidate_tree(rng, c)) for _ in live], dtype=np.uint8)
+        out = torch.full_like(to_dev(q, dtype), 3.0)
+        ap.apar_decode_attention_spec(h, to_dev(q, dtype), to_dev(ck, dtype), to_dev(cv, dtype), torch.from_numpy(masks).cuda(), c, live, out)
+        torch.cuda.synchronize()
+        assert_close(to_host(out), dense.decode_spec(q, ck, cv, masks, live), dtype, "candidates")
+
