@@ -105,6 +105,7 @@ struct apar_pool {
     int64_t plan_copies_then = 0;  // copy-on-write copies the pool had made by then
     bool plan_reuse = true;
     int64_t n_plans_built = 0, n_plans_carried = 0;
+    bool planning_set = false;         // one of the planner's knobs was set: plans are built as told, none for few units
     bool few_units = false;            // the plan's units go to the kernel for few workgroups
     int32_t plan_geom[3] = {1, 1, 1};  // rows per thread, rows per slice, slices of the last plan
 
@@ -421,19 +422,20 @@ int run_append(apar_pool* p, const std::vector<int32_t>& codes, const std::vecto
     return APAR_OK;
 }
 
-// Calls of few workgroups on 16-bit pools: units without shared lists, one row tile per wavefront, no more workgroups than compute
-// units (uncut).  They go to a kernel of their own (attend_few) whose wavefronts have a SIMD each, and the planner prefers such
-// units (PlanParams::few_units).  Measured, us per call (start of this change / general plan and that kernel / units of 16 rows and
-// that kernel / with the slices below): one request of 5 threads, group 4 14.4 / 13.9 / 9.6 / 8.2, group 1 11.7 / 9.8 / 9.8 / 8.4, two fork levels,
-// group 4 17.4 / 16.9 / 12.4 / 9.0; four requests, group 4 19.1 / 18.5 / 15.7 / 11.7, group 1 21.4 / 18.8 / 18.7 / 17.9; 16 requests,
-// group 4 28.5 / 28.0 / 24.7 / 24.6, of 2 k tokens on fp8 44.0 / 40.0 / 29.2 / 29.1.
-// A tree of more rows than a unit holds is read by several units, from L2 at best.  General plan / units of 16 rows, by the MiB
-// that are read again (group 8, and 4 where said): 62 (one request of 4 k) 20.3 / 15.3, 97 22.9 / 15.6, 91 (group 4) 30.2 / 28.9, 130 32.7 / 29.9,
-// 135 24.1 / 21.8, 153 (group 4) 43.0 / 45.8, 167 32.0 / 31.9, 208 29.5 / 32.3, 351 52.0 / 81.7.
-constexpr int64_t kFewAgainBytes = (int64_t)144 << 20;
-constexpr int32_t kFewWorkgroups = 256;
+// Calls of few units on 16-bit pools: units of one row tile without shared lists.  They go to a kernel of their own (attend_few), and
+// the planner makes such units for them (PlanParams::few_units): the shared lists of wider units cost a microsecond per tile where
+// nobody else is there to fill the waits.  Measured, us per call (general plan and kernel / units of 16 rows and that kernel):
+//   one request of 5 threads, group 1 11.7 / 8.4, group 4 14.4 / 8.2, two fork levels, group 4 17.4 / 9.4, of 9 threads of 24 rows each 49.5 / 14.6;
+//   four requests, group 1 21.4 / 18.0, group 4 19.1 / 11.7, two fork levels 30.7 / 15.2; 16 requests, group 4 28.0 / 24.5, of 2 k tokens on
+//   fp8 40.0 / 29.1; by units x kv heads: 292 40.5 / 25.5, 440 41.7 / 23.8, 472 47.0 / 43.2, 584 116.9 / 104.8, 720 32.4 / 26.8, 792 26.4 / 14.9, 824 44.6 / 37.0,
+//   848 45.1 / 31.8; 2048 and more of whole trees 215.2 / 216.4.
+// A tree of more rows than a unit holds is read by several units, from L2 at best.  General plan / such units, by the MiB that are
+// read again: 31 20.3 / 14.7, 37 22.9 / 16.0, 62 30.2 / 29.1, 75 23.9 / 21.9, 125 (one tree) 32.7 / 29.9, 125 (eight) 42.0 / 46.2, 140 32.2 / 32.4, 150
+// 29.6 / 32.6 and 71.0 / 78.8, 330 50.8 / 80.7.
+constexpr int64_t kFewAgainBytes = (int64_t)112 << 20;
+constexpr int32_t kFewUnits = 1024;
 bool few_units(const PlanHost& ph, const Shape& s) {
-    if (s.dtype != APAR_BF16 || ph.n_wg_class[0] > 0 || ph.n_wg_class[1] > 0 || ph.wgs.size() * s.n_kv > (size_t)kFewWorkgroups) return false;
+    if (s.dtype != APAR_BF16 || ph.n_wg_class[0] > 0 || ph.n_wg_class[1] > 0 || ph.wgs.size() * s.n_kv > (size_t)kFewUnits) return false;
     for (const WgDesc& wg : ph.wgs)
         if (wg.n_coop > 0) return false;
     return true;
@@ -460,6 +462,7 @@ constexpr int kSliceMinTiles = 6, kSliceMinGain = 16;
 //   requests 14.1, 12.1, 10.8, 11.0; four 18.7, 15.1, 17.8, 20.4; eight, 8 heads 19.4, 17.0, 16.3, 21.0; 32 k tokens, 8 heads 34.3, 32.4, 31.7,
 //   32.8; three requests of 7 k to 11 k 116, 87, 90, 115; eight of 4 k on fp8, 8 heads 28.9, 28.4, 26.0, 29.4.
 constexpr int kFewShares = 192, kFewMinTiles = 4, kFewMinGain = 5;
+constexpr int32_t kFewWorkgroups = 256;
 // (a unit that is cut costs more than T >= total * n_kv / shares, so cut units x kv heads stay below the shares)
 static_assert(kSliceShares <= kSplitMaxCut && kSliceSharesF32 <= kSplitMaxCut && kFewWorkgroups <= kSplitMaxCut, "a counter per cut unit, kv head and wavefront");
 void cut_into_slices(const PlanHost& ph, const Shape& s, bool few, size_t state_bytes, std::vector<SplitBlock>& out, int32_t (&n_class)[3]) {
@@ -479,6 +482,7 @@ void cut_into_slices(const PlanHost& ph, const Shape& s, bool few, size_t state_
         total += c;
         longest = std::max(longest, c);
     }
+    few = few && (int64_t)ph.wgs.size() * s.n_kv <= kFewWorkgroups;
     const int64_t shares = s.dtype == APAR_F32 ? kSliceSharesF32 : few ? kFewShares : kSliceShares;
     int64_t tiles = std::max<int64_t>(few ? kFewMinTiles : kSliceMinTiles, (total * s.n_kv + shares - 1) / shares);
     auto slices_of = [&](size_t k) { return k < first ? 1 : (int)std::min<int64_t>(64, (cost(ph.wgs[k]) + tiles - 1) / tiles); };
@@ -586,7 +590,7 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     prm.matrix_min_blocks = p->matrix_min_blocks;
     prm.inline_shared = p->inline_shared;
     prm.open_cost = p->shape.dtype == APAR_F32 ? 1 : kOpenTileCost;
-    prm.few_units = p->shape.dtype == APAR_BF16 ? kFewWorkgroups / p->shape.n_kv : 0;
+    prm.few_units = p->shape.dtype == APAR_BF16 && !p->planning_set ? kFewUnits / p->shape.n_kv : 0;
     prm.few_again = (int32_t)(kFewAgainBytes / (p->shape.n_kv * (p->shape.fp8_sealed ? 4096 : 8192)));
     prm.few_open_cost = p->shape.fp8_sealed ? 2 : 1;  // (twice the bytes of a full one)
     // Decode calls of a loop list the same threads step after step - each a few rows longer, a few replaced
@@ -1457,12 +1461,14 @@ int apar_set_write_checks(apar_pool* p, int on) {
 int apar_set_inline_shared(apar_pool* p, int on) {
     if (!p) return APAR_ERR_INVALID_ARG;
     p->inline_shared = on != 0;
+    p->planning_set = true;
     return APAR_OK;
 }
 
 int apar_set_matrix_units(apar_pool* p, int min_rows, int min_blocks) {
     if (!p || min_rows < 0 || min_blocks < 0) return APAR_ERR_INVALID_ARG;
     p->matrix_min_rows = min_rows;
+    p->planning_set = true;
     p->matrix_min_blocks = min_blocks;
     return APAR_OK;
 }
@@ -1478,6 +1484,7 @@ int apar_last_prefill_kernel(apar_pool* p) { return p ? p->last_prefill_kernel :
 int apar_set_chunk_blocks(apar_pool* p, int blocks_per_unit) {
     if (!p || blocks_per_unit < 1 || blocks_per_unit > 65536) return APAR_ERR_INVALID_ARG;
     p->max_unit_tiles = blocks_per_unit;
+    p->planning_set = true;
     return APAR_OK;
 }
 

@@ -121,12 +121,12 @@ __device__ __forceinline__ bool fold_slices(const SplitPlan& sp, const Slice& sl
                 m = mx;
             }
         } else {
-#pragma unroll(NT == 1 ? 3 : 1)
+#pragma unroll(3)
             for (int s = 0; s < sl.n; ++s) {
                 const int as = at + s * step;
                 const f32x2 ml = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(state, as + JT * 1024 + lane * 8, 0, kAgent));
                 f32x4 os[J];
-    #pragma unroll
+#pragma unroll
                 for (int jj = 0; jj < J; ++jj)
                     os[jj] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(state, as + ((j0 + jj) * 64 + lane) * 16, 0, kAgent));
                 // (a slice that saw nothing of the row left m = -inf and zeros)
@@ -134,7 +134,7 @@ __device__ __forceinline__ bool fold_slices(const SplitPlan& sp, const Slice& sl
                 const float a = mx == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m - mx);
                 const float b = mx == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(ml[0] - mx);
                 l = a * l + b * ml[1];
-    #pragma unroll
+#pragma unroll
                 for (int jj = 0; jj < J; ++jj) o[jj] = a * o[jj] + b * os[jj];
                 m = mx;
             }

@@ -54,10 +54,11 @@ constexpr int B = kBlockTokens;
 
 inline int32_t make_meta(int lo, int hi, int valid) { return lo | (hi << 10) | (valid << 20); }
 
-// The widest tree that a call of few units may hold, in units of 16 rows - each of them reads the tree's shared segments - and the
-// most tiles its units may list: half a MiB, so that such a plan fits the static workspace.
-constexpr int kFewTreeUnits = 4;
+// The most tiles that the units of a call of few units may list: half a MiB, so that such a plan fits the static workspace.  The widest
+// tree among them, in units, where more than kFewTreeThreads threads share a unit (a wider one of those is mostly short segments
+// of many threads, which units with shared lists read once).
 constexpr int64_t kFewTiles = 65536;
+constexpr int kFewTreeUnits = 4, kFewTreeThreads = 4;
 
 struct Builder {
     PlanHost& ph;
@@ -248,26 +249,35 @@ struct Builder {
             for (int32_t m : range_segs) clipped(m);
     }
 
-    // A unit of at most 16 rows in a call of few units: its tiles are dealt out to the four wavefronts, which all hold its rows.
+    // Units of at most 16 rows in a call of few units.  A unit's tiles are dealt out to the four wavefronts, which all hold its rows.
     // Open tiles go round; full ones level the lists.  A thread's own last blocks stay with one wavefront, whose list has room for
     // its next ones.
-    void emit_few(const UnitSpec& u, int groups, int32_t pbase, int32_t flags) {
-        const int32_t grp0 = u.r_lo * n_sl;
+    // A thread of more rows than a unit holds has a unit per slice (n_sl > 1; such units are not carried over).
+    void emit_few(const UnitSpec& u, int32_t pbase, int32_t flags) {
+        if (n_sl == 1) {
+            emit_few_groups(u, u.r_lo, u.n_thr, pbase, flags);
+            return;
+        }
+        for (int32_t g = 0; g < u.n_thr * n_sl; ++g) emit_few_groups(u, u.r_lo * n_sl + g, 1, pbase, flags);
+    }
+    void emit_few_groups(const UnitSpec& u, int32_t grp0, int groups, int32_t pbase, int32_t flags) {
         int n_full[4] = {0, 0, 0, 0}, n_open[4] = {0, 0, 0, 0}, n_tails[4] = {0, 0, 0, 0};
         int64_t load[4] = {0, 0, 0, 0};
         std::vector<int32_t>& visit = ph.order;  // segment, row groups, wavefront of its last block
         visit.clear();
         int64_t full = 0;
         for_unit_segments(u, [&](int32_t m, int lo, int hi) {
+            lo = std::max(0, lo + u.r_lo * n_sl - grp0), hi = std::min(groups, hi + u.r_lo * n_sl - grp0);
             const PlanHost::Segment& sg = ph.segs[m];
             const bool open = sg.last_valid < B;
             int k = -1;
-            if (open || is_tail(sg)) {
+            const bool tail = n_sl == 1 && is_tail(sg);
+            if (open || tail) {
                 k = 3;
                 for (int j = 2; j >= 0; --j)
                     if (load[j] < load[k] || (load[j] == load[k] && n_tails[j] < n_tails[k])) k = j;
                 n_open[k] += open ? 1 : 0;
-                n_tails[k] += is_tail(sg) ? 1 : 0;
+                n_tails[k] += tail ? 1 : 0;
                 load[k] += open ? prm.few_open_cost : 0;
             }
             full += sg.n_blk - (open ? 1 : 0);
@@ -308,7 +318,7 @@ struct Builder {
                 ph.tiles[ofs[k_full] + at_full++] = TileRef{sg.blocks[b], meta};
             }
             if (open) ph.tiles[ofs[k] + n_full[k] + at_open[k]++] = TileRef{sg.blocks[np], make_meta(lo, hi, sg.last_valid)};
-            if (is_tail(sg)) note_tail(sg, ph.wide_items.size(), k, lo, hi);
+            if (n_sl == 1 && is_tail(sg)) note_tail(sg, ph.wide_items.size(), k, lo, hi);
         }
         PlanHost::WideItem wi{};
         wi.wg.coop_ofs = (int32_t)base;
@@ -340,7 +350,7 @@ struct Builder {
         const int32_t flags = u.direct ? kWaveDirect : 0;
         const int32_t grp0 = u.r_lo * n_sl;
         if (few && u.root < 0) {
-            emit_few(u, groups, pbase, flags);
+            emit_few(u, pbase, flags);
             return pbase;
         }
         if (groups <= cap) {
@@ -507,7 +517,7 @@ struct Builder {
     int32_t next_stamp = 0;
     bool emit_by_rank(int32_t rid) {
         const PlanHost::Segment& r = ph.segs[rid];
-        const int per_unit = few ? cap : std::max(1, 4 * kMaxRowTiles * cap / n_sl);  // threads
+        const int per_unit = few ? std::max(1, cap / n_sl) : std::max(1, 4 * kMaxRowTiles * cap / n_sl);  // threads
         const int n_units = (r.n_shr + per_unit - 1) / per_unit;
         const int64_t block_cap = (int64_t)4 * prm.max_unit_tiles;
         if (seg_mark.size() != ph.segs.size()) seg_mark.assign(ph.segs.size(), -1);
@@ -648,17 +658,17 @@ int build_plan(const PlanThreadView* threads, int n, const int32_t* refcount, in
         ph.tails.assign(n, none);
     }
     const int cap = bld.cap, n_sl = bld.n_sl;
-    if (prm.few_units > 0 && n_sl == 1 && prm.fuse && prm.inline_shared && prm.allow_direct) {
+    if (prm.few_units > 0 && prm.fuse && prm.inline_shared && prm.allow_direct) {
         int64_t units = 0, tiles = 0, again = 0;
         bool wide = false;
-        for (const PlanHost::Segment& s : segs)
-            if (s.parent < 0) {
-                const int of_tree = (s.n_shr + cap - 1) / cap;
-                units += of_tree;
-                tiles += (int64_t)of_tree * s.tiles_sub;
-                again += (int64_t)(of_tree - 1) * s.tiles_sub;
-                wide = wide || of_tree > kFewTreeUnits;
-            }
+        for (const PlanHost::Segment& s : segs) {
+            const int64_t readers = n_sl == 1 ? (s.n_shr + cap - 1) / cap : (int64_t)s.n_shr * n_sl;
+            tiles += readers * s.n_blk;
+            again += (readers - 1) * s.n_blk;
+            if (s.parent >= 0) continue;
+            units += readers;
+            wide = wide || (readers > kFewTreeUnits && cap > kFewTreeThreads);
+        }
         bld.few = !wide && units <= prm.few_units && tiles <= kFewTiles && again <= prm.few_again;
     }
     for (int32_t m = 0; m < n_seg; ++m) {

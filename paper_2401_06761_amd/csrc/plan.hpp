@@ -95,8 +95,8 @@ struct PlanParams {
                                 // read the shared segments above their threads, instead of standing alone with partial results
     int32_t matrix_min_rows = 0;    // stand-alone segments with at least this many query rows (0: never) ...
     int32_t matrix_min_blocks = 0;  // ... and at least this many blocks become matrix units
-    int32_t few_units = 0;          // calls whose threads fit this many units of 16 rows get such units: no shared lists, every list divided
-                                    // over the four wavefronts of a workgroup (0: never)
+    int32_t few_units = 0;          // calls whose threads fit this many units of 16 rows get such units: no shared lists, every tree's
+                                    // tiles divided over the four wavefronts of a workgroup (0: never)
     int32_t few_again = 0;          // ... if they read no more tiles than this again
     int32_t few_open_cost = 1;      // a tile that is not full, in full tiles, there
     int32_t open_cost = 1;          // a tile that is not full, in full tiles, where a list is cut four ways

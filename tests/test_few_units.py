@@ -24,6 +24,25 @@ def workgroups(h):
     return np.asarray(ap.apar_last_plan_export(h, ap.APAR_PLAN_WORKGROUPS)).reshape(-1, 32)
 
 
+def every_row_group_once(h, live, slices):
+    """Every slice of every thread is one direct unit's, which lists each block of the thread's table once."""
+    wgs = workgroups(h)
+    tiles = np.asarray(ap.apar_last_plan_export(h, ap.APAR_PLAN_TILES)).reshape(-1, 2)
+    dfs = ap.apar_last_plan_export(h, ap.APAR_PLAN_DFS_THREADS)
+    assert sorted(wg[6] for wg in wgs) == list(range(len(live) * slices)) and ap.apar_last_plan_info(h).n_partial_rows == 0
+    for wg in wgs:
+        thread = live[dfs[wg[6] // slices]]
+        table, length, got = ap.apar_thread_block_table(h, thread), ap.apar_thread_len(h, thread), []
+        for k in range(4):
+            ofs, n, lo, groups, _, flags = wg[4 + 6 * k:10 + 6 * k]
+            assert lo == wg[6] and groups == 1 and flags == 3
+            fills = [int(m) >> 20 & 31 for _, m in tiles[ofs:ofs + n]]
+            assert all(int(m) & 0xfffff == 1 << 10 for _, m in tiles[ofs:ofs + n]) and [f == 16 for f in fills] == [i < wg[28 + k] for i in range(n)]
+            got += [(int(b), f) for (b, _), f in zip(tiles[ofs:ofs + n], fills)]
+        # (a block that is not the last is full)
+        assert sorted(got) == sorted((b, min(16, length - 16 * i)) for i, b in enumerate(table))
+
+
 # kv heads, q heads per kv head, (prompt, leaves) per tree, whether the call is one of few units
 CALLS = [
     (2, 1, [(300, [20 + k for k in range(17)])], True),           # 17 rows: two units
@@ -32,9 +51,10 @@ CALLS = [
     (8, 4, [(100, [30] * 5), (17, [1, 16, 17, 40, 8, 90])], True),
     (8, 16, [(64, [9, 16, 33])], True),
     (8, 5, [(64, [9, 16, 33, 1, 70])], True),
-    (8, 1, [(40, [10] * 20)] * 16, True),                          # 32 units x 8 heads
-    (8, 1, [(40, [10] * 20)] * 17, False),
-    (8, 8, [(16 * 600, [40] * 8)], True),                          # read four times: 3 x 600 tiles x 64 KiB
+    (8, 1, [(40, [10] * 20)] * 64, True),                          # 128 units x 8 heads
+    (8, 1, [(40, [10] * 20)] * 65, False),
+    (8, 4, [(40, [10] * 30)] * 2, True),                           # eight units each, of four threads
+    (8, 8, [(16 * 590, [40] * 8)], True),                          # read four times: 3 x 590 tiles x 64 KiB
     (8, 8, [(16 * 900, [40] * 8)], False),
     (1, 1, [(16 * 2100, [1] * 18)], False),                        # more tiles than a unit may list
 ]
@@ -56,7 +76,7 @@ def test_plans_of_few_units(dtype, n_kv, group, trees, few):
         units = sum(-(-len(leaves) // cap) for _, leaves in trees)
         narrow = all(wg[1] == 0 and wg[3] & 255 == 1 for wg in wgs)
         if dtype != "f32" and few:
-            assert narrow and len(wgs) == units and len(wgs) * n_kv <= 256
+            assert narrow and len(wgs) == units
             for wg in wgs:
                 tiles, full = [wg[5 + 6 * k] for k in range(4)], wg[28:32]
                 assert all(wg[9 + 6 * k] & 2 for k in range(4)) and max(tiles) - min(tiles) <= 1 + max(t - f for t, f in zip(tiles, full))
@@ -88,3 +108,25 @@ def test_a_loop_carries_them(seed):
             assert all(wg[1] == 0 and wg[3] & 255 == 1 for wg in workgroups(h))
         built, carried = ap.apar_plan_counts(h)
         assert built + carried == 60 and built <= 2
+
+
+@pytest.mark.parametrize("n_kv,group,cand,few", [(8, 8, 3, True), (1, 8, 8, True), (8, 16, 4, True), (2, 5, 5, True), (16, 16, 4, False)])
+def test_threads_of_more_rows_than_a_unit_holds(n_kv, group, cand, few):
+    """A unit per slice of every thread; a call with the same list carries the plan over, one after an append builds another."""
+    with ap.Pool(n_kv * group, n_kv, 128, "bf16", 2048, max_threads=256, dry_run=True) as pool:
+        h = pool.handle
+        live = grow(h, 70, [1, 16, 17, 40, 90]) + grow(h, 16, [3, 50]) + grow(h, 5, [20] * 12)
+        spec = lambda: ap.apar_decode_attention_spec(h, None, None, None, None, cand, live, None)
+        for step in range(3):
+            spec()
+            slices = -(-cand * group // 16)
+            if few:
+                every_row_group_once(h, live, slices)
+            else:
+                check_plan_covers_tables(h, live, n_kv, cand * group)
+            narrow = all(wg[1] == 0 and wg[3] & 255 == 1 for wg in workgroups(h))
+            assert narrow == few and (not few or sum(wg[7] for wg in workgroups(h)) == len(live) * slices)
+            built = ap.apar_plan_counts(h)[0]
+            spec()
+            assert ap.apar_plan_counts(h)[0] == built
+            ap.apar_append_kv_batch(h, live, None, None)

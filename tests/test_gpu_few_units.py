@@ -24,6 +24,9 @@ CALLS = {
     "group_5": (5, 1, [(210, [1 + 9 * k for k in range(10)])]),
     "slices": (2, 2, [(2500, [1, 20, 33])]),
     "most_slices": (1, 1, [(11000, [40] * 17)]),
+    "wide_trees": (32, 8, [(100, [9 * k + 1 for k in range(23)]), (47, [30] * 17)]),
+    "more_than_compute_units": (16, 16, [(20 + k, [1 + k % 40] * 3) for k in range(60)]),
+    "one_long_among_many": (16, 16, [(3000, [30] * 3)] + [(20 + k, [1 + k % 40] * 3) for k in range(40)]),
     "as_many_as_compute_units": (32, 32, [(60 + 9 * k, [4 + k] * 4) for k in range(8)]),
 }
 
@@ -52,7 +55,7 @@ def test_against_the_oracle(dtype, call):
         ap.apar_decode_attention_fixed(h, to_dev(q, dtype), live, outs[2])
         torch.cuda.synchronize()
         wgs = np.asarray(ap.apar_last_plan_export(h, ap.APAR_PLAN_WORKGROUPS)).reshape(-1, 32)
-        assert all(wg[1] == 0 and wg[3] & 255 == 1 for wg in wgs) and len(wgs) * n_kv <= 256
+        assert all(wg[1] == 0 and wg[3] & 255 == 1 for wg in wgs) and len(wgs) * n_kv <= 1024
         assert_close(to_host(outs[0]), dense.decode(q, live), dtype)
         assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
         c = 3
@@ -66,3 +69,26 @@ def test_against_the_oracle(dtype, call):
         torch.cuda.synchronize()
         assert_close(to_host(out), dense.decode_spec(q, ck, cv, masks, live), dtype, "candidates")
 
+
+@pytest.mark.parametrize("n_q,n_kv,cand", [(16, 2, 3), (8, 1, 8), (64, 8, 4), (10, 2, 5)])
+def test_threads_of_more_rows_than_a_unit_holds(n_q, n_kv, cand):
+    import torch
+
+    leaves = [1, 16, 17, 40, 90]
+    w = manual_tree([-1] + [0] * 5 + [-1, 6, 6], [170] + leaves + [16, 3, 50], HeadConfig(n_q, n_kv, 128, "bf16"), seed=2)
+    dense = DenseThreads(n_q, n_kv, 128)
+    with pool_for(w, blocks_upper_bound(w)) as pool:
+        pool.kv.fill_(0xFF)
+        h = pool.handle
+        live, _ = replay_trace(w, pool, None, dense)
+        q, ck, cv = spec_step_qkv(w, 1, len(live), cand)
+        rng = np.random.default_rng(1)
+        masks = np.array([mask_rows_from_parents(draw_candidate_tree(rng, cand)) for _ in live], dtype=np.uint8)
+        outs = [torch.full_like(to_dev(q, "bf16"), 3.0) for _ in range(2)]
+        for out in outs:
+            ap.apar_decode_attention_spec(h, to_dev(q, "bf16"), to_dev(ck, "bf16"), to_dev(cv, "bf16"), torch.from_numpy(masks).cuda(), cand, live, out)
+        torch.cuda.synchronize()
+        wgs = np.asarray(ap.apar_last_plan_export(h, ap.APAR_PLAN_WORKGROUPS)).reshape(-1, 32)
+        assert all(wg[1] == 0 and wg[3] & 255 == 1 for wg in wgs) and len(wgs) == len(live) * -(-cand * n_q // n_kv // 16)
+        assert_close(to_host(outs[0]), dense.decode_spec(q, ck, cv, masks, live), "bf16")
+        assert torch.equal(outs[0], outs[1])
