@@ -422,8 +422,8 @@ int run_append(apar_pool* p, const std::vector<int32_t>& codes, const std::vecto
     return APAR_OK;
 }
 
-// Calls of few units on 16-bit pools: units of one row tile without shared lists.  They go to a kernel of their own (attend_few), and
-// the planner makes such units for them (PlanParams::few_units): the shared lists of wider units cost a microsecond per tile where
+// Calls of few units: units of one row tile without shared lists, which the planner makes for them (PlanParams::few_units).  On 16-bit
+// pools they go to a kernel of their own (attend_few): the shared lists of wider units cost a microsecond per tile where
 // nobody else is there to fill the waits.  Measured, us per call (general plan and kernel / units of 16 rows and that kernel):
 //   one request of 5 threads, group 1 11.7 / 8.4, group 4 14.4 / 8.2, two fork levels, group 4 17.4 / 9.4, of 9 threads of 24 rows each 49.5 / 14.6;
 //   four requests, group 1 21.4 / 18.0, group 4 19.1 / 11.7, two fork levels 30.7 / 15.2; 16 requests, group 4 28.0 / 24.5, of 2 k tokens on
@@ -448,13 +448,12 @@ bool few_units(const PlanHost& ph, const Shape& s) {
 //   bf16, 32 kv heads:  1 request 36 / 24 / 24 / 24,  4: 88 / 44 / 44 / 47,  16: 182 / 170 / 162 / 162,  32: 251 / 252 / 266 / 258
 //   bf16, 8 kv heads:   1 request 41 / 22 / 22 / 22,  4: 98 / 67 / 70 / 70,  16: 136 / 96 / 97 / 96
 //   one thread family of 32 k tokens, 8 kv heads: 106 / 58 / 59 / 63;  five candidates, 16 requests: 189 / 189 / 221 / 222
-//   fp32, 12 requests, 8 kv heads: 356 / 165 / 137 / 139 (its wavefronts are busy with products, not waiting)
 // Slices of 4, 2 and 1 tiles instead of kSliceMinTiles: 25, 32 and 32 against 22 us for one request with 8 kv heads.
 // Slices are worth their states and their fold only where they shorten the longest walk by more than kSliceMinGain
 // tiles (26 requests, 8 kv heads, units of 19 to 27 tiles: 46 us uncut, 49 us with every unit cut in two).  Their room is an
 // eighth of the pool, at least 1 MiB and at most kSplitStateBytes; where it is short, T grows until the states fit (by a quarter
 // at a time: a pass over the units each, nothing is built) or nothing is worth cutting any more.
-constexpr int kSliceShares = 256, kSliceSharesF32 = 512;
+constexpr int kSliceShares = 256;
 constexpr int kSliceMinTiles = 6, kSliceMinGain = 16;
 // Calls of few workgroups: shorter slices pay, since every wavefront folds a quarter of them, but only as long as there are no
 // more workgroups than compute units (two on one share its 50 bytes per cycle).  Shares / least tiles / least gain, us per call:
@@ -463,8 +462,34 @@ constexpr int kSliceMinTiles = 6, kSliceMinGain = 16;
 //   32.8; three requests of 7 k to 11 k 116, 87, 90, 115; eight of 4 k on fp8, 8 heads 28.9, 28.4, 26.0, 29.4.
 constexpr int kFewShares = 192, kFewMinTiles = 4, kFewMinGain = 5;
 constexpr int32_t kFewWorkgroups = 256;
-// (a unit that is cut costs more than T >= total * n_kv / shares, so cut units x kv heads stay below the shares)
-static_assert(kSliceShares <= kSplitMaxCut && kSliceSharesF32 <= kSplitMaxCut && kFewWorkgroups <= kSplitMaxCut, "a counter per cut unit, kv head and wavefront");
+// fp32 pools: wavefronts are busy with products (a tile of d = 128 is 2048 cycles of them), so what a call takes is the largest sum
+// of walks on one compute unit.  Tiles per slice are those whose estimate is least:
+//   max(1.2 x longest slice, workgroups per compute unit, rounded up, x mean slice) + (3 + 0.45 x slices of the most cut unit)
+// in tiles; a workgroup alone on its compute unit has nobody to fill its softmax (1.2), and a state to fold costs 0.45 tiles.
+// Measured, us per call, by tiles per slice (workgroups): one request of 8 k tokens, 8 heads 3 to 4 (264) 33, 4 (256) 26.8, 6 (168) 25.7; of
+// 4 k to 14 k, group 5 7 (448) 45, 13 (256) 38.7, 17 (192) 37.9; eight of 2 k to 5 k 17 (256) 31.7, 9 (512) 30.5; one of 14 k with 30 threads of
+// four candidates 53 (256) 78, 35 (384) 60.8, 27 (512) 64.8; one of five threads, group 4 14 (16) 20.4, 4 (64) 13.2, 3 (80) 12.4; four of
+// group 4 4 (220) 18.4, 3 (264) 22.8.
+constexpr size_t kEstimatedUnits = 4096;  // (kv heads counted; larger calls fill the chip whole, but for a walk of more than a 512th of them)
+int64_t tiles_per_slice_f32(const std::vector<int32_t>& costs, int n_kv) {
+    int64_t total = 0, longest = 0;
+    for (int32_t c : costs) total += c, longest = std::max<int64_t>(longest, c);
+    if (costs.size() * n_kv > kEstimatedUnits) return std::max<int64_t>(6, (total * n_kv + 511) / 512);
+    double best = 0.0;
+    int64_t pick = longest;
+    for (int64_t t = longest;; t = t * 4 / 5) {
+        int64_t n = 0, slice = 0, most = 1;
+        for (int32_t c : costs) {
+            const int64_t k = std::min<int64_t>(64, (c + t - 1) / t);
+            n += k, most = std::max(most, k), slice = std::max(slice, (c + k - 1) / k);
+        }
+        const int64_t per_cu = (n * n_kv + 255) / 256;
+        const double est = std::max(1.2 * slice, (double)per_cu * total / n) + (most > 1 ? 3.0 + 0.45 * most : 0.0);
+        if (t == longest || est < best) best = est, pick = t;
+        if (t <= 3) break;
+    }
+    return pick;
+}
 void cut_into_slices(const PlanHost& ph, const Shape& s, bool few, size_t state_bytes, std::vector<SplitBlock>& out, int32_t (&n_class)[3]) {
     out.clear();
     n_class[0] = n_class[1] = n_class[2] = 0;
@@ -483,19 +508,26 @@ void cut_into_slices(const PlanHost& ph, const Shape& s, bool few, size_t state_
         longest = std::max(longest, c);
     }
     few = few && (int64_t)ph.wgs.size() * s.n_kv <= kFewWorkgroups;
-    const int64_t shares = s.dtype == APAR_F32 ? kSliceSharesF32 : few ? kFewShares : kSliceShares;
+    const int64_t shares = few ? kFewShares : kSliceShares;
     int64_t tiles = std::max<int64_t>(few ? kFewMinTiles : kSliceMinTiles, (total * s.n_kv + shares - 1) / shares);
+    int min_gain = few ? kFewMinGain : kSliceMinGain;
+    if (s.dtype == APAR_F32) {
+        std::vector<int32_t> costs;
+        for (const WgDesc& wg : ph.wgs) costs.push_back(cost(wg));
+        tiles = tiles_per_slice_f32(costs, s.n_kv);
+        min_gain = ph.wgs.size() * s.n_kv > kEstimatedUnits ? kSliceMinGain : 0;
+    }
     auto slices_of = [&](size_t k) { return k < first ? 1 : (int)std::min<int64_t>(64, (cost(ph.wgs[k]) + tiles - 1) / tiles); };
     const int64_t room = (int64_t)state_bytes / (s.n_kv * (int64_t)(s.d / 4 + 2) * 64 * (int64_t)sizeof(float));
     for (;; tiles += (tiles + 3) / 4) {
-        if (longest <= tiles + (few ? kFewMinGain : kSliceMinGain)) return;
-        int64_t state = 0, blocks = 0;
+        if (longest <= tiles + min_gain) return;
+        int64_t state = 0, blocks = 0, cut = 0;
         for (size_t k = first; k < ph.wgs.size(); ++k) {
             const int n = slices_of(k);
             blocks += n;
-            if (n > 1) state += (int64_t)n * state_of(ph.wgs[k]);
+            if (n > 1) state += (int64_t)n * state_of(ph.wgs[k]), cut += 1;
         }
-        if (state <= room && (!few || blocks * s.n_kv <= kFewWorkgroups)) break;
+        if (state <= room && cut * s.n_kv <= kSplitMaxCut && (!few || blocks * s.n_kv <= kFewWorkgroups)) break;
     }
     n_class[0] = (int32_t)first;
     int32_t state = 0, n_cut = 0;
@@ -590,8 +622,9 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     prm.matrix_min_blocks = p->matrix_min_blocks;
     prm.inline_shared = p->inline_shared;
     prm.open_cost = p->shape.dtype == APAR_F32 ? 1 : kOpenTileCost;
-    prm.few_units = p->shape.dtype == APAR_BF16 && !p->planning_set ? kFewUnits / p->shape.n_kv : 0;
-    prm.few_again = (int32_t)(kFewAgainBytes / (p->shape.n_kv * (p->shape.fp8_sealed ? 4096 : 8192)));
+    prm.few_units = p->planning_set ? 0 : kFewUnits / p->shape.n_kv;
+    // (the fp32 kernel's wavefronts read shared lists one by one: units of 16 rows read nothing more often)
+    prm.few_again = p->shape.dtype == APAR_F32 ? INT32_MAX : (int32_t)(kFewAgainBytes / (p->shape.n_kv * (p->shape.fp8_sealed ? 4096 : 8192)));
     prm.few_open_cost = p->shape.fp8_sealed ? 2 : 1;  // (twice the bytes of a full one)
     // Decode calls of a loop list the same threads step after step - each a few rows longer, a few replaced
     // by a thread forked from them - and the plan of the previous call then only needs its tails brought up

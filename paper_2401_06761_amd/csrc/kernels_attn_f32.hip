@@ -22,7 +22,9 @@
 // Measured against one wavefront per query row in plain vector arithmetic, every row reading its blocks for
 // itself: twelve depth-2 trees (32 / 8 heads, d = 128, 0.28 GB read) 704 -> 355 us; one request of three
 // threads (2 heads, d = 64) 56 -> 16 us for the call; error against 64 bits 5.2e-7 -> 4.5e-7 and 2.2e-7 -> 1.9e-7.
-// With its heaviest units cut into slices (attn_split.hpp) the first of these takes 137 us, error 3.1e-7.
+// With its heaviest units cut into slices (attn_split.hpp) the first of these took 137 us, in one launch 94, and in units of 16
+// rows without shared lists, as the plans of such calls have them now (PlanParams::few_units), 77; one request of five threads,
+// 8 kv heads 26.3 -> 12.5, of 14 k tokens and 30 threads of four candidates 91 -> 54, three of five candidates 117 -> 28.
 //
 // A row that does not see a block meets it with probability 0, and 0 times an infinity or a NaN is a NaN.  Blocks of
 // other threads must not do that to a row: a wavefront takes those of its rows that did not come out finite again, one
@@ -57,16 +59,18 @@ struct Row {  // the 16 rows of one tile: query operands and running softmax sta
 
 template <int D>
 __device__ __forceinline__ f32x4 products(const f32x4 (&k)[D / 16], const Row<D>& st) {
-    // two chains: half the latency, and sums of half the length
-    f32x4 a = {0.0f, 0.0f, 0.0f, 0.0f}, b = {0.0f, 0.0f, 0.0f, 0.0f};
+    // four chains: a quarter of the latency, and sums of a quarter of the length (twelve trees, two chains / four: error against
+    // 64 bits 3.4e-7 / 2.9e-7, three threads 2.1e-7 / 1.6e-7, the same time)
+    f32x4 a[4];
 #pragma unroll
-    for (int j = 0; j < D / 16; j += 2)
+    for (int h = 0; h < 4; ++h) a[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            a = __builtin_amdgcn_mfma_f32_16x16x4f32(k[j][i], st.q[j][i], a, 0, 0, 0);
-            b = __builtin_amdgcn_mfma_f32_16x16x4f32(k[j + 1][i], st.q[j + 1][i], b, 0, 0, 0);
-        }
-    return a + b;
+    for (int j = 0; j < D / 16; j += 4)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int h = 0; h < 4; ++h) a[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[j + h][i], st.q[j + h][i], a[h], 0, 0, 0);
+    return (a[0] + a[1]) + (a[2] + a[3]);
 }
 
 // One tile's logits into one row tile's state.  tok_mask: the token slots this lane's row sees (none: not its block).

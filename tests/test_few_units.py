@@ -1,4 +1,4 @@
-"""Plans of calls with few units (16-bit pools): trees of up to four units of 16 rows are cut by rank into units without shared
+"""Plans of calls with few units: trees of up to four units of 16 rows are cut by rank into units without shared
 lists, whose tiles are level over the four wavefronts; wider trees, many trees and trees that would be read too often go the
 general way, as every tree does with the knob that cuts by rank switched off.  Every plan shows every row its blocks, and a
 decode loop carries it over."""
@@ -63,8 +63,8 @@ CALLS = [
 @pytest.mark.parametrize("dtype", ["bf16", "bf16_fp8kv", "f32"])
 @pytest.mark.parametrize("n_kv,group,trees,few", CALLS)
 def test_plans_of_few_units(dtype, n_kv, group, trees, few):
-    if dtype == "bf16_fp8kv" and trees[0][0] > 16 * 700:
-        few = trees[0][0] <= 16 * 2048  # (half the bytes are read again)
+    if dtype != "bf16" and trees[0][0] > 16 * 700:
+        few = trees[0][0] <= 16 * 2048  # (fp8: half the bytes are read again; fp32: none that wider units do not)
     blocks = sum(p // 16 + 2 + sum(n // 16 + 2 for n in leaves) for p, leaves in trees)
     with ap.Pool(n_kv * group, n_kv, 128, dtype, blocks, max_threads=2048, dry_run=True) as pool:
         h = pool.handle
@@ -75,7 +75,7 @@ def test_plans_of_few_units(dtype, n_kv, group, trees, few):
         cap = 16 // group
         units = sum(-(-len(leaves) // cap) for _, leaves in trees)
         narrow = all(wg[1] == 0 and wg[3] & 255 == 1 for wg in wgs)
-        if dtype != "f32" and few:
+        if few:
             assert narrow and len(wgs) == units
             for wg in wgs:
                 tiles, full = [wg[5 + 6 * k] for k in range(4)], wg[28:32]

@@ -1,4 +1,4 @@
-"""Calls of few workgroups (16-bit pools), which have a kernel of their own: list lengths around the tiles that kernel keeps on
+"""Calls of few units (on 16-bit pools they have a kernel of their own): list lengths around the tiles that kernel keeps on
 their way, full, open and no tiles per wavefront, one to sixteen rows per unit, trees of two to four units, slices from two to
 the most, against the dense oracle; the entry point that allocates nothing gives the same bits."""
 import numpy as np
@@ -31,9 +31,9 @@ CALLS = {
 }
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "bf16_fp8kv"])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16_fp8kv", 128), ("f32", 64), ("f32", 128)])
 @pytest.mark.parametrize("call", list(CALLS))
-def test_against_the_oracle(dtype, call):
+def test_against_the_oracle(dtype, d, call):
     import torch
 
     n_q, n_kv, trees = CALLS[call]
@@ -42,8 +42,8 @@ def test_against_the_oracle(dtype, call):
         root = len(parents)
         parents += [-1] + [root] * len(leaves)
         lens += [prompt] + leaves
-    w = manual_tree(parents, lens, HeadConfig(n_q, n_kv, 128, dtype), seed=9)
-    dense = DenseThreads(n_q, n_kv, 128)
+    w = manual_tree(parents, lens, HeadConfig(n_q, n_kv, d, dtype), seed=9)
+    dense = DenseThreads(n_q, n_kv, d)
     with pool_for(w, blocks_upper_bound(w)) as pool:
         pool.kv.fill_(0xFF)
         h = pool.handle
@@ -70,12 +70,13 @@ def test_against_the_oracle(dtype, call):
         assert_close(to_host(out), dense.decode_spec(q, ck, cv, masks, live), dtype, "candidates")
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("n_q,n_kv,cand", [(16, 2, 3), (8, 1, 8), (64, 8, 4), (10, 2, 5)])
-def test_threads_of_more_rows_than_a_unit_holds(n_q, n_kv, cand):
+def test_threads_of_more_rows_than_a_unit_holds(dtype, n_q, n_kv, cand):
     import torch
 
     leaves = [1, 16, 17, 40, 90]
-    w = manual_tree([-1] + [0] * 5 + [-1, 6, 6], [170] + leaves + [16, 3, 50], HeadConfig(n_q, n_kv, 128, "bf16"), seed=2)
+    w = manual_tree([-1] + [0] * 5 + [-1, 6, 6], [170] + leaves + [16, 3, 50], HeadConfig(n_q, n_kv, 128, dtype), seed=2)
     dense = DenseThreads(n_q, n_kv, 128)
     with pool_for(w, blocks_upper_bound(w)) as pool:
         pool.kv.fill_(0xFF)
@@ -84,11 +85,11 @@ def test_threads_of_more_rows_than_a_unit_holds(n_q, n_kv, cand):
         q, ck, cv = spec_step_qkv(w, 1, len(live), cand)
         rng = np.random.default_rng(1)
         masks = np.array([mask_rows_from_parents(draw_candidate_tree(rng, cand)) for _ in live], dtype=np.uint8)
-        outs = [torch.full_like(to_dev(q, "bf16"), 3.0) for _ in range(2)]
+        outs = [torch.full_like(to_dev(q, dtype), 3.0) for _ in range(2)]
         for out in outs:
-            ap.apar_decode_attention_spec(h, to_dev(q, "bf16"), to_dev(ck, "bf16"), to_dev(cv, "bf16"), torch.from_numpy(masks).cuda(), cand, live, out)
+            ap.apar_decode_attention_spec(h, to_dev(q, dtype), to_dev(ck, dtype), to_dev(cv, dtype), torch.from_numpy(masks).cuda(), cand, live, out)
         torch.cuda.synchronize()
         wgs = np.asarray(ap.apar_last_plan_export(h, ap.APAR_PLAN_WORKGROUPS)).reshape(-1, 32)
         assert all(wg[1] == 0 and wg[3] & 255 == 1 for wg in wgs) and len(wgs) == len(live) * -(-cand * n_q // n_kv // 16)
-        assert_close(to_host(outs[0]), dense.decode_spec(q, ck, cv, masks, live), "bf16")
+        assert_close(to_host(outs[0]), dense.decode_spec(q, ck, cv, masks, live), dtype)
         assert torch.equal(outs[0], outs[1])
