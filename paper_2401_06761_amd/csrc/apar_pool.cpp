@@ -422,20 +422,21 @@ int run_append(apar_pool* p, const std::vector<int32_t>& codes, const std::vecto
     return APAR_OK;
 }
 
-// Calls of few units: units of one row tile without shared lists, which the planner makes for them (PlanParams::few_units).  On 16-bit
+// Calls of few units: units of one row tile (or two) without shared lists, which the planner makes for them (PlanParams::few_units).  On 16-bit
 // pools they go to a kernel of their own (attend_few): the shared lists of wider units cost a microsecond per tile where
 // nobody else is there to fill the waits.  Measured, us per call (general plan and kernel / units of 16 rows and that kernel):
 //   one request of 5 threads, group 1 11.7 / 8.4, group 4 14.4 / 8.2, two fork levels, group 4 17.4 / 9.4, of 9 threads of 24 rows each 49.5 / 14.6;
 //   four requests, group 1 21.4 / 18.0, group 4 19.1 / 11.7, two fork levels 30.7 / 15.2; 16 requests, group 4 28.0 / 24.5, of 2 k tokens on
 //   fp8 40.0 / 29.1; by units x kv heads: 292 40.5 / 25.5, 440 41.7 / 23.8, 472 47.0 / 43.2, 584 116.9 / 104.8, 720 32.4 / 26.8, 792 26.4 / 14.9, 824 44.6 / 37.0,
 //   848 45.1 / 31.8; 2048 and more of whole trees 215.2 / 216.4.
-// A tree of more rows than a unit holds is read by several units, from L2 at best.  General plan / such units, by the MiB that are
-// read again: 31 20.3 / 14.7, 37 22.9 / 16.0, 62 30.2 / 29.1, 75 23.9 / 21.9, 125 (one tree) 32.7 / 29.9, 125 (eight) 42.0 / 46.2, 140 32.2 / 32.4, 150
-// 29.6 / 32.6 and 71.0 / 78.8, 330 50.8 / 80.7.
-constexpr int64_t kFewAgainBytes = (int64_t)112 << 20;
+// A tree of more rows than a unit holds is read by several units, from L2 at best, so that units have 32 rows where units of 16 would
+// read too much again.  General plan / units of 16 / units of 32, by the MiB that units of 16 read again: 31 20.3 / 14.7, 37 22.9 /
+// 16.0, 62 30.2 / 29.4 / 26.2, 75 (group 8) 23.9 / 21.9 / 22.9, 84 47.0 / 42.9 / 39.1, on fp8 48.3 / 47.9 / 41.7, 125 42.0 / 46.2 / 36.4, 140 32.2 / 32.4 /
+// 27.8, 150 71.0 / 78.8 / 63.5 and 29.5 / 32.6 / 31.3; by what units of 32 read: 200 54.8 / - / 66.4, 72.0 / - / 82.3, 75.8 / - / 42.9 (28 rows per thread).
+constexpr int64_t kFewAgainBytes = (int64_t)56 << 20, kFewAgainWideBytes = (int64_t)112 << 20;
 constexpr int32_t kFewUnits = 1024;
 bool few_units(const PlanHost& ph, const Shape& s) {
-    if (s.dtype != APAR_BF16 || ph.n_wg_class[0] > 0 || ph.n_wg_class[1] > 0 || ph.wgs.size() * s.n_kv > (size_t)kFewUnits) return false;
+    if (s.dtype != APAR_BF16 || ph.n_wg_class[0] > 0 || ph.wgs.size() * s.n_kv > (size_t)kFewUnits) return false;
     for (const WgDesc& wg : ph.wgs)
         if (wg.n_coop > 0) return false;
     return true;
@@ -497,8 +498,9 @@ void cut_into_slices(const PlanHost& ph, const Shape& s, bool few, size_t state_
     auto cost = [](const WgDesc& wg) {
         return wg.n_coop + std::max(std::max(wg.w[0].n_tiles, wg.w[1].n_tiles), std::max(wg.w[2].n_tiles, wg.w[3].n_tiles));
     };
-    // 16-row tiles of state that a slice of the unit leaves
-    auto state_of = [](const WgDesc& wg) { return ((wg.w[0].flags & kWaveSplit) ? 1 : 4) * (wg.row_tiles & 255); };
+    // 16-row tiles of state that a slice of the unit leaves (the kernel for few units takes all of a call's as it takes the widest)
+    const int at_least = few && ph.n_wg_class[1] > 0 ? 2 : 1;
+    auto state_of = [at_least](const WgDesc& wg) { return ((wg.w[0].flags & kWaveSplit) ? 1 : 4) * std::max(at_least, wg.row_tiles & 255); };
     const size_t first = (size_t)ph.n_wg_class[0];  // (matrix units stay whole)
     int64_t total = 0;
     int longest = 0;
@@ -624,7 +626,10 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     prm.open_cost = p->shape.dtype == APAR_F32 ? 1 : kOpenTileCost;
     prm.few_units = p->planning_set ? 0 : kFewUnits / p->shape.n_kv;
     // (the fp32 kernel's wavefronts read shared lists one by one: units of 16 rows read nothing more often)
-    prm.few_again = p->shape.dtype == APAR_F32 ? INT32_MAX : (int32_t)(kFewAgainBytes / (p->shape.n_kv * (p->shape.fp8_sealed ? 4096 : 8192)));
+    const int64_t tile_read = p->shape.n_kv * (p->shape.fp8_sealed ? 4096 : 8192);
+    prm.few_row_tiles = p->shape.dtype == APAR_F32 ? 1 : 2;
+    prm.few_again = p->shape.dtype == APAR_F32 ? INT32_MAX : (int32_t)(kFewAgainBytes / tile_read);
+    prm.few_again_wide = (int32_t)(kFewAgainWideBytes / tile_read);
     prm.few_open_cost = p->shape.fp8_sealed ? 2 : 1;  // (twice the bytes of a full one)
     // Decode calls of a loop list the same threads step after step - each a few rows longer, a few replaced
     // by a thread forked from them - and the plan of the previous call then only needs its tails brought up

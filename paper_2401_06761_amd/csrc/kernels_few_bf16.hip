@@ -18,29 +18,45 @@ namespace apar {
 
 namespace {
 
+template <int NT>
 struct FewLds {
-    static constexpr int kStates = 4 * kOpenScratch;  // (apart from the scratch: nobody waits before leaving a state)
-    static constexpr int kBytes = kStates + 4 * kSplitState;
+    // one row tile: the states lie apart from the scratch, and nobody waits before leaving one; two: queries behind the scratch, the
+    // states, row tile by row tile, where both were
+    static constexpr int kQueries = 4 * kOpenScratch;
+    static constexpr int kStates = NT == 1 ? 4 * kOpenScratch : 0;
+    static constexpr int kBytes = NT == 1 ? kStates + 4 * kSplitState : kQueries + 4 * NT * 4096;
+    static_assert(NT == 1 || kBytes >= 4 * kSplitState, "states of one row tile");
 };
 
+template <int NT>
 struct FewWalk {
     const char* head_base;
     int64_t block_stride;
     float scale_log2e;
-    int my_j;       // row group of this lane's row, or 0x7fff
-    char* scratch;  // kOpenScratch bytes of LDS
+    int my_j[NT];     // row group of this lane's row of each row tile, or 0x7fff
+    int cap;          // row groups per row tile
+    char* scratch;    // kOpenScratch bytes of LDS
+    const char* q;    // NT = 2: the lane's query pieces in LDS, 1 KiB apart, row tile after row tile (NT = 1: in registers)
     int lane;
+
+    __device__ __forceinline__ void queries(RowState& st, int nt) const {
+        if constexpr (NT > 1) {
+            asm volatile("" ::: "memory");  // (read for every tile, not kept)
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) st.q[kk].u = *reinterpret_cast<const u32x4*>(q + (nt * 4 + kk) * 1024);
+        }
+    }
 };
 
 // A tile on its way: its rows or operand pieces (CODES: the codes of a full fp8 tile).
-template <bool CODES>
+template <bool CODES, int NT>
 struct FewTile {
     Frag k[4], v[4];
     u32x4 k8[CODES ? 2 : 1], v8[CODES ? 2 : 1];
     float ks, vs;
     int meta;
 
-    __device__ __forceinline__ void fetch_k(const FewWalk& w, const char* tile, int rows) {
+    __device__ __forceinline__ void fetch_k(const FewWalk<NT>& w, const char* tile, int rows) {
         if constexpr (CODES) {
 #pragma unroll
             for (int r = 0; r < 2; ++r) k8[r] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(tile + w.lane * 16 + r * 1024));
@@ -49,7 +65,7 @@ struct FewTile {
             fetch_half(w, tile, rows, k);
         }
     }
-    __device__ __forceinline__ void fetch_v(const FewWalk& w, const char* tile, int rows) {
+    __device__ __forceinline__ void fetch_v(const FewWalk<NT>& w, const char* tile, int rows) {
         if constexpr (CODES) {
 #pragma unroll
             for (int r = 0; r < 2; ++r)
@@ -60,14 +76,14 @@ struct FewTile {
         }
     }
     // The half's KiB r: the operands' piece r of a full tile, token rows 4r .. 4r + 3 of an open one (rows that are not filled: row 0).
-    __device__ __forceinline__ static void fetch_half(const FewWalk& w, const char* half, int rows, Frag (&f)[4]) {
+    __device__ __forceinline__ static void fetch_half(const FewWalk<NT>& w, const char* half, int rows, Frag (&f)[4]) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const uint32_t at = 4 * r + (w.lane >> 4) < rows ? r * 1024 + w.lane * 16 : (w.lane & 15) * 16;
             f[r].u = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(half + at));
         }
     }
-    __device__ __forceinline__ static void rows_to_lds(const FewWalk& w, const Frag (&f)[4]) {
+    __device__ __forceinline__ static void rows_to_lds(const FewWalk<NT>& w, const Frag (&f)[4]) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) *reinterpret_cast<u32x4*>(w.scratch + (4 * r + (w.lane >> 4)) * kOpenRowStride + (w.lane & 15) * 16) = f[r].u;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -77,10 +93,16 @@ struct FewTile {
     // Takes the tile; meanwhile the next one for these registers, `rows` rows of it, is fetched (rows = 1: there is none, and a row of
     // the list's last tile comes instead, so that no load lies behind a branch).
     template <bool MORE>
-    __device__ __forceinline__ void take(const FewWalk& w, RowState& st, const char* next, int next_meta, int rows) {
+    __device__ __forceinline__ void take(const FewWalk<NT>& w, RowState (&st)[NT], const char* next, int next_meta, int rows) {
         const int g4 = w.lane >> 4, c = w.lane & 15;
         const int lo = meta & 1023, hi = (meta >> 10) & 1023, valid = (meta >> 20) & 31;
         const bool causal = meta >> 30, open = !CODES && valid < kBlockTokens;
+        bool on[NT], in_range[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            on[nt] = NT == 1 || (lo < (nt + 1) * w.cap && hi > nt * w.cap);  // (wavefront-uniform)
+            in_range[nt] = w.my_j[nt] >= lo && w.my_j[nt] < hi;
+        }
         if constexpr (CODES) {
             fp8_operands(k8, ks, k);
         } else if (open) {
@@ -89,15 +111,23 @@ struct FewTile {
             for (int r = 0; r < 4; ++r) k[r].u = *reinterpret_cast<const u32x4*>(w.scratch + c * kOpenRowStride + g4 * 64 + r * 16);
             __builtin_amdgcn_wave_barrier();
         }
-        f32x4 s = products(k, st);
+        f32x4 s[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            if (on[nt]) {
+                w.queries(st[nt], nt);
+                s[nt] = products(k, st[nt]);
+            }
         if constexpr (MORE) fetch_k(w, next, rows);
         if (open || causal) {
             const int first = (meta >> 25) & 31;
-            const int limit = causal ? min(valid, max(0, first + w.my_j - lo)) : valid;
-            mask_tokens(s, (1u << limit) - 1u, g4);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const int limit = causal ? min(valid, max(0, first + w.my_j[nt] - lo)) : valid;
+                if (on[nt]) mask_tokens(s[nt], (1u << limit) - 1u, g4);
+            }
         }
-        const bool in_range = w.my_j >= lo && w.my_j < hi;
-        move_reference(st, s, in_range, w.scale_log2e);
+        move_references<NT>(st, s, on, in_range, w.scale_log2e);
         if constexpr (CODES) {
             fp8_operands(v8, vs, v);
         } else if (open) {
@@ -105,20 +135,22 @@ struct FewTile {
             v_operands_from_rows(w.scratch, kOpenRowStride, g4, c, v);
             __builtin_amdgcn_wave_barrier();
         }
-        weigh_values(v, st, s, in_range, w.scale_log2e);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            if (on[nt]) weigh_values(v, st[nt], s[nt], in_range[nt], w.scale_log2e);
         if constexpr (MORE) fetch_v(w, next, rows);
         meta = next_meta;
     }
 };
 
-template <bool CODES>
+template <bool CODES, int NT>
 struct FewList {
     static constexpr int kSets = CODES ? 3 : 2;
-    FewTile<CODES> set[kSets];
+    FewTile<CODES, NT> set[kSets];
     const TileRef* list;
     int n;
 
-    __device__ __forceinline__ void start(const FewWalk& w) {
+    __device__ __forceinline__ void start(const FewWalk<NT>& w) {
         if (n <= 0) return;
         TileRef ref[kSets];
 #pragma unroll
@@ -135,7 +167,7 @@ struct FewList {
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    __device__ __forceinline__ void walk(const FewWalk& w, RowState& st) {
+    __device__ __forceinline__ void walk(const FewWalk<NT>& w, RowState (&st)[NT]) {
         if (n <= 0) return;
         int t = 0;
         for (; t + kSets <= n; t += kSets) {
@@ -151,7 +183,7 @@ struct FewList {
     }
 };
 
-template <bool F8, bool SPLIT>
+template <int NT, bool F8, bool SPLIT>
 __device__ __forceinline__ void attend_few(char* lds, const Slice& slice, const char* __restrict__ pool, const uint16_t* __restrict__ q,
                                            const PlanDev& plan, int n_cand, int n_q, int n_kv, int group, float scale_log2e,
                                            const PartialBuf& part, const uint16_t* __restrict__ cand_k, const uint16_t* __restrict__ cand_v,
@@ -167,129 +199,150 @@ __device__ __forceinline__ void attend_few(char* lds, const Slice& slice, const 
     if (wi.n_grp == 0) return;  // (never one of the four wavefronts of a divided list)
     const TileRef* mine = plan.tiles + wi.tile_ofs;
 
-    // column c is row `within` of the wavefront's row group c / rps
-    const int rps = plan.rows_per_slice, n_sl = plan.n_slices;
+    // column c of row tile nt is row `within` of the wavefront's row group nt * cap + c / rps
+    const int rps = plan.rows_per_slice, n_sl = plan.n_slices, cap = 16 / rps;
     const int jc = c / rps, within = c - jc * rps;
-    const int grp = wi.grp_lo + jc, rank = grp / n_sl, rr = (grp - rank * n_sl) * rps + within;
-    const bool ok = jc < 16 / rps && jc < wi.n_grp && rr < plan.rows_per_thread;
-    const int listed = ok ? (plan.dfs_threads ? plan.dfs_threads[rank] : rank) : 0;
-    const int cc = ok ? rr / group : 0, hq = kvh * group + (ok ? rr - cc * group : 0);
-    const int64_t qrow = ((int64_t)listed * n_cand + cc) * n_q + hq;
-    RowState st[1];
-    st[0].m = -INFINITY;
-    st[0].l = 0.0f;
-#pragma unroll
-    for (int jj = 0; jj < 8; ++jj) st[0].o[jj] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    {
-        const u32x4* qp = reinterpret_cast<const u32x4*>(q + qrow * 128 + g4 * 32);
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) st[0].q[kk].u = qp[kk];  // (a column without a row: some row's queries, for no tile)
-    }
     char* scratch = lds + wave * kOpenScratch;
-    const FewWalk walk{pool + (int64_t)kvh * kTileBytes, (int64_t)n_kv * kTileBytes, scale_log2e, ok ? jc : 0x7fff, scratch, lane};
+    char* my_q = lds + FewLds<NT>::kQueries + wave * NT * 4096 + lane * 16;
+    FewWalk<NT> walk{pool + (int64_t)kvh * kTileBytes, (int64_t)n_kv * kTileBytes, scale_log2e, {}, cap, scratch, my_q, lane};
+    RowState st[NT];
+    int64_t qrow[NT];  // -1: no row
+    int64_t slot[NT];  // of the row's partial result
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        const int j = nt * cap + jc, grp = wi.grp_lo + j, rank = grp / n_sl, rr = (grp - rank * n_sl) * rps + within;
+        const bool ok = jc < cap && j < wi.n_grp && rr < plan.rows_per_thread;
+        const int listed = ok ? (plan.dfs_threads ? plan.dfs_threads[rank] : rank) : 0;
+        const int cc = ok ? rr / group : 0, hq = kvh * group + (ok ? rr - cc * group : 0);
+        const int64_t row = ((int64_t)listed * n_cand + cc) * n_q + hq;
+        walk.my_j[nt] = ok ? j : 0x7fff;
+        qrow[nt] = ok ? row : -1;
+        slot[nt] = ((int64_t)(wi.part_base + rank - wi.grp_lo / n_sl) * n_cand + cc) * n_q + hq;
+        st[nt].m = -INFINITY;
+        st[nt].l = 0.0f;
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) st[nt].o[jj] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        const u32x4* qp = reinterpret_cast<const u32x4*>(q + row * 128 + g4 * 32);
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {  // (a column without a row: some row's queries, for no tile)
+            if constexpr (NT == 1) st[nt].q[kk].u = qp[kk];
+            else *reinterpret_cast<u32x4*>(my_q + (nt * 4 + kk) * 1024) = qp[kk];
+        }
+    }
     if constexpr (F8) {  // full tiles are codes, open ones rows
-        FewList<true> codes;
-        FewList<false> rows;
+        FewList<true, NT> codes;
+        FewList<false, NT> rows;
         codes.list = mine, codes.n = own_full;
         rows.list = mine + own_full, rows.n = wi.n_tiles - own_full;
         codes.start(walk);
-        rows.start(walk);
-        codes.walk(walk, st[0]);
-        rows.walk(walk, st[0]);
+        if constexpr (NT == 1) rows.start(walk);
+        codes.walk(walk, st);
+        if constexpr (NT > 1) rows.start(walk);
+        rows.walk(walk, st);
     } else {
-        FewList<false> tiles;
+        FewList<false, NT> tiles;
         tiles.list = mine, tiles.n = wi.n_tiles;
         tiles.start(walk);
-        tiles.walk(walk, st[0]);
+        tiles.walk(walk, st);
     }
     const bool divided = wi.flags & kWaveSplit;
-    if ((wi.flags & kWaveDirect) && cand_mask != nullptr && (!SPLIT || slice.s == 0) && (!divided || wave == 0))
-        attend_candidates<1>(st, scratch, plan, wi, cand_k, cand_v, cand_mask, {walk.my_j}, within, n_cand, n_kv, kvh, group, scale_log2e);
+    if ((wi.flags & kWaveDirect) && cand_mask != nullptr && (!SPLIT || slice.s == 0) && (!divided || wave == 0)) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) walk.queries(st[nt], nt);
+        attend_candidates<NT>(st, scratch, plan, wi, cand_k, cand_v, cand_mask, walk.my_j, within, n_cand, n_kv, kvh, group, scale_log2e);
+    }
 
-    auto write = [&](auto quads, int j0, float l_all) {  // quads j0 .. of the lane's row
+    auto write = [&](auto quads, int j0, int nt) {  // quads j0 .. of the lane's row of row tile nt
         constexpr int J = decltype(quads)::value;
-        if (!ok) return;
+        float l = st[nt].l;
+        l += __shfl_xor(l, 16, 64);
+        l += __shfl_xor(l, 32, 64);
+        if (qrow[nt] < 0) return;
         if (wi.flags & kWaveDirect) {
-            const float inv = 1.0f / l_all;
-            uint16_t* dst = out + qrow * 128 + 4 * g4;
+            const float inv = 1.0f / l;
+            uint16_t* dst = out + qrow[nt] * 128 + 4 * g4;
 #pragma unroll
             for (int jj = 0; jj < J; ++jj) {
                 u32x2 pk;
-                pk.x = pack_bf16_pair(st[0].o[jj][0] * inv, st[0].o[jj][1] * inv);
-                pk.y = pack_bf16_pair(st[0].o[jj][2] * inv, st[0].o[jj][3] * inv);
+                pk.x = pack_bf16_pair(st[nt].o[jj][0] * inv, st[nt].o[jj][1] * inv);
+                pk.y = pack_bf16_pair(st[nt].o[jj][2] * inv, st[nt].o[jj][3] * inv);
                 *reinterpret_cast<u32x2*>(dst + 16 * (j0 + jj)) = pk;
             }
         } else {
-            const int64_t slot = ((int64_t)(wi.part_base + rank - wi.grp_lo / n_sl) * n_cand + cc) * n_q + hq;
 #pragma unroll
-            for (int jj = 0; jj < J; ++jj) *reinterpret_cast<f32x4*>(part.o + slot * 128 + 4 * g4 + 16 * (j0 + jj)) = st[0].o[jj];
+            for (int jj = 0; jj < J; ++jj) *reinterpret_cast<f32x4*>(part.o + slot[nt] * 128 + 4 * g4 + 16 * (j0 + jj)) = st[nt].o[jj];
             if (g4 == 0 && j0 == 0) {
-                part.ml[slot * 2] = st[0].m;
-                part.ml[slot * 2 + 1] = l_all;
+                part.ml[slot[nt] * 2] = st[nt].m;
+                part.ml[slot[nt] * 2 + 1] = l;
             }
         }
     };
-    auto sum_of_row = [&](float l) {
-        l += __shfl_xor(l, 16, 64);
-        return l + __shfl_xor(l, 32, 64);
-    };
     if (!divided) {
         if constexpr (SPLIT)
-            if (!fold_slices<1, 8>(plan.split, slice, n_kv, kvh, wave, 4, lane, st)) return;
-        write(std::integral_constant<int, 8>{}, 0, sum_of_row(st[0].l));
+            if (!fold_slices<NT, 8>(plan.split, slice, n_kv, kvh, wave, 4, lane, st)) return;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) write(std::integral_constant<int, 8>{}, 0, nt);
         return;
     }
     // the four wavefronts hold the same rows over different tiles: every one folds two of the eight accumulator quads
-    char* states = lds + FewLds::kStates;
-    {
-        char* to = states + wave * kSplitState;
-#pragma unroll
-        for (int jj = 0; jj < 8; ++jj) *reinterpret_cast<f32x4*>(to + (jj * 64 + lane) * 16) = st[0].o[jj];
-        *reinterpret_cast<f32x2*>(to + 8 * 1024 + lane * 8) = f32x2{st[0].m, st[0].l};
-    }
     // (not __syncthreads: it would wait for the rows fetched past the lists' ends)
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    auto meet = [] {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    char* states = lds + FewLds<NT>::kStates;
     const int j0 = 2 * wave;
-    f32x2 ml[4];
-    f32x4 o[4][2];
 #pragma unroll
-    for (int w2 = 0; w2 < 4; ++w2) {
-        const char* from = states + w2 * kSplitState;
-        ml[w2] = *reinterpret_cast<const f32x2*>(from + 8 * 1024 + lane * 8);
+    for (int nt = 0; nt < NT; ++nt) {
+        if (NT > 1) meet();  // (everyone is done with what the states overlap)
+        {
+            char* to = states + wave * kSplitState;
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj) o[w2][jj] = *reinterpret_cast<const f32x4*>(from + ((j0 + jj) * 64 + lane) * 16);
-    }
-    const float mx = fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x));
-    st[0].m = mx;
-    st[0].l = 0.0f;
+            for (int jj = 0; jj < 8; ++jj) *reinterpret_cast<f32x4*>(to + (jj * 64 + lane) * 16) = st[nt].o[jj];
+            *reinterpret_cast<f32x2*>(to + 8 * 1024 + lane * 8) = f32x2{st[nt].m, st[nt].l};
+        }
+        meet();
+        f32x2 ml[4];
+        f32x4 o[4][2];
 #pragma unroll
-    for (int jj = 0; jj < 2; ++jj) st[0].o[jj] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int w2 = 0; w2 < 4; ++w2) {
+            const char* from = states + w2 * kSplitState;
+            ml[w2] = *reinterpret_cast<const f32x2*>(from + 8 * 1024 + lane * 8);
 #pragma unroll
-    for (int w2 = 0; w2 < 4; ++w2) {
-        // a wavefront that saw no tile of a row left m = -inf and sums of zero for it
-        const float a = ml[w2].x == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(ml[w2].x - mx);
-        st[0].l += a * ml[w2].y;
+            for (int jj = 0; jj < 2; ++jj) o[w2][jj] = *reinterpret_cast<const f32x4*>(from + ((j0 + jj) * 64 + lane) * 16);
+        }
+        const float mx = fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x));
+        st[nt].m = mx;
+        st[nt].l = 0.0f;
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj) st[0].o[jj] += a * o[w2][jj];
+        for (int jj = 0; jj < 2; ++jj) st[nt].o[jj] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int w2 = 0; w2 < 4; ++w2) {
+            // a wavefront that saw no tile of a row left m = -inf and sums of zero for it
+            const float a = ml[w2].x == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(ml[w2].x - mx);
+            st[nt].l += a * ml[w2].y;
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj) st[nt].o[jj] += a * o[w2][jj];
+        }
     }
     if constexpr (SPLIT)
-        if (!fold_slices<1, 2, 8>(plan.split, slice, n_kv, kvh, wave, 1, lane, st, j0)) return;
-    write(std::integral_constant<int, 2>{}, j0, sum_of_row(st[0].l));
+        if (!fold_slices<NT, 2, 8>(plan.split, slice, n_kv, kvh, wave, 1, lane, st, j0)) return;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) write(std::integral_constant<int, 2>{}, j0, nt);
 }
 
 // Launches of few workgroups (attend_few): one wavefront per SIMD.
-template <bool F8, bool SPLIT, bool INLINE>
+template <int NT, bool F8, bool SPLIT, bool INLINE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attention_bf16_few(
     PlanWords<INLINE>, const char* __restrict__ pool, const uint16_t* __restrict__ q, PlanDev plan, int n_cand, int n_q, int n_kv,
     int group, float scale_log2e, PartialBuf part, const uint16_t* __restrict__ cand_k, const uint16_t* __restrict__ cand_v,
     const uint8_t* __restrict__ cand_mask, uint16_t* __restrict__ out) {
-    __shared__ __attribute__((aligned(16))) char lds[FewLds::kBytes];
+    __shared__ __attribute__((aligned(16))) char lds[FewLds<NT>::kBytes];
     const Slice slice = unit_of_block<SPLIT, INLINE>(plan, 0, n_kv);
     tables_unwritten(plan);
-    attend_few<F8, SPLIT>(lds, slice, pool, q, plan, n_cand, n_q, n_kv, group, scale_log2e, part, cand_k, cand_v, cand_mask, out);
+    attend_few<NT, F8, SPLIT>(lds, slice, pool, q, plan, n_cand, n_q, n_kv, group, scale_log2e, part, cand_k, cand_v, cand_mask, out);
 }
 
 }  // namespace
@@ -299,17 +352,22 @@ hipError_t launch_attention_few_bf16(const Shape& s, const void* pool, const voi
     if (plan.n_inline_words > kPlanInlineWords) return hipErrorInvalidValue;
     const bool split = plan.split.blocks != nullptr || plan.inline_words;
     const int32_t* n_class = split ? plan.split.n_blocks_class : plan.n_wg_class;
-    const int64_t n_wg = (int64_t)n_class[2] * s.n_kv;
-    if (n_class[0] > 0 || n_class[1] > 0 || n_wg > 0x7fffffff) return hipErrorInvalidValue;
+    const int64_t n_wg = ((int64_t)n_class[1] + n_class[2]) * s.n_kv;
+    if (n_class[0] > 0 || n_wg > 0x7fffffff) return hipErrorInvalidValue;
     if (n_wg == 0) return hipSuccess;
 #define APAR_LAUNCH(KERNEL, WORDS)                                                                           \
     hipLaunchKernelGGL(KERNEL, dim3((unsigned)n_wg), dim3(256), 0, st, WORDS, (const char*)pool,             \
                        (const uint16_t*)q, plan, n_cand, s.n_q, s.n_kv, s.group, s.scale_log2e, part,        \
                        (const uint16_t*)cand_k, (const uint16_t*)cand_v, mask, (uint16_t*)out)
+#define APAR_LAUNCH_NT(F8V, SPLITV, INLINEV, WORDS)                                                         \
+    do {                                                                                                     \
+        if (n_class[1] > 0) APAR_LAUNCH((attention_bf16_few<2, F8V, SPLITV, INLINEV>), WORDS);               \
+        else APAR_LAUNCH((attention_bf16_few<1, F8V, SPLITV, INLINEV>), WORDS);                              \
+    } while (0)
 #define APAR_LAUNCH_F8(SPLITV, INLINEV, WORDS)                                                               \
     do {                                                                                                     \
-        if (s.fp8_sealed) APAR_LAUNCH((attention_bf16_few<true, SPLITV, INLINEV>), WORDS);                   \
-        else APAR_LAUNCH((attention_bf16_few<false, SPLITV, INLINEV>), WORDS);                               \
+        if (s.fp8_sealed) APAR_LAUNCH_NT(true, SPLITV, INLINEV, WORDS);                                      \
+        else APAR_LAUNCH_NT(false, SPLITV, INLINEV, WORDS);                                                  \
     } while (0)
     if (plan.inline_words) {
         PlanWords<true> words;
@@ -321,6 +379,7 @@ hipError_t launch_attention_few_bf16(const Shape& s, const void* pool, const voi
         APAR_LAUNCH_F8(false, false, PlanWords<false>{});
     }
 #undef APAR_LAUNCH_F8
+#undef APAR_LAUNCH_NT
 #undef APAR_LAUNCH
     return hipGetLastError();
 }

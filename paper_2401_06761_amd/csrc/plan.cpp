@@ -64,7 +64,7 @@ struct Builder {
     PlanHost& ph;
     const PlanParams& prm;
     int n_sl, rps, cap;  // slices per thread, rows per slice, row groups per wavefront
-    bool few = false;    // units of 16 rows only (PlanParams::few_units)
+    int few = 0;         // row tiles that units may have in a call of few units (PlanParams::few_units); 0: another call
     // per segment: first partial row it produces itself (stand-alone: n_chunks * n_shr rows; unit root
     // that is not direct: n_shr rows), and how many chunks
     std::vector<int32_t> part0, n_chunks;
@@ -258,7 +258,9 @@ struct Builder {
             emit_few_groups(u, u.r_lo, u.n_thr, pbase, flags);
             return;
         }
-        for (int32_t g = 0; g < u.n_thr * n_sl; ++g) emit_few_groups(u, u.r_lo * n_sl + g, 1, pbase, flags);
+        for (int32_t t = 0; t < u.n_thr; ++t)
+            for (int32_t g = 0; g < n_sl; g += few * cap)
+                emit_few_groups(u, (u.r_lo + t) * n_sl + g, std::min(few * cap, n_sl - g), pbase, flags);
     }
     void emit_few_groups(const UnitSpec& u, int32_t grp0, int groups, int32_t pbase, int32_t flags) {
         int n_full[4] = {0, 0, 0, 0}, n_open[4] = {0, 0, 0, 0}, n_tails[4] = {0, 0, 0, 0};
@@ -268,6 +270,7 @@ struct Builder {
         int64_t full = 0;
         for_unit_segments(u, [&](int32_t m, int lo, int hi) {
             lo = std::max(0, lo + u.r_lo * n_sl - grp0), hi = std::min(groups, hi + u.r_lo * n_sl - grp0);
+            if (lo >= hi) return;  // (another thread's)
             const PlanHost::Segment& sg = ph.segs[m];
             const bool open = sg.last_valid < B;
             int k = -1;
@@ -323,7 +326,7 @@ struct Builder {
         PlanHost::WideItem wi{};
         wi.wg.coop_ofs = (int32_t)base;
         wi.wg.grp_base = grp0;
-        wi.wg.row_tiles = 1;
+        wi.wg.row_tiles = groups > cap ? 2 : 1;
         int longest = 0;
         for (int k = 0; k < 4; ++k) {
             const int32_t cnt = n_full[k] + n_open[k];
@@ -349,7 +352,7 @@ struct Builder {
         }
         const int32_t flags = u.direct ? kWaveDirect : 0;
         const int32_t grp0 = u.r_lo * n_sl;
-        if (few && u.root < 0) {
+        if (few && (u.root < 0 || groups > cap)) {
             emit_few(u, pbase, flags);
             return pbase;
         }
@@ -517,7 +520,7 @@ struct Builder {
     int32_t next_stamp = 0;
     bool emit_by_rank(int32_t rid) {
         const PlanHost::Segment& r = ph.segs[rid];
-        const int per_unit = few ? std::max(1, cap / n_sl) : std::max(1, 4 * kMaxRowTiles * cap / n_sl);  // threads
+        const int per_unit = few ? std::max(1, few * cap / n_sl) : std::max(1, 4 * kMaxRowTiles * cap / n_sl);  // threads
         const int n_units = (r.n_shr + per_unit - 1) / per_unit;
         const int64_t block_cap = (int64_t)4 * prm.max_unit_tiles;
         if (seg_mark.size() != ph.segs.size()) seg_mark.assign(ph.segs.size(), -1);
@@ -659,17 +662,20 @@ int build_plan(const PlanThreadView* threads, int n, const int32_t* refcount, in
     }
     const int cap = bld.cap, n_sl = bld.n_sl;
     if (prm.few_units > 0 && prm.fuse && prm.inline_shared && prm.allow_direct) {
-        int64_t units = 0, tiles = 0, again = 0;
-        bool wide = false;
-        for (const PlanHost::Segment& s : segs) {
-            const int64_t readers = n_sl == 1 ? (s.n_shr + cap - 1) / cap : (int64_t)s.n_shr * n_sl;
-            tiles += readers * s.n_blk;
-            again += (readers - 1) * s.n_blk;
-            if (s.parent >= 0) continue;
-            units += readers;
-            wide = wide || (readers > kFewTreeUnits && cap > kFewTreeThreads);
+        for (int nt = 1; nt <= std::min(prm.few_row_tiles, kMaxRowTiles) && !bld.few; ++nt) {
+            int64_t units = 0, tiles = 0, again = 0;
+            bool wide = false;
+            for (const PlanHost::Segment& s : segs) {
+                const int per_unit = nt * cap;
+                const int64_t readers = n_sl == 1 ? (s.n_shr + per_unit - 1) / per_unit : (int64_t)s.n_shr * ((n_sl + per_unit - 1) / per_unit);
+                tiles += readers * s.n_blk;
+                again += (readers - 1) * s.n_blk;
+                if (s.parent >= 0) continue;
+                units += readers;
+                wide = wide || ((s.n_shr + cap - 1) / cap > kFewTreeUnits && cap > kFewTreeThreads);
+            }
+            if (!wide && units <= prm.few_units && tiles <= kFewTiles && again <= (nt == 1 ? prm.few_again : prm.few_again_wide)) bld.few = nt;
         }
-        bld.few = !wide && units <= prm.few_units && tiles <= kFewTiles && again <= prm.few_again;
     }
     for (int32_t m = 0; m < n_seg; ++m) {
         PlanHost::Segment& s = segs[m];
@@ -685,7 +691,7 @@ int build_plan(const PlanThreadView* threads, int n, const int32_t* refcount, in
         }
         s.n_above = par >= 0 ? segs[par].n_above + bld.n_chunks[par] : 0;
         const int groups = s.n_shr * n_sl;
-        const bool few_rows = groups <= (bld.few ? 1 : 4 * kMaxRowTiles) * cap;
+        const bool few_rows = groups <= (bld.few ? bld.few : 4 * kMaxRowTiles) * cap;
         if (prm.fuse && few_rows && s.tiles_sub <= (int64_t)(groups <= cap && !bld.few ? 1 : 4) * prm.max_unit_tiles) {
             s.unit = m;  // a unit is named after its root segment
             bld.emit_fused(m);

@@ -97,7 +97,9 @@ struct PlanParams {
     int32_t matrix_min_blocks = 0;  // ... and at least this many blocks become matrix units
     int32_t few_units = 0;          // calls whose threads fit this many units of 16 rows get such units: no shared lists, every tree's
                                     // tiles divided over the four wavefronts of a workgroup (0: never)
-    int32_t few_again = 0;          // ... if they read no more tiles than this again
+    int32_t few_row_tiles = 1;      // ... or this many times 16 rows, where units of 16 do not fit ...
+    int32_t few_again = 0;          // ... if they read no more tiles than this again, ...
+    int32_t few_again_wide = 0;     // ... or this many, units of 32 rows
     int32_t few_open_cost = 1;      // a tile that is not full, in full tiles, there
     int32_t open_cost = 1;          // a tile that is not full, in full tiles, where a list is cut four ways
 
@@ -105,10 +107,10 @@ struct PlanParams {
     bool operator==(const PlanParams& b) const {
         return rows_per_thread == b.rows_per_thread && max_unit_tiles == b.max_unit_tiles && allow_direct == b.allow_direct &&
                fuse == b.fuse && inline_shared == b.inline_shared && matrix_min_rows == b.matrix_min_rows &&
-               matrix_min_blocks == b.matrix_min_blocks && few_units == b.few_units && few_again == b.few_again && few_open_cost == b.few_open_cost && open_cost == b.open_cost;
+               matrix_min_blocks == b.matrix_min_blocks && few_units == b.few_units && few_row_tiles == b.few_row_tiles && few_again == b.few_again && few_again_wide == b.few_again_wide && few_open_cost == b.few_open_cost && open_cost == b.open_cost;
     }
 };
-static_assert(sizeof(PlanParams) == 36, "a parameter more belongs into the comparison");
+static_assert(sizeof(PlanParams) == 44, "a parameter more belongs into the comparison");
 
 struct PrefillThreadView {  // one listed thread of a prefill call
     const int32_t* table;

@@ -25,63 +25,66 @@ def workgroups(h):
 
 
 def every_row_group_once(h, live, slices):
-    """Every slice of every thread is one direct unit's, which lists each block of the thread's table once."""
+    """Every slice of every thread is in one direct unit, which lists each block of the thread's table once."""
     wgs = workgroups(h)
     tiles = np.asarray(ap.apar_last_plan_export(h, ap.APAR_PLAN_TILES)).reshape(-1, 2)
     dfs = ap.apar_last_plan_export(h, ap.APAR_PLAN_DFS_THREADS)
-    assert sorted(wg[6] for wg in wgs) == list(range(len(live) * slices)) and ap.apar_last_plan_info(h).n_partial_rows == 0
+    assert sorted(g for wg in wgs for g in range(wg[6], wg[6] + wg[7])) == list(range(len(live) * slices))
+    assert ap.apar_last_plan_info(h).n_partial_rows == 0
     for wg in wgs:
+        assert wg[6] // slices == (wg[6] + wg[7] - 1) // slices and wg[3] & 255 == wg[7]  # (a row tile per slice, of one thread)
         thread = live[dfs[wg[6] // slices]]
         table, length, got = ap.apar_thread_block_table(h, thread), ap.apar_thread_len(h, thread), []
         for k in range(4):
             ofs, n, lo, groups, _, flags = wg[4 + 6 * k:10 + 6 * k]
-            assert lo == wg[6] and groups == 1 and flags == 3
+            assert lo == wg[6] and groups == wg[7] and flags == 3
             fills = [int(m) >> 20 & 31 for _, m in tiles[ofs:ofs + n]]
-            assert all(int(m) & 0xfffff == 1 << 10 for _, m in tiles[ofs:ofs + n]) and [f == 16 for f in fills] == [i < wg[28 + k] for i in range(n)]
+            assert all(int(m) & 0xfffff == groups << 10 for _, m in tiles[ofs:ofs + n]) and [f == 16 for f in fills] == [i < wg[28 + k] for i in range(n)]
             got += [(int(b), f) for (b, _), f in zip(tiles[ofs:ofs + n], fills)]
         # (a block that is not the last is full)
         assert sorted(got) == sorted((b, min(16, length - 16 * i)) for i, b in enumerate(table))
 
 
-# kv heads, q heads per kv head, (prompt, leaves) per tree, whether the call is one of few units
+# kv heads, q heads per kv head, (prompt, leaves) per tree, row tiles of the units by data type (0: not a call of few units)
+BF16, FP8, F32 = "bf16", "bf16_fp8kv", "f32"
 CALLS = [
-    (2, 1, [(300, [20 + k for k in range(17)])], True),           # 17 rows: two units
-    (2, 1, [(300, [5] * 64)], True),
-    (2, 1, [(300, [5] * 65)], False),                              # five units
-    (8, 4, [(100, [30] * 5), (17, [1, 16, 17, 40, 8, 90])], True),
-    (8, 16, [(64, [9, 16, 33])], True),
-    (8, 5, [(64, [9, 16, 33, 1, 70])], True),
-    (8, 1, [(40, [10] * 20)] * 64, True),                          # 128 units x 8 heads
-    (8, 1, [(40, [10] * 20)] * 65, False),
-    (8, 4, [(40, [10] * 30)] * 2, True),                           # eight units each, of four threads
-    (8, 8, [(16 * 590, [40] * 8)], True),                          # read four times: 3 x 590 tiles x 64 KiB
-    (8, 8, [(16 * 900, [40] * 8)], False),
-    (1, 1, [(16 * 2100, [1] * 18)], False),                        # more tiles than a unit may list
+    (2, 1, [(300, [20 + k for k in range(17)])], {BF16: 1, FP8: 1, F32: 1}),           # 17 rows: two units
+    (2, 1, [(300, [5] * 64)], {BF16: 1, FP8: 1, F32: 1}),
+    (2, 1, [(300, [5] * 65)], {BF16: 0, FP8: 0, F32: 0}),                                # five units of sixteen threads
+    (8, 4, [(100, [30] * 5), (17, [1, 16, 17, 40, 8, 90])], {BF16: 1, FP8: 1, F32: 1}),
+    (8, 16, [(64, [9, 16, 33])], {BF16: 1, FP8: 1, F32: 1}),
+    (8, 5, [(64, [9, 16, 33, 1, 70])], {BF16: 1, FP8: 1, F32: 1}),
+    (8, 1, [(40, [10] * 20)] * 64, {BF16: 1, FP8: 1, F32: 1}),                           # 128 units x 8 heads
+    (8, 1, [(40, [10] * 20)] * 65, {BF16: 2, FP8: 2, F32: 0}),                           # (130; 65 of two row tiles)
+    (8, 1, [(40, [10] * 20)] * 129, {BF16: 0, FP8: 0, F32: 0}),
+    (8, 4, [(40, [10] * 30)] * 2, {BF16: 1, FP8: 1, F32: 1}),                            # eight units each, of four threads
+    (8, 8, [(16 * 590, [40] * 8)], {BF16: 2, FP8: 1, F32: 1}),                           # three more readers of 590 tiles x 64 KiB
+    (8, 8, [(16 * 1000, [40] * 8)], {BF16: 2, FP8: 2, F32: 1}),
+    (8, 8, [(16 * 1000, [40] * 16)], {BF16: 0, FP8: 2, F32: 1}),                         # (and three of two row tiles)
+    (1, 1, [(16 * 2100, [1] * 18)], {BF16: 0, FP8: 0, F32: 0}),                          # more tiles than a unit may list
 ]
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "bf16_fp8kv", "f32"])
+@pytest.mark.parametrize("dtype", [BF16, FP8, F32])
 @pytest.mark.parametrize("n_kv,group,trees,few", CALLS)
 def test_plans_of_few_units(dtype, n_kv, group, trees, few):
-    if dtype != "bf16" and trees[0][0] > 16 * 700:
-        few = trees[0][0] <= 16 * 2048  # (fp8: half the bytes are read again; fp32: none that wider units do not)
     blocks = sum(p // 16 + 2 + sum(n // 16 + 2 for n in leaves) for p, leaves in trees)
-    with ap.Pool(n_kv * group, n_kv, 128, dtype, blocks, max_threads=2048, dry_run=True) as pool:
+    with ap.Pool(n_kv * group, n_kv, 128, dtype, blocks, max_threads=4096, dry_run=True) as pool:
         h = pool.handle
         live = [t for prompt, leaves in trees for t in grow(h, prompt, leaves)]
         ap.apar_decode_attention(h, None, live, None)
         check_plan_covers_tables(h, live, n_kv, group)
         wgs = workgroups(h)
-        cap = 16 // group
-        units = sum(-(-len(leaves) // cap) for _, leaves in trees)
-        narrow = all(wg[1] == 0 and wg[3] & 255 == 1 for wg in wgs)
-        if few:
-            assert narrow and len(wgs) == units
+        per_unit = max(1, few[dtype]) * (16 // group)
+        units = sum(-(-len(leaves) // per_unit) for _, leaves in trees)
+        shared = any(wg[1] > 0 for wg in wgs)
+        if few[dtype]:
+            assert not shared and len(wgs) == units and max(wg[3] & 255 for wg in wgs) == few[dtype]
             for wg in wgs:
                 tiles, full = [wg[5 + 6 * k] for k in range(4)], wg[28:32]
                 assert all(wg[9 + 6 * k] & 2 for k in range(4)) and max(tiles) - min(tiles) <= 1 + max(t - f for t, f in zip(tiles, full))
         else:
-            assert not narrow or len(wgs) != units
+            assert shared or ap.apar_last_plan_info(h).n_partial_rows > 0
         ap.apar_set_inline_shared(h, False)  # nothing is cut by rank
         ap.apar_decode_attention(h, None, live, None)
         check_plan_covers_tables(h, live, n_kv, group)
@@ -110,7 +113,7 @@ def test_a_loop_carries_them(seed):
         assert built + carried == 60 and built <= 2
 
 
-@pytest.mark.parametrize("n_kv,group,cand,few", [(8, 8, 3, True), (1, 8, 8, True), (8, 16, 4, True), (2, 5, 5, True), (16, 16, 4, False)])
+@pytest.mark.parametrize("n_kv,group,cand,few", [(8, 8, 3, 1), (1, 8, 8, 1), (8, 16, 4, 1), (2, 5, 5, 1), (16, 16, 4, 2), (16, 8, 5, 1), (32, 16, 4, 0)])
 def test_threads_of_more_rows_than_a_unit_holds(n_kv, group, cand, few):
     """A unit per slice of every thread; a call with the same list carries the plan over, one after an append builds another."""
     with ap.Pool(n_kv * group, n_kv, 128, "bf16", 2048, max_threads=256, dry_run=True) as pool:
@@ -124,8 +127,7 @@ def test_threads_of_more_rows_than_a_unit_holds(n_kv, group, cand, few):
                 every_row_group_once(h, live, slices)
             else:
                 check_plan_covers_tables(h, live, n_kv, cand * group)
-            narrow = all(wg[1] == 0 and wg[3] & 255 == 1 for wg in workgroups(h))
-            assert narrow == few and (not few or sum(wg[7] for wg in workgroups(h)) == len(live) * slices)
+            assert (max(wg[3] & 255 for wg in workgroups(h)) if not any(wg[1] for wg in workgroups(h)) else 0) == few
             built = ap.apar_plan_counts(h)[0]
             spec()
             assert ap.apar_plan_counts(h)[0] == built
