@@ -212,13 +212,24 @@ struct AppendBlock {
 };
 static_assert(sizeof(AppendBlock) == 16, "four words of the staged tables");
 constexpr int kAppendInlineWords = 480;
-template <bool INLINE>
+// Most blocks of a long append are a run: whole, in the order of the source rows.  Of those only the block goes along: words 0 and 1
+// are the number of the blocks before the run and the run's first source row, then come the former (from word 4) and the run.
+constexpr int kAppendRunWords = 960, kAppendRunMaxBefore = 8;
+// Where the run starts that ends a call's blocks, or -1 if they do not fit that way.
+inline int append_run(const AppendBlock* b, int n) {
+    int at = n;
+    while (at > 0 && b[at - 1].slots == 16 << 8 && b[at - 1].copy_of < 0 && (at == n || b[at - 1].first + 16 == b[at].first)) --at;
+    return at < n && at <= kAppendRunMaxBefore && 4 + 4 * at + (n - at) <= kAppendRunWords ? at : -1;
+}
+// Where an append's descriptors and source rows are: on the device, or the kernel's first argument, all of them or as a run.
+enum AppendFrom { kAppendDevice, kAppendArguments, kAppendRun };
+template <int FROM>
 struct AppendTables {
-    const int32_t* words;
+    int32_t words[FROM == kAppendRun ? kAppendRunWords : kAppendInlineWords];
 };
 template <>
-struct AppendTables<true> {
-    int32_t words[kAppendInlineWords];
+struct AppendTables<kAppendDevice> {
+    const int32_t* words;
 };
 
 // Partial results: for partial row p, candidate c, q head h the slot is
@@ -245,8 +256,8 @@ constexpr size_t kSplitCounterBytes = (size_t)kSplitMaxCut * 4 * sizeof(int32_t)
 hipError_t fixed_workspace_of_device(int device, char** out);
 
 // ---- launchers (defined next to their kernels) ------------------------------
-// words: n_blocks AppendBlocks, the n_open that stay open first, then n_src source rows; on the host (at most kAppendInlineWords words, which go along
-// with the kernel's arguments) or on the device.
+// words: n_blocks AppendBlocks, the n_open that stay open first, then n_src source rows; on the host (at most kAppendInlineWords words, or,
+// without source rows on 16-bit pools, blocks that append_run takes, which go along with the kernel's arguments) or on the device.
 hipError_t launch_append_blocks(const Shape& s, void* pool, const void* k, const void* v, const int32_t* words, bool on_host,
                                 int n_blocks, int n_open, int n_src, hipStream_t st);
 hipError_t launch_block_copies(const Shape& s, void* pool, const int32_t* src_dst_pairs, int n_pairs,

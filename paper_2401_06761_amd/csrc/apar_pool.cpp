@@ -377,13 +377,17 @@ int run_append(apar_pool* p, const std::vector<int32_t>& codes, const std::vecto
         for (size_t i = 0; i + 1 < copies.size(); i += 2) blocks[at[copies[i + 1]]].copy_of = copies[i];
     for (const AppendBlock& b : blocks) at[b.dst] = -1;
     int n_open = (int)blocks.size();  // the blocks that are not sealed come first
-    if (p->shape.dtype != APAR_F32)
-        n_open = (int)(std::partition(blocks.begin(), blocks.end(), [](const AppendBlock& b) { return b.slots >> 8 < kBlockTokens; }) -
-                       blocks.begin());
-
     const size_t words = blocks.size() * 4 + src.size();
     const size_t copy_words = copies_first ? copies.size() : 0;
-    const bool inlined = words <= (size_t)kAppendInlineWords && copy_words == 0;
+    bool inlined = words <= (size_t)kAppendInlineWords && copy_words == 0;
+    if (p->shape.dtype != APAR_F32) {
+        auto stays_open = [](const AppendBlock& b) { return b.slots >> 8 < kBlockTokens; };
+        const bool maybe_run = !inlined && copy_words == 0 && src.empty();
+        n_open = (int)((maybe_run ? std::stable_partition(blocks.begin(), blocks.end(), stays_open)
+                                  : std::partition(blocks.begin(), blocks.end(), stays_open)) -
+                       blocks.begin());
+        inlined = inlined || (maybe_run && append_run(blocks.data(), (int)blocks.size()) >= 0);
+    }
     const int32_t* tables = (const int32_t*)blocks.data();
     StageSlot* s = nullptr;
     int rc = APAR_OK;

@@ -1,6 +1,8 @@
 // Row writes, copy-on-write block copies, row read-back and the merge kernel (gfx950).
 #include <hip/hip_runtime.h>
 
+#include <cstring>
+
 #include "apar_internal.hpp"
 
 namespace apar {
@@ -66,23 +68,31 @@ __device__ __forceinline__ uint2 fp8_piece(const uint16_t (&x)[8], float inv) {
     return make_uint2(w[0], w[1]);
 }
 
-// ROW: bytes of one row of a half.  SEAL: 0 fp32 pools (nothing is sealed), 1 bf16, 2 fp8.  INLINE: the descriptors and
-// the source rows come with the kernel's arguments (the first one, so that they start the argument segment).
+// ROW: bytes of one row of a half.  SEAL: 0 fp32 pools (nothing is sealed), 1 bf16, 2 fp8.  FROM: where the descriptors and
+// the source rows are (in the kernel's arguments: its first one, so that they start the argument segment).  Blocks of a run go along
+// with a word each: a prompt of 2 k to 8 k tokens (8 kv heads) does without the copy of its table and the gap behind it (six such prompts
+// and their attention 1763 -> 1720 us).
 // In the tables the blocks that stay open come first, n_open of them.  The first workgroups take the full ones, a wavefront per
 // (block, kv head), so that the launch does not end on them; the others write the open ones, as many lanes as a row has
 // 16-byte pieces per (block, kv head).  A full block's earlier rows are read with non-temporal loads, other rows (the caller's,
 // shared tails) with plain ones.  Measured, us: 3.8 k threads, 32 heads, one row each, one block in sixteen full: full blocks
 // last 59.6, first 56.4, non-temporal loads for their own rows 47.0; for every row 51.4, and 1000 copies of a tail of 9
 // rows 76 instead of 44.
-template <int ROW, int SEAL, bool INLINE>
-__global__ __launch_bounds__(256) void append_blocks(AppendTables<INLINE> tables, char* __restrict__ pool, const char* __restrict__ k,
+template <int ROW, int SEAL, int FROM>
+__global__ __launch_bounds__(256) void append_blocks(AppendTables<FROM> tables, char* __restrict__ pool, const char* __restrict__ k,
                                                      const char* __restrict__ v, int n_blocks, int n_open, int n_src, int n_kv) {
     // one half's rows per wavefront: the open blocks' workgroups want the occupancy
     __shared__ __attribute__((aligned(16))) char lds[SEAL ? 4 : 1][SEAL ? 16 * kSealRowStride : 16];
     constexpr int64_t kTile = 2 * 16 * ROW;
     constexpr int kLanes = 2 * ROW / 16;      // lanes of one row: its K half, then its V half
     auto block_at = [&](int at) -> AppendBlock {
-        if constexpr (INLINE) {
+        if constexpr (FROM == kAppendRun) {
+            typedef const int32_t __attribute__((address_space(4))) * Words;
+            const auto w = (Words)__builtin_amdgcn_kernarg_segment_ptr();
+            const int before = w[0];
+            if (at < before) return AppendBlock{w[4 + 4 * at], w[5 + 4 * at], w[6 + 4 * at], w[7 + 4 * at]};
+            return AppendBlock{w[4 + 3 * before + at], -1, w[1] + 16 * (at - before), 16 << 8};
+        } else if constexpr (FROM == kAppendArguments) {
             typedef const AppendBlock __attribute__((address_space(4))) * Blocks;
             const auto* p = (Blocks)__builtin_amdgcn_kernarg_segment_ptr() + at;
             return AppendBlock{p->dst, p->copy_of, p->first, p->slots};
@@ -91,7 +101,9 @@ __global__ __launch_bounds__(256) void append_blocks(AppendTables<INLINE> tables
         }
     };
     auto src_of = [&](int i) -> int {
-        if constexpr (INLINE) {
+        if constexpr (FROM == kAppendRun) {
+            return i;  // (a run has no list of source rows)
+        } else if constexpr (FROM == kAppendArguments) {
             typedef const int32_t __attribute__((address_space(4))) * Words;
             return ((Words)__builtin_amdgcn_kernarg_segment_ptr())[4 * n_blocks + i];
         } else {
@@ -405,19 +417,36 @@ hipError_t launch_append_blocks(const Shape& s, void* pool, const void* k, const
     const int pairs = s.dtype == APAR_F32 && s.d == 128 ? 4 : 8;
     const int64_t grid = ((int64_t)n_open * s.n_kv + pairs - 1) / pairs + ((int64_t)(n_blocks - n_open) * s.n_kv + 3) / 4;
     if (grid > 0x7fffffff || (int64_t)n_blocks * s.n_kv > 0x7fffffff) return hipErrorInvalidValue;
-    AppendTables<false> ptr{words};
-    AppendTables<true> args;
+    AppendTables<kAppendDevice> ptr{words};
+    AppendTables<kAppendArguments> args;
+    if (on_host && (size_t)4 * n_blocks + n_src > sizeof(args.words) / sizeof(int32_t)) {
+        const AppendBlock* b = (const AppendBlock*)words;
+        const int before = n_src == 0 ? append_run(b, n_blocks) : -1;
+        if (before < 0 || s.dtype == APAR_F32) return hipErrorInvalidValue;
+        AppendTables<kAppendRun> run;
+        run.words[0] = before;
+        run.words[1] = b[before].first;
+        run.words[2] = run.words[3] = 0;
+        memcpy(run.words + 4, b, before * sizeof(AppendBlock));
+        for (int i = before; i < n_blocks; ++i) run.words[4 + 3 * before + i] = b[i].dst;
+        if (s.fp8_sealed)
+            hipLaunchKernelGGL((append_blocks<256, 2, kAppendRun>), dim3((unsigned)grid), dim3(256), 0, st, run, (char*)pool,
+                               (const char*)k, (const char*)v, n_blocks, n_open, 0, s.n_kv);
+        else
+            hipLaunchKernelGGL((append_blocks<256, 1, kAppendRun>), dim3((unsigned)grid), dim3(256), 0, st, run, (char*)pool,
+                               (const char*)k, (const char*)v, n_blocks, n_open, 0, s.n_kv);
+        return hipGetLastError();
+    }
     if (on_host) {
-        if ((size_t)4 * n_blocks + n_src > sizeof(args.words) / sizeof(int32_t)) return hipErrorInvalidValue;
         for (int i = 0; i < 4 * n_blocks + n_src; ++i) args.words[i] = words[i];
     }
 #define APAR_APPEND(ROWV, SEALV)                                                                                           \
     do {                                                                                                                   \
         if (on_host)                                                                                                       \
-            hipLaunchKernelGGL((append_blocks<ROWV, SEALV, true>), dim3((unsigned)grid), dim3(256), 0, st, args,           \
+            hipLaunchKernelGGL((append_blocks<ROWV, SEALV, kAppendArguments>), dim3((unsigned)grid), dim3(256), 0, st, args,           \
                                (char*)pool, (const char*)k, (const char*)v, n_blocks, n_open, n_src, s.n_kv);                      \
         else                                                                                                               \
-            hipLaunchKernelGGL((append_blocks<ROWV, SEALV, false>), dim3((unsigned)grid), dim3(256), 0, st, ptr,           \
+            hipLaunchKernelGGL((append_blocks<ROWV, SEALV, kAppendDevice>), dim3((unsigned)grid), dim3(256), 0, st, ptr,           \
                                (char*)pool, (const char*)k, (const char*)v, n_blocks, n_open, n_src, s.n_kv);                      \
     } while (0)
     if (s.dtype == APAR_F32) {
