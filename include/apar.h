@@ -469,7 +469,9 @@ enum { APAR_PLAN_WORKGROUPS = 0, APAR_PLAN_TILES = 1, APAR_PLAN_DFS_THREADS = 2,
        APAR_PLAN_PATH_IDS = 4, APAR_PLAN_GEOMETRY = 5, APAR_PLAN_CHANGED_WORKGROUP_WORDS = 6,
        APAR_PLAN_CHANGED_TILE_WORDS = 7 };
 APAR_API int apar_last_plan_export(apar_pool* pool, int which, int32_t* out, int64_t cap, int64_t* n_out);
-/* Tuning knob: the most blocks one wavefront is given in one work unit (1..65536; default 512).
+/* Tuning knob: the most blocks one wavefront is given in one work unit (1..65536; default 512).  A pool on which this
+ * knob or one of the next two was set, to whatever value, plans its decode calls by them alone: calls of few threads
+ * then get no units of their own.
  * Sharing subtrees with more blocks than that are cut into several units whose partial results are
  * merged afterwards; small values exist to exercise that path. */
 APAR_API int apar_set_chunk_blocks(apar_pool* pool, int blocks_per_unit);

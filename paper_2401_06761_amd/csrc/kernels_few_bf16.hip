@@ -1,12 +1,14 @@
-// Decode attention over bf16 KV tiles: launches of few workgroups.
+// Decode attention over bf16 KV tiles: calls of few units (PlanDev::few; the rule stands in apar_pool.cpp).
 //
-// Units without shared lists, one row tile, no more workgroups than the chip has compute units (PlanDev::few): what a call takes
-// is one wavefront's chain of latencies, and every wavefront has a SIMD's registers to itself.  What the chain was made of (one
-// request of five threads, 32 heads, cycles of 26 k): descriptor and queries 3.5 k, a tile 1180 with one in flight, an open tile
-// 1600 (its K gathered sixteen bytes a row), fold by one wavefront and output 4.5 k.  So here two tiles (three of fp8 codes) are
-// on their way at any time, open tiles among them: every tile is fetched the same way, KiB by KiB, and an open one's rows are
-// put into operand order through LDS.  The four wavefronts of a divided list fold and write a quarter of the dims each.
-// One compute unit takes 50 bytes per cycle however many loads are on their way: 640 cycles per tile and wavefront.
+// Units without shared lists, of one row tile or two.  What bounds such a call is one wavefront's chain of latencies; what it was made
+// of by the kernel for any unit (one request of five threads, 32 heads, 26 k cycles): descriptor and queries 3.5 k, a tile 1180 with one
+// in flight (products and softmax take 350), an open tile 1600 (its K gathered sixteen bytes a row), fold by one wavefront and output
+// 4.5 k.  So here two tiles (three of fp8 codes) are on their way at any time, open tiles among them: every tile is fetched the same
+// way, KiB by KiB, and an open one's rows are put into operand order through LDS.  The four wavefronts of a divided list fold and write
+// a quarter of the dims each.  13.5 -> 8.9 us per call; with 8 kv heads 14.4 -> 8.5 (in two units instead of one of two wavefronts).
+// One compute unit takes 50 bytes per cycle however many loads are on their way, 640 cycles per tile and wavefront, so that a tile
+// takes 720 with two on their way.  Two row tiles (where units of 16 rows would read shared segments too often): the queries lie in
+// LDS, which leaves registers for the two tiles (202; four requests of 4 k tokens, group 8 32.2 -> 27.8 us).
 #include <hip/hip_runtime.h>
 
 #include <cstring>
@@ -333,7 +335,7 @@ __device__ __forceinline__ void attend_few(char* lds, const Slice& slice, const 
     for (int nt = 0; nt < NT; ++nt) write(std::integral_constant<int, 2>{}, j0, nt);
 }
 
-// Launches of few workgroups (attend_few): one wavefront per SIMD.
+// (Two wavefronts per SIMD: declared for one, the compiler keeps accumulators in the other register file and copies them per tile.)
 template <int NT, bool F8, bool SPLIT, bool INLINE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attention_bf16_few(
     PlanWords<INLINE>, const char* __restrict__ pool, const uint16_t* __restrict__ q, PlanDev plan, int n_cand, int n_q, int n_kv,

@@ -29,6 +29,9 @@
 // with many rows that are better off on the matrix kernel) a top segment stands alone,
 // chunked, with one partial result per (chunk, thread), and its children are tried
 // again.  Attention is a set operation, so a unit may visit its blocks in any order.
+//
+// Calls of few units (PlanParams::few_units) are latency, not traffic: there every unit has 16 rows (or 32), no
+// shared list, and its tiles divided over the four wavefronts.
 #include "plan.hpp"
 
 #include <algorithm>
@@ -73,6 +76,11 @@ struct Builder {
         n_sl = (q.rows_per_thread + 15) / 16;
         rps = (q.rows_per_thread + n_sl - 1) / n_sl;
         cap = 16 / rps;
+    }
+
+    // a segment that is left to the matrix kernel where it stands alone
+    bool to_matrix(const PlanHost::Segment& s) const {
+        return prm.matrix_min_rows > 0 && (int64_t)s.n_shr * prm.rows_per_thread >= prm.matrix_min_rows && s.n_blk >= prm.matrix_min_blocks;
     }
 
     // fewest 16-row tiles per wavefront with which one workgroup holds `groups` row groups (the most if none does)
@@ -169,8 +177,7 @@ struct Builder {
                 if (tail_here) note_tail(s, ph.narrow_items.size(), kNarrowItem, 0, groups);
                 emit_narrow(ofs, (int32_t)ph.tiles.size() - ofs, n_full, grp0, groups, pbase, 0);
                 if (tail_here) leave_slack(1);
-            } else if (prm.matrix_min_rows > 0 && (int64_t)s.n_shr * prm.rows_per_thread >= prm.matrix_min_rows &&
-                       s.n_blk >= prm.matrix_min_blocks) {
+            } else if (to_matrix(s)) {
                 // matrix units: whole threads, as evenly over the workgroups as they go
                 const int per_wg = kMatrixUnitMaxRows / prm.rows_per_thread;  // >= 2: rows_per_thread <= 64
                 const int n_wg = (s.n_shr + per_wg - 1) / per_wg;
@@ -260,7 +267,7 @@ struct Builder {
         }
         for (int32_t t = 0; t < u.n_thr; ++t)
             for (int32_t g = 0; g < n_sl; g += few * cap)
-                emit_few_groups(u, (u.r_lo + t) * n_sl + g, std::min(few * cap, n_sl - g), pbase, flags);
+                emit_few_groups(u, (u.r_lo + t) * n_sl + g, std::min(few * cap, n_sl - g), u.direct ? pbase : pbase + t, flags);
     }
     void emit_few_groups(const UnitSpec& u, int32_t grp0, int groups, int32_t pbase, int32_t flags) {
         int n_full[4] = {0, 0, 0, 0}, n_open[4] = {0, 0, 0, 0}, n_tails[4] = {0, 0, 0, 0};
@@ -672,7 +679,7 @@ int build_plan(const PlanThreadView* threads, int n, const int32_t* refcount, in
                 again += (readers - 1) * s.n_blk;
                 if (s.parent >= 0) continue;
                 units += readers;
-                wide = wide || ((s.n_shr + cap - 1) / cap > kFewTreeUnits && cap > kFewTreeThreads);
+                wide = wide || ((s.n_shr + cap - 1) / cap > kFewTreeUnits && cap > kFewTreeThreads) || bld.to_matrix(s);
             }
             if (!wide && units <= prm.few_units && tiles <= kFewTiles && again <= (nt == 1 ? prm.few_again : prm.few_again_wide)) bld.few = nt;
         }
@@ -704,9 +711,7 @@ int build_plan(const PlanThreadView* threads, int n, const int32_t* refcount, in
         // matrix kernel, and with too many blocks for few rows a segment is better read once: those stand
         // alone - chunked, one partial result per (chunk, thread), merged afterwards - and their children
         // are tried again.
-        const bool to_matrix = prm.matrix_min_rows > 0 && (int64_t)s.n_shr * prm.rows_per_thread >= prm.matrix_min_rows &&
-                               s.n_blk >= prm.matrix_min_blocks;
-        if (prm.fuse && prm.inline_shared && prm.allow_direct && s.n_above == 0 && !to_matrix && !few_rows && bld.emit_by_rank(m))
+        if (prm.fuse && prm.inline_shared && prm.allow_direct && s.n_above == 0 && !bld.to_matrix(s) && !few_rows && bld.emit_by_rank(m))
             continue;
         bld.emit_standalone(m);
     }
