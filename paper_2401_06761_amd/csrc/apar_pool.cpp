@@ -582,13 +582,10 @@ bool inline_plan(apar_pool* p, const PlanHost& ph) {
     return true;
 }
 
-// What an open tile costs a wavefront of the 16-bit kernel: its V half takes a turn through LDS and nothing is in flight
-// meanwhile (one request of five threads, 32 heads: 1.3 us per open tile, 0.6 per full one, 12.6 us for the wavefront that has
-// all five against 10.0 for the others).  On fp32 pools every tile is alike.
-// Counted as one, two and three: one request 15.9 / 14.2 / 14.6 us, four requests 27.9 / 25.3 / 25.6, 64 with 8 heads
-// 65.5 / 61.1 / 60.9, two requests 22.4 / 13.3 / 12.7 (whose wavefronts were long enough to be cut into slices).  fp8 pools, whose full
-// tiles have to be widened and whose open ones have not: 15.5 / 14.8 / 13.4, 29.7 / 27.1 / 24.2, 48.0 / 44.8 / 42.9, 25.9 / 14.8 / 12.2, 64
-// requests with 32 heads 131 / 127 / 121 (there three is the better count still).
+// What an open tile costs a wavefront of the 16-bit kernels, in full ones, where a list is cut four ways: its V half take a turn through
+// LDS, and on fp8 pools it is twice the bytes.  On fp32 pools every tile is alike.  Counted as one, two and three, us per call: one request
+// of five threads, 32 heads 9.4 / 8.8 / 8.8, four requests 17.6 / 18.5 / 17.7, 60 requests, 4 heads 22.0 / 21.3 / 21.1, twelve short ones, 8 heads 12.6 /
+// 12.3 / 12.0, 64 requests, 32 heads 214.8 / 213.4 / 213.9; fp8 one request 10.0 / 9.4 / 9.1, three short ones 9.5 / 8.7 / 8.5, 64 requests, 8 heads 41.5 / 41.8 / 41.8.
 constexpr int kOpenTileCost = 2;
 
 // fixed: the plan and the partial results go to the device's static workspace, nothing is allocated, no
