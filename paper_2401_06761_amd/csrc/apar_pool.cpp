@@ -106,7 +106,6 @@ struct apar_pool {
     bool plan_reuse = true;
     int64_t n_plans_built = 0, n_plans_carried = 0;
     bool planning_set = false;         // one of the planner's knobs was set: plans are built as told, none for few units
-    bool few_units = false;            // the plan's units go to the kernel for few workgroups
     int32_t plan_geom[3] = {1, 1, 1};  // rows per thread, rows per slice, slices of the last plan
 
     StageSlot stage[kStageSlots];
@@ -439,12 +438,6 @@ int run_append(apar_pool* p, const std::vector<int32_t>& codes, const std::vecto
 // 27.8, 150 71.0 / 78.8 / 63.5 and 29.5 / 32.6 / 31.3; by what units of 32 read: 200 54.8 / - / 66.4, 72.0 / - / 82.3, 75.8 / - / 42.9 (28 rows per thread).
 constexpr int64_t kFewAgainBytes = (int64_t)56 << 20, kFewAgainWideBytes = (int64_t)112 << 20;
 constexpr int32_t kFewUnits = 1024;
-bool few_units(const PlanHost& ph, const Shape& s) {
-    if (s.dtype != APAR_BF16 || ph.n_wg_class[0] > 0 || ph.wgs.size() * s.n_kv > (size_t)kFewUnits) return false;
-    for (const WgDesc& wg : ph.wgs)
-        if (wg.n_coop > 0) return false;
-    return true;
-}
 
 // Which units of a decode plan are cut into slices (attn_split.hpp), and the launch's workgroups in order.  A unit's cost
 // is the tiles a wavefront of it walks.  With T = total cost / shares, but at least kSliceMinTiles, units of more than T
@@ -681,10 +674,8 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     DeviceGuard guard(p->device);
     hipStream_t st = (hipStream_t)stream;
 
-    if (!carried) {  // (a carried plan keeps its cut)
-        p->few_units = few_units(ph, p->shape);
-        cut_into_slices(ph, p->shape, p->few_units, p->split_bytes, p->split_blocks, p->n_split_class);
-    }
+    const bool few = ph.few_row_tiles > 0 && p->shape.dtype != APAR_F32;  // (fp32 pools have one kernel for all units)
+    if (!carried) cut_into_slices(ph, p->shape, few, p->split_bytes, p->split_blocks, p->n_split_class);  // (a carried plan keeps its cut)
     // stage the tables in one copy
     size_t ofs[7];
     ofs[0] = 0;
@@ -804,7 +795,7 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     pd.split.arrived = (int32_t*)p->split_dev;  // (no room: nothing is cut and nothing reads either)
     pd.split.state = p->split_dev ? (float*)(p->split_dev + kSplitCounterBytes) : nullptr;
 
-    pd.few = p->few_units;
+    pd.few = few;
 
     if (inlined) {
         pd.wgs = (const WgDesc*)p->inline_ofs[0];

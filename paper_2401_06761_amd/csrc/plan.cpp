@@ -49,6 +49,7 @@ void PlanHost::clear() {
     dirty_wg_words.clear(), dirty_tile_words.clear();
     reusable = false;
     n_patched = 0;
+    few_row_tiles = 0;
 }
 
 namespace {
@@ -521,29 +522,69 @@ struct Builder {
         return blocks;
     }
 
+    // The units that the threads of segment r's subtree are cut into by rank: the fewest that hold them, evenly filled.
+    int n_by_rank(const PlanHost::Segment& r) const {
+        const int per_unit = few ? std::max(1, few * cap / n_sl) : std::max(1, 4 * kMaxRowTiles * cap / n_sl);  // threads
+        return (r.n_shr + per_unit - 1) / per_unit;
+    }
+    static void unit_by_rank(const PlanHost::Segment& r, int n_units, int k, int32_t& lo, int32_t& cnt) {
+        lo = r.t_lo + (int32_t)((int64_t)r.n_shr * k / n_units);
+        cnt = r.t_lo + (int32_t)((int64_t)r.n_shr * (k + 1) / n_units) - lo;
+    }
+    // Whether none of them would read more blocks than it may.
+    bool fits_by_rank(const PlanHost::Segment& r) {
+        const int64_t block_cap = (int64_t)4 * prm.max_unit_tiles;
+        if (r.tiles_sub <= block_cap) return true;
+        if (seg_mark.size() != ph.segs.size()) seg_mark.assign(ph.segs.size(), -1);
+        const int n_units = n_by_rank(r);
+        for (int k = 0; k < n_units; ++k) {
+            int32_t lo, cnt;
+            unit_by_rank(r, n_units, k, lo, cnt);
+            if (collect_range(lo, cnt, next_stamp++) > block_cap) return false;
+        }
+        return true;
+    }
+
+    // Row tiles that this call's units have at most if it is one of few units (PlanParams::few_units), 0 if it is another.  It is one
+    // only if all its units are of that kind: the kernels that read shared lists do not fold divided units of two row tiles, and
+    // below a segment that stands alone narrow units leave more partial results than wide ones.  So trees that would stand alone
+    // for their blocks make a call another one, but for trees of one row tile: whatever those are cut into has one row tile and no
+    // shared list.
+    int row_tiles_of_few() {
+        if (prm.few_units <= 0 || !prm.fuse || !prm.inline_shared || !prm.allow_direct) return 0;
+        for (few = 1; few <= std::min(prm.few_row_tiles, kMaxRowTiles); ++few) {
+            const int per_unit = few * cap;
+            int64_t units = 0, tiles = 0, again = 0;
+            bool fits = true;
+            for (const PlanHost::Segment& s : ph.segs) {
+                const int64_t readers = n_sl == 1 ? (s.n_shr + per_unit - 1) / per_unit : (int64_t)s.n_shr * ((n_sl + per_unit - 1) / per_unit);
+                tiles += readers * s.n_blk;
+                again += (readers - 1) * s.n_blk;
+                if (s.parent >= 0) continue;
+                const bool wide = (s.n_shr + cap - 1) / cap > kFewTreeUnits && cap > kFewTreeThreads;
+                const bool one_unit = s.tiles_sub <= (int64_t)4 * prm.max_unit_tiles;  // (by its blocks)
+                const int groups = s.n_shr * n_sl;
+                units += groups <= cap && !one_unit ? s.tiles_sub / prm.max_unit_tiles : readers;  // (its chunks)
+                fits = !wide && !to_matrix(s) && (groups <= cap || (groups <= per_unit ? one_unit : fits_by_rank(s)));
+                if (!fits || units > prm.few_units) break;
+            }
+            if (fits && units <= prm.few_units && tiles <= kFewTiles && again <= (few == 1 ? prm.few_again : prm.few_again_wide)) return few;
+        }
+        return 0;
+    }
+
     // The subtree of segment rid has more query rows than one workgroup carries (and nothing above it leaves
-    // partial results): its threads are cut by rank into the fewest units that hold them, evenly filled.  Every
-    // unit is direct.  Returns false, with nothing emitted, if some unit would read more blocks than it may.
+    // partial results): its threads are cut by rank into direct units.  Returns false, with nothing emitted, if some unit
+    // would read more blocks than it may.
     int32_t next_stamp = 0;
     bool emit_by_rank(int32_t rid) {
         const PlanHost::Segment& r = ph.segs[rid];
-        const int per_unit = few ? std::max(1, few * cap / n_sl) : std::max(1, 4 * kMaxRowTiles * cap / n_sl);  // threads
-        const int n_units = (r.n_shr + per_unit - 1) / per_unit;
-        const int64_t block_cap = (int64_t)4 * prm.max_unit_tiles;
+        if (!fits_by_rank(r)) return false;
         if (seg_mark.size() != ph.segs.size()) seg_mark.assign(ph.segs.size(), -1);
-        auto slice = [&](int k, int32_t& lo, int32_t& cnt) {
-            lo = r.t_lo + (int32_t)((int64_t)r.n_shr * k / n_units);
-            cnt = r.t_lo + (int32_t)((int64_t)r.n_shr * (k + 1) / n_units) - lo;
-        };
-        if (r.tiles_sub > block_cap)  // (otherwise no slice can exceed the cap)
-            for (int k = 0; k < n_units; ++k) {
-                int32_t lo, cnt;
-                slice(k, lo, cnt);
-                if (collect_range(lo, cnt, next_stamp++) > block_cap) return false;
-            }
+        const int n_units = n_by_rank(r);
         for (int k = 0; k < n_units; ++k) {
             int32_t lo, cnt;
-            slice(k, lo, cnt);
+            unit_by_rank(r, n_units, k, lo, cnt);
             collect_range(lo, cnt, next_stamp++);
             emit_unit(UnitSpec{-1, lo, cnt, rid, true});
         }
@@ -552,6 +593,16 @@ struct Builder {
     }
 
 };
+
+// What the kernels rely on: a call of few units has no shared list and no matrix unit, and only such a call has divided units of two
+// row tiles.
+bool kernels_take(const PlanHost& ph) {
+    for (const WgDesc& wg : ph.wgs) {
+        const int row_tiles = wg.row_tiles & 255;
+        if (ph.few_row_tiles ? wg.n_coop > 0 || row_tiles > ph.few_row_tiles : row_tiles == 2 && (wg.w[0].flags & kWaveSplit)) return false;
+    }
+    return true;
+}
 
 }  // namespace
 
@@ -668,22 +719,7 @@ int build_plan(const PlanThreadView* threads, int n, const int32_t* refcount, in
         ph.tails.assign(n, none);
     }
     const int cap = bld.cap, n_sl = bld.n_sl;
-    if (prm.few_units > 0 && prm.fuse && prm.inline_shared && prm.allow_direct) {
-        for (int nt = 1; nt <= std::min(prm.few_row_tiles, kMaxRowTiles) && !bld.few; ++nt) {
-            int64_t units = 0, tiles = 0, again = 0;
-            bool wide = false;
-            for (const PlanHost::Segment& s : segs) {
-                const int per_unit = nt * cap;
-                const int64_t readers = n_sl == 1 ? (s.n_shr + per_unit - 1) / per_unit : (int64_t)s.n_shr * ((n_sl + per_unit - 1) / per_unit);
-                tiles += readers * s.n_blk;
-                again += (readers - 1) * s.n_blk;
-                if (s.parent >= 0) continue;
-                units += readers;
-                wide = wide || ((s.n_shr + cap - 1) / cap > kFewTreeUnits && cap > kFewTreeThreads) || bld.to_matrix(s);
-            }
-            if (!wide && units <= prm.few_units && tiles <= kFewTiles && again <= (nt == 1 ? prm.few_again : prm.few_again_wide)) bld.few = nt;
-        }
-    }
+    bld.few = ph.few_row_tiles = bld.row_tiles_of_few();
     for (int32_t m = 0; m < n_seg; ++m) {
         PlanHost::Segment& s = segs[m];
         ph.unique_blocks += s.n_blk;
@@ -874,7 +910,7 @@ int build_plan(const PlanThreadView* threads, int n, const int32_t* refcount, in
         }
         ph.reusable = true;
     }
-    return APAR_OK;
+    return kernels_take(ph) ? APAR_OK : APAR_ERR_INTERNAL;
 }
 
 namespace {

@@ -27,6 +27,7 @@ struct PlanHost {
     int64_t full_blocks = 0;            // of the unique blocks, those with all sixteen slots filled
     int64_t n_direct_threads = 0;
     bool any_partial = false;
+    int32_t few_row_tiles = 0;          // a call of few units (PlanParams::few_units): the row tiles its units have at most; 0: another call
 
     // scratch kept between calls so that steady-state planning does not allocate
     struct Segment {

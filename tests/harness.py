@@ -235,6 +235,8 @@ def check_plan_covers_tables(handle, threads: Sequence[int], n_kv: int, rows_per
             if n_g == 0:
                 assert n_t == 0
                 continue
+            # a divided unit of two row tiles is for the kernel that knows no shared lists and no matrix units
+            assert not (flags & 2 and row_tiles == 2) or not (wgs[:, 1] > 0).any()
             for g in range(g_lo, g_lo + n_g):
                 rank = g // n_sl
                 lst = seen.setdefault(g, [])

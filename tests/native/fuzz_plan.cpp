@@ -6,6 +6,7 @@
 // every index in the plan must lie inside its array (the sanitizers watch the builder's own accesses), and every list says
 // how many of its tiles are full.
 #include <algorithm>
+#include <climits>
 #include <cstdio>
 #include <cstdlib>
 #include <map>
@@ -25,6 +26,8 @@ using namespace apar;
         }                                                                          \
     } while (0)
 
+static int n_few = 0;  // plans of calls of few units
+
 static int one(int seed) {
     std::mt19937 rng(seed);
     auto rnd = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
@@ -32,11 +35,12 @@ static int one(int seed) {
     struct Node { int parent; std::vector<int32_t> blocks; int last_valid; std::vector<int> kids; };
     std::vector<Node> nodes;
     int32_t next_block = 0;
-    const int n_roots = rnd(1, 3), max_nodes = rnd(4, 400);
+    const bool small = seed % 2;  // (the size of calls of few units)
+    const int n_roots = rnd(1, 3), max_nodes = rnd(4, small ? 60 : 400);
     for (int r = 0; r < n_roots; ++r) nodes.push_back(Node{-1, {}, 16, {}});
     while ((int)nodes.size() < max_nodes) {
         const int p = rnd(0, (int)nodes.size() - 1);
-        const int fan = rnd(1, rng() % 8 == 0 ? 200 : 6);
+        const int fan = rnd(1, rng() % 8 == 0 ? (small ? 20 : 200) : 6);
         for (int k = 0; k < fan; ++k) {
             nodes[p].kids.push_back((int)nodes.size());
             nodes.push_back(Node{p, {}, 16, {}});
@@ -94,6 +98,18 @@ static int one(int seed) {
         const int mblk[] = {1, 3, 128};
         prm.matrix_min_blocks = mblk[rng() % 3];
         prm.open_cost = rnd(1, 3);
+        const int units[] = {0, 1, 40, 1024};
+        prm.few_units = units[rng() % 4];
+        prm.few_row_tiles = rnd(1, 2);
+        const int again[] = {0, 100, 3000, INT_MAX};
+        prm.few_again = again[rng() % 4];
+        prm.few_again_wide = again[rng() % 4];
+        prm.few_open_cost = rnd(1, 2);
+        if (round == 2) {  // as a pool asks for them, but for the blocks of a unit
+            prm.allow_direct = prm.fuse = prm.inline_shared = true;
+            prm.matrix_min_rows = 256, prm.matrix_min_blocks = 128;
+            prm.few_units = 1024;
+        }
         CHECK(build_plan(views.data(), n, refcount.data(), seg_of.data(), prm, ph) == 0);
         for (int32_t x : seg_of) CHECK(x == -1);
         const int n_sl = (prm.rows_per_thread + 15) / 16;
@@ -105,7 +121,12 @@ static int one(int seed) {
             if (valid < 1 || valid > 16 || lo >= hi) err = 1;
             if (g - base >= lo && g - base < hi) seen[g][t.blk] += valid;
         };
+        CHECK(ph.few_row_tiles >= 0 && ph.few_row_tiles <= (prm.few_units > 0 ? prm.few_row_tiles : 0));
+        n_few += ph.few_row_tiles > 0;
         for (const WgDesc& wg : ph.wgs) {
+            // which kernel takes the unit: all of a call's are for the one without shared lists or none is
+            if (ph.few_row_tiles) CHECK(wg.n_coop == 0 && (wg.row_tiles & 255) <= ph.few_row_tiles);
+            else CHECK((wg.row_tiles & 255) != 2 || !(wg.w[0].flags & kWaveSplit));
             CHECK(wg.coop_ofs >= 0 && wg.n_coop >= 0 && (size_t)wg.coop_ofs + wg.n_coop <= n_tiles);
             for (int k = 0; k < 4; ++k) {
                 const WaveItem& wi = wg.w[k];
@@ -150,18 +171,22 @@ static int one(int seed) {
 
 // A plan built under other parameters is not carried over: every one of them counts.
 static int parameters(int seed) {
-    const PlanParams a{4, 512, true, true, true, 256, 128, 2};
+    PlanParams a{};
+    a.rows_per_thread = 4, a.max_unit_tiles = 512, a.allow_direct = true, a.fuse = true;
     CHECK(a == a);
-    for (int k = 0; k < 8; ++k) {
+    int32_t PlanParams::*const numbers[] = {&PlanParams::rows_per_thread, &PlanParams::max_unit_tiles, &PlanParams::matrix_min_rows,
+                                            &PlanParams::matrix_min_blocks, &PlanParams::few_units, &PlanParams::few_row_tiles,
+                                            &PlanParams::few_again, &PlanParams::few_again_wide, &PlanParams::few_open_cost, &PlanParams::open_cost};
+    bool PlanParams::*const flags[] = {&PlanParams::allow_direct, &PlanParams::fuse, &PlanParams::inline_shared};
+    static_assert(sizeof(PlanParams) == sizeof numbers / sizeof numbers[0] * 4 + 4, "every parameter is named here (the flags share a word)");
+    for (auto m : numbers) {
         PlanParams b = a;
-        if (k == 0) b.rows_per_thread = 5;
-        if (k == 1) b.max_unit_tiles = 5;
-        if (k == 2) b.allow_direct = false;
-        if (k == 3) b.fuse = false;
-        if (k == 4) b.inline_shared = false;
-        if (k == 5) b.matrix_min_rows = 5;
-        if (k == 6) b.matrix_min_blocks = 5;
-        if (k == 7) b.open_cost = 3;
+        b.*m += 1;
+        CHECK(!(a == b));
+    }
+    for (auto m : flags) {
+        PlanParams b = a;
+        b.*m = !(b.*m);
         CHECK(!(a == b));
     }
     return 0;
@@ -172,6 +197,7 @@ int main(int argc, char** argv) {
     if (parameters(-1)) return 1;
     for (int seed = first; seed < first + count; ++seed)
         if (one(seed)) return 1;
-    std::printf("ok: %d forests\n", count);
+    if (count >= 50 && n_few < count / 10) return std::fprintf(stderr, "only %d plans of calls of few units\n", n_few), 1;
+    std::printf("ok: %d forests, %d plans of calls of few units\n", count, n_few);
     return 0;
 }

@@ -10,13 +10,19 @@ import paper_2401_06761_amd as ap
 from harness import check_plan_covers_tables
 
 
-def grow(h, prompt, leaves):
-    root = ap.apar_thread_create(h)
+def grow(h, prompt, leaves, root=None):
+    """A tree's threads; a leaf that is itself (tokens, leaves) forks again."""
+    if root is None:
+        root = ap.apar_thread_create(h)
     ap.apar_append_kv(h, root, None, None, prompt)
-    live = ap.apar_fork(h, root, len(leaves))
+    kids, live = ap.apar_fork(h, root, len(leaves)), []
     ap.apar_free_thread(h, root)
-    for t, n in zip(live, leaves):
-        ap.apar_append_kv(h, t, None, None, n)
+    for t, leaf in zip(kids, leaves):
+        if isinstance(leaf, tuple):
+            live += grow(h, *leaf, root=t)
+        else:
+            ap.apar_append_kv(h, t, None, None, leaf)
+            live.append(t)
     return live
 
 
@@ -89,6 +95,49 @@ def test_plans_of_few_units(dtype, n_kv, group, trees, few):
         ap.apar_set_inline_shared(h, False)  # nothing is cut by rank
         ap.apar_decode_attention(h, None, live, None)
         check_plan_covers_tables(h, live, n_kv, group)
+
+
+# Trees of more blocks than a unit may list (2048), whose top segment stands alone: kv heads, q heads per kv head, candidates, trees, and whether
+# the call still is one of few units (trees of one row tile: chunks without a shared list)
+LONG = [
+    (8, 8, 1, [(33600, [40] * 3), (100, [30] * 3)], False),
+    (4, 8, 1, [(33600, [40] * 6), (100, [30] * 3)], False),
+    (8, 4, 1, [(33000, [40] * 6), (100, [30] * 6)], False),
+    (8, 4, 1, [(33000, [40] * 5), (500, [30] * 8)], False),
+    (8, 4, 1, [(60000, [40] * 5), (500, [30] * 8)], False),
+    (8, 4, 1, [(40000, [50, (90, [20] * 6), 70])], False),
+    (1, 4, 1, [(40000, [(60, [20] * 6), (75, [30] * 6)])], False),
+    (8, 1, 1, [(40000, [(60, [20] * 20), (75, [30] * 20)])], False),
+    (8, 5, 1, [(33000, [20] * 4), (40, [16] * 7)], False),
+    (1, 1, 1, [(16 * 2100, [1] * 18), (300, [5] * 20)], False),
+    (8, 8, 3, [(33000, [40] * 2), (100, [30])], False),            # two slices per thread
+    (8, 4, 1, [(33600, [40] * 2), (100, [30] * 3)], True),
+    (8, 4, 1, [(33600, [40] * 2), (100, [30] * 6), (16 * 300, [9] * 4)], True),
+    (1, 1, 1, [(40000, [50, (70000, [20] * 6), 70])], True),
+]
+
+
+@pytest.mark.parametrize("dtype", [BF16, FP8, F32])
+@pytest.mark.parametrize("n_kv,group,cand,trees,few", LONG)
+def test_trees_that_stand_alone_for_their_blocks(dtype, n_kv, group, cand, trees, few):
+    with ap.Pool(n_kv * group, n_kv, 128, dtype, 16384, max_threads=256, dry_run=True) as pool:
+        h = pool.handle
+        attend = lambda: ap.apar_decode_attention_spec(h, None, None, None, None, cand, live, None)
+        live = [t for prompt, leaves in trees for t in grow(h, prompt, leaves)]
+        attend()
+        check_plan_covers_tables(h, live, n_kv, cand * group)
+        tables = range(ap.APAR_PLAN_WORKGROUPS, ap.APAR_PLAN_GEOMETRY + 1)
+        plan = [list(ap.apar_last_plan_export(h, k)) for k in tables]
+        assert ap.apar_last_plan_info(h).n_partial_rows > 0
+        if few:
+            assert all(wg[1] == 0 and wg[3] & 255 <= 2 for wg in workgroups(h))
+            ap.apar_append_kv_batch(h, live, None, None)
+            attend()
+            check_plan_covers_tables(h, live, n_kv, cand * group)
+        else:  # the plan of a pool that makes none of few units
+            ap.apar_set_inline_shared(h, True)
+            attend()
+            assert ap.apar_plan_counts(h)[0] == 2 and plan == [list(ap.apar_last_plan_export(h, k)) for k in tables]
 
 
 @pytest.mark.parametrize("seed", range(6))

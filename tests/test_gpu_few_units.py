@@ -73,6 +73,43 @@ def test_against_the_oracle(dtype, d, call):
         assert_close(to_host(out), dense.decode_spec(q, ck, cv, masks, live), dtype, "candidates")
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "bf16_fp8kv", "f32"])
+@pytest.mark.parametrize("n_q,n_kv,trees,shared", [
+    (32, 4, [(33600, [40] * 6), (100, [30] * 3)], True),              # a long tree of 48 rows: the general plan for every tree
+    (8, 4, [(33600, [40, 3]), (100, [30] * 11), (16, [1])], False),   # of 4 rows: chunks without a shared list, merged
+])
+def test_trees_that_stand_alone_for_their_blocks(dtype, n_q, n_kv, trees, shared):
+    import torch
+
+    parents, lens = [], []
+    for prompt, leaves in trees:
+        root = len(parents)
+        parents += [-1] + [root] * len(leaves)
+        lens += [prompt] + leaves
+    w = manual_tree(parents, lens, HeadConfig(n_q, n_kv, 128, dtype), seed=4)
+    dense = DenseThreads(n_q, n_kv, 128)
+    with pool_for(w, blocks_upper_bound(w)) as pool:
+        pool.kv.fill_(0xFF)
+        h = pool.handle
+        live, _ = replay_trace(w, pool, None, dense)
+        q, ck, cv = spec_step_qkv(w, 1, len(live), 2)
+        masks = np.array([[1, 3]] * len(live), dtype=np.uint8)
+        out = torch.full_like(to_dev(q, dtype), 3.0)
+        ap.apar_decode_attention_spec(h, to_dev(q, dtype), to_dev(ck, dtype), to_dev(cv, dtype), torch.from_numpy(masks).cuda(), 2, live, out)
+        wgs = np.asarray(ap.apar_last_plan_export(h, ap.APAR_PLAN_WORKGROUPS)).reshape(-1, 32)
+        assert ap.apar_last_plan_info(h).n_partial_rows > 0 and any(wg[1] > 0 for wg in wgs) == shared
+        assert_close(to_host(out), dense.decode_spec(q, ck, cv, masks, live), dtype, "candidates")
+        q = step_q(w, 0, len(live))
+        outs = [torch.full_like(to_dev(q, dtype), 3.0) for _ in range(2)]
+        ap.apar_decode_attention(h, to_dev(q, dtype), live, outs[0])
+        ap.apar_decode_attention_fixed(h, to_dev(q, dtype), live, outs[1])
+        torch.cuda.synchronize()
+        wgs = np.asarray(ap.apar_last_plan_export(h, ap.APAR_PLAN_WORKGROUPS)).reshape(-1, 32)
+        assert ap.apar_last_plan_info(h).n_partial_rows > 0 and any(wg[1] > 0 for wg in wgs) == shared
+        assert_close(to_host(outs[0]), dense.decode(q, live), dtype)
+        assert torch.equal(outs[0], outs[1])
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("n_q,n_kv,cand", [(16, 2, 3), (8, 1, 8), (64, 8, 4), (10, 2, 5), (640, 40, 4)])
 def test_threads_of_more_rows_than_a_unit_holds(dtype, n_q, n_kv, cand):
