@@ -257,8 +257,8 @@ struct Builder {
             for (int32_t m : range_segs) clipped(m);
     }
 
-    // Units of at most 16 rows in a call of few units.  A unit's tiles are dealt out to the four wavefronts, which all hold its rows.
-    // Open tiles go round; full ones level the lists.  A thread's own last blocks stay with one wavefront, whose list has room for
+    // Units of at most `few` row tiles in a call of few units.  A unit's tiles are dealt out to the four wavefronts, which all hold its
+    // rows.  Open tiles go round; full ones level the lists.  A thread's own last blocks stay with one wavefront, whose list has room for
     // its next ones.
     // A thread of more rows than a unit holds has a unit per slice (n_sl > 1; such units are not carried over).
     void emit_few(const UnitSpec& u, int32_t pbase, int32_t flags) {
@@ -553,22 +553,37 @@ struct Builder {
     int row_tiles_of_few() {
         if (prm.few_units <= 0 || !prm.fuse || !prm.inline_shared || !prm.allow_direct) return 0;
         for (few = 1; few <= std::min(prm.few_row_tiles, kMaxRowTiles); ++few) {
-            const int per_unit = few * cap;
-            int64_t units = 0, tiles = 0, again = 0;
+            const int per_unit = few * cap, units_per_thread = (n_sl + per_unit - 1) / per_unit;
+            int64_t units = 0;
             bool fits = true;
             for (const PlanHost::Segment& s : ph.segs) {
-                const int64_t readers = n_sl == 1 ? (s.n_shr + per_unit - 1) / per_unit : (int64_t)s.n_shr * ((n_sl + per_unit - 1) / per_unit);
-                tiles += readers * s.n_blk;
-                again += (readers - 1) * s.n_blk;
                 if (s.parent >= 0) continue;
                 const bool wide = (s.n_shr + cap - 1) / cap > kFewTreeUnits && cap > kFewTreeThreads;
                 const bool one_unit = s.tiles_sub <= (int64_t)4 * prm.max_unit_tiles;  // (by its blocks)
                 const int groups = s.n_shr * n_sl;
-                units += groups <= cap && !one_unit ? s.tiles_sub / prm.max_unit_tiles : readers;  // (its chunks)
-                fits = !wide && !to_matrix(s) && (groups <= cap || (groups <= per_unit ? one_unit : fits_by_rank(s)));
-                if (!fits || units > prm.few_units) break;
+                units += groups <= cap && !one_unit ? s.tiles_sub / prm.max_unit_tiles : n_by_rank(s) * units_per_thread;  // (its chunks)
+                fits = units <= prm.few_units && !wide && !to_matrix(s) &&
+                       (groups <= cap || (groups <= per_unit ? one_unit : fits_by_rank(s)));
+                if (!fits) break;
             }
-            if (fits && units <= prm.few_units && tiles <= kFewTiles && again <= (few == 1 ? prm.few_again : prm.few_again_wide)) return few;
+            if (!fits) continue;
+            // the tiles that the units list, and how many of them are listed by another unit too
+            int64_t tiles = 0, again = 0;
+            std::vector<int32_t>& root = ph.order;
+            root.assign(ph.segs.size(), 0);
+            for (size_t m = 0; m < ph.segs.size(); ++m) {
+                const PlanHost::Segment& s = ph.segs[m];
+                root[m] = s.parent < 0 ? (int32_t)m : root[s.parent];
+                const PlanHost::Segment& r = ph.segs[root[m]];
+                const int64_t n_units = n_by_rank(r);
+                // rank x of r's is in unit k where floor(n_shr * k / n_units) <= x < floor(n_shr * (k + 1) / n_units)
+                auto unit_of = [&](int64_t x) { return ((x + 1) * n_units - 1) / r.n_shr; };
+                const int32_t x = s.t_lo - r.t_lo;
+                const int64_t readers = (n_units == 1 ? 1 : unit_of(x + s.n_shr - 1) - unit_of(x) + 1) * units_per_thread;
+                tiles += readers * s.n_blk;
+                again += (readers - 1) * s.n_blk;
+            }
+            if (tiles <= kFewTiles && again <= (few == 1 ? prm.few_again : prm.few_again_wide)) return few;
         }
         return 0;
     }

@@ -123,6 +123,12 @@ static int one(int seed) {
         };
         CHECK(ph.few_row_tiles >= 0 && ph.few_row_tiles <= (prm.few_units > 0 ? prm.few_row_tiles : 0));
         n_few += ph.few_row_tiles > 0;
+        if (ph.few_row_tiles) {  // no more tiles listed again than allowed
+            int64_t listed = 0;
+            for (const WgDesc& wg : ph.wgs)
+                for (const WaveItem& wi : wg.w) listed += wi.n_tiles;
+            CHECK(listed - ph.unique_blocks <= (ph.few_row_tiles == 1 ? prm.few_again : prm.few_again_wide));
+        }
         for (const WgDesc& wg : ph.wgs) {
             // which kernel takes the unit: all of a call's are for the one without shared lists or none is
             if (ph.few_row_tiles) CHECK(wg.n_coop == 0 && (wg.row_tiles & 255) <= ph.few_row_tiles);

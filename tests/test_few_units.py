@@ -140,6 +140,34 @@ def test_trees_that_stand_alone_for_their_blocks(dtype, n_kv, group, cand, trees
             assert ap.apar_plan_counts(h)[0] == 2 and plan == [list(ap.apar_last_plan_export(h, k)) for k in tables]
 
 
+@pytest.mark.parametrize("dtype", [BF16, FP8, F32])
+@pytest.mark.parametrize("n_kv,group,cand,n_trees,tree", [
+    # a leaf beside a long paragraph that forks four times: cut by rank into 2 + 3 threads, the paragraph lies in both units
+    (8, 4, 1, 1, (32, [16, (16000, [9, 8, 7, 6])])),
+    (8, 4, 1, 8, (32, [16, (16000, [9, 8, 7, 6])])),
+    (8, 4, 1, 60, (32, [16, (16000, [9, 8, 7, 6])])),
+    (1, 4, 1, 60, (32, [16, (16000, [9, 8, 7, 6])])),
+    (8, 8, 1, 8, (160, [(4000, [9, 8]), 16, (8000, [9, 8])])),
+    (2, 1, 1, 40, (48, [(900, [5] * 15), (1700, [6] * 9), (33, [7] * 13)])),
+    (8, 8, 5, 10, (640, [(900, [5] * 3), 4])),
+])
+def test_tiles_that_several_units_list(dtype, n_kv, group, cand, n_trees, tree):
+    """What units of few may list and list again is what they do list, whichever units a segment of the trees lies in."""
+    with ap.Pool(n_kv * group, n_kv, 128, dtype, 1 << 17, max_threads=4096, dry_run=True) as pool:
+        h = pool.handle
+        live = [t for _ in range(n_trees) for t in grow(h, *tree)]
+        ap.apar_decode_attention_spec(h, None, None, None, None, cand, live, None)
+        wgs, info = workgroups(h), ap.apar_last_plan_info(h)
+        if any(wg[1] > 0 for wg in wgs) or info.n_partial_rows > 0:
+            return
+        assert dtype == F32 or len(wgs) * n_kv <= 1024
+        listed = sum(wg[5 + 6 * k] for wg in wgs for k in range(4))
+        assert listed <= 65536
+        # on 16-bit pools 56 MiB, 112 where there are units of two row tiles
+        limit = {BF16: 56 << 20, FP8: 112 << 20, F32: 1 << 60}[dtype] // (n_kv * 8192) << int(max(wg[3] & 255 for wg in wgs) - 1)
+        assert listed - info.unique_blocks <= limit
+
+
 @pytest.mark.parametrize("seed", range(6))
 def test_a_loop_carries_them(seed):
     rng = np.random.default_rng(seed)
