@@ -96,14 +96,18 @@ __device__ __forceinline__ bool fold_slices(const SplitPlan& sp, const Slice& sl
                 f32x2 ml[kAhead];
                 f32x4 os[kAhead][J];
 #pragma unroll
+                for (int i = 0; i < kAhead; ++i)
+                    ml[i] = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(state, at + min(s0 + i, sl.n - 1) * step + JT * 1024 + lane * 8, 0, kAgent));
+#pragma unroll
                 for (int i = 0; i < kAhead; ++i) {
-                    const int as = at + min(s0 + i, sl.n - 1) * step;
-                    ml[i] = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(state, as + JT * 1024 + lane * 8, 0, kAgent));
+                    // Past the last slice: past the descriptor's end, where a buffer load gives zeros.  (Not the last slice again, whose
+                    // infinities a weight of 0 would make NaN.)
+                    const int as = at + (s0 + i) * step + (((sl.n - 1 - s0 - i) >> 31) & (int)kSplitStateBytes);
 #pragma unroll
                     for (int jj = 0; jj < J; ++jj)
                         os[i][jj] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(state, as + ((j0 + jj) * 64 + lane) * 16, 0, kAgent));
                 }
-                float mx = m;
+                float mx = m;  // (of slices that are read twice too)
 #pragma unroll
                 for (int i = 0; i < kAhead; ++i) mx = fmaxf(mx, ml[i][0]);
                 const float a = mx == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m - mx);

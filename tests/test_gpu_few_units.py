@@ -111,6 +111,32 @@ def test_trees_that_stand_alone_for_their_blocks(dtype, n_q, n_kv, trees, shared
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("prompt", [500, 2500, 4100, 11000])  # 2 to 43 slices
+def test_an_infinity_in_every_slice_stays_one(dtype, prompt):
+    """Zero queries weigh every row alike: a dim that holds an infinity in each full block of the prompt comes out infinite, the others
+    as the mean of their values, however many slices the unit is folded from."""
+    import torch
+
+    n_kv, d = 2, 128
+    with ap.Pool(n_kv, n_kv, d, dtype, 1024, max_threads=16) as pool:
+        h = pool.handle
+        rng = np.random.default_rng(prompt)
+        k, v = rng.standard_normal((2, prompt, n_kv, d))
+        v[3::16, :, 5] = np.inf
+        v[prompt // 16 * 16:, :, 5] = 1.0
+        root = ap.apar_thread_create(h)
+        ap.apar_append_kv(h, root, to_dev(k, dtype), to_dev(v, dtype), prompt)
+        live = [root] + ap.apar_fork(h, root, 2)
+        out = to_dev(np.zeros((3, n_kv, d)), dtype)
+        ap.apar_decode_attention(h, to_dev(np.zeros((3, n_kv, d)), dtype), live, out)
+        got = to_host(out)
+        assert (got[:, :, 5] == np.inf).all()
+        want = to_host(to_dev(v, dtype)).astype(np.float64).mean(0)
+        rest = np.arange(d) != 5
+        assert_close(got[:, :, rest], np.broadcast_to(want[:, rest], (3, n_kv, d - 1)), dtype)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("n_q,n_kv,cand", [(16, 2, 3), (8, 1, 8), (64, 8, 4), (10, 2, 5), (640, 40, 4)])
 def test_threads_of_more_rows_than_a_unit_holds(dtype, n_q, n_kv, cand):
     import torch
