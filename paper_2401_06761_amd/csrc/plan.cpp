@@ -50,6 +50,7 @@ void PlanHost::clear() {
     reusable = false;
     n_patched = 0;
     few_row_tiles = 0;
+    tail_lists = 1;
 }
 
 namespace {
@@ -113,8 +114,9 @@ struct Builder {
     // which row groups; build_plan turns the item into the workgroup it ends up in.
     static constexpr int32_t kNarrowItem = 8;
     static bool is_tail(const PlanHost::Segment& sg) { return sg.n_shr == 1 && sg.n_end == 1; }
-    void note_tail(const PlanHost::Segment& sg, size_t item, int32_t slot, int lo, int hi) {
-        PlanHost::Tail& t = ph.tails[ph.end_threads[sg.end_ofs]];
+    // `list`: which of the thread's lists that is, where it has several (PlanHost::tail_lists).
+    void note_tail(const PlanHost::Segment& sg, size_t item, int32_t slot, int lo, int hi, int list = 0) {
+        PlanHost::Tail& t = ph.tails[(size_t)list * ph.end_threads.size() + ph.end_threads[sg.end_ofs]];
         t.wg = (int32_t)item;
         t.slot = slot;
         t.lohi = make_meta(lo, hi, 0);
@@ -260,7 +262,7 @@ struct Builder {
     // Units of at most `few` row tiles in a call of few units.  A unit's tiles are dealt out to the four wavefronts, which all hold its
     // rows.  Open tiles go round; full ones level the lists.  A thread's own last blocks stay with one wavefront, whose list has room for
     // its next ones.
-    // A thread of more rows than a unit holds has a unit per slice (n_sl > 1; such units are not carried over).
+    // A thread of more rows than a unit holds has several units, each with some of its slices (n_sl > 1).
     void emit_few(const UnitSpec& u, int32_t pbase, int32_t flags) {
         if (n_sl == 1) {
             emit_few_groups(u, u.r_lo, u.n_thr, pbase, flags);
@@ -282,7 +284,7 @@ struct Builder {
             const PlanHost::Segment& sg = ph.segs[m];
             const bool open = sg.last_valid < B;
             int k = -1;
-            const bool tail = n_sl == 1 && is_tail(sg);
+            const bool tail = is_tail(sg);
             if (open || tail) {
                 k = 3;
                 for (int j = 2; j >= 0; --j)
@@ -329,7 +331,7 @@ struct Builder {
                 ph.tiles[ofs[k_full] + at_full++] = TileRef{sg.blocks[b], meta};
             }
             if (open) ph.tiles[ofs[k] + n_full[k] + at_open[k]++] = TileRef{sg.blocks[np], make_meta(lo, hi, sg.last_valid)};
-            if (n_sl == 1 && is_tail(sg)) note_tail(sg, ph.wide_items.size(), k, lo, hi);
+            if (is_tail(sg)) note_tail(sg, ph.wide_items.size(), k, lo, hi, n_sl == 1 ? 0 : grp0 % n_sl / (few * cap));
         }
         PlanHost::WideItem wi{};
         wi.wg.coop_ofs = (int32_t)base;
@@ -731,10 +733,11 @@ int build_plan(const PlanThreadView* threads, int n, const int32_t* refcount, in
     {
         PlanHost::Tail none{};
         none.wg = none.slot = none.tile = -1;
-        ph.tails.assign(n, none);
+        bld.few = ph.few_row_tiles = bld.row_tiles_of_few();
+        ph.tail_lists = bld.few ? (bld.n_sl + bld.few * bld.cap - 1) / (bld.few * bld.cap) : 1;
+        ph.tails.assign((size_t)n * ph.tail_lists, none);
     }
     const int cap = bld.cap, n_sl = bld.n_sl;
-    bld.few = ph.few_row_tiles = bld.row_tiles_of_few();
     for (int32_t m = 0; m < n_seg; ++m) {
         PlanHost::Segment& s = segs[m];
         ph.unique_blocks += s.n_blk;
@@ -893,8 +896,8 @@ int build_plan(const PlanThreadView* threads, int n, const int32_t* refcount, in
         for (size_t k = 0; k < n_wide; ++k) wide_pos[ph.wide_items[k].id] = (int32_t)k;
         ph.tile_owner.assign(ph.tiles.size(), -1);
         ph.spare.assign(ph.wgs.size() * 5, 0);
-        for (int i = 0; i < n; ++i) {
-            PlanHost::Tail& t = ph.tails[i];
+        for (int32_t k = 0, i = 0; k < n * ph.tail_lists; ++k, i = i + 1 < n ? i + 1 : 0) {
+            PlanHost::Tail& t = ph.tails[k];
             const PlanThreadView& v = threads[i];
             t.len = v.len;
             t.n_blocks = v.n_blocks;
@@ -917,10 +920,10 @@ int build_plan(const PlanThreadView* threads, int n, const int32_t* refcount, in
                 const bool shared = t.slot == PlanHost::kSharedList;
                 const int32_t ofs = shared ? wg.coop_ofs : wg.w[t.slot].tile_ofs;
                 const int32_t cnt = shared ? wg.n_coop : wg.w[t.slot].n_tiles;
-                for (int32_t k = ofs + (shared ? wg.row_tiles >> 8 : wg.n_full[t.slot]); k < ofs + cnt; ++k)
-                    if (ph.tiles[k].blk == t.tail_block) t.tile = k;
+                for (int32_t at = ofs + (shared ? wg.row_tiles >> 8 : wg.n_full[t.slot]); at < ofs + cnt; ++at)
+                    if (ph.tiles[at].blk == t.tail_block) t.tile = at;
                 if (t.tile < 0) t.wg = -1;
-                else ph.tile_owner[t.tile] = i;
+                else ph.tile_owner[t.tile] = k;
             }
         }
         ph.reusable = true;
@@ -941,7 +944,7 @@ inline ListView list_of(const WgDesc& wg, int slot) {
 }  // namespace
 
 bool patch_plan(const PlanThreadView* threads, int n, bool no_copies, PlanHost& ph) {
-    if (!ph.reusable || (size_t)n != ph.tails.size()) return false;
+    if (!ph.reusable || (size_t)n * ph.tail_lists != ph.tails.size()) return false;
     ph.dirty_wg_words.clear(), ph.dirty_tile_words.clear();
     auto tile_changed = [&ph](int32_t idx, bool block_too = true) {
         if (block_too) ph.dirty_tile_words.push_back(2 * idx);
@@ -972,16 +975,16 @@ bool patch_plan(const PlanThreadView* threads, int n, bool no_copies, PlanHost& 
         if (slot == PlanHost::kSharedList) wg.row_tiles += 1 << 8;
         else wg.n_full[slot] += 1;
         count_changed(wg_index, slot, true);
-        ph.full_blocks += 1;
     };
-    for (int i = 0; i < n; ++i) {
+    for (int32_t k = 0, i = 0; k < n * ph.tail_lists; ++k, i = i + 1 < n ? i + 1 : 0) {  // thread i's lists, all first ones before all second ones
+        const bool first_list = k < n;
         if (i + 8 < n) {
-            const PlanHost::Tail& ahead = ph.tails[i + 8];
+            const PlanHost::Tail& ahead = ph.tails[k + 8];
             if (!no_copies) __builtin_prefetch(threads[i + 8].table + std::min(ahead.n_blocks, threads[i + 8].n_blocks) - 1);
             if (ahead.tile >= 0) __builtin_prefetch(&ph.tiles[ahead.tile], 1);
             else if (ahead.wg >= 0) __builtin_prefetch(&ph.wgs[ahead.wg], 1);  // a full last block: the next row opens a new one
         }
-        PlanHost::Tail& t = ph.tails[i];
+        PlanHost::Tail& t = ph.tails[k];
         const PlanThreadView& v = threads[i];
         if (v.n_blocks < t.n_blocks || v.len < t.len) return give_up();
         // (without a copy-on-write copy anywhere since, the block is the one it was)
@@ -1001,6 +1004,7 @@ bool patch_plan(const PlanThreadView* threads, int n, bool no_copies, PlanHost& 
             tile_changed(t.tile, at_tail != t.tail_block);
             if (now == B) {
                 to_full_part(t.wg, t.slot, t.tile);
+                ph.full_blocks += first_list;
                 t.tile = -1;
             }
         } else if (dn == 0 || at_tail != t.tail_block) {
@@ -1014,20 +1018,23 @@ bool patch_plan(const PlanThreadView* threads, int n, bool no_copies, PlanHost& 
             const int32_t idx = l.ofs + l.n;
             const int now = (int)(v.len - (int64_t)(v.n_blocks - 1) * B);
             ph.tiles[idx] = TileRef{v.table[v.n_blocks - 1], t.lohi | (now << 20)};
-            ph.tile_owner[idx] = i;
+            ph.tile_owner[idx] = k;
             tile_changed(idx);
             if (t.slot == PlanHost::kSharedList) wg.n_coop += 1;
             else wg.w[t.slot].n_tiles += 1;
             count_changed(t.wg, t.slot, false);
             t.tile = idx;
-            ph.unique_blocks += 1;
+            ph.unique_blocks += first_list;
             if (now == B) {
                 to_full_part(t.wg, t.slot, idx);
+                ph.full_blocks += first_list;
                 t.tile = -1;
             }
         }
-        ph.unique_tokens += v.len - t.len;
-        ph.path_tokens += v.len - t.len;
+        if (first_list) {
+            ph.unique_tokens += v.len - t.len;
+            ph.path_tokens += v.len - t.len;
+        }
         t.len = v.len;
         t.n_blocks = v.n_blocks;
         t.tail_block = v.table[v.n_blocks - 1];

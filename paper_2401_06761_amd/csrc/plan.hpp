@@ -74,8 +74,10 @@ struct PlanHost {
     };
     static constexpr int32_t kSharedList = 4;
     static constexpr int32_t kTailSlack = 4;  // unused tile entries left behind a list per thread whose tail is on it
-    std::vector<Tail> tails;
-    std::vector<int32_t> tile_owner;   // per entry of `tiles`: the listed thread whose filling last block it reads, else -1
+    std::vector<Tail> tails;           // all threads' first lists, then all their second ones, ...
+    int32_t tail_lists = 1;            // lists that read a thread's own last blocks: one, or one per unit of a call of few units whose
+                                       // threads have more rows than a unit
+    std::vector<int32_t> tile_owner;   // per entry of `tiles`: the entry of `tails` whose filling last block it reads, else -1
     std::vector<int32_t> spare;        // per (workgroup, list): unused tile entries behind the list
     std::vector<int32_t> item_wg, item_slot;  // build scratch: where each narrow item / wide item ended up
     // what the last patch_plan changed, for a copy of the tables that is brought up to date instead of

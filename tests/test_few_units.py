@@ -7,7 +7,7 @@ import pytest
 
 import paper_2401_06761_amd as ap
 
-from harness import check_plan_covers_tables
+from harness import PlanTablesOnDevice, check_plan_covers_tables
 
 
 def grow(h, prompt, leaves, root=None):
@@ -193,7 +193,7 @@ def test_a_loop_carries_them(seed):
 
 @pytest.mark.parametrize("n_kv,group,cand,few", [(8, 8, 3, 1), (1, 8, 8, 1), (8, 16, 4, 1), (2, 5, 5, 1), (16, 16, 4, 2), (16, 8, 5, 1), (32, 16, 4, 0)])
 def test_threads_of_more_rows_than_a_unit_holds(n_kv, group, cand, few):
-    """A unit per slice of every thread; a call with the same list carries the plan over, one after an append builds another."""
+    """A unit per slice of every thread, or per two; a call with the same list carries the plan over."""
     with ap.Pool(n_kv * group, n_kv, 128, "bf16", 2048, max_threads=256, dry_run=True) as pool:
         h = pool.handle
         live = grow(h, 70, [1, 16, 17, 40, 90]) + grow(h, 16, [3, 50]) + grow(h, 5, [20] * 12)
@@ -210,3 +210,31 @@ def test_threads_of_more_rows_than_a_unit_holds(n_kv, group, cand, few):
             spec()
             assert ap.apar_plan_counts(h)[0] == built
             ap.apar_append_kv_batch(h, live, None, None)
+
+
+@pytest.mark.parametrize("n_kv,group,cand,row_tiles", [(8, 8, 4, 1), (1, 8, 8, 1), (2, 5, 5, 1), (16, 16, 4, 2), (16, 16, 3, 2)])
+def test_a_loop_carries_threads_of_more_rows_than_a_unit(n_kv, group, cand, row_tiles):
+    """Every one of a thread's units follows its last blocks: rows appended, blocks that fill up, copies on write."""
+    with ap.Pool(n_kv * group, n_kv, 128, "bf16", 4096, max_threads=4096, dry_run=True) as pool:
+        h = pool.handle
+        live = grow(h, 70, [1, 16, 17, 40, 90, 31]) + (grow(h, 16, [3] * 18) if row_tiles == 2 else [])
+        rng, on_device = np.random.default_rng(cand), PlanTablesOnDevice(h)
+        for step in range(40):
+            if step:
+                ap.apar_append_kv_batch(h, live, None, None)
+                pos = int(rng.integers(0, len(live)))
+                (child,) = ap.apar_fork(h, live[pos], 1)
+                ap.apar_free_thread(h, live[pos])
+                live[pos] = child
+            ap.apar_decode_attention_spec(h, None, None, None, None, cand, live, None)
+            every_row_group_once(h, live, -(-cand * group // 16))
+            on_device.follow()
+            assert max(wg[3] & 255 for wg in workgroups(h)) == row_tiles
+            info, blocks = ap.apar_last_plan_info(h), {}
+            for t in live:
+                n = ap.apar_thread_len(h, t)
+                blocks.update({b: min(16, n - 16 * i) for i, b in enumerate(ap.apar_thread_block_table(h, t))})
+            assert info.unique_blocks == len(blocks) and info.unique_tokens == sum(blocks.values())
+            assert info.path_tokens == sum(ap.apar_thread_len(h, t) for t in live)
+        built, carried = ap.apar_plan_counts(h)
+        assert (built, carried) == (1, 39)

@@ -162,3 +162,27 @@ def test_threads_of_more_rows_than_a_unit_holds(dtype, n_q, n_kv, cand):
             assert {wg[3] & 255 for wg in wgs} == {2 if n_kv == 40 else 1}
         assert_close(to_host(outs[0]), dense.decode_spec(q, ck, cv, masks, live), dtype)
         assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "bf16_fp8kv", "f32"])
+@pytest.mark.parametrize("n_q,n_kv,cand,root", [(16, 2, 4, 40), (16, 2, 3, 900)])  # (tables with the arguments, and staged ones)
+def test_a_loop_carries_threads_of_more_rows_than_a_unit(dtype, n_q, n_kv, cand, root):
+    import torch
+
+    w = manual_tree([-1] + [0] * 3, [root, 1, 15, 40], HeadConfig(n_q, n_kv, 128, dtype), seed=2)
+    dense = DenseThreads(n_q, n_kv, 128)
+    with pool_for(w, blocks_upper_bound(w) + 32) as pool:
+        h = pool.handle
+        live, _ = replay_trace(w, pool, None, dense)
+        for step in range(20):
+            q, ck, cv = spec_step_qkv(w, step, len(live), cand)
+            masks = np.array([[1, 3, 5, 9][:cand]] * len(live), dtype=np.uint8)
+            out = torch.full_like(to_dev(q, dtype), 3.0)
+            ap.apar_decode_attention_spec(h, to_dev(q, dtype), to_dev(ck, dtype), to_dev(cv, dtype), torch.from_numpy(masks).cuda(), cand, live, out)
+            torch.cuda.synchronize()
+            assert_close(to_host(out), dense.decode_spec(q, ck, cv, masks, live), dtype, f"step {step}")
+            accept = np.full(len(live), 1, dtype=np.uint8)
+            ap.apar_commit_candidates(h, live, to_dev(ck, dtype), to_dev(cv, dtype), cand, accept)
+            dense.commit_candidates(live, ck, cv, accept)
+        assert all(wg[1] == 0 for wg in np.asarray(ap.apar_last_plan_export(h, ap.APAR_PLAN_WORKGROUPS)).reshape(-1, 32))
+        assert ap.apar_plan_counts(h) == (1, 19)
