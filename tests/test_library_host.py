@@ -572,3 +572,10 @@ def test_thread_ids_are_taken_from_any_sequence(kind):
         assert [int(t) for t in seq] == kept and [ap.apar_thread_len(h, t) for t in ids] == [1 if t in kept else 0 for t in ids]
         with pytest.raises(ValueError):
             ap.apar_append_kv_batch(h, np.zeros((2, 1), np.int32), None, None)
+
+
+def test_thread_ids_of_any_number_need_no_type_of_their_own():
+    """ctypes makes an array type per length (7 us, and garbage for the collector): a list's length is no part of what is passed."""
+    from paper_2401_06761_amd import binding
+
+    assert len({type(binding._ids(list(range(n)))[0]) for n in range(40)}) == 1
