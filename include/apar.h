@@ -469,11 +469,11 @@ enum { APAR_PLAN_WORKGROUPS = 0, APAR_PLAN_TILES = 1, APAR_PLAN_DFS_THREADS = 2,
        APAR_PLAN_PATH_IDS = 4, APAR_PLAN_GEOMETRY = 5, APAR_PLAN_CHANGED_WORKGROUP_WORDS = 6,
        APAR_PLAN_CHANGED_TILE_WORDS = 7 };
 APAR_API int apar_last_plan_export(apar_pool* pool, int which, int32_t* out, int64_t cap, int64_t* n_out);
-/* Tuning knob: the most blocks one wavefront is given in one work unit (1..65536; default 512).  A pool on which this
- * knob or one of the next two was set, to whatever value, plans its decode calls by them alone: calls of few threads
- * then get no units of their own.
+/* Tuning knob: the most blocks one wavefront is given in one work unit (1..65536; default 512).
  * Sharing subtrees with more blocks than that are cut into several units whose partial results are
- * merged afterwards; small values exist to exercise that path. */
+ * merged afterwards; small values exist to exercise that path.
+ * A pool on which this knob or one of the next two was set, to whatever value, plans its decode calls by them alone from
+ * then on: calls of few threads get no units of their own there, and every block is read once for up to 128 rows. */
 APAR_API int apar_set_chunk_blocks(apar_pool* pool, int blocks_per_unit);
 /* Tuning knob (bf16 pools): a shared segment that stands alone as a unit - its holders have more query rows
  * than one fused workgroup carries (128) - goes to the 32x32 matrix-core kernel, up to 128 rows per workgroup,
@@ -481,7 +481,7 @@ APAR_API int apar_set_chunk_blocks(apar_pool* pool, int blocks_per_unit);
  * and it has at least min_blocks blocks (default 128; shorter ones are cheaper read again by every unit below,
  * see apar_set_inline_shared).
  * Matrix units are launched ahead of the other units of a call, not beside them.  min_rows = 0 keeps every unit on the row-tile kernel; (1, 1) sends every such segment
- * to the matrix kernel.  Results agree to rounding.  fp32 pools ignore the knob. */
+ * to the matrix kernel.  Results agree to rounding.  fp32 and fp8 pools ignore the knob. */
 APAR_API int apar_set_matrix_units(apar_pool* pool, int min_rows, int min_blocks);
 /* Tuning knob: what happens to a sharing subtree whose threads bring more query rows than one unit carries
  * (128) and whose top segment does not go to the matrix kernel.  On (default): its threads, in depth-first

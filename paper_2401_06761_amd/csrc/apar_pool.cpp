@@ -85,6 +85,7 @@ struct apar_pool {
     // stand-alone segments with at least this many query rows and blocks run as matrix units (bf16 pools)
     int matrix_min_rows = 256, matrix_min_blocks = 128;
     bool inline_shared = true;  // subtrees with too many rows are cut by rank into direct units instead of leaving partial results
+    bool has_matrix_units() const { return shape.dtype == APAR_BF16 && !shape.fp8_sealed; }  // (the 32x32 kernels read bf16 tiles only)
     bool check_writes = false;  // verify before every launch that no destination block is shared
     int last_prefill_kernel = 0;  // which kernel the most recent prefill call ran (APAR_PREFILL_ROW_TILES / _MATRIX)
     std::vector<PlanThreadView> views;
@@ -625,8 +626,7 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     prm.max_unit_tiles = p->max_unit_tiles;
     prm.allow_direct = true;
     prm.fuse = true;
-    // (the 32x32 kernels read bf16 tiles only)
-    prm.matrix_min_rows = (p->shape.dtype == APAR_BF16 && !p->shape.fp8_sealed) ? p->matrix_min_rows : 0;
+    prm.matrix_min_rows = p->has_matrix_units() ? p->matrix_min_rows : 0;
     prm.matrix_min_blocks = p->matrix_min_blocks;
     prm.inline_shared = p->inline_shared;
     prm.open_cost = p->shape.dtype == APAR_F32 ? 1 : kOpenTileCost;
@@ -1510,8 +1510,8 @@ int apar_set_inline_shared(apar_pool* p, int on) {
 int apar_set_matrix_units(apar_pool* p, int min_rows, int min_blocks) {
     if (!p || min_rows < 0 || min_blocks < 0) return APAR_ERR_INVALID_ARG;
     p->matrix_min_rows = min_rows;
-    p->planning_set = true;
     p->matrix_min_blocks = min_blocks;
+    p->planning_set = p->planning_set || p->has_matrix_units();  // (other pools ignore the knob)
     return APAR_OK;
 }
 

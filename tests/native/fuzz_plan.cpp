@@ -3,12 +3,13 @@
 // thread's table is its root path's blocks, refcounts count the live holders, internal nodes end on block
 // boundaries - are planned under random geometry and policy parameters; the plan is checked for coverage:
 // every row group of every listed thread must be shown exactly the blocks of its thread's table, once, and
-// every index in the plan must lie inside its array (the sanitizers watch the builder's own accesses), and every list says
-// how many of its tiles are full.
+// every index in the plan must lie inside its array (the sanitizers watch the builder's own accesses), every list says
+// how many of its tiles are full, and a call that is not one of few units has the plan of a pool without such units.
 #include <algorithm>
 #include <climits>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <map>
 #include <random>
 #include <set>
@@ -25,6 +26,11 @@ using namespace apar;
             return 1;                                                              \
         }                                                                          \
     } while (0)
+
+template <class T>
+static bool same_table(const std::vector<T>& a, const std::vector<T>& b) {
+    return a.size() == b.size() && (a.empty() || std::memcmp(a.data(), b.data(), a.size() * sizeof(T)) == 0);
+}
 
 static int n_few = 0;  // plans of calls of few units
 
@@ -112,6 +118,14 @@ static int one(int seed) {
         }
         CHECK(build_plan(views.data(), n, refcount.data(), seg_of.data(), prm, ph) == 0);
         for (int32_t x : seg_of) CHECK(x == -1);
+        if (!ph.few_row_tiles && prm.few_units > 0) {  // another call's plan is the one without such units
+            PlanParams none = prm;
+            none.few_units = 0;
+            PlanHost general;
+            CHECK(build_plan(views.data(), n, refcount.data(), seg_of.data(), none, general) == 0);
+            CHECK(same_table(ph.wgs, general.wgs) && same_table(ph.tiles, general.tiles) && ph.path_ids == general.path_ids &&
+                  ph.path_ofs == general.path_ofs && ph.dfs_threads == general.dfs_threads && ph.n_partial_rows == general.n_partial_rows);
+        }
         const int n_sl = (prm.rows_per_thread + 15) / 16;
         // coverage: row group -> multiset of (block, valid)
         std::vector<std::map<int32_t, int>> seen((size_t)n * n_sl);

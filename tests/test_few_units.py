@@ -141,6 +141,25 @@ def test_trees_that_stand_alone_for_their_blocks(dtype, n_kv, group, cand, trees
 
 
 @pytest.mark.parametrize("dtype", [BF16, FP8, F32])
+def test_a_pool_whose_knobs_were_set_plans_by_them(dtype):
+    """The knob of the matrix kernel counts on the pools that have that kernel: others ignore it."""
+    with ap.Pool(8, 2, 128, dtype, 256, max_threads=64, dry_run=True) as pool:
+        h = pool.handle
+        live = grow(h, 300, [30] * 6)
+
+        def few():
+            ap.apar_decode_attention(h, None, live, None)
+            check_plan_covers_tables(h, live, 2, 4)
+            return all(wg[1] == 0 and wg[3] & 255 == 1 for wg in workgroups(h))
+
+        assert few()
+        ap.apar_set_matrix_units(h, 1, 1)
+        assert few() == (dtype != BF16)
+        ap.apar_set_chunk_blocks(h, 512)
+        assert not few()
+
+
+@pytest.mark.parametrize("dtype", [BF16, FP8, F32])
 @pytest.mark.parametrize("n_kv,group,cand,n_trees,tree", [
     # a leaf beside a long paragraph that forks four times: cut by rank into 2 + 3 threads, the paragraph lies in both units
     (8, 4, 1, 1, (32, [16, (16000, [9, 8, 7, 6])])),
