@@ -433,11 +433,19 @@ int run_append(apar_pool* p, const std::vector<int32_t>& codes, const std::vecto
 //   four requests, group 1 21.4 / 18.0, group 4 19.1 / 11.7, two fork levels 30.7 / 15.2; 16 requests, group 4 28.0 / 24.5, of 2 k tokens on
 //   fp8 40.0 / 29.1; by units x kv heads: 292 40.5 / 25.5, 440 41.7 / 23.8, 472 47.0 / 43.2, 584 116.9 / 104.8, 720 32.4 / 26.8, 792 26.4 / 14.9, 824 44.6 / 37.0,
 //   848 45.1 / 31.8; 2048 and more of whole trees 215.2 / 216.4.
-// A tree of more rows than a unit holds is read by several units, from L2 at best, so that units have 32 rows where units of 16 would
-// read too much again.  General plan / units of 16 / units of 32, by the MiB that units of 16 read again: 31 20.3 / 14.7, 37 22.9 /
-// 16.0, 62 30.2 / 29.4 / 26.2, 75 (group 8) 23.9 / 21.9 / 22.9, 84 47.0 / 42.9 / 39.1, on fp8 48.3 / 47.9 / 41.7, 125 42.0 / 46.2 / 36.4, 140 32.2 / 32.4 /
-// 27.8, 150 71.0 / 78.8 / 63.5 and 29.5 / 32.6 / 31.3; by what units of 32 read: 200 54.8 / - / 66.4, 72.0 / - / 82.3, 75.8 / - / 42.9 (28 rows per thread).
-constexpr int64_t kFewAgainBytes = (int64_t)56 << 20, kFewAgainWideBytes = (int64_t)112 << 20;
+// A tree of more rows than a unit holds is read by several units, from L2 at best, so that units have 32 rows where units of 16 would read
+// too much again, and there are none of either kind where those would too.  Time over the general plan's, mean and worst of 8150 drawn decode
+// and candidate calls of 0.7 MiB to 1.2 GiB, by the MiB read again and by all that the call reads (below 64 MiB / 64 to 256 / more):
+//   units of 16:                             up to 32 0.54, 1.04 / 0.80, 1.05 / 0.84, 1.04;  32 to 56 0.57, 1.04 / 0.81, 1.22 / 0.90, 1.11;
+//                                            56 to 112 0.60, 1.09 / 0.88, 1.32 / 0.93, 1.12;  112 to 200 0.63, 1.21 / 1.00, 1.78 / 1.00, 1.23;
+//   units of 32, trees of at most 64 rows:   up to 56 0.81, 1.30 / 0.91, 1.28 / 0.89, 1.20;  56 to 112 0.79, 0.99 / 1.00, 1.32 / 0.99, 1.38;
+//   trees of more, which are units of two
+//   row tiles per wavefront otherwise:       up to 56 0.54, 1.05 / 0.77, 1.04 / 0.76;  56 to 112 0.60, 1.07 / 0.86, 1.16 / 0.83, 0.95;
+//                                            112 to 200 0.63, 0.99 / 0.93, 1.47 / 0.94, 1.15.
+// With 112 MiB for all trees 292 of 4745 calls with trees of at most 64 rows were slower than under the general plan by more than 3 % (the worst
+// 1.38 times), now 133 (1.31), at the same mean (0.78).
+constexpr int64_t kFewAgainBytes = (int64_t)56 << 20, kFewAgainWideBytes = (int64_t)112 << 20, kFewAgainNarrowBytes = (int64_t)56 << 20;
+constexpr int64_t kFewSmallBytes = (int64_t)64 << 20;
 constexpr int32_t kFewUnits = 1024;
 
 // Which units of a decode plan are cut into slices (attn_split.hpp), and the launch's workgroups in order.  A unit's cost
@@ -636,6 +644,8 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     prm.few_row_tiles = p->shape.dtype == APAR_F32 ? 1 : 2;
     prm.few_again = p->shape.dtype == APAR_F32 ? INT32_MAX : (int32_t)(kFewAgainBytes / tile_read);
     prm.few_again_wide = (int32_t)(kFewAgainWideBytes / tile_read);
+    prm.few_again_narrow = (int32_t)(kFewAgainNarrowBytes / tile_read);
+    prm.few_small = (int32_t)(kFewSmallBytes / tile_read);
     prm.few_open_cost = p->shape.fp8_sealed ? 2 : 1;  // (twice the bytes of a full one)
     // Decode calls of a loop list the same threads step after step - each a few rows longer, a few replaced
     // by a thread forked from them - and the plan of the previous call then only needs its tails brought up

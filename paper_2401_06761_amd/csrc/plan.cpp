@@ -570,7 +570,7 @@ struct Builder {
             }
             if (!fits) continue;
             // the tiles that the units list, and how many of them are listed by another unit too
-            int64_t tiles = 0, again = 0;
+            int64_t tiles = 0, again = 0, again_narrow = 0, unique = 0;
             std::vector<int32_t>& root = ph.order;
             root.assign(ph.segs.size(), 0);
             for (size_t m = 0; m < ph.segs.size(); ++m) {
@@ -584,8 +584,12 @@ struct Builder {
                 const int64_t readers = (n_units == 1 ? 1 : unit_of(x + s.n_shr - 1) - unit_of(x) + 1) * units_per_thread;
                 tiles += readers * s.n_blk;
                 again += (readers - 1) * s.n_blk;
+                if (r.n_shr * n_sl <= 4 * cap) again_narrow += (readers - 1) * s.n_blk;
+                unique += s.n_blk;
             }
-            if (tiles <= kFewTiles && again <= (few == 1 ? prm.few_again : prm.few_again_wide)) return few;
+            if (tiles > kFewTiles) continue;
+            if (few == 1 ? again <= prm.few_again
+                         : again <= prm.few_again_wide && (again_narrow <= prm.few_again_narrow || unique <= prm.few_small)) return few;
         }
         return 0;
     }

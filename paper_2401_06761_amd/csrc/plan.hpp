@@ -102,7 +102,9 @@ struct PlanParams {
                                     // tiles divided over the four wavefronts of a workgroup (0: never)
     int32_t few_row_tiles = 1;      // ... or this many times 16 rows, where units of 16 do not fit ...
     int32_t few_again = 0;          // ... if they read no more tiles than this again, ...
-    int32_t few_again_wide = 0;     // ... or this many, units of 32 rows
+    int32_t few_again_wide = 0;     // ... or this many, units of 32 rows, ...
+    int32_t few_again_narrow = 0;   // ... and of those no more than this many in trees of at most 64 rows, ...
+    int32_t few_small = 0;          // ... unless the call reads no more tiles than this in all
     int32_t few_open_cost = 1;      // a tile that is not full, in full tiles, there
     int32_t open_cost = 1;          // a tile that is not full, in full tiles, where a list is cut four ways
 
@@ -110,10 +112,12 @@ struct PlanParams {
     bool operator==(const PlanParams& b) const {
         return rows_per_thread == b.rows_per_thread && max_unit_tiles == b.max_unit_tiles && allow_direct == b.allow_direct &&
                fuse == b.fuse && inline_shared == b.inline_shared && matrix_min_rows == b.matrix_min_rows &&
-               matrix_min_blocks == b.matrix_min_blocks && few_units == b.few_units && few_row_tiles == b.few_row_tiles && few_again == b.few_again && few_again_wide == b.few_again_wide && few_open_cost == b.few_open_cost && open_cost == b.open_cost;
+               matrix_min_blocks == b.matrix_min_blocks && few_units == b.few_units && few_row_tiles == b.few_row_tiles &&
+               few_again == b.few_again && few_again_wide == b.few_again_wide && few_again_narrow == b.few_again_narrow &&
+               few_small == b.few_small && few_open_cost == b.few_open_cost && open_cost == b.open_cost;
     }
 };
-static_assert(sizeof(PlanParams) == 44, "a parameter more belongs into the comparison");
+static_assert(sizeof(PlanParams) == 52, "a parameter more belongs into the comparison");
 
 struct PrefillThreadView {  // one listed thread of a prefill call
     const int32_t* table;

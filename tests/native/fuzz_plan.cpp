@@ -110,6 +110,8 @@ static int one(int seed) {
         const int again[] = {0, 100, 3000, INT_MAX};
         prm.few_again = again[rng() % 4];
         prm.few_again_wide = again[rng() % 4];
+        prm.few_again_narrow = again[rng() % 4];
+        prm.few_small = again[rng() % 4];
         prm.few_open_cost = rnd(1, 2);
         if (round == 2) {  // as a pool asks for them, but for the blocks of a unit
             prm.allow_direct = prm.fuse = prm.inline_shared = true;
@@ -142,6 +144,20 @@ static int one(int seed) {
             for (const WgDesc& wg : ph.wgs)
                 for (const WaveItem& wi : wg.w) listed += wi.n_tiles;
             CHECK(listed - ph.unique_blocks <= (ph.few_row_tiles == 1 ? prm.few_again : prm.few_again_wide));
+            int64_t again_narrow = 0;  // in trees of at most 64 rows: `listed` over the units of threads that share such a root, less the trees' blocks
+            std::map<int32_t, std::pair<int, std::set<int32_t>>> trees;  // by a tree's first block: its threads, its blocks
+            for (int i = 0; i < n; ++i) {
+                auto& tree = trees[tables[i][0]];
+                tree.first += 1;
+                tree.second.insert(tables[i].begin(), tables[i].end());
+            }
+            const int slices = (prm.rows_per_thread + 15) / 16, per_tile = 16 / ((prm.rows_per_thread + slices - 1) / slices);
+            for (const WgDesc& wg : ph.wgs)
+                if (const int32_t root = tables[order[ph.dfs_threads[wg.grp_base / slices]]][0]; trees[root].first * slices <= 4 * per_tile)
+                    for (const WaveItem& wi : wg.w) again_narrow += wi.n_tiles;
+            for (const auto& [root, tree] : trees)
+                if (tree.first * slices <= 4 * per_tile) again_narrow -= (int64_t)tree.second.size();
+            CHECK(ph.few_row_tiles == 1 || again_narrow <= prm.few_again_narrow || ph.unique_blocks <= prm.few_small);
         }
         for (const WgDesc& wg : ph.wgs) {
             // which kernel takes the unit: all of a call's are for the one without shared lists or none is
@@ -196,7 +212,8 @@ static int parameters(int seed) {
     CHECK(a == a);
     int32_t PlanParams::*const numbers[] = {&PlanParams::rows_per_thread, &PlanParams::max_unit_tiles, &PlanParams::matrix_min_rows,
                                             &PlanParams::matrix_min_blocks, &PlanParams::few_units, &PlanParams::few_row_tiles,
-                                            &PlanParams::few_again, &PlanParams::few_again_wide, &PlanParams::few_open_cost, &PlanParams::open_cost};
+                                            &PlanParams::few_again, &PlanParams::few_again_wide, &PlanParams::few_again_narrow, &PlanParams::few_small,
+                                            &PlanParams::few_open_cost, &PlanParams::open_cost};
     bool PlanParams::*const flags[] = {&PlanParams::allow_direct, &PlanParams::fuse, &PlanParams::inline_shared};
     static_assert(sizeof(PlanParams) == sizeof numbers / sizeof numbers[0] * 4 + 4, "every parameter is named here (the flags share a word)");
     for (auto m : numbers) {

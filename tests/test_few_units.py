@@ -67,6 +67,10 @@ CALLS = [
     (8, 8, [(16 * 590, [40] * 8)], {BF16: 2, FP8: 1, F32: 1}),                           # three more readers of 590 tiles x 64 KiB
     (8, 8, [(16 * 1000, [40] * 8)], {BF16: 2, FP8: 2, F32: 1}),
     (8, 8, [(16 * 1000, [40] * 16)], {BF16: 0, FP8: 2, F32: 1}),                         # (and three of two row tiles)
+    (8, 8, [(16 * 1008, [40] * 8)], {BF16: 0, FP8: 2, F32: 1}),                          # 64 rows: 63 MiB again of 64.5 (1008 tiles of 1032)
+    (8, 8, [(16 * 1008, [40] * 9)], {BF16: 0, FP8: 2, F32: 1}),                          # 72 rows: 126 MiB
+    (8, 8, [(16 * 880, [40] * 9)], {BF16: 2, FP8: 2, F32: 1}),                           # 110
+    (8, 8, [(2048, [40] * 8)] * 8, {BF16: 0, FP8: 2, F32: 1}),
     (1, 8, [(16 * 130, [20] * 32)], {BF16: 0, FP8: 1, F32: 1}),                          # 256 rows below 130 blocks: the matrix kernel's
     (1, 1, [(16 * 2100, [1] * 18)], {BF16: 0, FP8: 0, F32: 0}),                          # more tiles than a unit may list
 ]
