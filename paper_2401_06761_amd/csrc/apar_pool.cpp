@@ -477,11 +477,15 @@ constexpr int32_t kFewWorkgroups = 256;
 // 4 k to 14 k, group 5 7 (448) 45, 13 (256) 38.7, 17 (192) 37.9; eight of 2 k to 5 k 17 (256) 31.7, 9 (512) 30.5; one of 14 k with 30 threads of
 // four candidates 53 (256) 78, 35 (384) 60.8, 27 (512) 64.8; one of five threads, group 4 14 (16) 20.4, 4 (64) 13.2, 3 (80) 12.4; four of
 // group 4 4 (220) 18.4, 3 (264) 22.8.
-constexpr size_t kEstimatedUnits = 4096;  // (kv heads counted; larger calls fill the chip whole, but for a walk of more than a 512th of them)
-// (By kinds of units, the most costly first: those that are not cut need no division.  Unit by unit it took 65 us for 512 units of up
-// to 200 tiles and 520 for 4096 of them, now 13 and 15.)
+// The estimate knows units whose wavefronts leave one state of one row tile together.  Plans with shared lists, whose wavefronts leave one to two
+// row tiles of state each, and calls of more than 512 units (kv heads counted) are cut by shares, as 16-bit pools cut theirs, into 512.  Time by
+// the estimate over that by shares, mean and worst of 3000 drawn calls, by units:
+//   without shared lists, up to 128 0.79, 1.17; 128 to 256 0.94, 1.25; 256 to 512 0.93, 1.23; 512 to 1024 1.00, 1.11; 1024 to 4096 1.01, 1.08;
+//   with them, one row tile up to 512 0.93, 1.04, more 1.03, 1.17; two up to 512 0.97, 1.22, 512 to 1024 1.03, 1.33, more 1.02, 1.14.
+// (With the estimate up to 4096 units for every plan 169 of the 3000 calls were slower by more than 3 % than with shares and the general plan, now 43.)
+constexpr size_t kEstimatedUnits = 512;
+constexpr int kSliceSharesF32 = 512;
 int64_t tiles_per_slice_f32(const PlanHost& ph, const std::vector<int32_t>& units_of_cost, int64_t total, int n_kv) {
-    if (ph.wgs.size() * n_kv > kEstimatedUnits) return std::max<int64_t>(6, (total * n_kv + 511) / 512);
     const int32_t longest = (int32_t)units_of_cost.size() - 1;
     struct Kind {
         int32_t cost, units;
@@ -528,14 +532,15 @@ void cut_into_slices(const PlanHost& ph, const Shape& s, bool few, size_t state_
         longest = std::max(longest, c);
     }
     few = few && (int64_t)ph.wgs.size() * s.n_kv <= kFewWorkgroups;
-    const int64_t shares = few ? kFewShares : kSliceShares;
+    const int64_t shares = few ? kFewShares : s.dtype == APAR_F32 ? kSliceSharesF32 : kSliceShares;
     int64_t tiles = std::max<int64_t>(few ? kFewMinTiles : kSliceMinTiles, (total * s.n_kv + shares - 1) / shares);
     int min_gain = few ? kFewMinGain : kSliceMinGain;
-    if (s.dtype == APAR_F32) {
+    if (s.dtype == APAR_F32 && ph.wgs.size() * s.n_kv <= kEstimatedUnits &&
+        std::none_of(ph.wgs.begin(), ph.wgs.end(), [](const WgDesc& wg) { return wg.n_coop > 0; })) {
         std::vector<int32_t> units_of_cost((size_t)longest + 1, 0);
         for (const WgDesc& wg : ph.wgs) units_of_cost[cost(wg)] += 1;
         tiles = tiles_per_slice_f32(ph, units_of_cost, total, s.n_kv);
-        min_gain = ph.wgs.size() * s.n_kv > kEstimatedUnits ? kSliceMinGain : 0;
+        min_gain = 0;
     }
     auto slices_of = [&](size_t k) { return k < first ? 1 : (int)std::min<int64_t>(64, (cost(ph.wgs[k]) + tiles - 1) / tiles); };
     const int64_t room = (int64_t)state_bytes / (s.n_kv * (int64_t)(s.d / 4 + 2) * 64 * (int64_t)sizeof(float));
