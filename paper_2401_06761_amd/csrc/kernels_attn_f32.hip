@@ -60,7 +60,8 @@ struct Row {  // the 16 rows of one tile: query operands and running softmax sta
 template <int D>
 __device__ __forceinline__ f32x4 products(const f32x4 (&k)[D / 16], const Row<D>& st) {
     // four chains: a quarter of the latency, and sums of a quarter of the length (twelve trees, two chains / four: error against
-    // 64 bits 3.4e-7 / 2.9e-7, three threads 2.1e-7 / 1.6e-7, the same time)
+    // 64 bits 3.4e-7 / 2.9e-7, three threads 2.1e-7 / 1.6e-7; the eight additions more are 2 to 3 % of a call that is bound by products at
+    // d = 64 and 1 % at d = 128, prefill of segments for example)
     f32x4 a[4];
 #pragma unroll
     for (int h = 0; h < 4; ++h) a[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -73,15 +74,19 @@ __device__ __forceinline__ f32x4 products(const f32x4 (&k)[D / 16], const Row<D>
     return (a[0] + a[1]) + (a[2] + a[3]);
 }
 
-// One tile's logits into one row tile's state.  tok_mask: the token slots this lane's row sees (none: not its block).
-template <int D>
-__device__ __forceinline__ void accumulate(const f32x4 (&v)[4][D / 64], Row<D>& st, const f32x4& s, uint32_t tok_mask,
-                                           int g4, float scale_log2e) {
-    constexpr int J = D / 16;
+// tok_mask: the token slots this lane's row sees (none: not its block).
+__device__ __forceinline__ f32x4 masked(const f32x4& s, uint32_t tok_mask, int g4) {
     const uint32_t mine = tok_mask >> (4 * g4);
-    float x[4];
+    f32x4 x;
 #pragma unroll
     for (int i = 0; i < 4; ++i) x[i] = ((mine >> i) & 1u) ? s[i] : -INFINITY;
+    return x;
+}
+
+// One tile's logits, -inf where this lane's row does not see the token, into one row tile's state.
+template <int D>
+__device__ __forceinline__ void accumulate(const f32x4 (&v)[4][D / 64], Row<D>& st, const f32x4& x, float scale_log2e) {
+    constexpr int J = D / 16;
     const float top = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])) * scale_log2e;
     if (__builtin_amdgcn_ballot_w64(top > st.m + kSlack) != 0) {
         // some row ran away from its reference: every row's moves to its running maximum (its four lanes agree on it)
@@ -214,11 +219,20 @@ __device__ __forceinline__ void attend_unit(float (&lds)[4][16 * D + 32], const 
             for (int nt = 0; nt < NT; ++nt)
                 if (NT == 1 || (lo < (nt + 1) * cap && hi > nt * cap)) s[nt] = products<D>(k, st[nt]);
             issue_k(nx);
+            // (most tiles are full, and a row sees all of one or nothing: no token masks for these, prefill at d = 64 1 % faster)
+            const bool whole = ((cur.meta >> 20) & 31) == 16 && !(cur.meta >> 30);
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
-                if (NT == 1 || (lo < (nt + 1) * cap && hi > nt * cap))
-                    accumulate<D>(v, st[nt], s[nt], my_j[nt] >= max(lo, 0) && my_j[nt] < hi ? visible(cur.meta, my_j[nt] - lo) : 0u,
-                                  g4, scale_log2e);
+                if (NT == 1 || (lo < (nt + 1) * cap && hi > nt * cap)) {
+                    const bool in_range = my_j[nt] >= max(lo, 0) && my_j[nt] < hi;
+                    if (whole) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) s[nt][i] = in_range ? s[nt][i] : -INFINITY;
+                    } else {
+                        s[nt] = masked(s[nt], in_range ? visible(cur.meta, my_j[nt] - lo) : 0u, g4);
+                    }
+                    accumulate<D>(v, st[nt], s[nt], scale_log2e);
+                }
             issue_v(nx);
             cur = nx;
         }
@@ -247,7 +261,7 @@ __device__ __forceinline__ void attend_unit(float (&lds)[4][16 * D + 32], const 
                 if (row_of(nt, c, j, listed, cc, qrow, slot) && (wi.grp_lo + j) / n_sl == ru)
                     tm = cand_mask[(int64_t)listed_u * n_cand + cc] & ((1u << n_cand) - 1u);
                 if (__builtin_amdgcn_ballot_w64(tm != 0) == 0) continue;
-                accumulate<D>(v, st[nt], products<D>(k, st[nt]), tm, g4, scale_log2e);
+                accumulate<D>(v, st[nt], masked(products<D>(k, st[nt]), tm, g4), scale_log2e);
             }
         }
     }
