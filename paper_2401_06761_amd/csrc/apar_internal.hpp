@@ -244,8 +244,10 @@ struct PartialBuf {
 // 1827 + 41 / 1813 + 49, 50 k rows (831 MB) 3758 + 179 / 3675 + 173; 1600 rows of matrix units 186 + 10 / 188 + 11.
 constexpr size_t kStreamPartialBytes = (size_t)256 << 20;
 
-// Room for the row states of a launch some of whose units are cut into slices (attn_split.hpp): 256 shares of the work are
-// fewer than 512 slices x kv heads, of at most 8 row tiles of 8.5 KiB.  kSplitMaxCut: the most cut units x kv heads.
+// The most room for the row states of a launch some of whose units are cut into slices (attn_split.hpp), a pool has an eighth of its own size up
+// to this: 256 shares of a 16-bit call's work are fewer than 512 slices x kv heads, of at most 8 row tiles of 8.5 KiB.  fp32 calls may want
+// more (512 shares, or up to 64 slices a unit by an estimate): cut_into_slices makes slices longer until they fit.
+// kSplitMaxCut: the most cut units x kv heads, which it keeps to in the same way.
 constexpr size_t kSplitStateBytes = (size_t)32 << 20;
 constexpr int kSplitMaxCut = 512;
 constexpr size_t kSplitCounterBytes = (size_t)kSplitMaxCut * 4 * sizeof(int32_t);

@@ -1,4 +1,4 @@
-"""What the compiler makes of the 16-bit kernels: those that run units of either row-tile class read a plan's tables and fp8
+"""What the compiler makes of the attention kernels: those of 16-bit pools that run units of either row-tile class read a plan's tables and fp8
 scales as the kernels of one class do, by scalar loads, and none needs scratch memory."""
 import os
 import re
@@ -52,6 +52,12 @@ def test_kernels_of_both_classes_load_as_those_of_one_do(kernels, f8, split, inl
 
 def test_no_kernel_needs_scratch(kernels):
     assert len(kernels) == 18 and all(scratch == 0 for _, scratch in kernels.values()), kernels
+
+
+@pytest.mark.parametrize("source,n", [("kernels_few_bf16.hip", 12), ("kernels_attn_f32.hip", 6)])
+def test_no_kernel_of_other_sources_needs_scratch(tmp_path_factory, source, n):
+    found = _compiled(tmp_path_factory, source)
+    assert len(found) == n and all(scratch == 0 for _, scratch in found.values()), found
 
 
 def test_matrix_kernels(tmp_path_factory):

@@ -74,6 +74,38 @@ def test_against_the_oracle(dtype, d, call):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "bf16_fp8kv", "f32"])
+@pytest.mark.parametrize("n_q,n_kv,cand,n_trees,row_tiles", [(4, 2, 1, 3, 1), (4, 2, 4, 3, 1), (32, 2, 2, 3, 1), (40, 40, 4, 13, 2), (40, 40, 1, 25, 1)])
+def test_trees_of_two_fork_levels(dtype, n_q, n_kv, cand, n_trees, row_tiles):
+    """Segments below the top lie in one unit or across several; candidates on every pool type; 26 units of 16 rows x 40 heads are too many."""
+    import torch
+
+    parents, lens = [], []
+    for k in range(n_trees):  # eight threads: three of the prompt's children, five of its fourth
+        r = len(parents)
+        parents += [-1, r, r, r, r] + [r + 4] * 5
+        lens += [33 + 7 * k, 16, 5, 40, 50 + k, 1, 17, 30, 16, 9]
+    w = manual_tree(parents, lens, HeadConfig(n_q, n_kv, 128, dtype), seed=6)
+    dense = DenseThreads(n_q, n_kv, 128)
+    with pool_for(w, blocks_upper_bound(w)) as pool:
+        pool.kv.fill_(0xFF)
+        h = pool.handle
+        live, _ = replay_trace(w, pool, None, dense)
+        assert len(live) == 8 * n_trees
+        q, ck, cv = spec_step_qkv(w, 1, len(live), cand)
+        rng = np.random.default_rng(1)
+        masks = np.array([mask_rows_from_parents(draw_candidate_tree(rng, cand)) for _ in live], dtype=np.uint8)
+        outs = [torch.full_like(to_dev(q, dtype), 3.0) for _ in range(2)]
+        for out in outs:
+            ap.apar_decode_attention_spec(h, to_dev(q, dtype), to_dev(ck, dtype), to_dev(cv, dtype), torch.from_numpy(masks).cuda(), cand, live, out)
+        torch.cuda.synchronize()
+        wgs = np.asarray(ap.apar_last_plan_export(h, ap.APAR_PLAN_WORKGROUPS)).reshape(-1, 32)
+        if row_tiles == 1 or dtype != "f32":  # (fp32 pools have no wider units)
+            assert all(wg[1] == 0 for wg in wgs) and {wg[3] & 255 for wg in wgs} == {row_tiles}
+        assert_close(to_host(outs[0]), dense.decode_spec(q, ck, cv, masks, live), dtype, "candidates")
+        assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "bf16_fp8kv", "f32"])
 @pytest.mark.parametrize("n_q,n_kv,trees,shared", [
     (32, 4, [(33600, [40] * 6), (100, [30] * 3)], True),              # a long tree of 48 rows: the general plan for every tree
     (8, 4, [(33600, [40, 3]), (100, [30] * 11), (16, [1])], False),   # of 4 rows: chunks without a shared list, merged
