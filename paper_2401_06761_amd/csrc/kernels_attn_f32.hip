@@ -167,11 +167,10 @@ __device__ __forceinline__ void attend_unit(float (&lds)[4][16 * D + 32], const 
             st[nt].q[jj] = ok ? *reinterpret_cast<const f32x4*>(q + qrow * D + 16 * jj + 4 * g4) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         }
     }
-    // token slots of a tile that the row `ahead` row groups past its first one sees (causal tiles: one more per group)
-    auto visible = [](int meta, int ahead) -> uint32_t {
+    // how many of a tile's tokens the row `ahead` row groups past its first one sees (causal tiles: one more per group)
+    auto seen = [](int meta, int ahead) -> int {
         const int fill = (meta >> 20) & 31;
-        const int limit = (meta >> 30) ? min(fill, max(0, ((meta >> 25) & 31) + ahead)) : fill;
-        return (1u << limit) - 1u;
+        return (meta >> 30) ? min(fill, max(0, ((meta >> 25) & 31) + ahead)) : fill;
     };
 
     f32x4 k[J], v[4][D / 64];
@@ -219,18 +218,13 @@ __device__ __forceinline__ void attend_unit(float (&lds)[4][16 * D + 32], const 
             for (int nt = 0; nt < NT; ++nt)
                 if (NT == 1 || (lo < (nt + 1) * cap && hi > nt * cap)) s[nt] = products<D>(k, st[nt]);
             issue_k(nx);
-            // (most tiles are full, and a row sees all of one or nothing: no token masks for these, prefill at d = 64 1 % faster)
-            const bool whole = ((cur.meta >> 20) & 31) == 16 && !(cur.meta >> 30);
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
                 if (NT == 1 || (lo < (nt + 1) * cap && hi > nt * cap)) {
-                    const bool in_range = my_j[nt] >= max(lo, 0) && my_j[nt] < hi;
-                    if (whole) {
+                    // (a count of tokens, not a mask: seven instructions less per row tile, prefill at d = 64 1 % faster)
+                    const int mine = (my_j[nt] >= max(lo, 0) && my_j[nt] < hi ? seen(cur.meta, my_j[nt] - lo) : 0) - 4 * g4;
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) s[nt][i] = in_range ? s[nt][i] : -INFINITY;
-                    } else {
-                        s[nt] = masked(s[nt], in_range ? visible(cur.meta, my_j[nt] - lo) : 0u, g4);
-                    }
+                    for (int i = 0; i < 4; ++i) s[nt][i] = i < mine ? s[nt][i] : -INFINITY;
                     accumulate<D>(v, st[nt], s[nt], scale_log2e);
                 }
             issue_v(nx);
@@ -307,8 +301,8 @@ __device__ __forceinline__ void attend_unit(float (&lds)[4][16 * D + 32], const 
                     const int meta = tiles[t].meta, lo = meta & 1023, hi = (meta >> 10) & 1023;
                     if (jl < lo || jl >= hi) continue;
                     const float* tile = reinterpret_cast<const float*>(head_base + tiles[t].blk * block_stride);
-                    const int seen = __popc(visible(meta, jl - lo));
-                    for (int tok = 0; tok < seen; ++tok) take(tile + tok * D, tile + (16 + tok) * D);
+                    const int n_seen = seen(meta, jl - lo);
+                    for (int tok = 0; tok < n_seen; ++tok) take(tile + tok * D, tile + (16 + tok) * D);
                 }
             }
             if (with_cands) {
