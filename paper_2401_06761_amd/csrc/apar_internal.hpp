@@ -137,11 +137,34 @@ struct PlanDev {              // device pointers of one staged plan
     int32_t n_wg_class[3];       // matrix units, workgroups with 2 and with 1 row tiles per wavefront, stored in that order
     int32_t n_threads;
     int32_t rows_per_thread, rows_per_slice, n_slices;
-    int32_t few;                 // 16-bit pools: the units go to the kernel for few workgroups
+    int32_t few;                 // 16-bit pools: the units go to the kernel for few workgroups; 2: inline_words holds them packed
     SplitPlan split;
     const int32_t* inline_words; // small plans: the tables on the host, to go along with the kernel's arguments; every table
     int32_t n_inline_words;      // pointer above (split.blocks, always there then, included) is its offset in bytes
 };
+
+// Units of calls of few units, packed to go along with the kernel's arguments: two words per wavefront instead of a descriptor of 32, a word per
+// tile.  Such units list shared blocks once each, and where their tables did not fit any more but the general plan's did, every step of a loop
+// had a launch more than under that: of 70 drawn loops of that kind (a row per thread and step, 7 to 24 steps) 52 were slower than under the
+// general plan, in the mean 1.10 times its time and five requests of six threads, group 8, 1.28 times; packed 3, 0.85 and 1.02.
+// Blocks have 18 bits; larger pools send the tables as they are.  The other fields hold whatever fits kPlanInlineWords: less than 1024 tiles, at
+// most 832 threads of up to four slices, 32 row groups per unit.
+constexpr int64_t kFewPackedBlocks = 1 << 18;
+constexpr int kFewWaveWords = 2;
+__host__ __device__ inline uint32_t pack_few_tile(const TileRef& t) {
+    return (uint32_t)t.blk << 14 | (t.meta & 31) << 9 | (((t.meta >> 10) - 1) & 31) << 4 | (((t.meta >> 20) - 1) & 15);
+}
+__host__ __device__ inline TileRef unpack_few_tile(uint32_t w) {
+    return TileRef{(int32_t)(w >> 14), (int32_t)((w >> 9 & 31) | ((w >> 4 & 31) + 1) << 10 | ((w & 15) + 1) << 20)};
+}
+__host__ __device__ inline void pack_few_wave(const WaveItem& wi, int n_full, uint32_t (&w)[kFewWaveWords]) {
+    w[0] = (uint32_t)((wi.tile_ofs & 1023) | wi.n_tiles << 10 | (n_full < wi.n_tiles ? n_full : wi.n_tiles) << 20);
+    w[1] = (uint32_t)((wi.grp_lo & 4095) | wi.n_grp << 12 | wi.flags << 18);
+}
+__host__ __device__ inline WaveItem unpack_few_wave(uint32_t w0, uint32_t w1, int& n_full) {
+    n_full = (int)(w0 >> 20);
+    return WaveItem{(int32_t)(w0 & 1023), (int32_t)(w0 >> 10 & 1023), (int32_t)(w1 & 4095), (int32_t)(w1 >> 12 & 63), 0, (int32_t)(w1 >> 18)};
+}
 
 // The first argument of the attention kernels; they take it from the head of the argument segment.
 constexpr int kPlanInlineWords = 832;

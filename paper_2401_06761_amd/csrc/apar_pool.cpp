@@ -571,11 +571,12 @@ void cut_into_slices(const PlanHost& ph, const Shape& s, bool few, size_t state_
 // Lays a small plan's tables out for the kernels' arguments: no upload, no staging slot and no event.  Only where nothing
 // is left to merge (the merge kernel reads staged tables).  Measured per call: one request of five threads, 32 heads
 // 22.5 -> 15.6 us, three threads on an fp32 pool 16.7 -> 9.4 us, a whole response (prompt, 16 steps of five threads) 435 -> 374 us.
-bool inline_plan(apar_pool* p, const PlanHost& ph) {
+// pack: units of a call of few units, in their packed form.
+bool inline_plan(apar_pool* p, const PlanHost& ph, bool pack) {
     if (ph.any_partial || ph.n_wg_class[0] > 0) return false;
     const size_t n_blocks = p->split_blocks.empty() ? ph.wgs.size() : p->split_blocks.size();
-    const size_t words = ph.wgs.size() * (sizeof(WgDesc) / 4) + n_blocks * (sizeof(SplitBlock) / 4) + ph.tiles.size() * (sizeof(TileRef) / 4) +
-                         ph.dfs_threads.size();
+    const size_t wg_words = pack ? 4 * kFewWaveWords : sizeof(WgDesc) / 4, tile_words = pack ? 1 : sizeof(TileRef) / 4;
+    const size_t words = ph.wgs.size() * wg_words + n_blocks * (sizeof(SplitBlock) / 4) + ph.tiles.size() * tile_words + ph.dfs_threads.size();
     if (words > (size_t)kPlanInlineWords) return false;
     p->inline_words.resize(words);
     char* base = (char*)p->inline_words.data();
@@ -585,7 +586,18 @@ bool inline_plan(apar_pool* p, const PlanHost& ph) {
         memcpy(base + at, from, bytes);
         at += bytes;
     };
-    put(0, ph.wgs.data(), ph.wgs.size() * sizeof(WgDesc));
+    if (pack) {
+        p->inline_ofs[0] = at;
+        for (const WgDesc& wg : ph.wgs)
+            for (int k = 0; k < 4; ++k) {
+                uint32_t w[kFewWaveWords];
+                pack_few_wave(wg.w[k], wg.n_full[k], w);
+                memcpy(base + at, w, sizeof w);
+                at += sizeof w;
+            }
+    } else {
+        put(0, ph.wgs.data(), ph.wgs.size() * sizeof(WgDesc));
+    }
     if (p->split_blocks.empty()) {  // units as they are
         p->inline_ofs[3] = at;
         for (size_t k = 0; k < n_blocks; ++k) {
@@ -596,7 +608,16 @@ bool inline_plan(apar_pool* p, const PlanHost& ph) {
     } else {
         put(3, p->split_blocks.data(), n_blocks * sizeof(SplitBlock));
     }
-    put(1, ph.tiles.data(), ph.tiles.size() * sizeof(TileRef));
+    if (pack) {
+        p->inline_ofs[1] = at;
+        for (const TileRef& t : ph.tiles) {
+            const uint32_t w = pack_few_tile(t);
+            memcpy(base + at, &w, sizeof w);
+            at += sizeof w;
+        }
+    } else {
+        put(1, ph.tiles.data(), ph.tiles.size() * sizeof(TileRef));
+    }
     put(2, ph.dfs_threads.data(), ph.dfs_threads.size() * sizeof(int32_t));
     return true;
 }
@@ -721,7 +742,8 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     PartialBuf part = p->part;
     if (p->resident_behind) p->resident = nullptr;
     p->resident_behind = false;
-    const bool inlined = !fixed && inline_plan(p, ph);
+    const bool pack = few && p->cfg.num_blocks <= kFewPackedBlocks;
+    const bool inlined = !fixed && inline_plan(p, ph, pack);
     // a carried-over plan whose tables are still on the device from the previous call: only the words that
     // changed are sent, and written in place once the previous call's kernels are through (one launch, as a copy of the whole
     // tables is: a step of 64 requests, 32 heads, one row per thread and call 0.386 -> 0.380 ms; a serving loop with at most 64
@@ -822,7 +844,7 @@ int decode_common(apar_pool* p, const void* q, const void* cand_k, const void* c
     pd.split.arrived = (int32_t*)p->split_dev;  // (no room: nothing is cut and nothing reads either)
     pd.split.state = p->split_dev ? (float*)(p->split_dev + kSplitCounterBytes) : nullptr;
 
-    pd.few = few;
+    pd.few = few ? (inlined && pack ? 2 : 1) : 0;
 
     if (inlined) {
         pd.wgs = (const WgDesc*)p->inline_ofs[0];

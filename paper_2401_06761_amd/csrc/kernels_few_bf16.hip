@@ -145,11 +145,25 @@ struct FewTile {
     }
 };
 
-template <bool CODES, int NT>
+// A list of tiles; PACKED: as pack_few_tile leaves them.
+template <bool PACKED>
+struct FewRefs {
+    const TileRef* p;
+    __device__ __forceinline__ TileRef operator[](int i) const {
+        if constexpr (PACKED) return unpack_few_tile(reinterpret_cast<const uint32_t*>(p)[i]);
+        else return p[i];
+    }
+    __device__ __forceinline__ FewRefs from(int i) const {
+        if constexpr (PACKED) return {reinterpret_cast<const TileRef*>(reinterpret_cast<const uint32_t*>(p) + i)};
+        else return {p + i};
+    }
+};
+
+template <bool CODES, int NT, bool PACKED>
 struct FewList {
     static constexpr int kSets = CODES ? 3 : 2;
     FewTile<CODES, NT> set[kSets];
-    const TileRef* list;
+    FewRefs<PACKED> list;
     int n;
 
     __device__ __forceinline__ void start(const FewWalk<NT>& w) {
@@ -185,7 +199,7 @@ struct FewList {
     }
 };
 
-template <int NT, bool F8, bool SPLIT>
+template <int NT, bool F8, bool SPLIT, bool PACKED>
 __device__ __forceinline__ void attend_few(char* lds, const Slice& slice, const char* __restrict__ pool, const uint16_t* __restrict__ q,
                                            const PlanDev& plan, int n_cand, int n_q, int n_kv, int group, float scale_log2e,
                                            const PartialBuf& part, const uint16_t* __restrict__ cand_k, const uint16_t* __restrict__ cand_v,
@@ -194,12 +208,19 @@ __device__ __forceinline__ void attend_few(char* lds, const Slice& slice, const 
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int g4 = lane >> 4, c = lane & 15;
     const int kvh = blockIdx.x % n_kv;
-    const WgDesc* wg = plan.wgs + slice.wg;
-    WaveItem wi = wg->w[wave];
-    int own_full = min(wg->n_full[wave], wi.n_tiles);
+    WaveItem wi;
+    int own_full;
+    if constexpr (PACKED) {
+        const uint32_t* w = reinterpret_cast<const uint32_t*>(plan.wgs) + (slice.wg * 4 + wave) * kFewWaveWords;
+        wi = unpack_few_wave(w[0], w[1], own_full);
+    } else {
+        const WgDesc* wg = plan.wgs + slice.wg;
+        wi = wg->w[wave];
+        own_full = min(wg->n_full[wave], wi.n_tiles);
+    }
     if constexpr (SPLIT) cut_list(slice, wi.tile_ofs, wi.n_tiles, own_full);
     if (wi.n_grp == 0) return;  // (never one of the four wavefronts of a divided list)
-    const TileRef* mine = plan.tiles + wi.tile_ofs;
+    const FewRefs<PACKED> mine = FewRefs<PACKED>{plan.tiles}.from(wi.tile_ofs);
 
     // column c of row tile nt is row `within` of the wavefront's row group nt * cap + c / rps
     const int rps = plan.rows_per_slice, n_sl = plan.n_slices, cap = 16 / rps;
@@ -232,17 +253,17 @@ __device__ __forceinline__ void attend_few(char* lds, const Slice& slice, const 
         }
     }
     if constexpr (F8) {  // full tiles are codes, open ones rows
-        FewList<true, NT> codes;
-        FewList<false, NT> rows;
+        FewList<true, NT, PACKED> codes;
+        FewList<false, NT, PACKED> rows;
         codes.list = mine, codes.n = own_full;
-        rows.list = mine + own_full, rows.n = wi.n_tiles - own_full;
+        rows.list = mine.from(own_full), rows.n = wi.n_tiles - own_full;
         codes.start(walk);
         if constexpr (NT == 1) rows.start(walk);
         codes.walk(walk, st);
         if constexpr (NT > 1) rows.start(walk);
         rows.walk(walk, st);
     } else {
-        FewList<false, NT> tiles;
+        FewList<false, NT, PACKED> tiles;
         tiles.list = mine, tiles.n = wi.n_tiles;
         tiles.start(walk);
         tiles.walk(walk, st);
@@ -336,15 +357,17 @@ __device__ __forceinline__ void attend_few(char* lds, const Slice& slice, const 
 }
 
 // (Two wavefronts per SIMD: declared for one, the compiler keeps accumulators in the other register file and copies them per tile.)
-template <int NT, bool F8, bool SPLIT, bool INLINE>
+// Where the tables are: on the device, or the kernel's first argument, packed or not.
+enum FewFrom { kFewDevice, kFewArguments, kFewPacked };
+template <int NT, bool F8, bool SPLIT, int FROM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attention_bf16_few(
-    PlanWords<INLINE>, const char* __restrict__ pool, const uint16_t* __restrict__ q, PlanDev plan, int n_cand, int n_q, int n_kv,
+    PlanWords<FROM != kFewDevice>, const char* __restrict__ pool, const uint16_t* __restrict__ q, PlanDev plan, int n_cand, int n_q, int n_kv,
     int group, float scale_log2e, PartialBuf part, const uint16_t* __restrict__ cand_k, const uint16_t* __restrict__ cand_v,
     const uint8_t* __restrict__ cand_mask, uint16_t* __restrict__ out) {
     __shared__ __attribute__((aligned(16))) char lds[FewLds<NT>::kBytes];
-    const Slice slice = unit_of_block<SPLIT, INLINE>(plan, 0, n_kv);
+    const Slice slice = unit_of_block<SPLIT, FROM != kFewDevice>(plan, 0, n_kv);
     tables_unwritten(plan);
-    attend_few<NT, F8, SPLIT>(lds, slice, pool, q, plan, n_cand, n_q, n_kv, group, scale_log2e, part, cand_k, cand_v, cand_mask, out);
+    attend_few<NT, F8, SPLIT, FROM == kFewPacked>(lds, slice, pool, q, plan, n_cand, n_q, n_kv, group, scale_log2e, part, cand_k, cand_v, cand_mask, out);
 }
 
 }  // namespace
@@ -361,24 +384,25 @@ hipError_t launch_attention_few_bf16(const Shape& s, const void* pool, const voi
     hipLaunchKernelGGL(KERNEL, dim3((unsigned)n_wg), dim3(256), 0, st, WORDS, (const char*)pool,             \
                        (const uint16_t*)q, plan, n_cand, s.n_q, s.n_kv, s.group, s.scale_log2e, part,        \
                        (const uint16_t*)cand_k, (const uint16_t*)cand_v, mask, (uint16_t*)out)
-#define APAR_LAUNCH_NT(F8V, SPLITV, INLINEV, WORDS)                                                         \
+#define APAR_LAUNCH_NT(F8V, SPLITV, FROMV, WORDS)                                                         \
     do {                                                                                                     \
-        if (n_class[1] > 0) APAR_LAUNCH((attention_bf16_few<2, F8V, SPLITV, INLINEV>), WORDS);               \
-        else APAR_LAUNCH((attention_bf16_few<1, F8V, SPLITV, INLINEV>), WORDS);                              \
+        if (n_class[1] > 0) APAR_LAUNCH((attention_bf16_few<2, F8V, SPLITV, FROMV>), WORDS);               \
+        else APAR_LAUNCH((attention_bf16_few<1, F8V, SPLITV, FROMV>), WORDS);                              \
     } while (0)
-#define APAR_LAUNCH_F8(SPLITV, INLINEV, WORDS)                                                               \
+#define APAR_LAUNCH_F8(SPLITV, FROMV, WORDS)                                                               \
     do {                                                                                                     \
-        if (s.fp8_sealed) APAR_LAUNCH_NT(true, SPLITV, INLINEV, WORDS);                                      \
-        else APAR_LAUNCH_NT(false, SPLITV, INLINEV, WORDS);                                                  \
+        if (s.fp8_sealed) APAR_LAUNCH_NT(true, SPLITV, FROMV, WORDS);                                      \
+        else APAR_LAUNCH_NT(false, SPLITV, FROMV, WORDS);                                                  \
     } while (0)
     if (plan.inline_words) {
         PlanWords<true> words;
         memcpy(words.words, plan.inline_words, (size_t)plan.n_inline_words * sizeof(int32_t));
-        APAR_LAUNCH_F8(true, true, words);
+        if (plan.few == 2) APAR_LAUNCH_F8(true, kFewPacked, words);
+        else APAR_LAUNCH_F8(true, kFewArguments, words);
     } else if (split) {
-        APAR_LAUNCH_F8(true, false, PlanWords<false>{});
+        APAR_LAUNCH_F8(true, kFewDevice, PlanWords<false>{});
     } else {
-        APAR_LAUNCH_F8(false, false, PlanWords<false>{});
+        APAR_LAUNCH_F8(false, kFewDevice, PlanWords<false>{});
     }
 #undef APAR_LAUNCH_F8
 #undef APAR_LAUNCH_NT

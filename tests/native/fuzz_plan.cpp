@@ -32,7 +32,7 @@ static bool same_table(const std::vector<T>& a, const std::vector<T>& b) {
     return a.size() == b.size() && (a.empty() || std::memcmp(a.data(), b.data(), a.size() * sizeof(T)) == 0);
 }
 
-static int n_few = 0;  // plans of calls of few units
+static int n_few = 0, n_packed = 0;  // plans of calls of few units, those that were packed
 
 static int one(int seed) {
     std::mt19937 rng(seed);
@@ -159,6 +159,23 @@ static int one(int seed) {
                 if (tree.first * slices <= 4 * per_tile) again_narrow -= (int64_t)tree.second.size();
             CHECK(ph.few_row_tiles == 1 || again_narrow <= prm.few_again_narrow || ph.unique_blocks <= prm.few_small);
         }
+        if (ph.few_row_tiles && !ph.any_partial && ph.tiles.size() < 832 && n < 832) {  // (such may go along packed)
+            for (const TileRef& t : ph.tiles) {
+                const TileRef u = unpack_few_tile(pack_few_tile(t));
+                CHECK((t.meta >> 20) == 0 || (u.blk == t.blk && u.meta == t.meta));  // (0: room behind a list)
+            }
+            for (const WgDesc& wg : ph.wgs)
+                for (int k = 0; k < 4; ++k) {
+                    const WaveItem& wi = wg.w[k];
+                    uint32_t w[kFewWaveWords];
+                    pack_few_wave(wi, wg.n_full[k], w);
+                    int n_full;
+                    const WaveItem u = unpack_few_wave(w[0], w[1], n_full);
+                    CHECK(u.n_grp == wi.n_grp && (wi.n_grp == 0 || (u.tile_ofs == wi.tile_ofs && u.n_tiles == wi.n_tiles && u.grp_lo == wi.grp_lo &&
+                                                                    u.flags == wi.flags && n_full == std::min(wg.n_full[k], wi.n_tiles))));
+                }
+            n_packed += 1;
+        }
         for (const WgDesc& wg : ph.wgs) {
             // which kernel takes the unit: all of a call's are for the one without shared lists or none is
             if (ph.few_row_tiles) CHECK(wg.n_coop == 0 && (wg.row_tiles & 255) <= ph.few_row_tiles);
@@ -235,6 +252,7 @@ int main(int argc, char** argv) {
     for (int seed = first; seed < first + count; ++seed)
         if (one(seed)) return 1;
     if (count >= 50 && n_few < count / 10) return std::fprintf(stderr, "only %d plans of calls of few units\n", n_few), 1;
-    std::printf("ok: %d forests, %d plans of calls of few units\n", count, n_few);
+    if (count >= 50 && n_packed < count / 20) return std::fprintf(stderr, "only %d of them packed\n", n_packed), 1;
+    std::printf("ok: %d forests, %d plans of calls of few units, %d packed\n", count, n_few, n_packed);
     return 0;
 }

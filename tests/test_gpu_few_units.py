@@ -218,3 +218,37 @@ def test_a_loop_carries_threads_of_more_rows_than_a_unit(dtype, n_q, n_kv, cand,
             dense.commit_candidates(live, ck, cv, accept)
         assert all(wg[1] == 0 for wg in np.asarray(ap.apar_last_plan_export(h, ap.APAR_PLAN_WORKGROUPS)).reshape(-1, 32))
         assert ap.apar_plan_counts(h) == (1, 19)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "bf16_fp8kv"])
+@pytest.mark.parametrize("n_kv,group,trees", [(1, 1, [(60, [5, 16, 17])]), (2, 4, [(1500, [20, 3])]), (40, 4, [(40, [9, 1, 16, 17, 8])] * 13),
+                                              (1, 1, [(300, [5] * 20)] * 3)])
+def test_packed_tables_give_the_same_bits(dtype, n_kv, group, trees):
+    """Tables that go along packed, as they are (pools of more than 2^18 blocks) and staged: one and two row tiles, slices, packed ones that
+    would not fit otherwise."""
+    import torch
+
+    outs = []
+    for blocks in (4096, (1 << 18) + 1):
+        if blocks * n_kv > 1 << 20:
+            continue  # (80 GiB)
+        with ap.Pool(n_kv * group, n_kv, 128, dtype, blocks, max_threads=4096) as pool:
+            h = pool.handle
+            gen = torch.Generator(device="cuda")
+            gen.manual_seed(3)
+            rand = lambda n, heads=n_kv: torch.randn((n, heads, 128), generator=gen, device="cuda").to(torch.bfloat16)
+            live = []
+            for prompt, leaves in trees:
+                root = ap.apar_thread_create(h)
+                ap.apar_append_kv(h, root, rand(prompt), rand(prompt))
+                kids = ap.apar_fork(h, root, len(leaves))
+                for t, n in zip(kids, leaves):
+                    ap.apar_append_kv(h, t, rand(n), rand(n))
+                live += kids
+            q = rand(len(live), n_kv * group)
+            for call in (ap.apar_decode_attention, ap.apar_decode_attention_fixed):
+                outs.append(torch.full_like(q, 3.0))
+                call(h, q, live, outs[-1])
+            torch.cuda.synchronize()
+            assert all(wg[1] == 0 for wg in np.asarray(ap.apar_last_plan_export(h, ap.APAR_PLAN_WORKGROUPS)).reshape(-1, 32))
+    assert not (outs[0] == 3.0).any() and all(torch.equal(outs[0], o) for o in outs)
