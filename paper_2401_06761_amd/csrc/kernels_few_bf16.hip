@@ -5,7 +5,7 @@
 // in flight (products and softmax take 350), an open tile 1600 (its K gathered sixteen bytes a row), fold by one wavefront and output
 // 4.5 k.  So here two tiles (three of fp8 codes) are on their way at any time, open tiles among them: every tile is fetched the same
 // way, KiB by KiB, and an open one's rows are put into operand order through LDS.  The four wavefronts of a divided list fold and write
-// a quarter of the dims each.  13.5 -> 8.9 us per call; with 8 kv heads 14.4 -> 8.5 (in two units instead of one of two wavefronts).
+// a quarter of the dims each.  13.5 -> 8.6 us per call (8.9 before their tables were packed); with 8 kv heads 14.4 -> 8.5 (in two units instead of one of two wavefronts).
 // One compute unit takes 50 bytes per cycle however many loads are on their way, 640 cycles per tile and wavefront, so that a tile
 // takes 720 with two on their way.  Two row tiles (where units of 16 rows would read shared segments too often): the queries lie in
 // LDS, which leaves registers for the two tiles (202; four requests of 4 k tokens, group 8 32.2 -> 27.8 us).
