@@ -137,7 +137,7 @@ struct PlanDev {              // device pointers of one staged plan
     int32_t n_wg_class[3];       // matrix units, workgroups with 2 and with 1 row tiles per wavefront, stored in that order
     int32_t n_threads;
     int32_t rows_per_thread, rows_per_slice, n_slices;
-    int32_t few;                 // 16-bit pools: the units go to the kernel for few workgroups; 2: inline_words holds them packed
+    int32_t few;                 // 16-bit pools: the units go to the kernel for few workgroups; 2: its launcher packs inline_words
     SplitPlan split;
     const int32_t* inline_words; // small plans: the tables on the host, to go along with the kernel's arguments; every table
     int32_t n_inline_words;      // pointer above (split.blocks, always there then, included) is its offset in bytes
@@ -151,6 +151,9 @@ struct PlanDev {              // device pointers of one staged plan
 // most 832 threads of up to four slices, 32 row groups per unit.
 constexpr int64_t kFewPackedBlocks = 1 << 18;
 constexpr int kFewWaveWords = 2;
+inline size_t few_packed_words(size_t n_wg, size_t n_blocks, size_t n_tiles, size_t n_threads) {
+    return n_wg * 4 * kFewWaveWords + n_blocks * (sizeof(SplitBlock) / 4) + n_tiles + n_threads;
+}
 __host__ __device__ inline uint32_t pack_few_tile(const TileRef& t) {
     return (uint32_t)t.blk << 14 | (t.meta & 31) << 9 | (((t.meta >> 10) - 1) & 31) << 4 | (((t.meta >> 20) - 1) & 15);
 }

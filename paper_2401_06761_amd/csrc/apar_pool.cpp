@@ -571,13 +571,13 @@ void cut_into_slices(const PlanHost& ph, const Shape& s, bool few, size_t state_
 // Lays a small plan's tables out for the kernels' arguments: no upload, no staging slot and no event.  Only where nothing
 // is left to merge (the merge kernel reads staged tables).  Measured per call: one request of five threads, 32 heads
 // 22.5 -> 15.6 us, three threads on an fp32 pool 16.7 -> 9.4 us, a whole response (prompt, 16 steps of five threads) 435 -> 374 us.
-// pack: units of a call of few units, in their packed form.
+// pack: the launcher packs them (units of a call of few units).
 bool inline_plan(apar_pool* p, const PlanHost& ph, bool pack) {
     if (ph.any_partial || ph.n_wg_class[0] > 0) return false;
     const size_t n_blocks = p->split_blocks.empty() ? ph.wgs.size() : p->split_blocks.size();
-    const size_t wg_words = pack ? 4 * kFewWaveWords : sizeof(WgDesc) / 4, tile_words = pack ? 1 : sizeof(TileRef) / 4;
-    const size_t words = ph.wgs.size() * wg_words + n_blocks * (sizeof(SplitBlock) / 4) + ph.tiles.size() * tile_words + ph.dfs_threads.size();
-    if (words > (size_t)kPlanInlineWords) return false;
+    const size_t words = ph.wgs.size() * (sizeof(WgDesc) / 4) + n_blocks * (sizeof(SplitBlock) / 4) + ph.tiles.size() * (sizeof(TileRef) / 4) +
+                         ph.dfs_threads.size();
+    if ((pack ? few_packed_words(ph.wgs.size(), n_blocks, ph.tiles.size(), ph.dfs_threads.size()) : words) > (size_t)kPlanInlineWords) return false;
     p->inline_words.resize(words);
     char* base = (char*)p->inline_words.data();
     size_t at = 0;
@@ -586,18 +586,7 @@ bool inline_plan(apar_pool* p, const PlanHost& ph, bool pack) {
         memcpy(base + at, from, bytes);
         at += bytes;
     };
-    if (pack) {
-        p->inline_ofs[0] = at;
-        for (const WgDesc& wg : ph.wgs)
-            for (int k = 0; k < 4; ++k) {
-                uint32_t w[kFewWaveWords];
-                pack_few_wave(wg.w[k], wg.n_full[k], w);
-                memcpy(base + at, w, sizeof w);
-                at += sizeof w;
-            }
-    } else {
-        put(0, ph.wgs.data(), ph.wgs.size() * sizeof(WgDesc));
-    }
+    put(0, ph.wgs.data(), ph.wgs.size() * sizeof(WgDesc));
     if (p->split_blocks.empty()) {  // units as they are
         p->inline_ofs[3] = at;
         for (size_t k = 0; k < n_blocks; ++k) {
@@ -608,16 +597,7 @@ bool inline_plan(apar_pool* p, const PlanHost& ph, bool pack) {
     } else {
         put(3, p->split_blocks.data(), n_blocks * sizeof(SplitBlock));
     }
-    if (pack) {
-        p->inline_ofs[1] = at;
-        for (const TileRef& t : ph.tiles) {
-            const uint32_t w = pack_few_tile(t);
-            memcpy(base + at, &w, sizeof w);
-            at += sizeof w;
-        }
-    } else {
-        put(1, ph.tiles.data(), ph.tiles.size() * sizeof(TileRef));
-    }
+    put(1, ph.tiles.data(), ph.tiles.size() * sizeof(TileRef));
     put(2, ph.dfs_threads.data(), ph.dfs_threads.size() * sizeof(int32_t));
     return true;
 }

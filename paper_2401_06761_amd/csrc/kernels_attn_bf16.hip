@@ -735,7 +735,7 @@ hipError_t launch_attention_bf16(const Shape& s, const void* pool, const void* q
     // Matrix units go first, alone: their workgroups need 64 KB of LDS and most of a
     // SIMD's registers, and beside a kernel of small workgroups they wait until that kernel has drained
     // (measured: a 100 us launch took as long as the 800 us launch beside it).
-    if (plan.n_inline_words > kPlanInlineWords) return hipErrorInvalidValue;
+    if (plan.few != 2 && plan.n_inline_words > kPlanInlineWords) return hipErrorInvalidValue;
     const bool split = plan.split.blocks != nullptr || plan.inline_words;
     const int32_t* n_class = split ? plan.split.n_blocks_class : plan.n_wg_class;  // (matrix units are never cut)
     const int first = n_class[0];

@@ -372,9 +372,40 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 
 }  // namespace
 
-hipError_t launch_attention_few_bf16(const Shape& s, const void* pool, const void* q, const PlanDev& plan, int n_cand, PartialBuf part,
+// Lays the tables of inline_words out packed, in the order descriptors, blocks, tiles, threads; false if they do not fit.
+static bool pack_tables(PlanDev& plan, PlanWords<true>& to) {
+    const char* from = (const char*)plan.inline_words;
+    const size_t bytes = (size_t)plan.n_inline_words * 4, tiles_at = (size_t)plan.tiles, threads_at = (size_t)plan.dfs_threads;
+    size_t n_blocks = 0;
+    for (int k = 0; k < 3; ++k) n_blocks += (size_t)plan.split.n_blocks_class[k];
+    if (threads_at > bytes || tiles_at > threads_at) return false;
+    const size_t n_wg = (size_t)plan.n_wg, n_tiles = (threads_at - tiles_at) / sizeof(TileRef), n_threads = (bytes - threads_at) / 4;
+    if (few_packed_words(n_wg, n_blocks, n_tiles, n_threads) > (size_t)kPlanInlineWords) return false;
+    uint32_t* at = (uint32_t*)to.words;
+    const WgDesc* wgs = (const WgDesc*)(from + (size_t)plan.wgs);
+    plan.wgs = nullptr;  // (offsets from here on)
+    for (size_t g = 0; g < n_wg; ++g)
+        for (int k = 0; k < 4; ++k, at += kFewWaveWords) {
+            uint32_t w[kFewWaveWords];
+            pack_few_wave(wgs[g].w[k], wgs[g].n_full[k], w);
+            memcpy(at, w, sizeof w);
+        }
+    const char* blocks = from + (size_t)plan.split.blocks;
+    plan.split.blocks = (const SplitBlock*)((char*)at - (char*)to.words);
+    memcpy(at, blocks, n_blocks * sizeof(SplitBlock));
+    at += n_blocks * sizeof(SplitBlock) / 4;
+    const TileRef* tiles = (const TileRef*)(from + tiles_at);
+    plan.tiles = (const TileRef*)((char*)at - (char*)to.words);
+    for (size_t i = 0; i < n_tiles; ++i) *at++ = pack_few_tile(tiles[i]);
+    plan.dfs_threads = (const int32_t*)((char*)at - (char*)to.words);
+    memcpy(at, from + threads_at, n_threads * 4);
+    return true;
+}
+
+hipError_t launch_attention_few_bf16(const Shape& s, const void* pool, const void* q, const PlanDev& staged, int n_cand, PartialBuf part,
                                      const void* cand_k, const void* cand_v, const uint8_t* mask, void* out, hipStream_t st) {
-    if (plan.n_inline_words > kPlanInlineWords) return hipErrorInvalidValue;
+    PlanDev plan = staged;
+    if (plan.few != 2 && plan.n_inline_words > kPlanInlineWords) return hipErrorInvalidValue;
     const bool split = plan.split.blocks != nullptr || plan.inline_words;
     const int32_t* n_class = split ? plan.split.n_blocks_class : plan.n_wg_class;
     const int64_t n_wg = ((int64_t)n_class[1] + n_class[2]) * s.n_kv;
@@ -396,9 +427,13 @@ hipError_t launch_attention_few_bf16(const Shape& s, const void* pool, const voi
     } while (0)
     if (plan.inline_words) {
         PlanWords<true> words;
-        memcpy(words.words, plan.inline_words, (size_t)plan.n_inline_words * sizeof(int32_t));
-        if (plan.few == 2) APAR_LAUNCH_F8(true, kFewPacked, words);
-        else APAR_LAUNCH_F8(true, kFewArguments, words);
+        if (plan.few == 2) {
+            if (!pack_tables(plan, words)) return hipErrorInvalidValue;
+            APAR_LAUNCH_F8(true, kFewPacked, words);
+        } else {
+            memcpy(words.words, plan.inline_words, (size_t)plan.n_inline_words * sizeof(int32_t));
+            APAR_LAUNCH_F8(true, kFewArguments, words);
+        }
     } else if (split) {
         APAR_LAUNCH_F8(true, kFewDevice, PlanWords<false>{});
     } else {
